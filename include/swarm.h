@@ -208,7 +208,6 @@ swarm_status swarm_coact_density(swarm_ctx* ctx, const int32_t* C, int32_t H, in
  * a fresh build is known before C exists (it is the sum over trace rows of the squared number of
  * activated entries), so the radius test "d(i,j) <= tau" is an integer threshold on the count and is
  * applied to every tile of C while it is still in registers: C is written once and never read back.
- * (When N is not a multiple of 4 the two steps run one after the other, with the same results.)
  *
  * idx, rows, H, k, N, C   as in swarm_coact_accumulate; C is overwritten.
  * flags                   SWARM_CHECK_IDX or 0.

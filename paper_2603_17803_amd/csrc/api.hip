@@ -269,13 +269,6 @@ swarm_status swarm_coact_build_density(swarm_ctx* ctx, const int32_t* idx, int64
     int64_t* cstar = ctx->totals + H;
     int32_t* row_count = reinterpret_cast<int32_t*>(ctx->totals + 2 * (size_t)H);
 
-    if (N & 3) {
-        // rows of C are not 16-byte aligned: the epilogue has no vector pass to count in; build, then sweep
-        st = launch_trace_build(ctx, idx, rows, H, k, N, Npad, nruns, flags);
-        if (st == SWARM_OK) st = launch_coact_syrk(ctx, H, N, Npad, nruns, C, 0u);
-        if (st != SWARM_OK) return st;
-        return launch_density(ctx, C, H, N, nullptr, tau, rho_flags, rho, queue, totals);
-    }
     st = launch_trace_build(ctx, idx, rows, H, k, N, Npad, nruns, flags, row_count);
     if (st == SWARM_OK) st = launch_trace_totals_thresholds(ctx, row_count, H, nruns * 128, tau, rho_flags, totals, cstar);
     if (st == SWARM_OK) st = launch_fill_i32(ctx, rho, (size_t)H * N, 0);

@@ -21,6 +21,7 @@ namespace {
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4i_row __attribute__((ext_vector_type(4), aligned(4)));   // four counts of a row of C: rows are 4-byte aligned only when N is odd
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -182,7 +183,7 @@ __device__ __forceinline__ int lds_off(int row, int piece) { return row * KC + (
 // Because the operands travel as bits, the small tile costs next to nothing in memory traffic.
 // Workgroups are numbered so that the eight L2 slices (one per XCD, workgroups are dealt to them
 // round-robin) each walk a contiguous run of the tile schedule.
-// RHO (MODE 0, VEC): the epilogue also counts, for every row of C, the elements that reach the head's
+// RHO (MODE 0): the epilogue also counts, for every row of C, the elements that reach the head's
 // threshold cstar[h] (Algorithm 1, Step 3: the density of an entry is the number of entries within the
 // radius, and "within the radius" is "count >= threshold", see the density pass).  A lane's register
 // column of the direct tile gives the counts of the mirrored tile's rows, the mirrored tile's vectors
@@ -191,12 +192,12 @@ __device__ __forceinline__ int lds_off(int row, int piece) { return row * KC + (
 // atomic add per row and tile.
 typedef __attribute__((address_space(3))) void lds_void;
 
-template <int MODE, bool VEC, bool RHO = false>
+template <int MODE, bool RHO = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns, int32_t* __restrict__ C, uint32_t decay_q16,
                        int tiles_per_head, int total_tiles, int per_xcd, const int32_t* __restrict__ tile_order,
                        uint32_t* __restrict__ dev_flags, const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
-    static_assert(!RHO || (MODE == 0 && VEC), "the fused density count belongs to the overwriting, vectorised form");
+    static_assert(!RHO || MODE == 0, "the fused density count belongs to the overwriting form");
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;
     const int t = xcd * per_xcd + slot_id;
@@ -402,15 +403,30 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     auto combine = [&](int32_t old, int32_t v) __attribute__((always_inline)) {
         return updated_count<MODE == 0 ? 1 : MODE>(old, v, decay_q16, ovf);
     };
+    // four consecutive counts of a row, `cols` of them inside C (four unless the tile reaches past N)
+    auto load_row = [](const int32_t* p, int cols) __attribute__((always_inline)) {
+        if (cols >= 4) return (v4i) *reinterpret_cast<const v4i_row*>(p);
+        return v4i{p[0], cols > 1 ? p[1] : 0, cols > 2 ? p[2] : 0, 0};
+    };
+    auto store_row = [](int32_t* p, v4i w, int cols) __attribute__((always_inline)) {
+        if (cols >= 4) {
+            if (MODE == 0) __builtin_nontemporal_store((v4i_row)w, reinterpret_cast<v4i_row*>(p));
+            else *reinterpret_cast<v4i_row*>(p) = w;
+        } else {
+            p[0] = w.x;
+            if (cols > 1) p[1] = w.y;
+            if (cols > 2) p[2] = w.z;
+        }
+    };
     // GUARD: the tile reaches past N (only tiles of the last tile row / column when N is not a multiple of 128)
     auto emit = [&](auto guard_tag) __attribute__((always_inline)) {
         constexpr bool GUARD = decltype(guard_tag)::value;
-        // Overwriting form: the direct tile first, the two 32-column blocks of a row back to back, so that the two
-        // 128-byte halves of a 256-byte run reach the memory system together.
-        constexpr bool PAIRED = MODE == 0 && VEC;
-        if (PAIRED) {
-            int32_t* Cd = Ch + (size_t)gi_base * N + tj * TN + wx * 64;               // wave-uniform
-            const bool c0_ok = !GUARD || tj * TN + wx * 64 + col_in < N, c1_ok = !GUARD || tj * TN + wx * 64 + 32 + col_in < N;
+        const int gj_wave = tj * TN + wx * 64;                                        // the wave's 64 x 64 block: rows gi_base.., columns gj_wave..
+        if constexpr (MODE == 0) {
+            // The direct tile first, the two 32-column blocks of a row back to back, so that the two
+            // 128-byte halves of a 256-byte run reach the memory system together.
+            int32_t* Cd = Ch + (size_t)gi_base * N + gj_wave;                         // wave-uniform
+            const bool c0_ok = !GUARD || gj_wave + col_in < N, c1_ok = !GUARD || gj_wave + 32 + col_in < N;
             uint32_t colc0 = 0u, colc1 = 0u;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -430,99 +446,66 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
                 atomicAdd(&cnt_col[wx * 64 + 32 + col_in], colc1);
             }
         }
+        // A block of 32 rows x 64 columns of C goes through the wave's LDS staging as rows: eight accesses of 16 bytes per
+        // lane, each covering four rows.  The old counts are requested before the block is parked.
+        auto row_block = [&](auto park, int grow, int gcol) __attribute__((always_inline)) {
+            size_t off = (size_t)grow * N + gcol;                                     // wave-uniform
+            if (RHO) asm volatile("" : "+s"(off));
+            int32_t* Cb = Ch + off;
+            const int cols = GUARD ? N - gcol - c16 * 4 : 4;                          // columns of this lane's vector inside C
+            auto inside = [&](int s) __attribute__((always_inline)) { return !GUARD || (cols > 0 && grow + 4 * s + mrow < N); };
+            v4i old[8];
+            if (MODE != 0) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int gj_base = tj * TN + wx * 64 + j * 32;
-            // park the 64 x 32 block as [column][row] for the mirrored tile; the LDS executes one wave's
-            // accesses in order, so the block of the previous j has been read by then
-            if (VEC && !diag) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int rq = 0; rq < 4; ++rq) {
-                        const v4i v = {acc[i][j][rq * 4], acc[i][j][rq * 4 + 1], acc[i][j][rq * 4 + 2], acc[i][j][rq * 4 + 3]};
-                        *reinterpret_cast<v4i*>(tbuf + col_in * TROW + (i * 32 + rq * 8 + row_in) * 4) = v;
-                    }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                for (int s = 0; s < 8; ++s)
+                    if (inside(s)) old[s] = load_row(at(Cb + (size_t)(4 * s) * N, lane_mirror), cols);
             }
-            // direct tile: rows gi_base + 0..63, columns gj_base + 0..31
-            size_t cj_off = (size_t)gi_base * N + gj_base;                            // wave-uniform
-            if (RHO) asm volatile("" : "+s"(cj_off));   // own row pointers per column block: shared ones (128 scalar registers) do not fit beside the counting
-            int32_t* Cj = Ch + cj_off;
-            const bool col_ok = !GUARD || gj_base + col_in < N;
-            uint32_t colc = 0u;
+            park();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-            for (int ip = 0; ip < (PAIRED ? 0 : 2); ip += 2) {                        // 32 rows x 2 in flight when C is read back
-                int32_t old[2][16];
-                if (MODE != 0) {
-#pragma unroll
-                    for (int i = ip; i < ip + 2; ++i)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int urow = i * 32 + (r >> 2) * 8 + (r & 3);
-                            if (col_ok && (!GUARD || gi_base + urow + row_in < N)) old[i - ip][r] = *at(Cj + (size_t)urow * N, lane_direct);
-                        }
+            for (int s = 0; s < 8; ++s) {
+                v4i w = *reinterpret_cast<const v4i*>(tbuf + (4 * s + mrow) * TROW + c16 * 16);
+                if (inside(s)) {
+                    if (RHO) {
+                        // columns past N hold counts of padding entries; their counters are dropped
+                        rowc[0] += reaches(w.x); rowc[1] += reaches(w.y); rowc[2] += reaches(w.z); rowc[3] += reaches(w.w);
+                    }
+                    if (MODE != 0) {
+                        w.x = combine(old[s].x, w.x); w.y = combine(old[s].y, w.y); w.z = combine(old[s].z, w.z); w.w = combine(old[s].w, w.w);
+                    }
+                    store_row(at(Cb + (size_t)(4 * s) * N, lane_mirror), w, cols);
                 }
-#pragma unroll
-                for (int i = ip; i < ip + 2; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int urow = i * 32 + (r >> 2) * 8 + (r & 3);
-                        int32_t* p = Cj + (size_t)urow * N;
-                        if (col_ok && (!GUARD || gi_base + urow + row_in < N)) {
-                            if (MODE == 0) __builtin_nontemporal_store(acc[i][j][r], at(p, lane_direct));
-                            else *at(p, lane_direct) = combine(old[i - ip][r], acc[i][j][r]);
-                            if (RHO) colc += reaches(acc[i][j][r]);
-                            if (!VEC && !diag) {                                      // rows of C not 16-byte aligned: element-wise mirror
-                                int32_t* q = Ch + (size_t)(gj_base + col_in) * N + gi_base + urow + row_in;
-                                if (MODE == 0) *q = acc[i][j][r];
-                                else *q = combine(*q, acc[i][j][r]);
-                            }
-                        }
-                    }
-                if (MODE != 0) asm volatile("" ::: "memory");
             }
-            if (RHO && !PAIRED) atomicAdd(&cnt_col[wx * 64 + j * 32 + col_in], colc);
-            // mirrored tile: rows gj_base + 0..31, columns gi_base + 0..63
-            if (VEC && !diag) {
-                size_t cm_off = (size_t)gj_base * N + gi_base;                        // wave-uniform
-                if (RHO) asm volatile("" : "+s"(cm_off));
-                int32_t* Cm = Ch + cm_off;
-                const bool mcol_ok = !GUARD || gi_base + c16 * 4 < N;                 // N is a multiple of 4 here
-                constexpr int MB = MODE == 0 ? 8 : 4;                                 // rows in flight: the old counts need registers too
+            // the LDS executes one wave's accesses in order: the next block may be parked right away
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        };
+        if constexpr (MODE != 0) {
+            // read-modify-write: the direct tile as row blocks too
 #pragma unroll
-                for (int sp = 0; sp < 8; sp += MB) {
-                    v4i v[MB], o[MB];
+            for (int i = 0; i < 2; ++i)
+                row_block([&]() __attribute__((always_inline)) {
 #pragma unroll
-                    for (int sidx = sp; sidx < sp + MB; ++sidx) {
-                        v[sidx - sp] = *reinterpret_cast<const v4i*>(tbuf + (4 * sidx + mrow) * TROW + c16 * 16);
-                        if (MODE != 0 && mcol_ok && (!GUARD || gj_base + 4 * sidx + mrow < N))
-                            o[sidx - sp] = *reinterpret_cast<const v4i*>(at(Cm + (size_t)(4 * sidx) * N, lane_mirror));
-                    }
+                    for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int sidx = sp; sidx < sp + MB; ++sidx) {
-                        if (mcol_ok && (!GUARD || gj_base + 4 * sidx + mrow < N)) {
-                            v4i* p = reinterpret_cast<v4i*>(at(Cm + (size_t)(4 * sidx) * N, lane_mirror));
-                            if (RHO) {
-                                const v4i w = v[sidx - sp];
-                                rowc[0] += reaches(w.x); rowc[1] += reaches(w.y); rowc[2] += reaches(w.z); rowc[3] += reaches(w.w);
-                            }
-                            if (MODE == 0) __builtin_nontemporal_store(v[sidx - sp], p);
-                            else {
-                                v4i w = v[sidx - sp];
-                                const v4i q = o[sidx - sp];
-                                w.x = combine(q.x, w.x); w.y = combine(q.y, w.y); w.z = combine(q.z, w.z); w.w = combine(q.w, w.w);
-                                *p = w;
-                            }
+                        for (int r = 0; r < 16; ++r)
+                            *reinterpret_cast<int32_t*>(tbuf + ((r >> 2) * 8 + row_in + (r & 3)) * TROW + (j * 32 + col_in) * 4) = acc[i][j][r];
+                }, gi_base + i * 32, gj_wave);
+        }
+        if (!diag) {                                                                  // the mirrored tile, parked as [column][row]
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                row_block([&]() __attribute__((always_inline)) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int rq = 0; rq < 4; ++rq) {
+                            const v4i v = {acc[i][j][rq * 4], acc[i][j][rq * 4 + 1], acc[i][j][rq * 4 + 2], acc[i][j][rq * 4 + 3]};
+                            *reinterpret_cast<v4i*>(tbuf + col_in * TROW + (i * 32 + rq * 8 + row_in) * 4) = v;
                         }
-                    }
-                    if (MODE != 0) asm volatile("" ::: "memory");
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            }
+                }, gj_wave + j * 32, gi_base);
         }
     };
-    if (MODE == 0 && (ti + 1) * TM <= N && (tj + 1) * TN <= N) emit(std::false_type{});   // whole tile inside C: no per-store checks
+    if ((ti + 1) * TM <= N && (tj + 1) * TN <= N) emit(std::false_type{});   // whole tile inside C: no per-store checks
     else emit(std::true_type{});
     if (MODE != 0 && ovf) atomicOr(dev_flags, SWARM_DEV_OVERFLOW);
     if (RHO) {
@@ -700,7 +683,7 @@ swarm_status launch_fill_i32(swarm_ctx* ctx, int32_t* p, size_t n, int32_t v) {
     return swarm_check_launch(ctx, "fill_i32_kernel");
 }
 
-// cstar and rho both null: plain update of C.  Both given (overwriting form, N a multiple of 4 only): the
+// cstar and rho both null: plain update of C.  Both given (overwriting form only): the
 // epilogue adds to rho[h][i] the number of elements of row i that reach cstar[h]; rho must be zero.
 swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns, int32_t* C, uint32_t decay_q16,
                                const int64_t* cstar, int32_t* rho) {
@@ -716,26 +699,21 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     if (st != SWARM_OK) return st;
     const int per_xcd = (int)((total + 7) / 8);
     const int mode = decay_q16 == 0u ? 0 : decay_q16 == 65536u ? 1 : 2;
-    const bool vec = (N & 3) == 0;
     const bool fused = cstar != nullptr;
-    if (fused && (!rho || mode != 0 || !vec)) {
-        snprintf(ctx->err, sizeof(ctx->err), "coact: the fused density count needs the overwriting form and N a multiple of 4");
+    if (fused && (!rho || mode != 0)) {
+        snprintf(ctx->err, sizeof(ctx->err), "coact: the fused density count needs the overwriting form");
         return SWARM_EINVAL;
     }
     using kernel_t = void (*)(const v4i*, int, int, int, int32_t*, uint32_t, int, int, int, const int32_t*, uint32_t*,
                               const int64_t*, int32_t*);
-    static const kernel_t kernels[3][2] = {{coact_syrk_kernel<0, false>, coact_syrk_kernel<0, true>},
-                                           {coact_syrk_kernel<1, false>, coact_syrk_kernel<1, true>},
-                                           {coact_syrk_kernel<2, false>, coact_syrk_kernel<2, true>}};
-    static const kernel_t fused_kernel = coact_syrk_kernel<0, true, true>;
+    static const kernel_t kernels[3] = {coact_syrk_kernel<0>, coact_syrk_kernel<1>, coact_syrk_kernel<2>};
+    static const kernel_t fused_kernel = coact_syrk_kernel<0, true>;
     constexpr int RHO_LDS_BYTES = SYRK_LDS_BYTES + (TM + TN) * 4;
     if (!ctx->syrk_lds_opt_in) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            RHO_LDS_BYTES);
         for (int m = 0; m < 3 && e == hipSuccess; ++m)
-            for (int v = 0; v < 2 && e == hipSuccess; ++v)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[m][v]), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        SYRK_LDS_BYTES);
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[m]), hipFuncAttributeMaxDynamicSharedMemorySize, SYRK_LDS_BYTES);
         if (e != hipSuccess) {
             snprintf(ctx->err, sizeof(ctx->err), "coact: cannot opt in to %d bytes of LDS: %s", RHO_LDS_BYTES, hipGetErrorString(e));
             return SWARM_EHIP;
@@ -744,7 +722,7 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     }
     dim3 grid((unsigned)(per_xcd * 8)), block(64 * SYRK_WAVES);
     const int tph = (int)tiles_per_head, tot = (int)total;
-    hipLaunchKernelGGL(fused ? fused_kernel : kernels[mode][vec ? 1 : 0], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
+    hipLaunchKernelGGL(fused ? fused_kernel : kernels[mode], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
                        ctx->stream, reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, tph, tot, per_xcd,
                        tile_order, ctx->dev_flags, cstar, rho);
     return swarm_check_launch(ctx, "coact_syrk_kernel");
