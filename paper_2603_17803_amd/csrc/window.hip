@@ -13,58 +13,120 @@ namespace {
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 constexpr int WIN_MAX_RUNS = 16;      // window length up to 2048 steps held in registers
+constexpr int WIN_PER_SEG = 8;            // new entries of a run and pass
 
-// one workgroup per (new entry, head); threads stride over the medoids
-__global__ __launch_bounds__(256) void window_count_kernel(const v4u* __restrict__ bits, int nruns, int Npad, int N, int W,
-                                                           const int32_t* __restrict__ new_ids, int n_new,
-                                                           const int32_t* __restrict__ medoids, int Nc, double tau,
-                                                           int32_t* __restrict__ f_out, uint8_t* __restrict__ member,
-                                                           uint32_t* __restrict__ dev_flags) {
-    const int a = blockIdx.x, h = blockIdx.y;
-    const int32_t e = new_ids[(size_t)h * n_new + a];
-    const bool e_ok = e >= 0 && e < N;
+// A workgroup owns 32 clusters of a head and walks all new entries, 2 NW runs of up to 8 of them at a time: lane l of a wave
+// holds the trace words of medoid l % 32 in registers, its half of the wave takes one run, the words of a new entry are the
+// same for the whole half (one broadcast load each).  A new entry's place depends on how many entries before it joined the
+// cluster: each half wave counts the joiners of its run, the counts meet in LDS and every half adds up those before it.
+// So membership, counts and places leave in one pass.  Before, one thread per cluster walked the entries in order in a
+// kernel of its own, a load latency per entry: 67 us for 256 entries x 8 x 1024 clusters, beside 23 us for the counts.
+// What is left is writing: 9 bytes per pair, in half-wave rows of 128 bytes.
+template <int NR, int NW>
+__global__ __launch_bounds__(64 * NW) void window_kernel(const v4u* __restrict__ bits, int nruns, int Npad, int N, int W,
+                                                                const int32_t* __restrict__ new_ids, int n_new,
+                                                                const int32_t* __restrict__ medoids, int Nc, double tau,
+                                                                const int32_t* __restrict__ primary, const int32_t* __restrict__ size, int D,
+                                                                int32_t* __restrict__ f_out, uint8_t* __restrict__ member,
+                                                                int32_t* __restrict__ disk, uint32_t* __restrict__ dev_flags) {
+    constexpr int SEGS = 2 * NW;                               // runs of consecutive new entries, one per half wave
+    __shared__ uint32_t joined[SEGS][32];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int cl = lane & 31, seg = wave * 2 + (lane >> 5);
+    const int h = blockIdx.y;
+    const int c = blockIdx.x * 32 + cl;
+    const bool c_in = c < Nc;
     const v4u* hb = bits + (size_t)h * nruns * Npad;
-    v4u mine[WIN_MAX_RUNS];
+    const v4u zero = {0u, 0u, 0u, 0u};
+
+    const int32_t m = c_in ? medoids[(size_t)h * Nc + c] : 0;
+    const bool m_ok = m >= 0 && m < N;
+    bool bad = !m_ok;
+    v4u mw[NR];
 #pragma unroll
-    for (int r = 0; r < WIN_MAX_RUNS; ++r) {
-        mine[r] = v4u{0u, 0u, 0u, 0u};
-        if (r < nruns && e_ok) mine[r] = hb[(size_t)r * Npad + e];
+    for (int r = 0; r < NR; ++r) mw[r] = (r < nruns && m_ok) ? hb[(size_t)r * Npad + m] : zero;
+
+    // d = 1 - f / W falls as f grows, so "d < tau" is "f >= fstar": the smallest passing f in [0, W], W + 1 when none passes;
+    // 64 candidates per round, the same fp64 expression as per pair
+    int fstar = 0;
+#pragma unroll
+    for (int width = 64; width >= 1; width /= 64) {
+        const int f = fstar + (lane + 1) * width - 1;
+        const uint64_t pass = __ballot(1.0 - (double)f / (double)W < tau);
+        fstar = pass ? fstar + (__ffsll((unsigned long long)pass) - 1) * width : W + 1;
+        if (!pass) break;
     }
-    bool bad = !e_ok;
-    for (int c = threadIdx.x; c < Nc; c += 256) {
-        const int32_t m = medoids[(size_t)h * Nc + c];
-        int32_t f = 0;
-        if (m >= 0 && m < N) {
+
+    int64_t base64 = 0;
+    if (disk && c_in) base64 = (int64_t)primary[(size_t)h * Nc + c] + size[(size_t)h * Nc + c] + 1;
+    const uint32_t base = (disk && base64 >= 0) ? (uint32_t)(base64 % D) : 0u;
+
+    // new entries per run: as few as let one pass hold all of them, at most WIN_PER_SEG
+    const int per = min(WIN_PER_SEG, (n_new + SEGS - 1) / SEGS);
+    uint32_t grown = 0;                                        // joiners of earlier passes
+    for (int a0 = 0; a0 < n_new; a0 += SEGS * per) {
+        const int first = a0 + seg * per, count = min(per, n_new - first);          // <= 0: an empty run
+        uint32_t joins = 0;
+        constexpr int AHEAD = NR <= 2 ? 4 : NR <= 4 ? 2 : 1;   // new entries whose trace words are in flight together
+        for (int e0 = 0; e0 < per; e0 += AHEAD) {
+            int32_t id[AHEAD];
+            v4u o[AHEAD][NR];
 #pragma unroll
-            for (int r = 0; r < WIN_MAX_RUNS; ++r)
-                if (r < nruns) {
-                    const v4u o = hb[(size_t)r * Npad + m];
-                    f += __popc(mine[r].x & o.x) + __popc(mine[r].y & o.y) + __popc(mine[r].z & o.z) + __popc(mine[r].w & o.w);
+            for (int u = 0; u < AHEAD; ++u) id[u] = new_ids[(size_t)h * n_new + min(first + e0 + u, n_new - 1)];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                const bool e_ok = id[u] >= 0 && id[u] < N;
+                bad |= !e_ok;
+#pragma unroll
+                for (int r = 0; r < NR; ++r) o[u][r] = (r < nruns && e_ok) ? hb[(size_t)r * Npad + id[u]] : zero;
+            }
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                int32_t f = 0;
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    f += __popc(mw[r].x & o[u][r].x) + __popc(mw[r].y & o[u][r].y) + __popc(mw[r].z & o[u][r].z) + __popc(mw[r].w & o[u][r].w);
+                if (e0 + u < count) {
+                    const bool join = f >= fstar;
+                    joins |= (uint32_t)join << (e0 + u);
+                    if (c_in) {
+                        const size_t at = ((size_t)h * n_new + first + e0 + u) * Nc + c;
+                        if (f_out) f_out[at] = f;
+                        member[at] = join ? 1 : 0;
+                    }
                 }
-        } else {
-            bad = true;
+            }
         }
-        const double d = 1.0 - (double)f / (double)W;
-        const size_t o = ((size_t)h * n_new + a) * Nc + c;
-        if (f_out) f_out[o] = f;
-        member[o] = d < tau ? 1 : 0;
+        if (disk) {
+            joined[seg][cl] = (uint32_t)__popc(joins);
+            __syncthreads();
+            uint32_t before = 0, all = 0;
+#pragma unroll
+            for (int s = 0; s < SEGS; ++s) {
+                const uint32_t v = joined[s][cl];
+                before += s < seg ? v : 0u;
+                all += v;
+            }
+            __syncthreads();                                   // the counts have been read: the next pass may overwrite them
+            if (c_in) {
+                uint32_t g = grown + before;
+                uint32_t place = (base + g) % (uint32_t)D;       // both below 2^31
+                int32_t* dst = disk + ((size_t)h * n_new + first) * Nc + c;
+#pragma unroll 1
+                for (int e = 0; e < count; ++e, dst += Nc) {
+                    int32_t v = -1;
+                    if ((joins >> e) & 1u) {
+                        v = base64 >= 0 ? (int32_t)place : (int32_t)((base64 + (int64_t)g) % D);   // a negative first SSD or size: the remainder as the language defines it
+                        ++g;
+                        place = place + 1 == (uint32_t)D ? 0u : place + 1;
+                    }
+                    *dst = v;
+                }
+            }
+            grown += all;
+        }
     }
     if (bad) atomicOr(dev_flags, SWARM_DEV_BAD_ENTRY);
-}
-
-// one thread per (cluster, head): walks the new entries in order, the cluster grows as they join
-__global__ void window_place_kernel(const uint8_t* __restrict__ member, int n_new, int Nc, const int32_t* __restrict__ primary,
-                                    const int32_t* __restrict__ size, int D, int32_t* __restrict__ disk) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x, h = blockIdx.y;
-    if (c >= Nc) return;
-    const int64_t base = (int64_t)primary[(size_t)h * Nc + c] + size[(size_t)h * Nc + c] + 1;
-    int64_t grown = 0;
-    for (int a = 0; a < n_new; ++a) {
-        const size_t o = ((size_t)h * n_new + a) * Nc + c;
-        int32_t v = -1;
-        if (member[o]) { v = (int32_t)((base + grown) % D); ++grown; }
-        disk[o] = v;
-    }
 }
 
 }  // namespace
@@ -72,12 +134,13 @@ __global__ void window_place_kernel(const uint8_t* __restrict__ member, int n_ne
 swarm_status launch_window(swarm_ctx* ctx, int nruns, int Npad, int N, int W, int H, const int32_t* new_ids, int n_new,
                            const int32_t* medoids, int Nc, double tau, const int32_t* primary, const int32_t* size, int D,
                            int32_t* f_out, uint8_t* member, int32_t* disk) {
-    hipLaunchKernelGGL(window_count_kernel, dim3((unsigned)n_new, (unsigned)H), dim3(256), 0, ctx->stream,
-                       reinterpret_cast<const v4u*>(ctx->trace), nruns, Npad, N, W, new_ids, n_new, medoids, Nc, tau, f_out,
-                       member, ctx->dev_flags);
-    swarm_status st = swarm_check_launch(ctx, "window_count_kernel");
-    if (st != SWARM_OK || !disk) return st;
-    hipLaunchKernelGGL(window_place_kernel, dim3((unsigned)((Nc + 127) / 128), (unsigned)H), dim3(128), 0, ctx->stream, member,
-                       n_new, Nc, primary, size, D, disk);
-    return swarm_check_launch(ctx, "window_place_kernel");
+    const dim3 grid((unsigned)((Nc + 31) / 32), (unsigned)H);
+#define SWARM_WINDOW(NR, NW) hipLaunchKernelGGL((window_kernel<NR, NW>), grid, dim3(64 * NW), 0, ctx->stream, reinterpret_cast<const v4u*>(ctx->trace), \
+                                                nruns, Npad, N, W, new_ids, n_new, medoids, Nc, tau, primary, size, D, f_out, member, disk, ctx->dev_flags)
+    if (nruns <= 2) SWARM_WINDOW(2, 16);
+    else if (nruns <= 4) SWARM_WINDOW(4, 16);
+    else if (nruns <= 8) SWARM_WINDOW(8, 16);
+    else SWARM_WINDOW(WIN_MAX_RUNS, 8);                       // 64 registers of medoid words: half the waves, twice the registers
+#undef SWARM_WINDOW
+    return swarm_check_launch(ctx, "window_kernel");
 }
