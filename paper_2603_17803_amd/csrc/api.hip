@@ -261,17 +261,17 @@ swarm_status swarm_coact_build_density(swarm_ctx* ctx, const int32_t* idx, int64
     const int Npad = (N + 255) / 256 * 256;
     st = swarm_grow(ctx, &ctx->trace, &ctx->trace_bytes, (size_t)H * nruns * Npad * 16);
     if (st != SWARM_OK) return st;
-    // auxiliary scratch: totals [H] and thresholds [H] (int64), then the trace rows' entry counts [H][nruns * 128] (int32)
+    // auxiliary scratch: totals [H] and thresholds [H] (int64), then the trace rows' entry counts [slabs][H][nruns * 128] (int32)
+    const int slabs = trace_slabs(nruns, H, Npad);
     st = swarm_grow(ctx, reinterpret_cast<void**>(&ctx->totals), &ctx->totals_bytes,
-                    sizeof(int64_t) * 2 * (size_t)H + sizeof(int32_t) * (size_t)H * nruns * 128);
+                    sizeof(int64_t) * 2 * (size_t)H + sizeof(int32_t) * (size_t)slabs * H * nruns * 128);
     if (st != SWARM_OK) return st;
     int64_t* totals = totals_out ? totals_out : ctx->totals;
     int64_t* cstar = ctx->totals + H;
     int32_t* row_count = reinterpret_cast<int32_t*>(ctx->totals + 2 * (size_t)H);
 
-    st = launch_trace_build(ctx, idx, rows, H, k, N, Npad, nruns, flags, row_count);
-    if (st == SWARM_OK) st = launch_trace_totals_thresholds(ctx, row_count, H, nruns * 128, tau, rho_flags, totals, cstar);
-    if (st == SWARM_OK) st = launch_fill_i32(ctx, rho, (size_t)H * N, 0);
+    st = launch_trace_build(ctx, idx, rows, H, k, N, Npad, nruns, flags, row_count, rho);
+    if (st == SWARM_OK) st = launch_trace_totals_thresholds(ctx, row_count, slabs, H, nruns * 128, tau, rho_flags, totals, cstar);
     if (st == SWARM_OK) st = launch_coact_syrk(ctx, H, N, Npad, nruns, C, 0u, cstar, rho);
     if (st == SWARM_OK && (rho_flags & SWARM_RHO_EXCLUDE_SELF)) st = launch_rho_exclude_self(ctx, C, H, N, cstar, rho);
     if (st == SWARM_OK && queue) st = launch_medoid_rank(ctx, rho, H, N, queue);

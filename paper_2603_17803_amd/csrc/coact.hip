@@ -32,60 +32,81 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 // this one makes the expansion to 4-bit operands a shift and a mask.
 __device__ __forceinline__ int trace_bit(int r) { return 4 * (r & 7) + (r >> 3); }
 
-constexpr int TRACE_SPAN = 8192;   // entries one trace-building workgroup covers (128 KiB of LDS)
+constexpr int TRACE_SPAN = 8192;   // entries one trace-building workgroup covers at most (128 KiB of LDS)
+constexpr int TRACE_SPAN_MIN = 512;
+constexpr int TRACE_THREADS = 1024;
 
 // One workgroup per (run of 128 trace rows, head, span of entries): the 128 selections are merged
 // into an LDS image of the run's bit words, which then leaves as one contiguous, fully written block
 // (no separate clearing pass, no global atomics).
+// The run's selections are one flat list of ids, VEC: taken four at a time (k a multiple of 4, idx 16-byte aligned), so that
+// a division by k (a multiplication by its reciprocal, where that is exact) and a load serve four ids: 8192 rows of 1024
+// ids over 65536 entries, counted, 109 -> 56 us (8 spans scan each id), 4096 rows of 256 over 8 x 8192 entries 24 -> 16 us.
+// (The image as four planes of dwords, free of bank conflicts on consecutive ids: no gain, 7.1 -> 7.9 us on short runs.)
 // COUNT: also count, per trace row, the bits this workgroup sets for the first time (= the row's number
-// of distinct valid entries inside the span) and add them to row_count[h][run * 128 + row].
-template <bool COUNT>
-__global__ __launch_bounds__(1024) void trace_build_kernel(const int32_t* __restrict__ idx, int64_t rows, int H, int k, int N,
-                                                           int Npad, int nruns, uint4* __restrict__ bits,
-                                                           uint32_t* __restrict__ dev_flags, int32_t* __restrict__ row_count) {
+// of distinct valid entries inside the span) into row_count[span][h][run * 128 + row], and clear rho for the build's epilogue.
+template <bool COUNT, bool VEC>
+__global__ __launch_bounds__(TRACE_THREADS) void trace_build_kernel(const int32_t* __restrict__ idx, int64_t rows, int H, int k, int N,
+                                                           int Npad, int nruns, int max_span, uint32_t reciprocal, uint4* __restrict__ bits,
+                                                           uint32_t* __restrict__ dev_flags, int32_t* __restrict__ row_count,
+                                                           int32_t* __restrict__ rho) {
     extern __shared__ __attribute__((aligned(16))) uint32_t words[];          // [span][4], then 128 row counters when COUNT
+    constexpr int Q = VEC ? 4 : 1;                                            // ids per list item
+    constexpr int AHEAD = VEC ? 4 : 8;                                        // list items in flight per thread
     const int run = blockIdx.x, h = blockIdx.y;
-    const int e0 = blockIdx.z * TRACE_SPAN;
-    const int span = min(TRACE_SPAN, Npad - e0);
+    const int e0 = blockIdx.z * max_span;
+    const int span = min(max_span, Npad - e0);
     uint32_t* fresh = words + span * 4;
-    for (int i = threadIdx.x; i < span; i += blockDim.x) reinterpret_cast<uint4*>(words)[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = threadIdx.x; i < span; i += TRACE_THREADS) reinterpret_cast<uint4*>(words)[i] = make_uint4(0u, 0u, 0u, 0u);
     if (COUNT && threadIdx.x < 128) fresh[threadIdx.x] = 0u;
     __syncthreads();
     const int64_t row0 = (int64_t)run * 128;
     const int nrows = (int)min((int64_t)128, rows - row0);                       // <= 0 for a run of pure padding
     bool bad = false;
-    // the run's nrows x k selected ids as one flat list: every thread busy, four independent loads in flight
-    const int total = nrows > 0 ? nrows * k : 0;
+    const int kq = k / Q;
+    const int total = nrows > 0 ? nrows * kq : 0;
     const int64_t row_stride = (int64_t)H * k;
     const int32_t* sel0 = idx + (row0 * H + h) * (int64_t)k;
-    for (int i0 = threadIdx.x; i0 < total; i0 += 4 * blockDim.x) {
-        int32_t e[4];
-        int s[4];
+    for (int i0 = threadIdx.x; i0 < total; i0 += AHEAD * TRACE_THREADS) {
+        int32_t e[AHEAD][Q];
+        int s[AHEAD];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = i0 + u * blockDim.x;
-            s[u] = i / k;
-            e[u] = i < total ? sel0[s[u] * row_stride + (i - s[u] * k)] : -1;
+        for (int u = 0; u < AHEAD; ++u) {
+            const int i = min(i0 + u * TRACE_THREADS, total - 1);                       // past the end: a valid load that is not used
+            s[u] = reciprocal ? (int)__umulhi((uint32_t)i, reciprocal) : i / kq;
+            const int32_t* p = sel0 + s[u] * row_stride + (i - s[u] * kq) * Q;
+            if constexpr (VEC) {
+                const int4 v = *reinterpret_cast<const int4*>(p);
+                e[u][0] = v.x; e[u][1] = v.y; e[u][2] = v.z; e[u][3] = v.w;
+            } else {
+                e[u][0] = *p;
+            }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (i0 + u * (int)blockDim.x >= total) continue;
-            if (e[u] < 0 || e[u] >= N) bad = true;
-            else if (e[u] >= e0 && e[u] < e0 + span) {
-                const uint32_t bit = 1u << trace_bit(s[u] & 31);
-                if (COUNT) {
-                    const bool first = !(atomicOr(&words[(e[u] - e0) * 4 + (s[u] >> 5)], bit) & bit);
-                    // the lanes of a wave mostly work on one trace row (k consecutive list items): one add per wave then
-                    const int s0 = __builtin_amdgcn_readfirstlane(s[u]);
-                    if (__builtin_amdgcn_ballot_w64(s[u] != s0) == 0) {
-                        const uint64_t firsts = __builtin_amdgcn_ballot_w64(first);
-                        if (firsts && (threadIdx.x & 63) == (unsigned)__builtin_ctzll(__builtin_amdgcn_ballot_w64(true)))
-                            atomicAdd(&fresh[s0], (uint32_t)__builtin_popcountll(firsts));
-                    } else if (first) {
-                        atomicAdd(&fresh[s[u]], 1u);
-                    }
-                } else {
-                    atomicOr(&words[(e[u] - e0) * 4 + (s[u] >> 5)], bit);
+        for (int u = 0; u < AHEAD; ++u) {
+            if (i0 + u * TRACE_THREADS >= total) continue;
+            const uint32_t bit = 1u << trace_bit(s[u] & 31);
+            uint32_t* row_words = words + (s[u] >> 5);
+            uint32_t nfirst = 0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int32_t id = e[u][q];
+                bad |= (uint32_t)id >= (uint32_t)N;
+                if ((uint32_t)id < (uint32_t)N && (uint32_t)(id - e0) < (uint32_t)span) {
+                    const uint32_t old = atomicOr(row_words + (id - e0) * 4, bit);
+                    if (COUNT) nfirst += (old & bit) == 0u;
+                }
+            }
+            if (COUNT) {
+                // the lanes of a wave mostly work on one trace row (consecutive list items): one add per wave then
+                const int s0 = __builtin_amdgcn_readfirstlane(s[u]);
+                if (__builtin_amdgcn_ballot_w64(s[u] != s0) == 0) {
+                    uint32_t sum = 0;
+#pragma unroll
+                    for (int b = 0; b < (VEC ? 3 : 1); ++b) sum += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64((nfirst >> b) & 1u)) << b;
+                    if (sum && (threadIdx.x & 63) == (unsigned)__builtin_ctzll(__builtin_amdgcn_ballot_w64(true))) atomicAdd(&fresh[s0], sum);
+                } else if (nfirst) {
+                    atomicAdd(&fresh[s[u]], nfirst);
                 }
             }
         }
@@ -93,14 +114,12 @@ __global__ __launch_bounds__(1024) void trace_build_kernel(const int32_t* __rest
     if (bad && blockIdx.z == 0) atomicOr(dev_flags, SWARM_DEV_BAD_ENTRY);
     __syncthreads();
     uint4* out = bits + ((size_t)h * nruns + run) * Npad + e0;
-    const uint4* src = reinterpret_cast<const uint4*>(words);
-    for (int i = threadIdx.x; i < span; i += blockDim.x) out[i] = src[i];
-    if (COUNT && threadIdx.x < 128 && fresh[threadIdx.x])
-        atomicAdd(&row_count[((size_t)h * nruns + run) * 128 + threadIdx.x], (int32_t)fresh[threadIdx.x]);
-}
-
-__global__ void fill_i32_kernel(int32_t* __restrict__ p, size_t n, int32_t v) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
+    for (int i = threadIdx.x; i < span; i += TRACE_THREADS) out[i] = reinterpret_cast<const uint4*>(words)[i];
+    if (COUNT) {
+        if (threadIdx.x < 128) row_count[(((size_t)blockIdx.z * H + h) * nruns + run) * 128 + threadIdx.x] = (int32_t)fresh[threadIdx.x];
+        if (run == 0)
+            for (int i = threadIdx.x; i < span && e0 + i < N; i += TRACE_THREADS) rho[(size_t)h * N + e0 + i] = 0;
+    }
 }
 
 // Optional validation: flags a repeated entry inside one (row, head) selection.
@@ -588,41 +607,53 @@ __global__ __launch_bounds__(256) void coact_popcount_kernel(const v4i* __restri
 
 }  // namespace
 
+// Entries per trace-building workgroup.  A workgroup scans all selections of its run whatever its span, so spans are as
+// long as they can be while there is a workgroup for every compute unit: a window of 256 steps over 8 heads of 8192
+// entries takes 16.5 us as 16 workgroups and 6.5 us as 256; four workgroups per compute unit cost 24 against 16.5 us on
+// 4096 steps (256 against 512 or 1024 threads each: 20 and 17 against 16.5 us).
+static int trace_span(int nruns, int H, int Npad) {
+    int span = TRACE_SPAN;
+    while (span > TRACE_SPAN_MIN && (int64_t)nruns * H * ((Npad + span - 1) / span) < 256) span /= 2;
+    return span;
+}
+
+int trace_slabs(int nruns, int H, int Npad) {
+    const int span = trace_span(nruns, H, Npad);
+    return (Npad + span - 1) / span;
+}
+
 swarm_status launch_trace_build(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int H, int k, int N, int Npad,
-                                int nruns, uint32_t flags, int32_t* row_count) {
+                                int nruns, uint32_t flags, int32_t* row_count, int32_t* rho) {
     if (flags & SWARM_CHECK_IDX) {
         hipLaunchKernelGGL(check_distinct_kernel, dim3((unsigned)(rows * H)), dim3(256), 0, ctx->stream, idx, k,
                            ctx->dev_flags);
         const swarm_status st = swarm_check_launch(ctx, "check_distinct_kernel");
         if (st != SWARM_OK) return st;
     }
-    const int span = Npad < TRACE_SPAN ? Npad : TRACE_SPAN;
-    const size_t lds_bytes = (size_t)span * 16 + (row_count ? 512 : 0);
+    using kernel_t = void (*)(const int32_t*, int64_t, int, int, int, int, int, int, uint32_t, uint4*, uint32_t*, int32_t*, int32_t*);
+    static const kernel_t kernels[2][2] = {{trace_build_kernel<false, false>, trace_build_kernel<false, true>},
+                                           {trace_build_kernel<true, false>, trace_build_kernel<true, true>}};
     if (!ctx->trace_lds_opt_in) {                          // per context: the attribute belongs to the device the context is bound to
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&trace_build_kernel<false>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, TRACE_SPAN * 16);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&trace_build_kernel<true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, TRACE_SPAN * 16 + 512);
-        if (e != hipSuccess) {
-            snprintf(ctx->err, sizeof(ctx->err), "coact: cannot opt in to %d bytes of LDS: %s", TRACE_SPAN * 16 + 512, hipGetErrorString(e));
-            return SWARM_EHIP;
-        }
+        for (int c = 0; c < 2; ++c)
+            for (int v = 0; v < 2; ++v) {
+                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[c][v]), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                         TRACE_SPAN * 16 + 512);
+                if (e != hipSuccess) {
+                    snprintf(ctx->err, sizeof(ctx->err), "coact: cannot opt in to %d bytes of LDS: %s", TRACE_SPAN * 16 + 512, hipGetErrorString(e));
+                    return SWARM_EHIP;
+                }
+            }
         ctx->trace_lds_opt_in = true;
     }
-    const dim3 grid((unsigned)nruns, (unsigned)H, (unsigned)((Npad + TRACE_SPAN - 1) / TRACE_SPAN));
-    if (row_count) {
-        const size_t n = (size_t)H * nruns * 128;
-        hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((n + 1023) / 1024 < 1024 ? (n + 1023) / 1024 : 1024)), dim3(1024), 0,
-                           ctx->stream, row_count, n, 0);
-        const swarm_status st = swarm_check_launch(ctx, "fill_i32_kernel");
-        if (st != SWARM_OK) return st;
-        hipLaunchKernelGGL(trace_build_kernel<true>, grid, dim3(1024), lds_bytes, ctx->stream, idx, rows, H, k, N, Npad, nruns,
-                           reinterpret_cast<uint4*>(ctx->trace), ctx->dev_flags, row_count);
-    } else {
-        hipLaunchKernelGGL(trace_build_kernel<false>, grid, dim3(1024), lds_bytes, ctx->stream, idx, rows, H, k, N, Npad, nruns,
-                           reinterpret_cast<uint4*>(ctx->trace), ctx->dev_flags, row_count);
-    }
+    const int span = trace_span(nruns, H, Npad);
+    const bool vec = (k & 3) == 0 && (reinterpret_cast<uintptr_t>(idx) & 15) == 0;
+    const uint64_t kq = (uint64_t)(vec ? k / 4 : k);
+    // ceil(2^32 / kq) divides every list position below 128 kq exactly as long as 128 kq^2 < 2^32; otherwise the kernel divides
+    const uint32_t reciprocal = kq > 1 && 128 * kq * kq < (1ull << 32) ? (uint32_t)(((1ull << 32) + kq - 1) / kq) : 0u;
+    const dim3 grid((unsigned)nruns, (unsigned)H, (unsigned)((Npad + span - 1) / span));
+    const size_t lds_bytes = (size_t)(Npad < span ? Npad : span) * 16 + (row_count ? 512 : 0);
+    hipLaunchKernelGGL(kernels[row_count ? 1 : 0][vec ? 1 : 0], grid, dim3(TRACE_THREADS), lds_bytes, ctx->stream, idx, rows, H, k, N, Npad, nruns, span,
+                       reciprocal, reinterpret_cast<uint4*>(ctx->trace), ctx->dev_flags, row_count, rho);
     return swarm_check_launch(ctx, "trace_build_kernel");
 }
 
@@ -675,12 +706,6 @@ static swarm_status tile_order_for(swarm_ctx* ctx, int ntm, const int32_t** out)
     free(host);
     *out = dev;
     return st;
-}
-
-swarm_status launch_fill_i32(swarm_ctx* ctx, int32_t* p, size_t n, int32_t v) {
-    hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((n + 1023) / 1024 < 1024 ? (n + 1023) / 1024 : 1024)), dim3(1024), 0,
-                       ctx->stream, p, n, v);
-    return swarm_check_launch(ctx, "fill_i32_kernel");
 }
 
 // cstar and rho both null: plain update of C.  Both given (overwriting form only): the

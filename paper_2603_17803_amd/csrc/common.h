@@ -90,10 +90,11 @@ bool select_uses_slices(int64_t rows, int N, int k);   // long rows, few of them
 swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t rows, int N, int k, int* M_out, int* stride_out,
                                   int32_t** cand_out, const swarm_fixed_scratch* fixed = nullptr);
 swarm_status launch_trace_build(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int H, int k, int N, int Npad,
-                                int nruns, uint32_t flags, int32_t* row_count = nullptr);   // row_count: int32 [H][nruns*128] out, optional
-swarm_status launch_trace_totals_thresholds(swarm_ctx* ctx, const int32_t* row_count, int H, int nrows, double tau, uint32_t flags,
+                                int nruns, uint32_t flags, int32_t* row_count = nullptr, int32_t* rho = nullptr);
+                                // row_count (optional): int32 [trace_slabs][H][nruns*128] out, with it rho [H][N] is cleared
+int trace_slabs(int nruns, int H, int Npad);           // spans of entries the builder splits a head into
+swarm_status launch_trace_totals_thresholds(swarm_ctx* ctx, const int32_t* row_count, int slabs, int H, int nrows, double tau, uint32_t flags,
                                             int64_t* totals, int64_t* cstar);
-swarm_status launch_fill_i32(swarm_ctx* ctx, int32_t* p, size_t n, int32_t v);
 swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns, int32_t* C, uint32_t decay_q16,
                                const int64_t* cstar = nullptr, int32_t* rho = nullptr);
 swarm_status launch_rho_exclude_self(swarm_ctx* ctx, const int32_t* C, int H, int N, const int64_t* cstar, int32_t* rho);

@@ -113,21 +113,27 @@ __global__ __launch_bounds__(256) void density_count_kernel(const int32_t* __res
 // Grand total of A^T A per head straight from the trace, and the threshold that goes with it, for a
 // build that counts the density in its own epilogue: total = sum over trace rows of the square of the
 // row's number of activated entries (each of a row's activated pairs adds one to C).
-__global__ __launch_bounds__(256) void trace_total_threshold_kernel(const int32_t* __restrict__ row_count, int nrows, double tau,
-                                                                    uint32_t flags, int64_t* __restrict__ totals,
-                                                                    int64_t* __restrict__ cstar) {
-    __shared__ int64_t part[4];
+__global__ __launch_bounds__(1024) void trace_total_threshold_kernel(const int32_t* __restrict__ row_count, int slabs, int nrows, double tau,
+                                                                     uint32_t flags, int64_t* __restrict__ totals,
+                                                                     int64_t* __restrict__ cstar) {
+    __shared__ int64_t part[16];
     const int h = blockIdx.x;
+    const size_t slab = (size_t)gridDim.x * nrows;
     int64_t sum = 0;
-    for (int r = threadIdx.x; r < nrows; r += 256) {
-        const int64_t n = row_count[(size_t)h * nrows + r];
+    for (int r = threadIdx.x; r < nrows; r += 1024) {
+        const int32_t* c = row_count + (size_t)h * nrows + r;
+        int64_t n = 0;
+#pragma unroll 8
+        for (int s = 0; s < slabs; ++s) n += c[s * slab];
         sum += n * n;
     }
     sum = wave_sum_i64(sum);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
     __syncthreads();
     if (threadIdx.x < 64) {
-        const int64_t total = part[0] + part[1] + part[2] + part[3];
+        int64_t total = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) total += part[w];
         const int64_t c = count_threshold(total, tau, flags & SWARM_RHO_STRICT);
         if (threadIdx.x == 0) { totals[h] = total; cstar[h] = c; }
     }
@@ -209,9 +215,9 @@ swarm_status launch_medoid_rank(swarm_ctx* ctx, const int32_t* rho, int H, int N
     return swarm_check_launch(ctx, "medoid_rank_kernel");
 }
 
-swarm_status launch_trace_totals_thresholds(swarm_ctx* ctx, const int32_t* row_count, int H, int nrows, double tau, uint32_t flags,
+swarm_status launch_trace_totals_thresholds(swarm_ctx* ctx, const int32_t* row_count, int slabs, int H, int nrows, double tau, uint32_t flags,
                                             int64_t* totals, int64_t* cstar) {
-    hipLaunchKernelGGL(trace_total_threshold_kernel, dim3((unsigned)H), dim3(256), 0, ctx->stream, row_count, nrows, tau, flags,
+    hipLaunchKernelGGL(trace_total_threshold_kernel, dim3((unsigned)H), dim3(1024), 0, ctx->stream, row_count, slabs, nrows, tau, flags,
                        totals, cstar);
     return swarm_check_launch(ctx, "trace_total_threshold_kernel");
 }

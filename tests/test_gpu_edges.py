@@ -51,3 +51,42 @@ def test_counts_of_ragged_matrices(sw, N):
             assert np.array_equal(g.cpu().numpy(), e)
     assert (flat[H * N * N:] == -12345).all()
     assert sw.device_status() == 0
+
+
+@pytest.mark.parametrize("Wn,k,N,n_new,Nc", [
+    (1, 3, 40, 1, 1), (128, 7, 300, 31, 31), (129, 8, 300, 32, 33), (256, 12, 513, 33, 32), (257, 5, 700, 255, 64), (512, 16, 900, 256, 65),
+    (513, 9, 900, 257, 40), (1024, 4, 600, 513, 96), (1025, 20, 1500, 300, 130), (2048, 6, 515, 17, 95),
+    (3, 24001, 30000, 40, 70), (3, 24000, 30000, 70, 40)])
+def test_window_edges(sw, Wn, k, N, n_new, Nc):
+    """Window lengths around the kernel's register widths, entries and clusters around its runs and half waves, selections
+    whose length is no multiple of four and long enough that their list is divided, not multiplied by a reciprocal."""
+    H, D = 2, 5
+    rng = np.random.default_rng(N + Wn)
+    sel = np.stack([np.stack([np.sort(rng.choice(N, k, replace=False)) for _ in range(H)]) for _ in range(Wn)]).astype(np.int32)
+    new_ids = np.stack([rng.choice(N, n_new, replace=False) for _ in range(H)]).astype(np.int32)
+    med = np.stack([rng.choice(N, Nc, replace=False) for _ in range(H)]).astype(np.int32)
+    primary = rng.integers(0, D, (H, Nc)).astype(np.int32)
+    size = rng.integers(0, 2 ** 31 - 1, (H, Nc)).astype(np.int32)
+    for tau in (1.0, 1.0 - 0.5 / Wn, 1.0 - 1.5 / Wn, 0.0, -0.5):
+        got = sw.window_assign(dev(sel), N, dev(new_ids), dev(med), tau, dev(primary), dev(size), D)
+        for g, e in zip(got, oracle.window_assign(sel, N, new_ids, med, tau, primary, size, D)):
+            assert np.array_equal(g.cpu().numpy(), e), tau
+    assert sw.device_status() == 0
+
+
+@pytest.mark.parametrize("rows,k,N,shift", [(130, 8, 9000, 0), (130, 8, 9000, 1), (5, 21, 8193, 2), (300, 4, 1025, 3), (640, 33, 520, 0)])
+def test_trace_spans_and_alignment(sw, rows, k, N, shift):
+    """Selections that start at any 4-byte address, several spans of entries per run."""
+    sel = W.random_selections(rows, 1, k, N, seed=rows)
+    flat = torch.zeros(sel.size + 4, dtype=torch.int32, device="cuda")
+    idx = flat[shift:shift + sel.size].view(sel.shape)
+    idx.copy_(dev(sel))
+    Cd = torch.zeros((1, N, N), dtype=torch.int32, device="cuda")
+    sw.coact_accumulate(idx, N, Cd, decay_q16=0)
+    ref = oracle.coact_update(sel, N, nthreads=8)
+    assert np.array_equal(Cd.cpu().numpy(), ref)
+    tau = 1.0 - 2.0 / (rows * k * k)
+    rho, queue, tot = sw.coact_build_density(idx, N, Cd, tau)
+    assert np.array_equal(Cd.cpu().numpy(), ref) and int(tot[0]) == rows * k * k
+    assert np.array_equal(rho.cpu().numpy(), oracle.density(ref, tau, 0, nthreads=8)[0])
+    assert sw.device_status() == 0
