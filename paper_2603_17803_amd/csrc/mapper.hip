@@ -882,7 +882,7 @@ template <int IPT, bool CAND, int NT = selcore::NT>
 __global__ __launch_bounds__(NT) void select_map_kernel(const float* __restrict__ scores, int N, int k,
                                                         int32_t* __restrict__ out_idx, MapArgs a, int stage_e2c,
                                                         int stage_tab, int sel_off, const int32_t* __restrict__ cand,
-                                                        int cand_stride, int M) {
+                                                        const uint32_t* __restrict__ cand_key, int cand_stride, int M) {
     __shared__ selcore::SmemT<NT> sm;
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     const int tid = threadIdx.x;
@@ -895,10 +895,7 @@ __global__ __launch_bounds__(NT) void select_map_kernel(const float* __restrict_
     uint32_t key[IPT];
     const int32_t* c = CAND ? cand + (size_t)h * cand_stride : nullptr;
     if (CAND) {
-        const float* srow = scores + (size_t)h * N;
-        const int base = tid * IPT;
-#pragma unroll
-        for (int e = 0; e < IPT; ++e) key[e] = (base + e < M) ? selcore::order_key(srow[c[base + e]]) : 0u;
+        selcore::load_winner_keys<IPT>(scores + (size_t)h * N, c, cand_key ? cand_key + (size_t)h * cand_stride : nullptr, M, key);
     } else {
         selcore::load_keys<IPT>(scores + (size_t)h * N, N, key);
     }
@@ -916,11 +913,9 @@ __global__ __launch_bounds__(NT) void select_map_kernel(const float* __restrict_
     }
     for (int w = tid; w < L.nwords; w += NT) L.bitmap[w] = 0;
 
-    selcore::block_select<IPT, NT>(key, CAND ? M : N, k, sel_lds, sm);
-    if (CAND) {
-        __syncthreads();
-        for (int i = tid; i < k; i += NT) sel_lds[i] = c[sel_lds[i]];
-    }
+    selcore::block_select<IPT, NT>(key, CAND ? M : N, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) {
+        sel_lds[pos] = CAND ? c[tid * IPT + e] : tid * IPT + e;
+    });
 
     if (stage_e2c) {
 #pragma unroll
@@ -999,23 +994,22 @@ swarm_status launch_select_map(swarm_ctx* ctx, const float* scores, int H, int N
     const dim3 grid((unsigned)H), block(NT);
     hipStream_t st = ctx->stream;
     if (sliced) {
-        int M = 0, stride = 0;
-        int32_t* cand = nullptr;
-        const swarm_status rc = launch_select_slices(ctx, scores, H, N, k, &M, &stride, &cand);
+        swarm_winners w;
+        const swarm_status rc = launch_select_slices(ctx, scores, H, N, k, &w);
         if (rc != SWARM_OK) return rc;
-#define SWARM_MERGEMAP(IPT) hipLaunchKernelGGL((select_map_kernel<IPT, true>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, cand, stride, M)
-        if (M <= 4 * NT) SWARM_MERGEMAP(4);
-        else if (M <= 8 * NT) SWARM_MERGEMAP(8);
-        else if (M <= 16 * NT) SWARM_MERGEMAP(16);
-        else if (M <= 32 * NT) SWARM_MERGEMAP(32);
+#define SWARM_MERGEMAP(IPT) hipLaunchKernelGGL((select_map_kernel<IPT, true>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, w.ids, w.keys, w.stride, w.M)
+        if (w.M <= 4 * NT) SWARM_MERGEMAP(4);
+        else if (w.M <= 8 * NT) SWARM_MERGEMAP(8);
+        else if (w.M <= 16 * NT) SWARM_MERGEMAP(16);
+        else if (w.M <= 32 * NT) SWARM_MERGEMAP(32);
         else SWARM_MERGEMAP(64);
 #undef SWARM_MERGEMAP
         *launched = hipGetLastError() == hipSuccess;      // a refused launch (e.g. its LDS request) leaves the two-kernel route to the caller
         return SWARM_OK;
     }
-#define SWARM_SELMAP(IPT) hipLaunchKernelGGL((select_map_kernel<IPT, false>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, nullptr, 0, 0)
-    if (NT == 256) hipLaunchKernelGGL((select_map_kernel<4, false, 256>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, nullptr, 0, 0);
-    else if (NT == 512) hipLaunchKernelGGL((select_map_kernel<4, false, 512>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, nullptr, 0, 0);
+#define SWARM_SELMAP(IPT) hipLaunchKernelGGL((select_map_kernel<IPT, false>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, nullptr, nullptr, 0, 0)
+    if (NT == 256) hipLaunchKernelGGL((select_map_kernel<4, false, 256>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, nullptr, nullptr, 0, 0);
+    else if (NT == 512) hipLaunchKernelGGL((select_map_kernel<4, false, 512>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, nullptr, nullptr, 0, 0);
     else if (N <= 4 * NT) SWARM_SELMAP(4);
     else if (N <= 8 * NT) SWARM_SELMAP(8);
     else if (N <= 16 * NT) SWARM_SELMAP(16);

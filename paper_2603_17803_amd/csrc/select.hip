@@ -16,7 +16,8 @@ __global__ __launch_bounds__(NTH) void topk_select_kernel(const float* __restric
     __shared__ selcore::SmemT<NTH> sm;
     uint32_t key[IPT];
     selcore::load_keys<IPT>(scores + (size_t)blockIdx.x * N, N, key);
-    selcore::block_select<IPT, NTH>(key, N, k, out_idx + (size_t)blockIdx.x * k, sm);
+    int32_t* out = out_idx + (size_t)blockIdx.x * k;
+    selcore::block_select<IPT, NTH>(key, N, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) { out[pos] = (int)threadIdx.x * IPT + e; });
 }
 
 // ---- long rows, few of them: two stages -----------------------------------------------------------
@@ -26,11 +27,13 @@ __global__ __launch_bounds__(NTH) void topk_select_kernel(const float* __restric
 // among the slices' winners.  An entry dropped by its slice is beaten by that many entries of the same
 // slice, each with a higher score or an equal score and a lower index, so it cannot belong to the
 // row's result; the winners are listed in ascending entry id, so position order is index order and
-// the lowest-index tie-break carries over.
+// the lowest-index tie-break carries over.  The winners' order keys are kept beside their ids where the scratch has room for
+// them (cand_key), so that the second stage reads one contiguous list instead of gathering scores through the ids.
 constexpr int SLICE = 8192, SLICE_IPT = 8;
 
 __global__ __launch_bounds__(selcore::NT) void topk_slice_kernel(const float* __restrict__ scores, int N, int k,
-                                                                 int32_t* __restrict__ cand, int cand_stride) {
+                                                                 int32_t* __restrict__ cand, uint32_t* __restrict__ cand_key,
+                                                                 int cand_stride) {
     __shared__ selcore::Smem sm;
     const int p = blockIdx.x;
     const int64_t row = blockIdx.y;
@@ -39,25 +42,25 @@ __global__ __launch_bounds__(selcore::NT) void topk_slice_kernel(const float* __
     uint32_t key[SLICE_IPT];
     selcore::load_keys<SLICE_IPT>(scores + row * N + lo, len, key);
     // slices before this one are full, so their winner counts are min(k, SLICE) each
-    selcore::block_select<SLICE_IPT>(key, len, kk, cand + row * cand_stride + (size_t)p * min(k, SLICE), sm, lo);
+    const size_t at = row * cand_stride + (size_t)p * min(k, SLICE);
+    selcore::block_select<SLICE_IPT, selcore::NT, true>(key, len, kk, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) {
+        cand[at + pos] = lo + (int)threadIdx.x * SLICE_IPT + e;
+        if (cand_key) cand_key[at + pos] = key[e];
+    });
 }
 
 template <int IPT>
 __global__ __launch_bounds__(selcore::NT) void topk_merge_kernel(const float* __restrict__ scores, int N, int k,
-                                                                 const int32_t* __restrict__ cand, int cand_stride, int M,
-                                                                 int32_t* __restrict__ out_idx) {
+                                                                 const int32_t* __restrict__ cand, const uint32_t* __restrict__ cand_key,
+                                                                 int cand_stride, int M, int32_t* __restrict__ out_idx) {
     __shared__ selcore::Smem sm;
     const int64_t row = blockIdx.x;
     const int32_t* c = cand + row * cand_stride;
-    const float* s = scores + row * N;
     uint32_t key[IPT];
-    const int base = threadIdx.x * IPT;
-#pragma unroll
-    for (int e = 0; e < IPT; ++e) key[e] = (base + e < M) ? order_key(s[c[base + e]]) : 0u;
+    selcore::load_winner_keys<IPT>(scores + row * N, c, cand_key ? cand_key + row * cand_stride : nullptr, M, key);
     int32_t* out = out_idx + row * k;
-    selcore::block_select<IPT>(key, M, k, out, sm);      // positions in the winners' list, ascending
-    __syncthreads();
-    for (int j = threadIdx.x; j < k; j += selcore::NT) out[j] = c[out[j]];
+    // the list is in ascending id, so ascending positions are ascending ids
+    selcore::block_select<IPT>(key, M, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) { out[pos] = c[(int)threadIdx.x * IPT + e]; });
 }
 
 constexpr int SEL_THREADS = 1024;
@@ -150,24 +153,28 @@ bool select_uses_slices(int64_t rows, int N, int k) {
     return M <= N / 2 && M <= 64 * selcore::NT;
 }
 
-size_t select_cand_bytes(int64_t rows, int N, int k) {
+// Scratch for the winners of the sliced selection: their ids, or (keyed) their ids and order keys.
+size_t select_cand_bytes(int64_t rows, int N, int k, bool keyed) {
     if (!select_uses_slices(rows, N, k)) return 0;
     const int64_t P = (N + SLICE - 1) / SLICE;
-    return sizeof(int32_t) * (size_t)rows * (size_t)(P * (k < SLICE ? k : SLICE));
+    return (keyed ? sizeof(int32_t) + sizeof(uint32_t) : sizeof(int32_t)) * (size_t)rows * (size_t)(P * (k < SLICE ? k : SLICE));
 }
 
-// First stage of the sliced selection: the slices' winners of every row into *cand_out ([rows][*stride], *M of them per
-// row), which is the context's scratch (grown on demand) or the fixed scratch when one is given.
-swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t rows, int N, int k, int* M_out, int* stride_out,
-                                  int32_t** cand_out, const swarm_fixed_scratch* fixed) {
+// First stage of the sliced selection: the slices' winners of every row into out->ids ([rows][stride], M of them per row), which
+// is the context's scratch (grown on demand) or the fixed scratch when one is given.
+swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t rows, int N, int k, swarm_winners* out,
+                                  const swarm_fixed_scratch* fixed) {
     const int P = (N + SLICE - 1) / SLICE;
     const int per = k < SLICE ? k : SLICE;
     const int last = N - (P - 1) * SLICE;
-    *M_out = (P - 1) * per + (k < last ? k : last);
-    *stride_out = P * per;
-    const size_t need = sizeof(int32_t) * (size_t)rows * *stride_out;
+    out->M = (P - 1) * per + (k < last ? k : last);
+    out->stride = P * per;
+    size_t need = select_cand_bytes(rows, N, k, true);
     int32_t* cand = nullptr;
+    bool keyed = true;
     if (fixed) {
+        keyed = need <= fixed->cand_bytes;
+        if (!keyed) need = select_cand_bytes(rows, N, k, false);
         if (need > fixed->cand_bytes) {
             snprintf(ctx->err, sizeof(ctx->err), "select: the slices' winners need %zu bytes, the fixed scratch has %zu", need, fixed->cand_bytes);
             return SWARM_EINVAL;
@@ -178,9 +185,11 @@ swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t r
         if (rc != SWARM_OK) return rc;
         cand = ctx->cand;
     }
-    *cand_out = cand;
-    hipLaunchKernelGGL(topk_slice_kernel, dim3((unsigned)P, (unsigned)rows), dim3(selcore::NT), 0, ctx->stream, scores, N, k, cand,
-                       *stride_out);
+    uint32_t* key = keyed ? reinterpret_cast<uint32_t*>(cand + (size_t)rows * out->stride) : nullptr;
+    out->ids = cand;
+    out->keys = key;
+    hipLaunchKernelGGL(topk_slice_kernel, dim3((unsigned)P, (unsigned)rows), dim3(selcore::NT), 0, ctx->stream, scores, N, k, cand, key,
+                       out->stride);
     return swarm_check_launch(ctx, "topk_slice_kernel");
 }
 
@@ -189,15 +198,16 @@ swarm_status launch_select(swarm_ctx* ctx, const float* scores, int64_t rows, in
     const dim3 grid((unsigned)rows), block(selcore::NT);
     hipStream_t st = ctx->stream;
     if (select_uses_slices(rows, N, k)) {
-        int M = 0, stride = 0;
-        int32_t* cand = nullptr;
-        const swarm_status rc = launch_select_slices(ctx, scores, rows, N, k, &M, &stride, &cand, fixed);
+        swarm_winners w;
+        const swarm_status rc = launch_select_slices(ctx, scores, rows, N, k, &w, fixed);
         if (rc != SWARM_OK) return rc;
-        if (M <= 4 * selcore::NT) hipLaunchKernelGGL(topk_merge_kernel<4>, grid, block, 0, st, scores, N, k, cand, stride, M, out_idx);
-        else if (M <= 8 * selcore::NT) hipLaunchKernelGGL(topk_merge_kernel<8>, grid, block, 0, st, scores, N, k, cand, stride, M, out_idx);
-        else if (M <= 16 * selcore::NT) hipLaunchKernelGGL(topk_merge_kernel<16>, grid, block, 0, st, scores, N, k, cand, stride, M, out_idx);
-        else if (M <= 32 * selcore::NT) hipLaunchKernelGGL(topk_merge_kernel<32>, grid, block, 0, st, scores, N, k, cand, stride, M, out_idx);
-        else hipLaunchKernelGGL(topk_merge_kernel<64>, grid, block, 0, st, scores, N, k, cand, stride, M, out_idx);
+#define SWARM_MERGE(IPT) hipLaunchKernelGGL(topk_merge_kernel<IPT>, grid, block, 0, st, scores, N, k, w.ids, w.keys, w.stride, w.M, out_idx)
+        if (w.M <= 4 * selcore::NT) SWARM_MERGE(4);
+        else if (w.M <= 8 * selcore::NT) SWARM_MERGE(8);
+        else if (w.M <= 16 * selcore::NT) SWARM_MERGE(16);
+        else if (w.M <= 32 * selcore::NT) SWARM_MERGE(32);
+        else SWARM_MERGE(64);
+#undef SWARM_MERGE
         return swarm_check_launch(ctx, "topk_merge_kernel");
     }
     // Short rows take smaller blocks, four scores per thread: measured per row of 2048 scores, 512 threads select in

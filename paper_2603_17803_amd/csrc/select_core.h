@@ -88,13 +88,13 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t a, uint32_t b, uint32_
 }
 
 // key[e] is the key of index tid*IPT + e; slots at or beyond N must hold key 0.
-// All NTH threads of the block must call this.  out receives k ascending indices.
-// index_offset is added to every emitted index (a block selecting inside a slice of a longer row).
+// All NTH threads of the block must call this.  emit(pos, e) is called once for each of the k selected entries, by the thread
+// that holds it: pos is its place in the result (ascending index order), e its slot in the thread's run.  EMIT_KEYS: emit
+// needs the entry's key, so the slots are walked unrolled (key[e] stays in its register); otherwise only the set ones are.
 // Short per-thread runs keep every score's bin in a register after the histogram pass (the candidate collection and
 // the compaction then compare small integers); long runs recompute it, their registers hold the keys.
-template <int IPT, int NTH = NT>
-__device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, int k, int32_t* __restrict__ out,
-                                             SmemT<NTH>& sm, int index_offset = 0) {
+template <int IPT, int NTH = NT, bool EMIT_KEYS = false, typename Emit>
+__device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, int k, SmemT<NTH>& sm, Emit emit) {
     constexpr int NW = NTH / 64;
     constexpr bool KEEP = IPT <= 32;                    // bins kept in registers
     constexpr int NBINS_KEPT = KEEP ? IPT : 1;
@@ -247,11 +247,21 @@ __device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, 
         const uint32_t room = need_eq > eq_before ? need_eq - eq_before : 0u;
         uint32_t m = eq_mask;
         for (uint32_t i = 0; i < room && m; ++i) { take_mask |= m & (0u - m); m &= m - 1u; }
-        while (take_mask) {
-            const int e = __ffs(take_mask) - 1;
-            take_mask &= take_mask - 1u;
-            if (pos < (uint32_t)k) out[pos] = index_offset + base + e;     // pos < k always holds; the guard keeps a slip in bounds
-            ++pos;
+        if constexpr (EMIT_KEYS) {
+#pragma unroll
+            for (int e = 0; e < IPT; ++e) {
+                if ((take_mask >> e) & 1u) {
+                    if (pos < (uint32_t)k) emit(pos, e);                   // pos < k always holds; the guard keeps a slip in bounds
+                    ++pos;
+                }
+            }
+        } else {
+            while (take_mask) {
+                const int e = __ffs(take_mask) - 1;
+                take_mask &= take_mask - 1u;
+                if (pos < (uint32_t)k) emit(pos, e);
+                ++pos;
+            }
         }
     } else {
         uint32_t eq_seen = eq_before;
@@ -262,7 +272,7 @@ __device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, 
             const bool take = (b < bstar) || (b == bstar && key[e] > T) || (is_eq && eq_seen < need_eq);
             eq_seen += is_eq;
             if (take) {
-                if (pos < (uint32_t)k) out[pos] = index_offset + base + e;
+                if (pos < (uint32_t)k) emit(pos, e);
                 ++pos;
             }
         }
@@ -287,6 +297,38 @@ __device__ __forceinline__ void load_keys(const float* __restrict__ row, int N, 
 #pragma unroll
         for (int e = 0; e < IPT; ++e) key[e] = (base + e < N) ? order_key(row[base + e]) : 0u;
     }
+}
+
+// Loads the keys of a thread's IPT consecutive winners (of M, listed in ascending entry id).  keys: their order keys as the
+// slices wrote them; without room for those (nullptr) the winners' scores are gathered.  Every load is clamped to a valid
+// position instead of being branched around, so that all of a thread's loads are in flight together: behind a branch each,
+// the eight of a 65536-entry row's second stage were eight pairs of dependent round trips, 12 of its 23 us.
+template <int IPT>
+__device__ __forceinline__ void load_winner_keys(const float* __restrict__ row, const int32_t* __restrict__ ids,
+                                                 const uint32_t* __restrict__ keys, int M, uint32_t (&key)[IPT]) {
+    const int base = threadIdx.x * IPT;
+    if (keys && (reinterpret_cast<uintptr_t>(keys) & 15) == 0 && base + IPT <= M) {
+        const uint4* p = reinterpret_cast<const uint4*>(keys + base);
+#pragma unroll
+        for (int e = 0; e < IPT / 4; ++e) {
+            const uint4 v = p[e];
+            key[4 * e] = v.x;
+            key[4 * e + 1] = v.y;
+            key[4 * e + 2] = v.z;
+            key[4 * e + 3] = v.w;
+        }
+    } else if (keys) {
+#pragma unroll
+        for (int e = 0; e < IPT; ++e) key[e] = keys[min(base + e, M - 1)];
+    } else {
+        int32_t id[IPT];
+#pragma unroll
+        for (int e = 0; e < IPT; ++e) id[e] = ids[min(base + e, M - 1)];
+#pragma unroll
+        for (int e = 0; e < IPT; ++e) key[e] = order_key(row[id[e]]);
+    }
+#pragma unroll
+    for (int e = 0; e < IPT; ++e) key[e] = base + e < M ? key[e] : 0u;
 }
 
 }  // namespace selcore

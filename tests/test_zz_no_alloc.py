@@ -65,3 +65,21 @@ def test_static_scratch_entry_point_matches_the_allocating_one():
         assert rc == binding.SWARM_OK and flags == 0
     finally:
         binding.swarm_destroy(ctx)
+
+
+@pytest.mark.parametrize("N,k,B,keyed", [(65536, 256, 30, True), (65536, 400, 30, False), (16385, 8192, 1, True), (20001, 3, 7, True)])
+def test_sliced_rows_with_and_without_room_for_the_winners_keys(N, k, B, keyed):
+    """Long rows whose winners' order keys just fit the static scratch and whose do not: the second stage then gathers the
+    scores.  Both agree with the route of the context's own buffers, which always keeps the keys."""
+    from paper_2603_17803_amd import binding
+    cfg = W.CONFIGS["token_stress"].scaled(T=1, N=N, k=k, B=B, d=8)
+    P, per = (N + 8191) // 8192, min(k, 8192)
+    assert (4 * B * N + 8 * B * P * per <= 8 << 20) == keyed
+    ctx = binding.swarm_create(0, torch.cuda.current_stream().cuda_stream)
+    try:
+        rc_a, rc_b, a, b = both(binding, ctx, cfg)
+        assert rc_a == binding.SWARM_OK and rc_b == binding.SWARM_OK, binding.swarm_last_error(ctx)
+        assert np.array_equal(a, b)
+        assert (np.diff(a, axis=-1) > 0).all() and a.min() >= 0 and a.max() < N
+    finally:
+        binding.swarm_destroy(ctx)
