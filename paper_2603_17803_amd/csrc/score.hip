@@ -163,12 +163,41 @@ __global__ __launch_bounds__(256) void score_kernel(const u32x4* __restrict__ ro
 }
 
 
+// Sums of four rows' partial sums p over the LPR lanes of a row's group, one row per lane: lanes exchange with the partner one
+// lane away and keep rows {0,1} (even lane) or {2,3} (odd lane), then two lanes away and keep one row; the lanes of a group
+// that agree in their two low bits then add up.  The lane ends up with row reduced_row(lane).
+__device__ __forceinline__ int reduced_row(int lane) { return 2 * (lane & 1) + ((lane >> 1) & 1); }
+
+template <int LPR>
+__device__ __forceinline__ float reduce_rows(const float (&p)[4], int lane) {
+    auto dpp = [](float v, auto ctrl) __attribute__((always_inline)) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    const bool b0 = lane & 1, b1 = lane & 2;
+    float k0 = b0 ? p[2] : p[0], k1 = b0 ? p[3] : p[1];
+    const float s0 = b0 ? p[0] : p[2], s1 = b0 ? p[1] : p[3];
+    k0 += dpp(s0, std::integral_constant<int, 0xB1>{});       // quad_perm [1,0,3,2]
+    k1 += dpp(s1, std::integral_constant<int, 0xB1>{});
+    float v = b1 ? k1 : k0;
+    const float sv = b1 ? k0 : k1;
+    v += dpp(sv, std::integral_constant<int, 0x4E>{});        // quad_perm [2,3,0,1]
+    if (LPR == 8) {
+        v += __shfl_xor(v, 4, 64);                            // a rotation inside 16 lanes would reach into the neighbouring group of 8
+    } else {
+        v += dpp(v, std::integral_constant<int, 0x124>{});    // row_ror:4  (rotation inside a row of 16 lanes)
+        v += dpp(v, std::integral_constant<int, 0x128>{});    // row_ror:8
+    }
+    if (LPR >= 32) v += __shfl_xor(v, 16, 64);
+    return v;
+}
+
+
 // Lean form of the sweep for the shapes the decode path runs on: one query head per KV head (G = 1), a row of
 // exactly LPR chunks, a power-of-two number of heads (heads fastest over the workgroup id, as above), no row list.
 // The sweep moves 16 KiB per workgroup and every one of the 2048 workgroups of a 33.5 MB launch runs its code once:
 // measured on one device, the launch takes 7.3 us with 430 instructions per wave, 6.7 us with 254 and 6.5 us with
 // 125 -- what a wave executes around its four loads is time the memory system waits for its next request.  Hence:
-// compile-time row length, one address per wave with literal offsets for the other rows, and a reduction that
+// compile-time row length, one address per wave with literal offsets for the other rows, and a reduction (reduce_rows) that
 // halves the values a lane carries while it halves the lanes (two exchange steps bring a lane's four partial sums
 // down to one, which then needs one add per remaining lane stride: 6 exchanges instead of 20).
 template <int LPR, bool PAGE>
@@ -208,29 +237,113 @@ __global__ __launch_bounds__(256) void score_lean_kernel(const u32x4* __restrict
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) p[u] = dot8(x[u], w);
 
-    // lanes exchange with the partner one lane away and keep rows {0,1} (even lane) or {2,3} (odd lane), then two lanes
-    // away and keep one row; the lanes of a row's group that agree in their two low bits then add up
-    auto dpp = [](float v, auto ctrl) __attribute__((always_inline)) {
-        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true));
-    };
-    const bool b0 = lane & 1, b1 = lane & 2;
-    float k0 = b0 ? p[2] : p[0], k1 = b0 ? p[3] : p[1];
-    const float s0 = b0 ? p[0] : p[2], s1 = b0 ? p[1] : p[3];
-    k0 += dpp(s0, std::integral_constant<int, 0xB1>{});       // quad_perm [1,0,3,2]
-    k1 += dpp(s1, std::integral_constant<int, 0xB1>{});
-    float v = b1 ? k1 : k0;
-    const float sv = b1 ? k0 : k1;
-    v += dpp(sv, std::integral_constant<int, 0x4E>{});        // quad_perm [2,3,0,1]
-    if (LPR == 8) {
-        v += __shfl_xor(v, 4, 64);                            // a rotation inside 16 lanes would reach into the neighbouring group of 8
-    } else {
-        v += dpp(v, std::integral_constant<int, 0x124>{});    // row_ror:4  (rotation inside a row of 16 lanes)
-        v += dpp(v, std::integral_constant<int, 0x128>{});    // row_ror:8
-    }
-    if (LPR >= 32) v += __shfl_xor(v, 16, 64);
+    const float v = reduce_rows<LPR>(p, lane);
     // lane (b0, b1) of a group now holds row 2 b0 + b1 of its group's four rows
-    const int n = row0 + (2 * (int)b0 + (int)(b1 ? 1 : 0)) * RPW;
+    const int n = row0 + reduced_row(lane) * RPW;
     if (sub < UNROLL && n < N) out[((size_t)b * H + h) * N + n] = v;
+}
+
+// The same sweep for everything around that: grouped query heads (G > 1), a few streams over the same keys, row lists.
+// The weights -- the query, clamped for page rows, summed over the G heads of its group -- are the same for all rows of a
+// head: the workgroup folds them once into LDS, two channels per thread, while its rows are on their way, where every wave
+// used to fold all of them for itself behind its four loads (64 to 200 instructions with G = 4).  And NB streams share one
+// read of the keys: a row's sixteen bytes per lane meet NB sets of weights, where every stream used to sweep the keys
+// again.  The products and their order inside a lane are those of the lean kernel.
+// Four streams of four query heads over 8 x 4001 pages (16 MB of keys): 16.1 -> 6.0 us; one stream over 8 x 2003: 4.5 -> 3.4 us.
+// grid: x row groups (heads fastest, HM) or row groups by y heads, z groups of NB streams (the last one may be partial).
+template <int LPR, bool PAGE, int NB, bool HM, bool LISTED>
+__global__ __launch_bounds__(256) void score_group_kernel(const u32x4* __restrict__ rows, const uint16_t* __restrict__ q,
+                                                          float* __restrict__ out, int N, int H, int hshift, int B, int G,
+                                                          const int32_t* __restrict__ row_ids, int M, uint32_t* __restrict__ dev_flags) {
+    constexpr int RPW = 64 / LPR, UNROLL = 4, RPB = 4 * UNROLL * RPW, CH = LPR;
+    constexpr int D = PAGE ? CH * 4 : CH * 8;                 // head dimension
+    static_assert(LPR >= 8 && LPR <= 32, "");
+    // chunk c of stream s: channels 0..3 at [s][0][c], 4..7 at [s][1][c] -- the lanes of a row read consecutive 16-byte slots
+    __shared__ float4 weights[NB][2][CH];
+    const int b0 = (int)blockIdx.z * NB;
+    const int h = HM ? (int)(blockIdx.x & (H - 1)) : (int)blockIdx.y;
+    const int bx = HM ? (int)(blockIdx.x >> hshift) : (int)blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sub = lane % LPR, grp = lane / LPR;
+    const int nout = LISTED ? M : N;
+    const int row0 = bx * RPB + wave * UNROLL * RPW + grp;
+    const u32x4* base = rows + (size_t)h * N * CH + sub;
+
+    u32x4 x[UNROLL];
+    bool use[UNROLL];
+    if (LISTED) {
+        const int32_t* ids = row_ids + (size_t)h * M;
+        int src[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) src[u] = ids[min(row0 + u * RPW, M - 1)];
+        bool bad = false;
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            use[u] = (uint32_t)src[u] < (uint32_t)N;          // an id outside [0, N) scores 0 and is flagged
+            bad |= !use[u];
+            x[u] = __builtin_nontemporal_load(base + (size_t)(use[u] ? src[u] : 0) * CH);
+        }
+        if (bad) atomicOr(dev_flags, SWARM_DEV_BAD_ENTRY);
+    } else {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) x[u] = __builtin_nontemporal_load(base + (size_t)min(row0 + u * RPW, N - 1) * CH);
+    }
+
+    // fold: item i = channel pair i % (D / 2) of stream i / (D / 2); a page query's pair makes two, clamped from above and below
+    constexpr int PAIRS = D / 2;
+#pragma unroll
+    for (int i0 = 0; i0 < NB * PAIRS; i0 += 256) {
+        const int i = i0 + (int)threadIdx.x;
+        if (i < NB * PAIRS) {
+            const int s = i / PAIRS, c = i % PAIRS;
+            const uint32_t* qp = reinterpret_cast<const uint32_t*>(q + ((size_t)min(b0 + s, B - 1) * H + h) * (size_t)G * D) + c;
+            float a0 = 0.f, a1 = 0.f, m0 = 0.f, m1 = 0.f;
+            for (int g0 = 0; g0 < G; g0 += 4) {
+                uint32_t v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = qp[(size_t)min(g0 + u, G - 1) * PAIRS];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float f0 = g0 + u < G ? bf16_lo(v[u]) : 0.f, f1 = g0 + u < G ? bf16_hi(v[u]) : 0.f;
+                    if (PAGE) {
+                        a0 += fminf(f0, 0.f);
+                        a1 += fminf(f1, 0.f);
+                        m0 += fmaxf(f0, 0.f);
+                        m1 += fmaxf(f1, 0.f);
+                    } else {
+                        a0 += f0;
+                        a1 += f1;
+                    }
+                }
+            }
+            const int chunk = c >> 2, half = (c >> 1) & 1, pos = (c & 1) * 2;
+            float* w = reinterpret_cast<float*>(&weights[s][half][chunk]) + pos;
+            w[0] = a0;
+            w[1] = a1;
+            if (PAGE) {
+                w = reinterpret_cast<float*>(&weights[s][half][chunk + CH / 2]) + pos;
+                w[0] = m0;
+                w[1] = m1;
+            }
+        }
+    }
+    __syncthreads();
+    if (LISTED) {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+            if (!use[u]) x[u] = u32x4{0, 0, 0, 0};
+    }
+    const int n = row0 + reduced_row(lane) * RPW;
+#pragma unroll
+    for (int s = 0; s < NB; ++s) {
+        const float4 lo = weights[s][0][sub], hi = weights[s][1][sub];
+        const float w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        float p[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) p[u] = dot8(x[u], w);
+        const float v = reduce_rows<LPR>(p, lane);
+        if (sub < UNROLL && n < nout && b0 + s < B) out[((size_t)(b0 + s) * H + h) * nout + n] = v;
+    }
 }
 
 template <int LPR, int NCH, bool PAGE>
@@ -258,14 +371,46 @@ void launch_lean(hipStream_t st, const swarm_keys* keys, const void* q, int B, f
                        static_cast<const uint16_t*>(q), scores, keys->N, keys->H, __builtin_ctz(keys->H));
 }
 
+template <int LPR, bool PAGE, int NB, bool LISTED>
+void launch_group_nb(hipStream_t st, const swarm_keys* keys, const void* q, int B, float* scores, const int32_t* row_ids, int M,
+                     uint32_t* dev_flags) {
+    constexpr int RPB = 4 * 4 * (64 / LPR);
+    const int gxn = ((LISTED ? M : keys->N) + RPB - 1) / RPB, nz = (B + NB - 1) / NB;
+    const u32x4* rows = static_cast<const u32x4*>(keys->data);
+    const uint16_t* qq = static_cast<const uint16_t*>(q);
+    if ((keys->H & (keys->H - 1)) == 0)                       // power of two: heads fastest over the workgroup id
+        hipLaunchKernelGGL((score_group_kernel<LPR, PAGE, NB, true, LISTED>), dim3(gxn * keys->H, 1, nz), dim3(256), 0, st, rows, qq, scores,
+                           keys->N, keys->H, __builtin_ctz(keys->H), B, keys->G, row_ids, M, dev_flags);
+    else
+        hipLaunchKernelGGL((score_group_kernel<LPR, PAGE, NB, false, LISTED>), dim3(gxn, keys->H, nz), dim3(256), 0, st, rows, qq, scores,
+                           keys->N, keys->H, 0, B, keys->G, row_ids, M, dev_flags);
+}
+
+template <int LPR, bool PAGE>
+void launch_group(hipStream_t st, const swarm_keys* keys, const void* q, int B, float* scores, const int32_t* row_ids, int M,
+                  uint32_t* dev_flags) {
+    if (row_ids) {
+        if (B == 1) launch_group_nb<LPR, PAGE, 1, true>(st, keys, q, B, scores, row_ids, M, dev_flags);
+        else launch_group_nb<LPR, PAGE, 4, true>(st, keys, q, B, scores, row_ids, M, dev_flags);
+    } else {
+        if (B == 1) launch_group_nb<LPR, PAGE, 1, false>(st, keys, q, B, scores, row_ids, M, dev_flags);
+        else if (B == 2) launch_group_nb<LPR, PAGE, 2, false>(st, keys, q, B, scores, row_ids, M, dev_flags);
+        else launch_group_nb<LPR, PAGE, 4, false>(st, keys, q, B, scores, row_ids, M, dev_flags);
+    }
+}
+
 template <bool PAGE>
 void dispatch(hipStream_t st, const swarm_keys* keys, const void* q, int B, float* scores, int CH, const int32_t* row_ids, int M,
               uint32_t* dev_flags) {
-    if (!row_ids && keys->G == 1 && (keys->H & (keys->H - 1)) == 0) {      // the decode path's shapes: the lean kernel
+    if (!row_ids && keys->G == 1 && B == 1 && (keys->H & (keys->H - 1)) == 0) {      // one stream, no grouped heads: the lean kernel
         if (CH == 32) return launch_lean<32, PAGE>(st, keys, q, B, scores);
         if (CH == 16) return launch_lean<16, PAGE>(st, keys, q, B, scores);
         if (CH == 8) return launch_lean<8, PAGE>(st, keys, q, B, scores);
     }
+    // the other calls with rows of these lengths (token keys of d = 64, 128, 256, page rows of d = 32, 64, 128)
+    if (CH == 32) return launch_group<32, PAGE>(st, keys, q, B, scores, row_ids, M, dev_flags);
+    if (CH == 16) return launch_group<16, PAGE>(st, keys, q, B, scores, row_ids, M, dev_flags);
+    if (CH == 8) return launch_group<8, PAGE>(st, keys, q, B, scores, row_ids, M, dev_flags);
     if (CH > 64) return launch_one<64, 2, PAGE>(st, keys, q, B, scores, CH, row_ids, M, dev_flags);
     if (CH > 32) return launch_one<64, 1, PAGE>(st, keys, q, B, scores, CH, row_ids, M, dev_flags);
     if (CH > 16) return launch_one<32, 1, PAGE>(st, keys, q, B, scores, CH, row_ids, M, dev_flags);
@@ -449,7 +594,6 @@ swarm_status launch_score(swarm_ctx* ctx, const swarm_keys* keys, const void* q,
     const bool page = keys->kind == SWARM_KEYS_PAGE_MINMAX;
     const int L = page ? 2 * keys->d : keys->d;
     const int CH = L / 8;
-    // many streams: matrix-core path (row lengths of 128 and 256 values, i.e. d = 128 or page rows of d = 64 / 128)
     // many streams: matrix-core path (row lengths of 128 and 256 values, i.e. d = 128 or page rows of d = 64 / 128)
     if (score_is_batched(keys, B, row_ids != nullptr)) {
         if (page) return L == 256 ? launch_batched<16, true>(ctx, keys, q, B, scores) : launch_batched<8, true>(ctx, keys, q, B, scores);

@@ -90,3 +90,31 @@ def test_trace_spans_and_alignment(sw, rows, k, N, shift):
     assert np.array_equal(Cd.cpu().numpy(), ref) and int(tot[0]) == rows * k * k
     assert np.array_equal(rho.cpu().numpy(), oracle.density(ref, tau, 0, nthreads=8)[0])
     assert sw.device_status() == 0
+
+
+@pytest.mark.parametrize("unit,d,H,G,B,N", [
+    ("page", 128, 8, 4, 4, 33), ("page", 128, 1, 3, 3, 31), ("page", 128, 3, 5, 2, 64), ("page", 64, 2, 4, 1, 65), ("page", 32, 4, 2, 7, 129),
+    ("token", 256, 2, 1, 2, 32), ("token", 128, 5, 1, 1, 63), ("token", 128, 2, 8, 5, 97), ("token", 64, 1, 4, 9, 127), ("token", 64, 6, 1, 4, 1)])
+def test_grouped_and_few_stream_scores(sw, unit, d, H, G, B, N):
+    """The sweep that shares a read of the keys between streams and folds grouped heads once per workgroup: partial groups of
+    streams, heads that are not a power of two, rows past the last workgroup; whole sweeps and row lists with a bad id."""
+    cfg = W.CONFIGS["llama8b_32k"].scaled(N=N, k=1, T=1, H=H, G=G, B=B, d=d, unit=unit, page_size=16 if unit == "page" else 1)
+    K, q = W.keys(cfg), W.queries(cfg, 0, 1)[0]
+    flat = torch.full((B * H * N + 64,), -7.5, dtype=torch.float32, device="cuda")
+    sw.score(unit, dev(K), dev(q), G=G, out_scores=flat[:B * H * N].view(B, H, N))
+    _, ref64, ab = oracle.score(unit, K, q, G)
+    # fp32 sums of exact products of bf16 rows and fp32 weights: one rounding per addition (row and heads), each below 2^-24 of the terms
+    tol = (d * (2 if unit == "page" else 1) + G) * 2.0 ** -24 * ab
+    assert (np.abs(flat[:B * H * N].view(B, H, N).cpu().numpy() - ref64) <= tol).all()
+    assert (flat[B * H * N:] == -7.5).all()
+    M = 45
+    ids = np.random.default_rng(N).integers(0, N, (H, M)).astype(np.int32)
+    ids[:, 7] = N
+    _, sc = sw.score_select_indexed(unit, dev(K), dev(ids), dev(q), 1, G=G, want_scores=True)
+    h = np.arange(H)[:, None]
+    ok = np.arange(M) != 7
+    sc = sc.cpu().numpy()
+    assert (np.abs(sc - ref64[:, h, np.minimum(ids, N - 1)]) <= tol[:, h, np.minimum(ids, N - 1)])[..., ok].all()
+    assert (sc[..., 7] == 0).all()
+    from paper_2603_17803_amd import binding
+    assert sw.device_status() == binding.SWARM_DEV_BAD_ENTRY
