@@ -118,3 +118,24 @@ def test_grouped_and_few_stream_scores(sw, unit, d, H, G, B, N):
     assert (sc[..., 7] == 0).all()
     from paper_2603_17803_amd import binding
     assert sw.device_status() == binding.SWARM_DEV_BAD_ENTRY
+
+
+@pytest.mark.parametrize("Sc,Nc,most,cap", [
+    (1, 1, 5, 7), (3, 33, 0, 4), (31, 64, 1, 31), (32, 1024, 16, 300), (256, 257, 9, 3000), (257, 8193, 4, 2000), (2048, 9000, 7, 20000),
+    (2048, 500, 7, 1000), (2049, 9000, 7, 20000), (300, 1 << 18, 3, 1000)])
+def test_expansion_edges(sw, Sc, Nc, most, cap):
+    """Picks on both sides of the listed form, repeated and skipped ones, empty clusters, bitmaps of many words, truncation."""
+    H, groups = 2, 4
+    rng = np.random.default_rng(Sc * 7 + Nc)
+    sizes = rng.integers(0, most + 1, (H, Nc))
+    off = np.zeros((H, Nc + 1), np.int32)
+    off[:, 1:] = np.cumsum(sizes, 1)
+    E = max(1, int(off.max()))
+    ent = rng.integers(0, 1 << 20, (H, E)).astype(np.int32)
+    picks = rng.integers(0, Nc, (groups, Sc)).astype(np.int32)
+    picks[rng.random((groups, Sc)) < 0.1] = -1
+    entries, count = sw.expand_clusters(dev(picks), H, Nc, dev(off), dev(ent), cap)
+    ref, ref_n = oracle.expand_clusters(picks, H, Nc, off, ent, max(cap, E))           # the oracle refuses to truncate
+    assert np.array_equal(entries.cpu().numpy(), ref[:, :cap]) and np.array_equal(count.cpu().numpy(), np.minimum(ref_n, cap))
+    from paper_2603_17803_amd import binding
+    assert sw.device_status() == (binding.SWARM_DEV_CAP if ref_n.max() > cap else 0)
