@@ -68,7 +68,7 @@ struct swarm_ctx {
 swarm_status swarm_check_score_args(swarm_ctx* ctx, const char* fn, const swarm_keys* keys, const void* q, int32_t B);
 // Resolves this device's copy of the library's static scratch (called by swarm_create with the device current).
 swarm_status swarm_static_scratch_init(swarm_ctx* ctx);
-size_t select_cand_bytes(int64_t rows, int N, int k, bool keyed);   // scratch the sliced selection takes for its winners (0: not sliced)
+size_t select_cand_bytes(int64_t rows, int N, int k, bool scored);   // scratch the sliced selection takes for its winners (0: not sliced)
 
 // Grows a scratch buffer to at least `bytes` (never shrinks).  Allocation synchronises the stream.
 swarm_status swarm_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes);
@@ -89,7 +89,7 @@ swarm_status launch_select(swarm_ctx* ctx, const float* scores, int64_t rows, in
 bool select_uses_slices(int64_t rows, int N, int k);   // long rows, few of them: sliced two-stage selection
 struct swarm_winners {          // what the first stage of the sliced selection left for the second
     int32_t* ids = nullptr;     // [rows][stride], M of them per row, ascending
-    uint32_t* keys = nullptr;   // their order keys, laid out the same; nullptr where the scratch had no room
+    float* scores = nullptr;    // their scores, laid out the same; nullptr where the scratch had no room
     int M = 0, stride = 0;
 };
 swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t rows, int N, int k, swarm_winners* out,

@@ -376,13 +376,14 @@ struct MapLds {
 // When the head's lookup tables are small they are staged in LDS by one burst of independent loads,
 // so that the kernel pays one memory round trip instead of three dependent ones (selection ->
 // cluster of entry -> replica row).  PRESTAGED: the caller has already filled the staged tables,
-// cleared the bitmap and synchronised, and `sel` points into LDS.
+// cleared the bitmap and synchronised, and `sel` points into LDS; or it has set the activated clusters' bits as well (merged),
+// resident ones among them: those are left out through the bitmap `skip`.
 // BIG: the kernel is meant for long lists (thousands of merged picks, hundreds of clusters): the per-item pass and
 // the SSD adjacency run on every thread and the merge marks bytes.  The short-list kernels leave that code out --
 // it is not only unused there, its mere presence between the phases cost them 0.25 us per launch.
 template <int NT, bool PRESTAGED, bool BIG, bool STRIDED = false>
 __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int32_t* __restrict__ sel, uint32_t* smem,
-                                          int stage_e2c, int stage_tab) {
+                                          int stage_e2c, int stage_tab, bool merged = false, const uint32_t* skip = nullptr) {
     // position of the group's s-th entry behind `sel`
     auto at = [&](int s0) __attribute__((always_inline)) {
         if (!STRIDED) return s0;
@@ -512,9 +513,11 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
             for (int u = 0; u < MB; ++u) set_bit(c[u]);
         }
     };
-    if (stage_e2c) merge_all(std::true_type{});
-    else merge_all(std::false_type{});
-    __syncthreads();
+    if (!(PRESTAGED && merged)) {
+        if (stage_e2c) merge_all(std::true_type{});
+        else merge_all(std::false_type{});
+        __syncthreads();
+    }
     if (byte_marks) {
         for (int base = wave * 64; base < a.Nc; base += NT) {            // 64 clusters per wave and pass: two bitmap words
             const uint64_t set = __ballot(marks[base + lane] != 0);      // bytes past Nc were cleared and are never marked
@@ -570,7 +573,8 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     for (int s0 = 0; s0 < (par_compact ? 0 : nslices); s0 += 64) {
         const int sl = s0 + lane;
         const int w = sl >> pw_shift, sh = (sl & ((1 << pw_shift) - 1)) * sbits;
-        uint32_t bits = (sl < nslices) ? ((bitmap[w] >> sh) & (sbits == 32 ? 0xffffffffu : (1u << sbits) - 1u)) : 0u;
+        const uint32_t word = sl < nslices ? bitmap[w] & ~(PRESTAGED && !BIG && skip ? skip[w] : 0u) : 0u;
+        uint32_t bits = (sl < nslices) ? ((word >> sh) & (sbits == 32 ? 0xffffffffu : (1u << sbits) - 1u)) : 0u;
         uint32_t total;
         uint32_t pos = m + wave_excl_scan(__popc(bits), &total);
         while (bits) {
@@ -870,66 +874,107 @@ __global__ __launch_bounds__(NT) void map_requests_kernel(MapArgs a, int stage_e
     map_group<NT, false, (NT > 256), STRIDED>(a, g, sel, smem, stage_e2c, stage_tab);
 }
 
+// Copies n words to LDS through registers in two steps, so that the loads are in flight while something else runs: up to 4 VECS
+// words per thread, 16 bytes at a time (the source may start at any word), the last n % 4 one by one.
+typedef int v4i_words __attribute__((ext_vector_type(4), aligned(4)));
+template <int NT, int VECS>
+struct TableInFlight {
+    v4i_words v[VECS];
+    int32_t rest;
+    __device__ __forceinline__ void load(const int32_t* __restrict__ src, int n) {
+        const int tid = threadIdx.x;
+#pragma unroll
+        for (int u = 0; u < VECS; ++u)
+            if (tid + u * NT < (n >> 2)) v[u] = reinterpret_cast<const v4i_words*>(src)[tid + u * NT];
+        if (tid < (n & 3)) rest = src[(n & ~3) + tid];
+    }
+    __device__ __forceinline__ void store(int32_t* dst, int n) const {
+        const int tid = threadIdx.x;
+#pragma unroll
+        for (int u = 0; u < VECS; ++u)
+            if (tid + u * NT < (n >> 2)) reinterpret_cast<int4*>(dst)[tid + u * NT] = make_int4(v[u].x, v[u].y, v[u].z, v[u].w);
+        if (tid < (n & 3)) dst[(n & ~3) + tid] = rest;
+    }
+};
+
 // Selection and request mapping of one decode step of a single stream in one kernel: block h selects
-// the k entries of head h (selcore::block_select, into LDS), writes them out, and maps them.  The
-// lookup tables of the mapping do not depend on the selection: their loads are issued first and are
-// in flight while the selection runs.  Per thread: up to 2 x 16 bytes of the entry->cluster table,
-// 16 bytes of the replica table and 16 bytes of the weights (the host stages a table only if it fits
-// that and is 16-byte aligned).
-// CAND: second stage of the sliced selection of a long row -- the keys are the scores of the M listed winners of
+// the k entries of head h (selcore::block_select), writes them out, and maps them.  The lookup tables of the mapping do not
+// depend on the selection: their loads are issued with the scores', and they are parked in LDS after the selection's
+// histogram.  Then a thread that finds a selected entry writes it out and marks its cluster on the spot: the merge needs no
+// list of the selection, no pass over it and no barrier of its own (parked after the selection, merged from a list in LDS: 17.6
+// instead of 17.2 us per decode step over 8 x 8192 pages, scoring included).  Clusters in DRAM are marked like the others and left out when the marks are compacted.
+// An entry->cluster table too large for LDS is read through the list of the selection, all look-ups of a batch in flight.
+// CAND: second stage of the sliced selection of a long row -- the scores are those of the M listed winners of
 // the row's slices (ascending entry id), and the selected list positions are turned back into entry ids.
 template <int IPT, bool CAND, int NT = selcore::NT>
 __global__ __launch_bounds__(NT) void select_map_kernel(const float* __restrict__ scores, int N, int k,
                                                         int32_t* __restrict__ out_idx, MapArgs a, int stage_e2c,
                                                         int stage_tab, int sel_off, const int32_t* __restrict__ cand,
-                                                        const uint32_t* __restrict__ cand_key, int cand_stride, int M) {
+                                                        const float* __restrict__ cand_score, int cand_stride, int M) {
     __shared__ selcore::SmemT<NT> sm;
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     const int tid = threadIdx.x;
     const int h = blockIdx.x;                                 // one stream: group = head
     const int64_t cbase = (int64_t)h * a.Nc;
     const MapLds L(smem, a, stage_e2c, stage_tab);
+    constexpr bool IDS = CAND && IPT <= 16;                   // winners' ids in registers
 
     // the scores first (the selection waits for them), then the tables (needed only after it)
-    int32_t* sel_lds = reinterpret_cast<int32_t*>(smem + sel_off);
-    uint32_t key[IPT];
+    int32_t* sel_lds = reinterpret_cast<int32_t*>(smem + sel_off);      // the selection's list; with the direct merge: the resident clusters' bits
+    float x[IPT];
+    int32_t id[IDS ? IPT : 1];
     const int32_t* c = CAND ? cand + (size_t)h * cand_stride : nullptr;
-    if (CAND) {
-        selcore::load_winner_keys<IPT>(scores + (size_t)h * N, c, cand_key ? cand_key + (size_t)h * cand_stride : nullptr, M, key);
+    if constexpr (CAND) {
+        selcore::load_winners<IPT>(scores + (size_t)h * N, c, cand_score ? cand_score + (size_t)h * cand_stride : nullptr, M, x);
+        if constexpr (IDS) selcore::load_winner_ids<IPT>(c, M, id);
     } else {
-        selcore::load_keys<IPT>(scores + (size_t)h * N, N, key);
+        selcore::load_scores<IPT>(scores + (size_t)h * N, N, x);
     }
-    int4 r_e2c[2] = {make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0)}, r_rep = make_int4(0, 0, 0, 0), r_wgt = make_int4(0, 0, 0, 0);
-    const int n4_e2c = a.N >> 2, n4_rep = (a.Nc * a.R) >> 2, n4_wgt = a.Nc >> 2;
-    if (stage_e2c) {
-        const int4* src = reinterpret_cast<const int4*>(a.e2c + (size_t)h * a.N);
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            if (tid + u * NT < n4_e2c) r_e2c[u] = src[tid + u * NT];
-    }
+    TableInFlight<NT, 2> t_e2c;
+    TableInFlight<NT, 1> t_rep, t_wgt;
+    if (stage_e2c) t_e2c.load(a.e2c + (size_t)h * a.N, a.N);
     if (stage_tab) {
-        if (tid < n4_rep) r_rep = reinterpret_cast<const int4*>(a.replicas + cbase * a.R)[tid];
-        if (a.weight && tid < n4_wgt) r_wgt = reinterpret_cast<const int4*>(a.weight + cbase)[tid];
+        t_rep.load(a.replicas + cbase * a.R, a.Nc * a.R);
+        if (a.weight) t_wgt.load(a.weight + cbase, a.Nc);
     }
-    for (int w = tid; w < L.nwords; w += NT) L.bitmap[w] = 0;
-
-    selcore::block_select<IPT, NT>(key, CAND ? M : N, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) {
-        sel_lds[pos] = CAND ? c[tid * IPT + e] : tid * IPT + e;
-    });
-
-    if (stage_e2c) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            if (tid + u * NT < n4_e2c) reinterpret_cast<int4*>(L.s_e2c)[tid + u * NT] = r_e2c[u];
-    }
-    if (stage_tab) {
-        if (tid < n4_rep) reinterpret_cast<int4*>(L.s_rep)[tid] = r_rep;
-        if (a.weight) { if (tid < n4_wgt) reinterpret_cast<int4*>(L.s_wgt)[tid] = r_wgt; }
-        else for (int i = tid; i < a.Nc; i += NT) L.s_wgt[i] = 1;
-    }
+    const bool direct = !CAND && stage_e2c;
+    uint32_t* skip = direct && a.resident ? reinterpret_cast<uint32_t*>(sel_lds) : nullptr;
+    auto meanwhile = [&]() __attribute__((always_inline)) {
+        for (int w = tid; w < L.nwords; w += NT) {
+            L.bitmap[w] = 0;
+            if (skip) {                                       // the head's resident bits, shifted to start at its cluster 0
+                const int64_t first = cbase + 32 * (int64_t)w, words = ((int64_t)a.H * a.Nc + 31) >> 5;
+                const uint32_t r0 = a.resident[first >> 5], r1 = (first >> 5) + 1 < words ? a.resident[(first >> 5) + 1] : 0u;
+                skip[w] = __builtin_amdgcn_alignbit(r1, r0, (uint32_t)(first & 31));
+            }
+        }
+        if (stage_e2c) t_e2c.store(L.s_e2c, a.N);
+        if (stage_tab) {
+            t_rep.store(L.s_rep, a.Nc * a.R);
+            if (a.weight) t_wgt.store(L.s_wgt, a.Nc);
+            else for (int i = tid; i < a.Nc; i += NT) L.s_wgt[i] = 1;
+        }
+    };
+    uint32_t flags = 0;
+    selcore::block_select<IPT, NT, IDS>(x, CAND ? M : N, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) {
+        if constexpr (CAND) {
+            if constexpr (IDS) sel_lds[pos] = id[e];
+            else sel_lds[pos] = c[tid * IPT + e];
+        } else if (direct) {
+            const int entry = tid * IPT + e;
+            out_idx[(size_t)h * k + pos] = entry;
+            const int32_t cl = L.s_e2c[entry];
+            if ((uint32_t)cl < (uint32_t)a.Nc) atomicOr(&L.bitmap[cl >> 5], 1u << (cl & 31));
+            else flags |= SWARM_DEV_BAD_CLUSTER;
+        } else {
+            sel_lds[pos] = tid * IPT + e;
+        }
+    }, meanwhile);
+    if (flags) atomicOr(a.dev_flags, flags);
     __syncthreads();
-    for (int i = tid; i < k; i += NT) out_idx[(size_t)h * k + i] = sel_lds[i];
-    map_group<NT, true, CAND>(a, h, sel_lds, smem, stage_e2c, stage_tab);
+    if (!direct)
+        for (int i = tid; i < k; i += NT) out_idx[(size_t)h * k + i] = sel_lds[i];
+    map_group<NT, true, CAND>(a, h, sel_lds, smem, stage_e2c, stage_tab, direct, skip);
 }
 
 }  // namespace
@@ -981,13 +1026,13 @@ swarm_status launch_select_map(swarm_ctx* ctx, const float* scores, int H, int N
     lds = (lds + 15) / 16 * 16;
     int stage_tab = 0, stage_e2c = 0;
     const size_t tab_bytes = ((size_t)Nc * R + 3) / 4 * 16 + ((size_t)Nc + 3) / 4 * 16, e2c_bytes = ((size_t)N + 3) / 4 * 16;
-    const bool tab_regs = (Nc * R) % 4 == 0 && Nc % 4 == 0 && Nc * R <= 4 * NT && Nc <= 4 * NT &&
-                          (reinterpret_cast<uintptr_t>(replicas) & 15) == 0 && (!weight || (reinterpret_cast<uintptr_t>(weight) & 15) == 0);
-    const bool e2c_regs = N % 4 == 0 && N <= 8 * NT && (reinterpret_cast<uintptr_t>(e2c) & 15) == 0;
+    const bool tab_regs = (int64_t)Nc * R <= 4 * NT;       // TableInFlight: one vector per thread, two of the entry->cluster table
+    const bool e2c_regs = N <= 8 * NT;
     if (tab_regs && lds + tab_bytes <= budget) { stage_tab = 1; lds += tab_bytes; }
     if (e2c_regs && lds + e2c_bytes <= budget) { stage_e2c = 1; lds += e2c_bytes; }
-    const int sel_off = (int)(lds / 4);
-    lds += (size_t)k * 4;
+    const int sel_off = (int)(lds / 4);                    // the selection's list, or (never both) the resident clusters' bits
+    const size_t skip_words = resident ? ((size_t)Nc + 31) / 32 : 0;
+    lds += ((size_t)k > skip_words ? (size_t)k : skip_words) * 4;
     if (lds > budget) return SWARM_OK;
     lds = (lds + 15) / 16 * 16;
     if (lds + (size_t)cap * 8 <= budget) { a.split_off = (int)(lds / 4); lds += (size_t)cap * 8; }
@@ -997,7 +1042,7 @@ swarm_status launch_select_map(swarm_ctx* ctx, const float* scores, int H, int N
         swarm_winners w;
         const swarm_status rc = launch_select_slices(ctx, scores, H, N, k, &w);
         if (rc != SWARM_OK) return rc;
-#define SWARM_MERGEMAP(IPT) hipLaunchKernelGGL((select_map_kernel<IPT, true>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, w.ids, w.keys, w.stride, w.M)
+#define SWARM_MERGEMAP(IPT) hipLaunchKernelGGL((select_map_kernel<IPT, true>), grid, block, lds, st, scores, N, k, out_idx, a, stage_e2c, stage_tab, sel_off, w.ids, w.scores, w.stride, w.M)
         if (w.M <= 4 * NT) SWARM_MERGEMAP(4);
         else if (w.M <= 8 * NT) SWARM_MERGEMAP(8);
         else if (w.M <= 16 * NT) SWARM_MERGEMAP(16);

@@ -52,7 +52,7 @@ extern "C" swarm_status swarm_score_select_static(swarm_ctx* ctx, const swarm_ke
 
     const int64_t rows = (int64_t)B * keys->H;
     const size_t scores_bytes = align256(sizeof(float) * (size_t)rows * keys->N);
-    // the winners' order keys only where they fit: they save a gather, nothing depends on them
+    // the winners' scores only where they fit: they save a gather, nothing depends on them
     size_t cand_bytes = align256(select_cand_bytes(rows, keys->N, k, true));
     if (scores_bytes + cand_bytes > SCRATCH_BYTES) cand_bytes = align256(select_cand_bytes(rows, keys->N, k, false));
     const size_t need = scores_bytes + cand_bytes;

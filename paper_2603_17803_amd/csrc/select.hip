@@ -14,10 +14,11 @@ template <int IPT, int NTH = selcore::NT>
 __global__ __launch_bounds__(NTH) void topk_select_kernel(const float* __restrict__ scores, int N, int k,
                                                            int32_t* __restrict__ out_idx) {
     __shared__ selcore::SmemT<NTH> sm;
-    uint32_t key[IPT];
-    selcore::load_keys<IPT>(scores + (size_t)blockIdx.x * N, N, key);
+    float x[IPT];
+    selcore::load_scores<IPT>(scores + (size_t)blockIdx.x * N, N, x);
     int32_t* out = out_idx + (size_t)blockIdx.x * k;
-    selcore::block_select<IPT, NTH>(key, N, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) { out[pos] = (int)threadIdx.x * IPT + e; });
+    selcore::block_select<IPT, NTH>(x, N, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) { out[pos] = (int)threadIdx.x * IPT + e; },
+                                    []() {});
 }
 
 // ---- long rows, few of them: two stages -----------------------------------------------------------
@@ -27,40 +28,41 @@ __global__ __launch_bounds__(NTH) void topk_select_kernel(const float* __restric
 // among the slices' winners.  An entry dropped by its slice is beaten by that many entries of the same
 // slice, each with a higher score or an equal score and a lower index, so it cannot belong to the
 // row's result; the winners are listed in ascending entry id, so position order is index order and
-// the lowest-index tie-break carries over.  The winners' order keys are kept beside their ids where the scratch has room for
-// them (cand_key), so that the second stage reads one contiguous list instead of gathering scores through the ids.
+// the lowest-index tie-break carries over.  The winners' scores are kept beside their ids where the scratch has room for
+// them (cand_score), so that the second stage reads one contiguous list instead of gathering scores through the ids.
 constexpr int SLICE = 8192, SLICE_IPT = 8;
 
 __global__ __launch_bounds__(selcore::NT) void topk_slice_kernel(const float* __restrict__ scores, int N, int k,
-                                                                 int32_t* __restrict__ cand, uint32_t* __restrict__ cand_key,
+                                                                 int32_t* __restrict__ cand, float* __restrict__ cand_score,
                                                                  int cand_stride) {
     __shared__ selcore::Smem sm;
     const int p = blockIdx.x;
     const int64_t row = blockIdx.y;
     const int lo = p * SLICE, len = min(SLICE, N - lo);
     const int kk = min(k, len);
-    uint32_t key[SLICE_IPT];
-    selcore::load_keys<SLICE_IPT>(scores + row * N + lo, len, key);
+    float x[SLICE_IPT];
+    selcore::load_scores<SLICE_IPT>(scores + row * N + lo, len, x);
     // slices before this one are full, so their winner counts are min(k, SLICE) each
     const size_t at = row * cand_stride + (size_t)p * min(k, SLICE);
-    selcore::block_select<SLICE_IPT, selcore::NT, true>(key, len, kk, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) {
+    selcore::block_select<SLICE_IPT, selcore::NT, true>(x, len, kk, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) {
         cand[at + pos] = lo + (int)threadIdx.x * SLICE_IPT + e;
-        if (cand_key) cand_key[at + pos] = key[e];
-    });
+        if (cand_score) cand_score[at + pos] = x[e];
+    }, []() {});
 }
 
 template <int IPT>
 __global__ __launch_bounds__(selcore::NT) void topk_merge_kernel(const float* __restrict__ scores, int N, int k,
-                                                                 const int32_t* __restrict__ cand, const uint32_t* __restrict__ cand_key,
+                                                                 const int32_t* __restrict__ cand, const float* __restrict__ cand_score,
                                                                  int cand_stride, int M, int32_t* __restrict__ out_idx) {
     __shared__ selcore::Smem sm;
     const int64_t row = blockIdx.x;
     const int32_t* c = cand + row * cand_stride;
-    uint32_t key[IPT];
-    selcore::load_winner_keys<IPT>(scores + row * N, c, cand_key ? cand_key + row * cand_stride : nullptr, M, key);
+    float x[IPT];
+    selcore::load_winners<IPT>(scores + row * N, c, cand_score ? cand_score + row * cand_stride : nullptr, M, x);
     int32_t* out = out_idx + row * k;
     // the list is in ascending id, so ascending positions are ascending ids
-    selcore::block_select<IPT>(key, M, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) { out[pos] = c[(int)threadIdx.x * IPT + e]; });
+    selcore::block_select<IPT>(x, M, k, sm, [&](uint32_t pos, int e) __attribute__((always_inline)) { out[pos] = c[(int)threadIdx.x * IPT + e]; },
+                               []() {});
 }
 
 constexpr int SEL_THREADS = 1024;
@@ -153,11 +155,11 @@ bool select_uses_slices(int64_t rows, int N, int k) {
     return M <= N / 2 && M <= 64 * selcore::NT;
 }
 
-// Scratch for the winners of the sliced selection: their ids, or (keyed) their ids and order keys.
-size_t select_cand_bytes(int64_t rows, int N, int k, bool keyed) {
+// Scratch for the winners of the sliced selection: their ids, or (scored) their ids and scores.
+size_t select_cand_bytes(int64_t rows, int N, int k, bool scored) {
     if (!select_uses_slices(rows, N, k)) return 0;
     const int64_t P = (N + SLICE - 1) / SLICE;
-    return (keyed ? sizeof(int32_t) + sizeof(uint32_t) : sizeof(int32_t)) * (size_t)rows * (size_t)(P * (k < SLICE ? k : SLICE));
+    return (scored ? sizeof(int32_t) + sizeof(uint32_t) : sizeof(int32_t)) * (size_t)rows * (size_t)(P * (k < SLICE ? k : SLICE));
 }
 
 // First stage of the sliced selection: the slices' winners of every row into out->ids ([rows][stride], M of them per row), which
@@ -171,10 +173,10 @@ swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t r
     out->stride = P * per;
     size_t need = select_cand_bytes(rows, N, k, true);
     int32_t* cand = nullptr;
-    bool keyed = true;
+    bool scored = true;
     if (fixed) {
-        keyed = need <= fixed->cand_bytes;
-        if (!keyed) need = select_cand_bytes(rows, N, k, false);
+        scored = need <= fixed->cand_bytes;
+        if (!scored) need = select_cand_bytes(rows, N, k, false);
         if (need > fixed->cand_bytes) {
             snprintf(ctx->err, sizeof(ctx->err), "select: the slices' winners need %zu bytes, the fixed scratch has %zu", need, fixed->cand_bytes);
             return SWARM_EINVAL;
@@ -185,10 +187,10 @@ swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t r
         if (rc != SWARM_OK) return rc;
         cand = ctx->cand;
     }
-    uint32_t* key = keyed ? reinterpret_cast<uint32_t*>(cand + (size_t)rows * out->stride) : nullptr;
+    float* kept = scored ? reinterpret_cast<float*>(cand + (size_t)rows * out->stride) : nullptr;
     out->ids = cand;
-    out->keys = key;
-    hipLaunchKernelGGL(topk_slice_kernel, dim3((unsigned)P, (unsigned)rows), dim3(selcore::NT), 0, ctx->stream, scores, N, k, cand, key,
+    out->scores = kept;
+    hipLaunchKernelGGL(topk_slice_kernel, dim3((unsigned)P, (unsigned)rows), dim3(selcore::NT), 0, ctx->stream, scores, N, k, cand, kept,
                        out->stride);
     return swarm_check_launch(ctx, "topk_slice_kernel");
 }
@@ -201,7 +203,7 @@ swarm_status launch_select(swarm_ctx* ctx, const float* scores, int64_t rows, in
         swarm_winners w;
         const swarm_status rc = launch_select_slices(ctx, scores, rows, N, k, &w, fixed);
         if (rc != SWARM_OK) return rc;
-#define SWARM_MERGE(IPT) hipLaunchKernelGGL(topk_merge_kernel<IPT>, grid, block, 0, st, scores, N, k, w.ids, w.keys, w.stride, w.M, out_idx)
+#define SWARM_MERGE(IPT) hipLaunchKernelGGL(topk_merge_kernel<IPT>, grid, block, 0, st, scores, N, k, w.ids, w.scores, w.stride, w.M, out_idx)
         if (w.M <= 4 * selcore::NT) SWARM_MERGE(4);
         else if (w.M <= 8 * selcore::NT) SWARM_MERGE(8);
         else if (w.M <= 16 * selcore::NT) SWARM_MERGE(16);

@@ -3,10 +3,9 @@
 // Selection step (Section 2.3): the k highest scores of a row, equal scores won by the lower
 // index, result in ascending index order.
 //
-// A block of 1024 threads holds the row as IPT consecutive scores per thread.  Scores are mapped
-// to order-preserving 32-bit keys.  One pass bins every score *linearly in value* between the
-// row's minimum and maximum into 2048 LDS counters (float subtraction, scaling and truncation are
-// all monotone, so bin order agrees with score order); a scan finds the bin b* that holds the k-th
+// A block of 1024 threads holds the row as IPT consecutive scores per thread.  One pass bins every score *linearly in value*
+// between the row's minimum and maximum into 2048 LDS counters (clamping, subtraction, scaling and truncation are all
+// monotone, so bin order agrees with score order); a scan finds the bin b* that holds the k-th
 // largest score.  Bins above b* are selected outright; inside b* (a handful of scores for any
 // smooth distribution) the exact threshold key T and the number of entries equal to T that still
 // belong to the result are found by ranking the candidates against each other, or -- when b*
@@ -14,6 +13,11 @@
 // radix select restricted to b*.  A final ordered compaction (block prefix scan over the
 // contiguous per-thread chunks) writes the indices in ascending order, which also makes the
 // lowest-index tie-break deterministic.
+//
+// A row is one block's work and a block has one compute unit, so what bounds this is instructions per score (four waves per
+// SIMD take 16 cycles for each).  The scores therefore stay floats -- five instructions to bin one -- and only those of b*
+// are mapped to order-preserving 32-bit keys; what is above b* and what is inside is kept as two bit masks per thread.
+// (Every score carried as a key, mapped and mapped back for binning: 5.3 instead of 4.9 us for 32 rows of 4001 scores.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -33,7 +37,7 @@ template <int NTH = NT>
 struct SmemT {
     static constexpr int NW = NTH / 64;
     uint32_t hist[NB];
-    uint32_t cand[CMAX];
+    __attribute__((aligned(16))) uint32_t cand[CMAX];
     uint32_t wave_a[16], wave_b[16];
     __attribute__((aligned(16))) uint32_t wave_kmax[16];
     __attribute__((aligned(16))) uint32_t wave_kmin[16];
@@ -51,20 +55,23 @@ __device__ __forceinline__ uint32_t order_key(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Value used for binning only: finite, and monotone in the key (NaN and -inf share the bottom).
-__device__ __forceinline__ float bin_value(uint32_t key) {
-    const uint32_t bits = (key & 0x80000000u) ? (key & 0x7fffffffu) : ~key;
-    float v = __uint_as_float(bits);
-    if (key == 0u) v = -3.0e38f;
-    v = fminf(fmaxf(v, -3.0e38f), 3.0e38f);
-    return v * 0.25f;                                   // keeps hi - v finite
+// Scores are clamped to +-VMAX for binning, so that a difference of two is finite; what the clamp merges (infinities, NaN with
+// -inf) shares a bin and is told apart by key.
+constexpr float VMAX = 1.5e38f;
+__device__ __forceinline__ float bin_value(float x) { return __builtin_amdgcn_fmed3f(x, -VMAX, VMAX); }     // a NaN becomes -VMAX
+
+__device__ __forceinline__ int bin_of(float x, float hi, float scale) {
+    return (int)fminf((hi - bin_value(x)) * scale, (float)(NB - 1));      // hi - v >= 0: non-increasing in the score
 }
 
-__device__ __forceinline__ int bin_of(uint32_t key, float hi, float scale) {
-    const float x = (hi - bin_value(key)) * scale;      // >= 0, non-increasing in the score
-    return (int)fminf(x, (float)(NB - 1));
+// Monotone unsigned image of a float that is not NaN, and its inverse.
+__device__ __forceinline__ uint32_t plain_key(float f) {
+    const uint32_t u = __float_as_uint(f);
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
-
+__device__ __forceinline__ float plain_value(uint32_t key) {
+    return __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
+}
 
 // Exclusive block scan of two counters at once.  The wave totals (at most 16) are scanned by every wave on its own (lane l
 // reads total l % 16, four DPP steps inside the row of 16 lanes) instead of being read and conditionally added one by one.
@@ -87,34 +94,46 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t a, uint32_t b, uint32_
     eb = ib - b + (wave > 0 ? pb : 0u);
 }
 
-// key[e] is the key of index tid*IPT + e; slots at or beyond N must hold key 0.
+// x[e] is the score of index tid*IPT + e; slots at or beyond N must hold NaN, which ranks below every score.
 // All NTH threads of the block must call this.  emit(pos, e) is called once for each of the k selected entries, by the thread
-// that holds it: pos is its place in the result (ascending index order), e its slot in the thread's run.  EMIT_KEYS: emit
-// needs the entry's key, so the slots are walked unrolled (key[e] stays in its register); otherwise only the set ones are.
-// Short per-thread runs keep every score's bin in a register after the histogram pass (the candidate collection and
-// the compaction then compare small integers); long runs recompute it, their registers hold the keys.
-template <int IPT, int NTH = NT, bool EMIT_KEYS = false, typename Emit>
-__device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, int k, SmemT<NTH>& sm, Emit emit) {
+// that holds it: pos is its place in the result (ascending index order), e its slot in the thread's run.  STATIC_E: emit
+// uses e to index registers, so the slots are walked unrolled; otherwise only the set ones are.
+// meanwhile() is called by every thread after the histogram (what it loaded beside the row has had the time for that to
+// arrive): what it writes to LDS is visible to every emit().
+template <int IPT, int NTH = NT, bool STATIC_E = false, typename Emit, typename Meanwhile>
+__device__ __forceinline__ void block_select(const float (&x)[IPT], int N, int k, SmemT<NTH>& sm, Emit emit, Meanwhile meanwhile) {
     constexpr int NW = NTH / 64;
-    constexpr bool KEEP = IPT <= 32;                    // bins kept in registers
+    constexpr bool KEEP = IPT <= 32;                    // bins kept in registers between the histogram and the masks, not computed again
     constexpr int NBINS_KEPT = KEEP ? IPT : 1;
+    constexpr int NM = (IPT + 31) / 32;                 // mask words per thread
+    constexpr int MB = IPT < 32 ? IPT : 32;             // slots per mask word
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int base = tid * IPT;
 
-    // Row extrema of the binning value.  bin_value is monotone in the key, so they are the binning values of the
-    // largest and the smallest key: integer max / min per score (slots at or beyond N hold key 0, which cannot raise the
-    // maximum and is kept out of the minimum), two conversions at the end.
-    uint32_t kmax = 0u, kmin = 0xffffffffu;
+    // row extrema of the binning value, from the slots that hold an entry
+    float vmax = -VMAX, vmin = VMAX;
+    if (base + IPT <= N) {
 #pragma unroll
-    for (int e = 0; e < IPT; ++e) {
-        kmax = max(kmax, key[e]);
-        kmin = min(kmin, (base + e < N) ? key[e] : 0xffffffffu);
+        for (int e = 0; e < IPT; ++e) {
+            const float v = bin_value(x[e]);
+            vmax = fmaxf(vmax, v);
+            vmin = fminf(vmin, v);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < IPT; ++e) {
+            const float v = bin_value(x[e]);
+            vmax = fmaxf(vmax, v);                      // NaN slots cannot raise it
+            vmin = fminf(vmin, base + e < N ? v : VMAX);
+        }
     }
-    kmax = ~waveops::wave_min_u32(~kmax);
-    kmin = waveops::wave_min_u32(kmin);
+    uint32_t kmax = ~waveops::wave_min_u32(~plain_key(vmax));
+    uint32_t kmin = waveops::wave_min_u32(plain_key(vmin));
     if (lane == 0) { sm.wave_kmax[wave] = kmax; sm.wave_kmin[wave] = kmin; }
 #pragma unroll
     for (int i = 0; i < NB / NTH; ++i) sm.hist[tid + i * NTH] = 0;
+#pragma unroll
+    for (int i = 0; i < CMAX / NTH; ++i) sm.cand[tid + i * NTH] = 0;
     if (tid == 0) { sm.cand_count = 0; sm.thr_key = 0; sm.thr_need = 0xffffffffu; }
     __syncthreads();
     {
@@ -129,20 +148,21 @@ __device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, 
             if (4 * w + 3 < NW) { kmax = max(kmax, a.w); kmin = min(kmin, b.w); }
         }
     }
-    // an empty row (N = 0) leaves kmax < kmin: hi < lo, and the scale below becomes 0
-    const float hi = bin_value(kmax), lo = bin_value(kmin);
+    // an empty row (N = 0) leaves hi < lo, and the scale becomes 0
+    const float hi = plain_value(kmax), lo = plain_value(kmin);
     const float range = hi - lo;
     const float scale = range > 0.f ? fminf((float)NB / range, 1.0e30f) : 0.f;
 
     // value histogram
     int bin[NBINS_KEPT];
-    auto bin_at = [&](int e) __attribute__((always_inline)) { return KEEP ? bin[e] : bin_of(key[e], hi, scale); };
+    auto bin_at = [&](int e) __attribute__((always_inline)) { return KEEP ? bin[e] : bin_of(x[e], hi, scale); };
 #pragma unroll
     for (int e = 0; e < IPT; ++e) {
-        const int b = bin_of(key[e], hi, scale);
+        const int b = bin_of(x[e], hi, scale);
         if (KEEP) bin[e] = b;
         atomicAdd(&sm.hist[b], 1u);
     }
+    meanwhile();
     __syncthreads();
 
     // bin b* holding the k-th largest: cumulative count from bin 0 (highest scores) first reaches k
@@ -166,20 +186,40 @@ __device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, 
     const uint32_t need = (uint32_t)k - sm.above;       // entries of bin b* that belong to the result
     const uint32_t c = sm.hist[bstar];
 
+    // bit e of a word: slot e (+ 32 per word) lies above b* / inside it; a sign bit is shifted in per slot
+    uint32_t take[NM], inside[NM], some_inside = 0;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        uint32_t above = 0, upto = 0;
+#pragma unroll
+        for (int e = MB - 1; e >= 0; --e) {
+            const int b = bin_at(m * 32 + e);
+            above = __builtin_amdgcn_alignbit(above, (uint32_t)(b - bstar), 31);
+            upto = __builtin_amdgcn_alignbit(upto, (uint32_t)(b - bstar - 1), 31);
+        }
+        take[m] = above;
+        inside[m] = upto & ~above;
+        some_inside |= inside[m];
+    }
+
     if (need < c) {
         if (__builtin_expect(c <= (uint32_t)CMAX, 1)) {           // the massive-tie path is laid out off the straight line
             // rank the candidates of b* against each other
+            if (some_inside) {
 #pragma unroll
-            for (int e = 0; e < IPT; ++e)
-                if (bin_at(e) == bstar) sm.cand[atomicAdd(&sm.cand_count, 1u)] = key[e];
+                for (int e = 0; e < IPT; ++e)
+                    if ((inside[e / 32] >> (e & 31)) & 1u) sm.cand[atomicAdd(&sm.cand_count, 1u)] = order_key(x[e]);
+            }
             __syncthreads();
             for (uint32_t t = tid; t < c; t += NTH) {
                 const uint32_t mine = sm.cand[t];
                 uint32_t gt = 0, eq = 0;
-                for (uint32_t j = 0; j < c; ++j) {
-                    const uint32_t other = sm.cand[j];
-                    gt += other > mine;
-                    eq += other == mine;
+                // four at a time; the zeros behind the last one can only look equal to a zero, the lowest key, for which
+                // gt + eq reaches `need` anyway
+                for (uint32_t j = 0; j < c; j += 4) {
+                    const uint4 other = *reinterpret_cast<const uint4*>(&sm.cand[j]);
+                    gt += (other.x > mine) + (other.y > mine) + (other.z > mine) + (other.w > mine);
+                    eq += (other.x == mine) + (other.y == mine) + (other.z == mine) + (other.w == mine);
                 }
                 if (gt < need && need <= gt + eq) { sm.thr_key = mine; sm.thr_need = need - gt; }
             }
@@ -192,9 +232,10 @@ __device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, 
                 if (tid < 256) sm.hist[tid] = 0;
                 __syncthreads();
 #pragma unroll
-                for (int e = 0; e < IPT; ++e)
-                    if (bin_at(e) == bstar && (key[e] & mask) == prefix)
-                        atomicAdd(&sm.hist[(key[e] >> shift) & 255u], 1u);
+                for (int e = 0; e < IPT; ++e) {
+                    const uint32_t key = order_key(x[e]);
+                    if (((inside[e / 32] >> (e & 31)) & 1u) && (key & mask) == prefix) atomicAdd(&sm.hist[(key >> shift) & 255u], 1u);
+                }
                 __syncthreads();
                 if (wave == 0) {
                     const uint32_t h0 = sm.hist[4 * lane], h1 = sm.hist[4 * lane + 1], h2 = sm.hist[4 * lane + 2],
@@ -228,50 +269,44 @@ __device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, 
 
     // ordered compaction.  A score is taken outright when it lies in a bin above b*, or in b* above the threshold key;
     // scores equal to the threshold key are taken in index order until need_eq of them are in.
-    uint32_t gt = 0, eq = 0;
-    uint32_t take_mask = 0, eq_mask = 0;                // bit e (KEEP only; IPT <= 32)
+    uint32_t same[NM];
 #pragma unroll
-    for (int e = 0; e < IPT; ++e) {
-        const int b = bin_at(e);
-        const bool g = (b < bstar) || (b == bstar && key[e] > T);
-        const bool q = (b == bstar && key[e] == T);
-        gt += g;
-        eq += q;
-        if (KEEP) { take_mask |= (uint32_t)g << e; eq_mask |= (uint32_t)q << e; }
+    for (int m = 0; m < NM; ++m) same[m] = 0;
+    if (some_inside) {
+#pragma unroll
+        for (int e = 0; e < IPT; ++e) {
+            if ((inside[e / 32] >> (e & 31)) & 1u) {
+                const uint32_t key = order_key(x[e]);
+                take[e / 32] |= (uint32_t)(key > T) << (e & 31);
+                same[e / 32] |= (uint32_t)(key == T) << (e & 31);
+            }
+        }
     }
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) { gt += __popc(take[m]); eq += __popc(same[m]); }
     uint32_t gt_before, eq_before;
     block_excl_scan2<NTH>(gt, eq, gt_before, eq_before, sm, lane, wave);
     uint32_t pos = gt_before + min(eq_before, need_eq);
-    if (KEEP) {
-        // the equal scores this thread still takes: its first (need_eq - eq_before) of them
-        const uint32_t room = need_eq > eq_before ? need_eq - eq_before : 0u;
-        uint32_t m = eq_mask;
-        for (uint32_t i = 0; i < room && m; ++i) { take_mask |= m & (0u - m); m &= m - 1u; }
-        if constexpr (EMIT_KEYS) {
+    // the equal scores this thread still takes: its first (need_eq - eq_before) of them
+    uint32_t room = need_eq > eq_before ? need_eq - eq_before : 0u;
 #pragma unroll
-            for (int e = 0; e < IPT; ++e) {
-                if ((take_mask >> e) & 1u) {
-                    if (pos < (uint32_t)k) emit(pos, e);                   // pos < k always holds; the guard keeps a slip in bounds
-                    ++pos;
-                }
-            }
-        } else {
-            while (take_mask) {
-                const int e = __ffs(take_mask) - 1;
-                take_mask &= take_mask - 1u;
-                if (pos < (uint32_t)k) emit(pos, e);
-                ++pos;
-            }
-        }
-    } else {
-        uint32_t eq_seen = eq_before;
+    for (int m = 0; m < NM; ++m)
+        for (; room && same[m]; --room) { take[m] |= same[m] & (0u - same[m]); same[m] &= same[m] - 1u; }
+    if constexpr (STATIC_E) {
 #pragma unroll
         for (int e = 0; e < IPT; ++e) {
-            const int b = bin_of(key[e], hi, scale);
-            const bool is_eq = (b == bstar && key[e] == T);
-            const bool take = (b < bstar) || (b == bstar && key[e] > T) || (is_eq && eq_seen < need_eq);
-            eq_seen += is_eq;
-            if (take) {
+            if ((take[e / 32] >> (e & 31)) & 1u) {
+                if (pos < (uint32_t)k) emit(pos, e);                       // pos < k always holds; the guard keeps a slip in bounds
+                ++pos;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            while (take[m]) {
+                const int e = m * 32 + __ffs(take[m]) - 1;
+                take[m] &= take[m] - 1u;
                 if (pos < (uint32_t)k) emit(pos, e);
                 ++pos;
             }
@@ -279,56 +314,66 @@ __device__ __forceinline__ void block_select(const uint32_t (&key)[IPT], int N, 
     }
 }
 
-// Loads IPT consecutive scores of a row into keys (slots beyond N get key 0).
+typedef float f32x4_row __attribute__((ext_vector_type(4), aligned(4)));    // rows of scores are 4-byte aligned; 16-byte loads need no more
+
+// Loads IPT consecutive scores of a row (NaN in the slots beyond N).
 template <int IPT>
-__device__ __forceinline__ void load_keys(const float* __restrict__ row, int N, uint32_t (&key)[IPT]) {
+__device__ __forceinline__ void load_scores(const float* __restrict__ row, int N, float (&x)[IPT]) {
     const int base = threadIdx.x * IPT;
-    if (((reinterpret_cast<uintptr_t>(row) & 15) == 0) && base + IPT <= N) {
-        const float4* p = reinterpret_cast<const float4*>(row + base);
+    if (base + IPT <= N) {
 #pragma unroll
         for (int e = 0; e < IPT / 4; ++e) {
-            const float4 v = p[e];
-            key[4 * e] = order_key(v.x);
-            key[4 * e + 1] = order_key(v.y);
-            key[4 * e + 2] = order_key(v.z);
-            key[4 * e + 3] = order_key(v.w);
+            const f32x4_row v = reinterpret_cast<const f32x4_row*>(row + base)[e];
+            x[4 * e] = v.x;
+            x[4 * e + 1] = v.y;
+            x[4 * e + 2] = v.z;
+            x[4 * e + 3] = v.w;
         }
     } else {
 #pragma unroll
-        for (int e = 0; e < IPT; ++e) key[e] = (base + e < N) ? order_key(row[base + e]) : 0u;
+        for (int e = 0; e < IPT; ++e) x[e] = (base + e < N) ? row[base + e] : __uint_as_float(0x7fc00000u);
     }
 }
 
-// Loads the keys of a thread's IPT consecutive winners (of M, listed in ascending entry id).  keys: their order keys as the
-// slices wrote them; without room for those (nullptr) the winners' scores are gathered.  Every load is clamped to a valid
-// position instead of being branched around, so that all of a thread's loads are in flight together: behind a branch each,
-// the eight of a 65536-entry row's second stage were eight pairs of dependent round trips, 12 of its 23 us.
+// The ids of a thread's IPT consecutive winners of M; slots beyond M repeat the last one.  (One by one, at a stride of IPT words
+// between lanes, they cost a cache line per lane and load: 8 us for the 8192 winners of a 65536-entry row.)
+typedef int i32x4_row __attribute__((ext_vector_type(4), aligned(4)));
 template <int IPT>
-__device__ __forceinline__ void load_winner_keys(const float* __restrict__ row, const int32_t* __restrict__ ids,
-                                                 const uint32_t* __restrict__ keys, int M, uint32_t (&key)[IPT]) {
+__device__ __forceinline__ void load_winner_ids(const int32_t* __restrict__ ids, int M, int32_t (&id)[IPT]) {
     const int base = threadIdx.x * IPT;
-    if (keys && (reinterpret_cast<uintptr_t>(keys) & 15) == 0 && base + IPT <= M) {
-        const uint4* p = reinterpret_cast<const uint4*>(keys + base);
+    if (base + IPT <= M) {
 #pragma unroll
         for (int e = 0; e < IPT / 4; ++e) {
-            const uint4 v = p[e];
-            key[4 * e] = v.x;
-            key[4 * e + 1] = v.y;
-            key[4 * e + 2] = v.z;
-            key[4 * e + 3] = v.w;
+            const i32x4_row v = reinterpret_cast<const i32x4_row*>(ids + base)[e];
+            id[4 * e] = v.x;
+            id[4 * e + 1] = v.y;
+            id[4 * e + 2] = v.z;
+            id[4 * e + 3] = v.w;
         }
-    } else if (keys) {
-#pragma unroll
-        for (int e = 0; e < IPT; ++e) key[e] = keys[min(base + e, M - 1)];
     } else {
-        int32_t id[IPT];
 #pragma unroll
         for (int e = 0; e < IPT; ++e) id[e] = ids[min(base + e, M - 1)];
-#pragma unroll
-        for (int e = 0; e < IPT; ++e) key[e] = order_key(row[id[e]]);
     }
+}
+
+// Loads the scores of a thread's IPT consecutive winners (of M, listed in ascending entry id).  kept: their scores as the
+// slices wrote them beside the ids; without room for those (nullptr) they are gathered from the row.  Every load is clamped
+// to a valid position instead of being branched around, so that all of a thread's loads are in flight together: behind a
+// branch each, the eight of a 65536-entry row's second stage were eight pairs of dependent round trips, 12 of its 23 us.
+template <int IPT>
+__device__ __forceinline__ void load_winners(const float* __restrict__ row, const int32_t* __restrict__ ids,
+                                             const float* __restrict__ kept, int M, float (&x)[IPT]) {
+    if (kept) {
+        load_scores<IPT>(kept, M, x);
+        return;
+    }
+    const int base = threadIdx.x * IPT;
+    int32_t id[IPT];
+    load_winner_ids<IPT>(ids, M, id);
 #pragma unroll
-    for (int e = 0; e < IPT; ++e) key[e] = base + e < M ? key[e] : 0u;
+    for (int e = 0; e < IPT; ++e) x[e] = row[id[e]];
+#pragma unroll
+    for (int e = 0; e < IPT; ++e) x[e] = base + e < M ? x[e] : __uint_as_float(0x7fc00000u);
 }
 
 }  // namespace selcore

@@ -139,3 +139,33 @@ def test_expansion_edges(sw, Sc, Nc, most, cap):
     assert np.array_equal(entries.cpu().numpy(), ref[:, :cap]) and np.array_equal(count.cpu().numpy(), np.minimum(ref_n, cap))
     from paper_2603_17803_amd import binding
     assert sw.device_status() == (binding.SWARM_DEV_CAP if ref_n.max() > cap else 0)
+
+
+@pytest.mark.parametrize("N,k,Nc,R,H", [
+    (1, 1, 1, 1, 1), (3, 2, 5, 2, 3), (255, 255, 33, 3, 3), (1023, 64, 341, 3, 2), (1025, 100, 1023, 2, 3), (2047, 300, 65, 1, 5), (2049, 17, 700, 3, 2),
+    (4095, 512, 1365, 3, 1), (4097, 256, 1024, 4, 2), (8191, 1024, 2047, 2, 3), (8193, 200, 1024, 3, 2), (16383, 900, 1000, 2, 1), (33001, 640, 1500, 2, 2)])
+def test_one_call_step_edges(sw, N, k, Nc, R, H):
+    """The one-call step against the separate calls and the oracle, with resident clusters: tables parked with and without
+    room, ragged in every length, on both sides of each block size; equal scores in quantity and NaN among them."""
+    rng = np.random.default_rng(N + k)
+    D, d = 6, 8
+    K = rng.integers(0, 7, (H, N, d)).astype(np.float32)
+    K = (K.view(np.uint32) >> 16).astype(np.uint16)                       # small whole numbers: many equal scores
+    K[:, rng.integers(0, N, max(1, N // 50)), 0] = 0x7FC0                 # NaN
+    q = np.full((1, H, d), 0x3F80, np.uint16)
+    e2c = rng.integers(0, Nc, (H, N)).astype(np.int32)
+    rep = np.stack([rng.permutation(D)[:R] for _ in range(H * Nc)]).astype(np.int32)
+    weight = rng.integers(0, 50, H * Nc).astype(np.int32)
+    res = rng.integers(0, 2 ** 32, (H * Nc + 31) // 32, dtype=np.uint32) & rng.integers(0, 2 ** 32, (H * Nc + 31) // 32, dtype=np.uint32)
+    args = (dev(e2c), Nc, dev(rep), D)
+    for resident in (None, res):
+        r = None if resident is None else dev(resident)
+        got = sw.step("token", dev(K), dev(q[0]), k, *args, weight=dev(weight), resident=r)
+        idx, sc = sw.score_select("token", dev(K), dev(q), k, want_scores=True)
+        assert np.array_equal(idx.cpu().numpy(), oracle.select(sc.cpu().numpy(), k))
+        got_idx = got[0].cpu().numpy().reshape(H, k)
+        assert np.array_equal(got_idx, idx.cpu().numpy()[0])
+        ref = oracle.map_requests(got_idx, H, N, e2c, Nc, rep, D, weight, resident, cap=min(k, Nc))
+        for g, e in zip(got[2], ref):
+            assert np.array_equal(g.cpu().numpy(), e)
+    assert sw.device_status() == 0

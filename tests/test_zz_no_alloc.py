@@ -67,14 +67,14 @@ def test_static_scratch_entry_point_matches_the_allocating_one():
         binding.swarm_destroy(ctx)
 
 
-@pytest.mark.parametrize("N,k,B,keyed", [(65536, 256, 30, True), (65536, 400, 30, False), (16385, 8192, 1, True), (20001, 3, 7, True)])
-def test_sliced_rows_with_and_without_room_for_the_winners_keys(N, k, B, keyed):
-    """Long rows whose winners' order keys just fit the static scratch and whose do not: the second stage then gathers the
-    scores.  Both agree with the route of the context's own buffers, which always keeps the keys."""
+@pytest.mark.parametrize("N,k,B,kept", [(65536, 256, 30, True), (65536, 400, 30, False), (16385, 8192, 1, True), (20001, 3, 7, True)])
+def test_sliced_rows_with_and_without_room_for_the_winners_scores(N, k, B, kept):
+    """Long rows whose winners' scores just fit the static scratch and whose do not: the second stage then gathers
+    them.  Both agree with the route of the context's own buffers, which always keeps them."""
     from paper_2603_17803_amd import binding
     cfg = W.CONFIGS["token_stress"].scaled(T=1, N=N, k=k, B=B, d=8)
     P, per = (N + 8191) // 8192, min(k, 8192)
-    assert (4 * B * N + 8 * B * P * per <= 8 << 20) == keyed
+    assert (4 * B * N + 8 * B * P * per <= 8 << 20) == kept
     ctx = binding.swarm_create(0, torch.cuda.current_stream().cuda_stream)
     try:
         rc_a, rc_b, a, b = both(binding, ctx, cfg)
