@@ -295,6 +295,38 @@ __device__ __forceinline__ void run_chain_packed(int D, uint32_t m, int lane, co
     else greedy_chain_packed<6>(m, lane, order, mask_lo, mask_hi, wgt, assign, keybase, cnt, D, identity);
 }
 
+// The items with a single candidate, which come first in the visiting order: nothing is compared, so they are placed 64 at a
+// time -- a ballot per SSD gives the positions, LDS adds the loads into acc[ssd] (zero before; SSDs of this sub-problem only) --
+// instead of taking a link of the chain each.  Items without a candidate are passed over.
+__device__ __forceinline__ void place_singles(uint32_t n, int lane, const uint32_t* order, bool identity, const uint32_t* mask_lo,
+                                              const uint32_t* mask_hi, const uint32_t* wgt, uint32_t* assign, uint32_t* acc,
+                                              uint32_t& keybase, uint32_t& cnt, int D, uint64_t ssds) {
+    const uint64_t below = (1ull << lane) - 1ull;
+    for (uint32_t base = 0; base < n; base += 64) {
+        uint32_t it = 0;
+        int d = -1;
+        if (base + lane < n) {
+            it = identity ? base + lane : order[base + lane];
+            const uint64_t mask = ((uint64_t)mask_hi[it] << 32) | mask_lo[it];
+            if (mask) {
+                d = __ffsll((unsigned long long)mask) - 1;
+                atomicAdd(&acc[d], wgt[it]);
+            }
+        }
+        uint32_t as = INF32;
+        for (int e = 0; e < D; ++e) {
+            const uint64_t b = __ballot(d == e);
+            if (!b) continue;
+            const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cnt, e);
+            if (d == e) as = ((uint32_t)e << 24) | (c + (uint32_t)__popcll(b & below));
+            if (lane == e) cnt += (uint32_t)__popcll(b);
+        }
+        if (as != INF32) assign[it] = as;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    if (n && ((ssds >> lane) & 1ull)) keybase += acc[lane] << 6;
+}
+
 constexpr int MAP_THREADS = 256;
 constexpr uint32_t MAP_SPLIT_MIN_ITEMS = 96;     // below this a single chain is shorter than finding the sub-problems
 
@@ -378,9 +410,9 @@ struct MapLds {
 // cluster of entry -> replica row).  PRESTAGED: the caller has already filled the staged tables,
 // cleared the bitmap and synchronised, and `sel` points into LDS; or it has set the activated clusters' bits as well (merged),
 // resident ones among them: those are left out through the bitmap `skip`.
-// BIG: the kernel is meant for long lists (thousands of merged picks, hundreds of clusters): the per-item pass and
-// the SSD adjacency run on every thread and the merge marks bytes.  The short-list kernels leave that code out --
-// it is not only unused there, its mere presence between the phases cost them 0.25 us per launch.
+// BIG: the kernel is meant for thousands of merged picks: it takes eight of them per thread in its first burst and the merge
+// marks bytes.  The fused kernel of short selections (PRESTAGED, not BIG) also leaves out the split into sub-problems -- it is
+// not only unused there, its mere presence between the phases cost 0.25 us per launch.
 template <int NT, bool PRESTAGED, bool BIG, bool STRIDED = false>
 __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int32_t* __restrict__ sel, uint32_t* smem,
                                           int stage_e2c, int stage_tab, bool merged = false, const uint32_t* skip = nullptr) {
@@ -548,19 +580,45 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     }
     uint32_t m = 0, load = 0, cnt = 0, wsum = 0;
     const int D = a.D;
-    // Long lists: every thread places the cluster of its own bitmap bit (the words' popcounts are scanned by every wave
-    // for itself: lane j = word j), instead of wave 0 walking the bitmap alone.
-    const bool par_compact = BIG && try_split && nwords <= 64;
+    // Long lists are compacted by every thread instead of wave 0 alone walking the bitmap.  A short bitmap: a thread places the
+    // cluster of its own bit (the words' popcounts are scanned by every wave for itself: lane j = word j).  A long one: a thread
+    // owns a run of words, mostly with a bit or none (256 words on wave 0: 4700 cycles).
+    const bool par_compact = SPLIT && try_split;
     uint32_t m_par = 0;
     if (par_compact) {
-        const uint32_t wexcl = wave_excl_scan(lane < nwords ? (uint32_t)__popc(bitmap[lane]) : 0u, &m_par);
-        for (int b0 = 0; b0 < nwords * 32; b0 += NT) {
-            const int bit = b0 + tid, w = bit >> 5;
-            const uint32_t word = w < nwords ? bitmap[w] : 0u;
-            const uint32_t before = (uint32_t)__shfl((int)wexcl, w & 63, 64);
-            if ((word >> (bit & 31)) & 1u) {
-                const uint32_t pos = before + (uint32_t)__popc(word & ((1u << (bit & 31)) - 1u));
-                if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)bit;
+        if (nwords <= 64) {
+            const uint32_t wexcl = wave_excl_scan(lane < nwords ? (uint32_t)__popc(bitmap[lane]) : 0u, &m_par);
+            for (int b0 = 0; b0 < nwords * 32; b0 += NT) {
+                const int bit = b0 + tid, w = bit >> 5;
+                const uint32_t word = w < nwords ? bitmap[w] : 0u;
+                const uint32_t before = (uint32_t)__shfl((int)wexcl, w & 63, 64);
+                if ((word >> (bit & 31)) & 1u) {
+                    const uint32_t pos = before + (uint32_t)__popc(word & ((1u << (bit & 31)) - 1u));
+                    if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)bit;
+                }
+            }
+        } else {
+            const int wpt = (nwords + NT - 1) / NT;
+            const int w0 = min(tid * wpt, nwords), w1 = min(w0 + wpt, nwords);
+            uint32_t mine = 0, wtot;
+            for (int w = w0; w < w1; ++w) mine += (uint32_t)__popc(bitmap[w]);
+            uint32_t pos = wave_excl_scan(mine, &wtot);
+            if (lane == 0) L.pub_cnt[wave] = wtot;
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < NT / 64; ++v) {
+                const uint32_t t = L.pub_cnt[v];
+                pos += v < wave ? t : 0u;
+                m_par += t;
+            }
+            for (int w = w0; w < w1; ++w) {
+                uint32_t bits = bitmap[w];
+                while (bits) {
+                    const int bit = __ffs(bits) - 1;
+                    bits &= bits - 1;
+                    if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)(w * 32 + bit);
+                    ++pos;
+                }
             }
         }
     }
@@ -586,7 +644,8 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
         m += total;
     }
     if (__builtin_expect(m > (uint32_t)a.cap, 0)) { flags |= SWARM_DEV_CAP; m = a.cap; }
-    if (BIG && try_split) {                          // what the other waves need for their share of the per-item pass
+    L.pub_load[lane] = 0u;
+    if (SPLIT && try_split) {                        // what the other waves need for their share of the per-item pass
         if (lane == 0) { off[1] = m; off[2] = INF32; off[3] = 0u; off[4] = 0u; }
         L.adj_lo[lane] = 0u;
         L.adj_hi[lane] = 0u;
@@ -643,9 +702,10 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
         (void)wave_excl_scan(min(wsum, (1u << 26) - 1u), &total);     // <= 64 * (2^26 - 1): no wrap
         wsum = any_big ? (1u << 26) : min(total, 1u << 26);
     };
-    if (BIG && try_split) {
+    if (SPLIT && try_split) {
         __syncthreads();
         const uint32_t mm = off[1];
+        // with it, which SSDs share an item, and how many items have each SSD as their lowest candidate
         for (uint32_t i = tid; i < mm; i += NT) {
             uint64_t bits = stage_tab ? item(i, std::true_type{}) : item(i, std::false_type{});
             const uint32_t lo = (uint32_t)bits, hi = (uint32_t)(bits >> 32);
@@ -666,7 +726,7 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
         __syncthreads();
     }
     if (wave == 0) {
-    if (BIG && try_split) {
+    if (SPLIT && try_split) {
         rf_min = off[2];
         rf_max = off[3];
         wsum = min(off[4], 1u << 26);
@@ -677,11 +737,12 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
 
-    // visiting order: stable by replication factor (identity when all factors agree)
+    // visiting order: stable by replication factor (identity when all factors agree); a list that may be split is brought into
+    // this order when a sub-problem gathers its items
     const bool identity = m > 0 && rf_min == rf_max;
-    if (lane == 0) off[5] = identity ? 1u : 0u;
-    if (__builtin_expect(identity, 1)) {
-        // the list order is the visiting order: the chains and the split read it without a look-up, the table stays unwritten
+    uint32_t singles = identity && rf_min <= 1 ? m : 0u;             // items with at most one candidate: the first ones visited
+    if (try_split || __builtin_expect(identity, 1)) {
+        // the list order is the visiting order: the chains read it without a look-up, the table stays unwritten
     } else if (m > 0) {
         uint32_t* rfv = assign;                      // assign is rewritten below, before the chain runs
         for (uint32_t i = lane; i < m; i += 64) rfv[i] = order[i];
@@ -695,6 +756,7 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
                 if (hit) order[outpos + __popcll(b & ((1ull << lane) - 1ull))] = i;
                 outpos += __popcll(b);
             }
+            if (v <= 1) singles = outpos;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         for (uint32_t i = lane; i < m; i += 64) assign[i] = INF32;
@@ -708,25 +770,6 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     // by rows; a component is named by its lowest SSD.
     uint32_t ncomp = 1;
     if (try_split && wsum < (1u << 26)) {
-        if (!BIG) {                                  // the adjacency was not gathered with the per-item pass
-            L.adj_lo[lane] = 0u;
-            L.adj_hi[lane] = 0u;
-            L.seg_cnt[lane] = 0u;
-            L.seg_first[lane] = 0u;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-            for (uint32_t i = lane; i < m; i += 64) {
-                const uint32_t lo = mask_lo[i], hi = mask_hi[i];
-                uint64_t bits = ((uint64_t)hi << 32) | lo;
-                if (bits) atomicAdd(&L.seg_first[__ffsll((unsigned long long)bits) - 1], 1u);
-                while (bits) {
-                    const int d = __ffsll((unsigned long long)bits) - 1;
-                    bits &= bits - 1;
-                    if (lo) atomicOr(&L.adj_lo[d], lo);
-                    if (hi) atomicOr(&L.adj_hi[d], hi);
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        }
         uint64_t reach = ((uint64_t)L.adj_hi[lane] << 32) | L.adj_lo[lane];
         const bool active = reach != 0ull;           // some routed item has SSD `lane` as a candidate (then reach holds lane itself)
         for (int kk = 0; kk < D; ++kk) {
@@ -744,67 +787,79 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     }
     if (lane == 0) off[0] = ncomp;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    if (ncomp <= 1) {
+    if (!try_split) {
         // greedy least-loaded assignment, one chain
         if (__builtin_expect(wsum < (1u << 26), 1)) {
             uint32_t keybase = (uint32_t)lane;
-            run_chain_packed(D, m, lane, order, mask_lo, mask_hi, wgt, assign, keybase, cnt, identity);
+            if (singles) place_singles(singles, lane, order, identity, mask_lo, mask_hi, wgt, assign, L.pub_load, keybase, cnt, D, ~0ull);
+            if (m > singles) run_chain_packed(D, m - singles, lane, order + singles, mask_lo, mask_hi, wgt, assign, keybase, cnt, identity);
             load = keybase >> 6;
         } else {
             if (D <= 16) greedy_chain_wide<4>(m, lane, order, mask_lo, mask_hi, wgt, assign, load, cnt, identity);
             else greedy_chain_wide<6>(m, lane, order, mask_lo, mask_hi, wgt, assign, load, cnt, identity);
         }
     }
-    if (lane == 0) off[1] = m;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     }   // wave 0
-    uint32_t ncomp = 1;
-    if (try_split) {
+    bool wide = false;                                     // loads beyond the packed chain's range: one chain over everything
+    if (SPLIT && try_split) {
         __syncthreads();
-        ncomp = off[0];
-        if (ncomp > 1) {
-            const uint32_t mm = off[1];
-            const bool identity = off[5] != 0u;            // the visiting order is the list order: no look-up
-            // component c on wave c mod (number of waves): the wave gathers the component's items in visiting
-            // order (stable), then runs their chain; a wave that gets several components runs them one after the
+        const uint32_t ncomp = off[0], mm = off[1], rf_lo = off[2], rf_hi = off[3];
+        wide = off[4] >= (1u << 26);
+        constexpr uint32_t NW = NT / 64;
+        // A wave gathers a sub-problem's items (those with a candidate among the SSDs given) in visiting order: a pass over the
+        // list per replication factor, stable, four batches of look-ups in flight together.
+        auto gather = [&](uint64_t ssds, uint32_t* dst, uint32_t& singles) __attribute__((always_inline)) -> uint32_t {
+            const uint32_t ssds_lo = (uint32_t)ssds, ssds_hi = (uint32_t)(ssds >> 32);
+            uint32_t run = 0;
+            singles = 0;
+            for (uint32_t v = max(rf_lo, 1u); v <= rf_hi; ++v) {
+                for (uint32_t i0 = 0; i0 < mm; i0 += 256) {
+                    uint32_t ml[4], mh[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t i = i0 + u * 64 + lane;
+                        ml[u] = mask_lo[min(i, mm - 1)];              // clamped, not branched around: the four are in flight together
+                        mh[u] = D > 32 ? mask_hi[min(i, mm - 1)] : 0u;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        // an item's candidates all lie in one sub-problem: any of them tells which
+                        const bool hit = i0 + u * 64 + lane < mm && ((ml[u] & ssds_lo) | (mh[u] & ssds_hi)) != 0u &&
+                                         (uint32_t)(__popc(ml[u]) + __popc(mh[u])) == v;
+                        const uint64_t b = __ballot(hit);
+                        if (hit) dst[run + (uint32_t)__popcll(b & ((1ull << lane) - 1ull))] = i0 + u * 64 + lane;
+                        run += (uint32_t)__popcll(b);
+                    }
+                }
+                if (v == 1) singles = run;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            return run;
+        };
+        uint32_t singles;
+        if (wide) {
+            if (wave == 0) {
+                const uint32_t run = gather(~0ull, order2, singles);
+                if (D <= 16) greedy_chain_wide<4>(run, lane, order2, mask_lo, mask_hi, wgt, assign, load, cnt);
+                else greedy_chain_wide<6>(run, lane, order2, mask_lo, mask_hi, wgt, assign, load, cnt);
+            }
+        } else {
+            // component c on wave c mod (number of waves): a wave that gets several components runs them one after the
             // other on the same registers (their SSDs are disjoint)
-            constexpr uint32_t NW = NT / 64;
             uint32_t routed;
             const uint32_t seg = wave_excl_scan(L.seg_cnt[lane], &routed);      // lanes >= ncomp hold 0
             uint32_t keybase = (uint32_t)lane, mycnt = 0;
             for (uint32_t c = (uint32_t)wave; c < ncomp; c += NW) {
                 const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)seg, (int)c);
                 const uint64_t ssds = __ballot(lane < D && L.comp_of[lane] == c);         // the component's SSDs
-                const uint32_t ssds_lo = (uint32_t)ssds, ssds_hi = (uint32_t)(ssds >> 32);
-                uint32_t run = 0;
-                for (uint32_t i0 = 0; i0 < mm; i0 += 256) {          // four batches of look-ups in flight together
-                    uint32_t it[4], ml[4], mh[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const uint32_t i = i0 + u * 64 + lane;
-                        it[u] = i < mm ? (identity ? i : order[i]) : 0u;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const bool in = i0 + u * 64 + lane < mm;
-                        ml[u] = in ? mask_lo[it[u]] : 0u;
-                        mh[u] = (in && D > 32) ? mask_hi[it[u]] : 0u;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        // an item's candidates all lie in one sub-problem: any of them tells which
-                        const bool hit = ((ml[u] & ssds_lo) | (mh[u] & ssds_hi)) != 0u;
-                        const uint64_t b = __ballot(hit);
-                        if (hit) order2[base + run + (uint32_t)__popcll(b & ((1ull << lane) - 1ull))] = it[u];
-                        run += (uint32_t)__popcll(b);
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+                const uint32_t run = gather(ssds, order2 + base, singles);
                 if (D <= 32 && __popcll(ssds) <= 2 && ssds != 0ull) {
                     const int sa = __ffsll((unsigned long long)ssds) - 1, sb = 63 - __clzll((unsigned long long)ssds);
                     greedy_chain_pair(run, lane, order2 + base, mask_lo, wgt, assign, keybase, mycnt, sa, sb != sa ? sb : -1);
                 } else {
-                    run_chain_packed(D, run, lane, order2 + base, mask_lo, mask_hi, wgt, assign, keybase, mycnt);
+                    if (singles) place_singles(singles, lane, order2 + base, false, mask_lo, mask_hi, wgt, assign, L.pub_load, keybase, mycnt, D, ssds);
+                    if (run > singles)
+                        run_chain_packed(D, run - singles, lane, order2 + base + singles, mask_lo, mask_hi, wgt, assign, keybase, mycnt);
                 }
             }
             if (lane < D) {
@@ -819,14 +874,14 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     }
     // Bucket offsets are single-wave work; the scatter of the queues is per-item work, which the long-list kernels
     // leave to all their waves when those are still here (they are after a split into sub-problems).
-    const bool all_emit = BIG && try_split;
+    const bool all_emit = SPLIT && try_split;
     if (wave != 0 && !all_emit) {
         if (flags) atomicOr(a.dev_flags, flags);
         return;
     }
     uint32_t total = 0;
     if (wave == 0) {
-        if (ncomp > 1) {
+        if (SPLIT && try_split && !wide) {
             const bool active = lane < D && L.comp_of[lane] != 0xffu;
             load = active ? L.pub_load[lane] : 0u;
             cnt = active ? L.pub_cnt[lane] : 0u;

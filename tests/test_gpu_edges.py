@@ -169,3 +169,30 @@ def test_one_call_step_edges(sw, N, k, Nc, R, H):
         for g, e in zip(got[2], ref):
             assert np.array_equal(g.cpu().numpy(), e)
     assert sw.device_status() == 0
+
+
+@pytest.mark.parametrize("D,Nc,S,R,heavy", [
+    (1, 200, 150, 1, False), (5, 97, 400, 3, False), (6, 3000, 300, 3, False), (15, 8192, 512, 4, False), (16, 4100, 700, 2, True), (17, 700, 900, 3, False),
+    (40, 9000, 500, 4, False), (64, 300, 3000, 5, False), (8, 2049, 96, 1, False), (12, 130, 2048, 4, True)])
+def test_mapping_of_lists_with_single_copies(sw, D, Nc, S, R, heavy):
+    """Clusters with no, one and several copies side by side, in few and many sub-problems, long and short bitmaps, loads
+    beyond the packed chain's range (heavy), short lists that stay one chain; queues against the oracle."""
+    H, N, groups = 2, Nc + 50, 5
+    rng = np.random.default_rng(D * 1000 + S)
+    e2c = np.stack([rng.permutation(np.concatenate([np.arange(Nc), rng.integers(0, Nc, 50)])) for _ in range(H)]).astype(np.int32)
+    rep = np.stack([rng.permutation(D)[:R] for _ in range(H * Nc)]).astype(np.int32)
+    if D % 4 == 0:                                                   # families of four SSDs: independent sub-problems
+        fam = rng.integers(0, D // 4, H * Nc) * 4
+        rep = fam[:, None] + np.stack([rng.permutation(4)[:min(R, 4)] for _ in range(H * Nc)]).astype(np.int64)
+        rep = rep.astype(np.int32)
+    keep = rng.integers(1, rep.shape[1] + 1, H * Nc)
+    rep[np.arange(rep.shape[1])[None] >= keep[:, None]] = -1
+    rep[rng.random(H * Nc) < 0.4, 1:] = -1
+    weight = (rng.integers(0, 1 << 20, H * Nc) if heavy else rng.integers(0, 300, H * Nc)).astype(np.int32)
+    for s in (S, max(1, S // 8)):
+        sel = rng.integers(0, N, (groups, s)).astype(np.int32)
+        cap = min(s, Nc)
+        got = sw.map_requests(dev(sel), H, N, dev(e2c), Nc, dev(rep), D, dev(weight), cap=cap)
+        for g, e in zip(got, oracle.map_requests(sel, H, N, e2c, Nc, rep, D, weight, cap=cap)):
+            assert np.array_equal(g.cpu().numpy(), e)
+    assert sw.device_status() == 0
