@@ -196,3 +196,36 @@ def test_mapping_of_lists_with_single_copies(sw, D, Nc, S, R, heavy):
         for g, e in zip(got, oracle.map_requests(sel, H, N, e2c, Nc, rep, D, weight, cap=cap)):
             assert np.array_equal(g.cpu().numpy(), e)
     assert sw.device_status() == 0
+
+
+@pytest.mark.parametrize("N,Nc,S,D,top", [
+    (1024, 300, 2048, 8, 4), (1023, 200, 2049, 6, 1), (700, 110, 4097, 2, 3), (513, 513, 9000, 8, 40), (2050, 640, 16500, 12, 2), (1300, 97, 2600, 4, 9),
+    (3, 3, 2048, 4, 2), (1500, 180, 3000, 16, 5000000)])
+def test_merged_lists_of_replica_pairs(sw, N, Nc, S, D, top):
+    """More picks than entries (the entries are marked, then looked up), just beyond and short of that rule, with padding,
+    foreign ids and foreign clusters among them; pairs of SSDs as sub-problems with weights small enough for ties and zeros."""
+    H, groups = 2, 3
+    rng = np.random.default_rng(N + S)
+    e2c = rng.integers(0, Nc, (H, N)).astype(np.int32)
+    first = rng.integers(0, D // 2, H * Nc)
+    rep = np.stack([first, first + D // 2], 1).astype(np.int32)
+    rep[rng.random(H * Nc) < 0.5] = rep[0, ::-1]                                   # many of one pair, listed the other way round
+    weight = rng.integers(0, top + 1, H * Nc).astype(np.int32)
+    res = rng.integers(0, 2 ** 32, (H * Nc + 31) // 32, dtype=np.uint32) & rng.integers(0, 2 ** 32, (H * Nc + 31) // 32, dtype=np.uint32)
+    for bad in (False, True):
+        if bad:
+            e2c[rng.random((H, N)) < 0.02] = Nc
+        for s in (S, 2 * N - 1):
+            sel = rng.integers(0, N, (groups, s)).astype(np.int32)
+            if bad:
+                sel[rng.random(sel.shape) < 0.05] = -1
+                sel[:, 0], sel[:, -1] = N, -7
+            good = sel.copy()                                        # what of it is left when foreign ids and clusters are passed over
+            for g in range(groups):
+                ok = (sel[g] >= 0) & (sel[g] < N)
+                good[g] = np.where(ok & (e2c[g % H][np.where(ok, sel[g], 0)] < Nc), sel[g], -1)
+            cap = min(s, Nc)
+            got = sw.map_requests(dev(sel), H, N, dev(e2c), Nc, dev(rep), D, dev(weight), dev(res), cap=cap)
+            for g, e in zip(got, oracle.map_requests(good, H, N, np.minimum(e2c, Nc - 1), Nc, rep, D, weight, res, cap=cap)):
+                assert np.array_equal(g.cpu().numpy(), e)
+        assert (sw.device_status() != 0) == bad
