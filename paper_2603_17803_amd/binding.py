@@ -260,10 +260,12 @@ class Swarm:
             raise SwarmError(fn, rc, swarm_last_error(self.ctx))
 
     def _dev(self, t, dtype=None, name="tensor"):
-        if t.device != self.device or not t.is_contiguous():
+        # the usual tensor is told by its device number, without a device object made for each of a call's ten tensors
+        if not (getattr(t, "is_cuda", False) and t.get_device() == self.device.index and t.is_contiguous()):
             raise ValueError(f"{name} must be a contiguous tensor on {self.device}")
-        if dtype is not None and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
-            raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype}")
+        have = t.dtype
+        if dtype is not None and have is not dtype and have not in (dtype if isinstance(dtype, tuple) else (dtype,)):
+            raise ValueError(f"{name} has dtype {have}, expected {dtype}")
         return t.data_ptr()
 
     def score_select(self, kind: str, keys, q, k: int, G: int = 1, out_idx=None, out_scores=None,
@@ -501,16 +503,17 @@ class Swarm:
         """One decode step of one stream: q [H*G][d] -> (idx int32 [H][k], scores or None, (q_off, q_cluster, q_load))."""
         torch = self.torch
         b16 = (torch.bfloat16, torch.int16, torch.uint16)
-        H, N, d = keys.shape[0], keys.shape[1], keys.shape[-1]
+        shape = tuple(keys.shape)
+        H, N, d = shape[0], shape[1], shape[-1]
         R = replicas.shape[1]
-        if tuple(q.shape) != (H * G, d):
+        if q.shape != (H * G, d):
             raise ValueError(f"q has shape {tuple(q.shape)}, expected {(H * G, d)}")
         want = (H, N, d) if kind == "token" else (H, N, 2, d)
-        if tuple(keys.shape) != want:
+        if shape != want:
             raise ValueError(f"keys has shape {tuple(keys.shape)}, expected {want}")
-        if tuple(e2c.shape) != (H, N) or tuple(replicas.shape) != (H * Nc, R):
+        if e2c.shape != (H, N) or replicas.shape != (H * Nc, R):
             raise ValueError("e2c must be [H][N] and replicas [H*Nc][R]")
-        if weight is not None and tuple(weight.shape) != (H * Nc,):
+        if weight is not None and weight.shape != (H * Nc,):
             raise ValueError("weight must be [H*Nc]")
         if resident is not None and resident.numel() < (H * Nc + 31) // 32:
             raise ValueError("resident bitmap too short")
