@@ -135,9 +135,9 @@ def swarm_step(ctx: int, kind: int, data: int, H: int, N: int, d: int, G: int, q
                out_scores: Optional[int], e2c: int, Nc: int, replicas: int, R: int, D: int, weight: Optional[int],
                resident: Optional[int], q_off: int, q_cluster: int, q_load: int, cap: int) -> int:
     ks = swarm_keys(kind, data, H, N, d, G)
-    return load().swarm_step(C.c_void_p(ctx), C.byref(ks), C.c_void_p(q), k, C.c_void_p(out_idx), C.c_void_p(out_scores),
-                             C.c_void_p(e2c), Nc, C.c_void_p(replicas), R, D, C.c_void_p(weight), C.c_void_p(resident),
-                             C.c_void_p(q_off), C.c_void_p(q_cluster), C.c_void_p(q_load), cap)
+    # addresses go as they are: the declared argument types convert them
+    return load().swarm_step(ctx, C.byref(ks), q, k, out_idx, out_scores, e2c, Nc, replicas, R, D, weight, resident, q_off, q_cluster,
+                             q_load, cap)
 
 
 SWARM_CAL_HBM_READ, SWARM_CAL_HBM_WRITE, SWARM_CAL_MFMA_I8, SWARM_CAL_MFMA_FP4 = 0, 1, 2, 3
