@@ -264,7 +264,7 @@ swarm_status swarm_coact_build_density(swarm_ctx* ctx, const int32_t* idx, int64
     // auxiliary scratch: totals [H] and thresholds [H] (int64), then the trace rows' entry counts [slabs][H][nruns * 128] (int32)
     const int slabs = trace_slabs(nruns, H, Npad);
     st = swarm_grow(ctx, reinterpret_cast<void**>(&ctx->totals), &ctx->totals_bytes,
-                    sizeof(int64_t) * 2 * (size_t)H + sizeof(int32_t) * (size_t)slabs * H * nruns * 128);
+                    sizeof(int64_t) * 2 * (size_t)H + sizeof(int32_t) * trace_count_words(nruns, H, Npad));
     if (st != SWARM_OK) return st;
     int64_t* totals = totals_out ? totals_out : ctx->totals;
     int64_t* cstar = ctx->totals + H;

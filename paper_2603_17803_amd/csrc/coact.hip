@@ -622,6 +622,14 @@ int trace_slabs(int nruns, int H, int Npad) {
     return (Npad + span - 1) / span;
 }
 
+// Room for the builder's row counts.  Their number, runs x heads x slabs, does not grow with the shape: shorter spans make more
+// slabs.  But the spans are halved only while there are fewer than 256 workgroups, so it is either the number at full spans or
+// below 512, and the larger of the two bounds grows with every argument.
+size_t trace_count_words(int nruns, int H, int Npad) {
+    const size_t full = (size_t)nruns * H * ((Npad + TRACE_SPAN - 1) / TRACE_SPAN);
+    return (full > 512 ? full : 512) * 128;
+}
+
 swarm_status launch_trace_build(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int H, int k, int N, int Npad,
                                 int nruns, uint32_t flags, int32_t* row_count, int32_t* rho) {
     if (flags & SWARM_CHECK_IDX) {

@@ -98,6 +98,7 @@ swarm_status launch_trace_build(swarm_ctx* ctx, const int32_t* idx, int64_t rows
                                 int nruns, uint32_t flags, int32_t* row_count = nullptr, int32_t* rho = nullptr);
                                 // row_count (optional): int32 [trace_slabs][H][nruns*128] out, with it rho [H][N] is cleared
 int trace_slabs(int nruns, int H, int Npad);           // spans of entries the builder splits a head into
+size_t trace_count_words(int nruns, int H, int Npad);  // room for row_count: at least what the call needs, never less for a larger shape
 swarm_status launch_trace_totals_thresholds(swarm_ctx* ctx, const int32_t* row_count, int slabs, int H, int nrows, double tau, uint32_t flags,
                                             int64_t* totals, int64_t* cstar);
 swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns, int32_t* C, uint32_t decay_q16,

@@ -122,3 +122,40 @@ def test_recording_refuses_calls_that_would_allocate():
         finally:
             binding.swarm_graph_destroy(graph)
             sw.close()
+
+
+@pytest.mark.parametrize("H,N,large,small", [(1, 1000, 32768, 20480), (8, 600, 4096, 2560), (3, 1500, 11264, 10752)])
+def test_a_build_no_larger_than_an_earlier_one_can_be_recorded(H, N, large, small):
+    """After a build over a long run of selections, one over a shorter run needs no more scratch, however the trace
+    builder cuts the shorter run: it may be recorded at once, and replays give what the eager call gives."""
+    from paper_2603_17803_amd import binding
+    k, tau = 4, 1.0 - 1e-5
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        sw = binding.Swarm(0, stream=stream)
+        sel = dev(W.random_selections(large, H, k, N, seed=5))
+        Cm = torch.zeros((H, N, N), dtype=torch.int32, device="cuda")
+        out = (torch.empty((H, N), dtype=torch.int32, device="cuda"), torch.empty((H, N), dtype=torch.int32, device="cuda"),
+               torch.empty((H,), dtype=torch.int64, device="cuda"))
+        sw.coact_build_density(sel, N, Cm, tau, out=out)
+        stream.synchronize()
+        sw.capture_begin()
+        try:
+            sw.coact_build_density(sel[:small], N, Cm, tau, out=out)
+        finally:
+            graph = sw.capture_end()
+        try:
+            ref = oracle.coact_update(sel[:small].cpu().numpy(), N, nthreads=8)
+            want = oracle.density(ref, tau, 0, nthreads=8)
+            for _ in range(2):
+                Cm.fill_(-1)
+                sw.coact_build_density(sel, N, torch.empty_like(Cm), tau, out=out)        # other work in between, on the same scratch
+                sw.graph_launch(graph)
+                stream.synchronize()
+                assert np.array_equal(Cm.cpu().numpy(), ref)
+                for g, e in zip(out, want):
+                    assert np.array_equal(g.cpu().numpy(), e)
+            assert sw.device_status() == 0
+        finally:
+            binding.swarm_graph_destroy(graph)
+            sw.close()
