@@ -87,6 +87,7 @@ swarm_status launch_score(swarm_ctx* ctx, const swarm_keys* keys, const void* q,
 swarm_status launch_select(swarm_ctx* ctx, const float* scores, int64_t rows, int N, int k, int32_t* out_idx,
                            const swarm_fixed_scratch* fixed = nullptr);
 bool select_uses_slices(int64_t rows, int N, int k);   // long rows, few of them: sliced two-stage selection
+void select_reserve(swarm_ctx* ctx, int64_t rows, int N, int k);   // scratch that smaller, sliced calls will need
 struct swarm_winners {          // what the first stage of the sliced selection left for the second
     int32_t* ids = nullptr;     // [rows][stride], M of them per row, ascending
     float* scores = nullptr;    // their scores, laid out the same; nullptr where the scratch had no room

@@ -1114,6 +1114,7 @@ swarm_status launch_select_map(swarm_ctx* ctx, const float* scores, int H, int N
     if (lds + (size_t)cap * 8 <= budget) { a.split_off = (int)(lds / 4); lds += (size_t)cap * 8; }
     const dim3 grid((unsigned)H), block(NT);
     hipStream_t st = ctx->stream;
+    if (!sliced) select_reserve(ctx, H, N, k);
     if (sliced) {
         swarm_winners w;
         const swarm_status rc = launch_select_slices(ctx, scores, H, N, k, &w);

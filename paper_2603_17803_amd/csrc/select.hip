@@ -162,6 +162,21 @@ size_t select_cand_bytes(int64_t rows, int N, int k, bool scored) {
     return (scored ? sizeof(int32_t) + sizeof(uint32_t) : sizeof(int32_t)) * (size_t)rows * (size_t)(P * (k < SLICE ? k : SLICE));
 }
 
+// Room for the winners of this call and of every smaller one.  A call that takes one stage (too many rows, too many winners) can be
+// followed by a smaller one that takes two, so the context's scratch is sized by a bound that grows with every argument: at
+// most 32 rows are sliced, and the lists of a row end below 64 * NT + SLICE winners.
+static size_t select_cand_room(int64_t rows, int N, int k) {
+    if (N <= 2 * SLICE) return 0;
+    const int64_t all = (int64_t)((N + SLICE - 1) / SLICE) * (k < SLICE ? k : SLICE), most = 64 * selcore::NT + SLICE;
+    return (sizeof(int32_t) + sizeof(uint32_t)) * (size_t)((rows < 32 ? rows : 32) * (all < most ? all : most));
+}
+
+// For a call that does not slice itself: nothing of its own depends on the room, so a recording goes without, and so does a
+// device without memory to spare.
+void select_reserve(swarm_ctx* ctx, int64_t rows, int N, int k) {
+    if (!ctx->capturing) (void)swarm_grow(ctx, reinterpret_cast<void**>(&ctx->cand), &ctx->cand_bytes, select_cand_room(rows, N, k));
+}
+
 // First stage of the sliced selection: the slices' winners of every row into out->ids ([rows][stride], M of them per row), which
 // is the context's scratch (grown on demand) or the fixed scratch when one is given.
 swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t rows, int N, int k, swarm_winners* out,
@@ -183,7 +198,7 @@ swarm_status launch_select_slices(swarm_ctx* ctx, const float* scores, int64_t r
         }
         cand = fixed->cand;
     } else {
-        const swarm_status rc = swarm_grow(ctx, reinterpret_cast<void**>(&ctx->cand), &ctx->cand_bytes, need);
+        const swarm_status rc = swarm_grow(ctx, reinterpret_cast<void**>(&ctx->cand), &ctx->cand_bytes, select_cand_room(rows, N, k));
         if (rc != SWARM_OK) return rc;
         cand = ctx->cand;
     }
@@ -212,6 +227,7 @@ swarm_status launch_select(swarm_ctx* ctx, const float* scores, int64_t rows, in
 #undef SWARM_MERGE
         return swarm_check_launch(ctx, "topk_merge_kernel");
     }
+    if (!fixed) select_reserve(ctx, rows, N, k);
     // Short rows take smaller blocks, four scores per thread: measured per row of 2048 scores, 512 threads select in
     // 3.6 us where 1024 (half of them idle, sixteen waves at every barrier) take 5.6 us; rows of 8192 are fastest with 1024.
     if (N <= 4 * 256) {

@@ -159,3 +159,59 @@ def test_a_build_no_larger_than_an_earlier_one_can_be_recorded(H, N, large, smal
         finally:
             binding.swarm_graph_destroy(graph)
             sw.close()
+
+
+@pytest.mark.parametrize("H,large,small", [
+    (8, (5, 16500, 100), (4, 16500, 100)), (1, (1, 20000, 12000), (1, 20000, 1000)), (1, (1, 200000, 4000), (1, 60000, 3000)),
+    (1, (1, 16385, 8192), (1, 16385, 4000)), (8, (2, 60000, 9000), (2, 40000, 1000))])
+def test_a_selection_no_larger_than_an_earlier_one_can_be_recorded(H, large, small):
+    """Streams, entries and winners (B, N, k): a call that selects in one stage followed by a smaller one that cuts its rows into
+    slices.  The smaller one may be recorded at once; direct steps on the same shapes too."""
+    from paper_2603_17803_amd import binding
+    d, D, Nc = 8, 4, 50
+    rng = np.random.default_rng(H)
+    K = dev((rng.standard_normal((H, max(large[1], small[1]), d)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16))
+    q = dev((rng.standard_normal((max(large[0], small[0]), H, d)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16))
+    rep = torch.zeros((H * Nc, 1), dtype=torch.int32, device="cuda")
+
+    def args(B, N, k):
+        e2c = (torch.arange(N, device="cuda", dtype=torch.int32) % Nc).expand(H, N).contiguous()
+        queues = tuple(torch.empty((H, n), dtype=torch.int32, device="cuda") for n in (D + 1, min(k, Nc), D))
+        return (K[:, :N].contiguous(), q[:B].contiguous(), k, e2c, queues, torch.empty((B, H, k), dtype=torch.int32, device="cuda"),
+                torch.empty((H, k), dtype=torch.int32, device="cuda"))
+
+    def one(sw, a):
+        keys, qs, k, e2c, queues, idx, step_idx = a
+        sw.score_select("token", keys, qs, k, out_idx=idx)
+        sw.step("token", keys, qs[0], k, e2c, Nc, rep, D, out_idx=step_idx, out=queues)
+        return [idx, step_idx, *queues]
+
+    stream = torch.cuda.Stream()
+    a, b = args(*large), args(*small)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        sw = binding.Swarm(0, stream=stream)
+        one(sw, a)
+        stream.synchronize()
+        sw.capture_begin()
+        try:
+            out = one(sw, b)
+        finally:
+            graph = sw.capture_end()
+        try:
+            want = None
+            for _ in range(2):
+                for o in out:
+                    o.fill_(-9)
+                sw.graph_launch(graph)
+                stream.synchronize()
+                got = [o.clone() for o in out]
+                want = want or [o.clone() for o in one(sw, b)]
+                one(sw, a)
+                stream.synchronize()
+                for g, w in zip(got, want):
+                    assert torch.equal(g, w)
+            assert torch.equal(got[0][0], got[1]) and sw.device_status() == 0
+        finally:
+            binding.swarm_graph_destroy(graph)
+            sw.close()
