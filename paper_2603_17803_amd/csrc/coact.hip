@@ -63,18 +63,18 @@ __global__ __launch_bounds__(TRACE_THREADS) void trace_build_kernel(const int32_
     const int64_t row0 = (int64_t)run * 128;
     const int nrows = (int)min((int64_t)128, rows - row0);                       // <= 0 for a run of pure padding
     bool bad = false;
-    const int kq = k / Q;
-    const int total = nrows > 0 ? nrows * kq : 0;
+    const uint32_t kq = (uint32_t)k / Q;
+    const uint32_t total = nrows > 0 ? (uint32_t)nrows * kq : 0u;                // at most 2^31 (a window over 2^24 entries): unsigned, so that a step past the end does not wrap
     const int64_t row_stride = (int64_t)H * k;
     const int32_t* sel0 = idx + (row0 * H + h) * (int64_t)k;
-    for (int i0 = threadIdx.x; i0 < total; i0 += AHEAD * TRACE_THREADS) {
+    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += AHEAD * TRACE_THREADS) {
         int32_t e[AHEAD][Q];
         int s[AHEAD];
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) {
-            const int i = min(i0 + u * TRACE_THREADS, total - 1);                       // past the end: a valid load that is not used
-            s[u] = reciprocal ? (int)__umulhi((uint32_t)i, reciprocal) : i / kq;
-            const int32_t* p = sel0 + s[u] * row_stride + (i - s[u] * kq) * Q;
+            const uint32_t i = min(i0 + u * TRACE_THREADS, total - 1);                  // past the end: a valid load that is not used
+            s[u] = (int)(reciprocal ? __umulhi(i, reciprocal) : i / kq);
+            const int32_t* p = sel0 + s[u] * row_stride + (i - (uint32_t)s[u] * kq) * Q;
             if constexpr (VEC) {
                 const int4 v = *reinterpret_cast<const int4*>(p);
                 e[u][0] = v.x; e[u][1] = v.y; e[u][2] = v.z; e[u][3] = v.w;

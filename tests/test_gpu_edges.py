@@ -74,6 +74,19 @@ def test_window_edges(sw, Wn, k, N, n_new, Nc):
     assert sw.device_status() == 0
 
 
+def test_window_of_nearly_all_of_the_most_entries(sw):
+    """128 steps that each select all but one of 2^24 entries: the list of a run's ids ends 128 short of 2^31, less than what
+    the trace builder steps past it.  A few seconds: each of the 2048 spans scans the whole list."""
+    N, k, steps = 1 << 24, (1 << 24) - 1, 128
+    sel = torch.arange(k, dtype=torch.int32, device="cuda").repeat(steps, 1).view(steps, 1, k)
+    new_ids = torch.tensor([[0, 8191, 8192, N - 2, N - 1]], dtype=torch.int32, device="cuda")
+    med = torch.tensor([[1, N - 1, N - 2, N // 2]], dtype=torch.int32, device="cuda")
+    f, member, _ = sw.window_assign(sel, N, new_ids, med, 0.5)
+    want = np.where((new_ids.cpu().numpy()[0][:, None] < k) & (med.cpu().numpy()[0][None] < k), steps, 0)
+    assert np.array_equal(f.cpu().numpy()[0], want) and np.array_equal(member.cpu().numpy()[0], want == steps)
+    assert sw.device_status() == 0
+
+
 @pytest.mark.parametrize("rows,k,N,shift", [(130, 8, 9000, 0), (130, 8, 9000, 1), (5, 21, 8193, 2), (300, 4, 1025, 3), (640, 33, 520, 0)])
 def test_trace_spans_and_alignment(sw, rows, k, N, shift):
     """Selections that start at any 4-byte address, several spans of entries per run."""
