@@ -22,9 +22,11 @@ constexpr int WIN_PER_SEG = 8;            // new entries of a run and pass
 // So membership, counts and places leave in one pass.  Before, one thread per cluster walked the entries in order in a
 // kernel of its own, a load latency per entry: 67 us for 256 entries x 8 x 1024 clusters, beside 23 us for the counts.
 // What is left is writing: 9 bytes per pair, in half-wave rows of 128 bytes.
-template <int NR, int NW>
+// Without places nothing ties the new entries together: they are dealt to gridDim.z workgroups of `share` entries each, so
+// that few clusters do not leave the device idle.  With places (PLACE) one workgroup walks them all.
+template <int NR, int NW, bool PLACE>
 __global__ __launch_bounds__(64 * NW) void window_kernel(const v4u* __restrict__ bits, int nruns, int Npad, int N, int W,
-                                                                const int32_t* __restrict__ new_ids, int n_new,
+                                                                const int32_t* __restrict__ new_ids, int n_new, int share,
                                                                 const int32_t* __restrict__ medoids, int Nc, double tau,
                                                                 const int32_t* __restrict__ primary, const int32_t* __restrict__ size, int D,
                                                                 int32_t* __restrict__ f_out, uint8_t* __restrict__ member,
@@ -58,14 +60,15 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const v4u* __restrict__
     }
 
     int64_t base64 = 0;
-    if (disk && c_in) base64 = (int64_t)primary[(size_t)h * Nc + c] + size[(size_t)h * Nc + c] + 1;
-    const uint32_t base = (disk && base64 >= 0) ? (uint32_t)(base64 % D) : 0u;
+    if (PLACE && c_in) base64 = (int64_t)primary[(size_t)h * Nc + c] + size[(size_t)h * Nc + c] + 1;
+    const uint32_t base = (PLACE && base64 >= 0) ? (uint32_t)(base64 % D) : 0u;
 
-    // new entries per run: as few as let one pass hold all of them, at most WIN_PER_SEG
-    const int per = min(WIN_PER_SEG, (n_new + SEGS - 1) / SEGS);
+    // new entries per run: as few as let one pass hold all of this workgroup's, at most WIN_PER_SEG
+    const int per = min(WIN_PER_SEG, ((PLACE ? n_new : share) + SEGS - 1) / SEGS);
+    const int a_begin = PLACE ? 0 : (int)blockIdx.z * share, a_end = PLACE ? n_new : min(n_new, a_begin + share);
     uint32_t grown = 0;                                        // joiners of earlier passes
-    for (int a0 = 0; a0 < n_new; a0 += SEGS * per) {
-        const int first = a0 + seg * per, count = min(per, n_new - first);          // <= 0: an empty run
+    for (int a0 = a_begin; a0 < a_end; a0 += SEGS * per) {
+        const int first = a0 + seg * per, count = min(per, a_end - first);          // <= 0: an empty run
         uint32_t joins = 0;
         constexpr int AHEAD = NR <= 2 ? 4 : NR <= 4 ? 2 : 1;   // new entries whose trace words are in flight together
         for (int e0 = 0; e0 < per; e0 += AHEAD) {
@@ -97,7 +100,7 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const v4u* __restrict__
                 }
             }
         }
-        if (disk) {
+        if (PLACE) {
             joined[seg][cl] = (uint32_t)__popc(joins);
             __syncthreads();
             uint32_t before = 0, all = 0;
@@ -134,9 +137,20 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const v4u* __restrict__
 swarm_status launch_window(swarm_ctx* ctx, int nruns, int Npad, int N, int W, int H, const int32_t* new_ids, int n_new,
                            const int32_t* medoids, int Nc, double tau, const int32_t* primary, const int32_t* size, int D,
                            int32_t* f_out, uint8_t* member, int32_t* disk) {
-    const dim3 grid((unsigned)((Nc + 31) / 32), (unsigned)H);
-#define SWARM_WINDOW(NR, NW) hipLaunchKernelGGL((window_kernel<NR, NW>), grid, dim3(64 * NW), 0, ctx->stream, reinterpret_cast<const v4u*>(ctx->trace), \
-                                                nruns, Npad, N, W, new_ids, n_new, medoids, Nc, tau, primary, size, D, f_out, member, disk, ctx->dev_flags)
+    // Shares of the new entries when no places are asked for: one entry per half wave while that makes at most WGS workgroups
+    // (two to a compute unit), larger ones otherwise.  8192 entries against 64 clusters of one head, window of 256 steps: 120 us on the two workgroups of
+    // the clusters alone, 10.6 us on 512; 65536 entries 890 and 17 us (a workgroup per entry, as it once was: 23 and 106 us).
+    constexpr int64_t WGS = 512;
+    const int64_t blocks = (int64_t)((Nc + 31) / 32) * H;
+    const int halves = nruns <= 8 ? 32 : 16;                   // half waves of a workgroup
+    int64_t parts = disk ? 1 : WGS / blocks;
+    const int64_t most = ((int64_t)n_new + halves - 1) / halves;
+    parts = parts < 1 ? 1 : parts > most ? most : parts;
+    const int share = (int)((n_new + parts - 1) / parts);
+    const dim3 grid((unsigned)((Nc + 31) / 32), (unsigned)H, (unsigned)((n_new + share - 1) / share));
+#define SWARM_WINDOW(NR, NW) hipLaunchKernelGGL((disk ? window_kernel<NR, NW, true> : window_kernel<NR, NW, false>), grid, dim3(64 * NW), 0, ctx->stream, \
+                                                reinterpret_cast<const v4u*>(ctx->trace), nruns, Npad, N, W, new_ids, n_new, share, medoids, Nc, tau, \
+                                                primary, size, D, f_out, member, disk, ctx->dev_flags)
     if (nruns <= 2) SWARM_WINDOW(2, 16);
     else if (nruns <= 4) SWARM_WINDOW(4, 16);
     else if (nruns <= 8) SWARM_WINDOW(8, 16);

@@ -74,6 +74,33 @@ def test_window_edges(sw, Wn, k, N, n_new, Nc):
     assert sw.device_status() == 0
 
 
+@pytest.mark.parametrize("Wn,N,n_new,Nc", [
+    (40, 900, 700, 1), (256, 1500, 33, 64), (300, 2500, 2000, 600), (130, 9500, 9000, 600), (700, 1200, 1100, 65), (1100, 1300, 1000, 31), (2048, 400, 17, 300)])
+def test_window_membership_without_places(sw, Wn, N, n_new, Nc):
+    """Membership alone, with and without the counts: new entries in shares of one to several passes, a last share that is not
+    full, workgroups of either size; entries and medoids out of range count as never activated and are flagged."""
+    from paper_2603_17803_amd import binding
+    H, k = 2, max(1, N // 9)
+    rng = np.random.default_rng(n_new + Nc)
+    sel = W.random_selections(Wn, H, k, N, seed=Nc)
+    new_ids = np.stack([rng.choice(N, n_new, replace=False) for _ in range(H)]).astype(np.int32)
+    med = np.stack([rng.choice(N, Nc, replace=False) for _ in range(H)]).astype(np.int32)
+    for tau in (1.0 - 1.5 / Wn, 1.0):
+        f, member, _ = oracle.window_assign(sel, N, new_ids, med, tau)
+        for counts in (True, False):
+            got = sw.window_assign(dev(sel), N, dev(new_ids), dev(med), tau, want_counts=counts)
+            assert np.array_equal(got[1].cpu().numpy(), member) and got[2] is None
+            assert np.array_equal(got[0].cpu().numpy(), f) if counts else got[0] is None
+    assert sw.device_status() == 0
+    new_ids[0, -1], med[1, 0] = N, -1
+    got = sw.window_assign(dev(sel), N, dev(new_ids), dev(med), 0.99)
+    f = f.copy()
+    f[0, -1], f[1, :, 0] = 0, 0
+    assert np.array_equal(got[0].cpu().numpy(), f)
+    assert np.array_equal(got[1].cpu().numpy(), 1.0 - f / Wn < 0.99)
+    assert sw.device_status() == binding.SWARM_DEV_BAD_ENTRY
+
+
 def test_window_of_nearly_all_of_the_most_entries(sw):
     """128 steps that each select all but one of 2^24 entries: the list of a run's ids ends 128 short of 2^31, less than what
     the trace builder steps past it.  A few seconds: each of the 2048 spans scans the whole list."""
