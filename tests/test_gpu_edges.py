@@ -101,6 +101,29 @@ def test_window_membership_without_places(sw, Wn, N, n_new, Nc):
     assert sw.device_status() == binding.SWARM_DEV_BAD_ENTRY
 
 
+@pytest.mark.parametrize("n_new,Nc", [(9, 3), (300, 33)])
+def test_window_places_from_negative_first_disks(sw, n_new, Nc):
+    """First SSDs and sizes below zero, sums that pass zero while entries join and sums beyond 32 bits: the place is the
+    remainder as C defines it, that of a negative sum negative or zero."""
+    N, H, D, Wn = 400, 2, 5, 60
+    rng = np.random.default_rng(Nc)
+    sel = W.random_selections(Wn, H, 90, N, seed=3)
+    new_ids = np.stack([rng.choice(N, n_new, replace=False) for _ in range(H)]).astype(np.int32)
+    med = np.stack([rng.choice(N, Nc, replace=False) for _ in range(H)]).astype(np.int32)
+    primary, size = rng.integers(-12, 3, (H, Nc)).astype(np.int32), rng.integers(-9, 3, (H, Nc)).astype(np.int32)
+    primary[:, 0], size[:, 0] = -2 ** 31, -2 ** 31
+    primary[0, 1], size[0, 1] = -2, 1                                     # the sum is zero for the first to join
+    primary[1, 1], size[1, 1] = 2 ** 31 - 1, 2 ** 31 - 1
+    for tau in (1.0, 1.0 - 2.5 / Wn):
+        f, member, disk = sw.window_assign(dev(sel), N, dev(new_ids), dev(med), tau, dev(primary), dev(size), D)
+        rf, rm, _ = oracle.window_assign(sel, N, new_ids, med, tau)
+        assert np.array_equal(f.cpu().numpy(), rf) and np.array_equal(member.cpu().numpy(), rm)
+        before = np.cumsum(rm, 1, dtype=np.int64) - rm
+        place = np.fmod(primary.astype(np.int64)[:, None] + size[:, None] + before + 1, D)
+        assert np.array_equal(disk.cpu().numpy(), np.where(rm == 1, place, -1))
+    assert sw.device_status() == 0
+
+
 def test_window_of_nearly_all_of_the_most_entries(sw):
     """128 steps that each select all but one of 2^24 entries: the list of a run's ids ends 128 short of 2^31, less than what
     the trace builder steps past it.  A few seconds: each of the 2048 spans scans the whole list."""
