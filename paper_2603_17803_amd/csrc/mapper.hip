@@ -2,14 +2,16 @@
 // DRAM-resident ones, and fill one bucket per SSD by sending each cluster -- in ascending
 // (replication factor, cluster id) -- to its least-loaded replica.
 //
-// One wavefront per group.  The merge is an LDS bitmap (atomic-or per selected entry), compacted
-// in ascending cluster id.  The greedy assignment is an inherently sequential chain over the
+// One workgroup per group.  All its waves merge: an LDS bitmap (an atomic-or per selected entry, or byte marks folded into bits),
+// compacted in ascending cluster id.  The greedy assignment is an inherently sequential chain over the
 // distinct clusters, so the kernel is built around the length of one link: the per-item data
-// (candidate-SSD mask, weight) is staged 64 items at a time in registers, one item per lane, and
+// (candidate-SSD mask, weight) is staged 32 items at a time in registers, one item per lane, and
 // handed to the chain through v_readlane; lane d carries bucket d's load packed as
 // (load << 6 | d), so one DPP min-reduction over the candidate lanes yields the least-loaded
 // replica with ties to the lower SSD id, and only the compare-and-add of the winner stays on the
 // dependent path.  Bucket positions are computed afterwards, in parallel, from the winners.
+// A short list is one chain, on wave 0.  A long one is prepared and written out by all waves, and its items fall into
+// sub-problems that share no SSD: each is a chain of its own, on a wave of its own.
 #include <type_traits>
 
 #include "common.h"
@@ -296,11 +298,16 @@ __device__ __forceinline__ void run_chain_packed(int D, uint32_t m, int lane, co
 }
 
 // The items with a single candidate, which come first in the visiting order: nothing is compared, so they are placed 64 at a
-// time -- a ballot per SSD gives the positions, LDS adds the loads into acc[ssd] (zero before; SSDs of this sub-problem only) --
-// instead of taking a link of the chain each.  Items without a candidate are passed over.
+// time -- a ballot per SSD among them gives the positions, LDS adds the loads into acc[ssd] (zero before; SSDs of this sub-problem
+// only) -- instead of taking a link of the chain each.  Items without a candidate are passed over.  Set-up and ballots cost
+// what eight links of a chain do in the long lists' kernels and over more than 16 SSDs (whose links are longer), what 24 do in a
+// short list over fewer: fewer items than that stay with the chain (short lists over 8 SSDs, seventeen single copies among 50
+// items: 8.4 us placed, 8.2 chained; thirty alone: 5.6 and 6.1.  1500 items over 64 SSDs, 23 to each: 61 and 140).
+__device__ __forceinline__ uint32_t place_singles_min(bool split, int D) { return split || D > 16 ? 8u : 24u; }
+
 __device__ __forceinline__ void place_singles(uint32_t n, int lane, const uint32_t* order, bool identity, const uint32_t* mask_lo,
                                               const uint32_t* mask_hi, const uint32_t* wgt, uint32_t* assign, uint32_t* acc,
-                                              uint32_t& keybase, uint32_t& cnt, int D, uint64_t ssds) {
+                                              uint32_t& keybase, uint32_t& cnt, uint64_t ssds) {
     const uint64_t below = (1ull << lane) - 1ull;
     for (uint32_t base = 0; base < n; base += 64) {
         uint32_t it = 0;
@@ -314,9 +321,10 @@ __device__ __forceinline__ void place_singles(uint32_t n, int lane, const uint32
             }
         }
         uint32_t as = INF32;
-        for (int e = 0; e < D; ++e) {
+        for (uint64_t left = __ballot(d >= 0); left;) {
+            const int e = __builtin_amdgcn_readlane(d, __ffsll((unsigned long long)left) - 1);
             const uint64_t b = __ballot(d == e);
-            if (!b) continue;
+            left &= ~b;
             const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cnt, e);
             if (d == e) as = ((uint32_t)e << 24) | (c + (uint32_t)__popcll(b & below));
             if (lane == e) cnt += (uint32_t)__popcll(b);
@@ -328,7 +336,7 @@ __device__ __forceinline__ void place_singles(uint32_t n, int lane, const uint32
 }
 
 constexpr int MAP_THREADS = 256;
-constexpr uint32_t MAP_SPLIT_MIN_ITEMS = 96;     // below this a single chain is shorter than finding the sub-problems
+constexpr uint32_t MAP_SPLIT_MIN_ITEMS = 96;     // lists that cannot be longer stay one chain: it is shorter than finding the sub-problems
 
 // Copies n words from global memory to LDS with batches of independent loads (all loads of a batch
 // are in flight together, so a small table costs one memory round trip).  16-byte loads when the
@@ -403,17 +411,374 @@ struct MapLds {
     }
 };
 
-// One group on a block of NT threads.  All waves cooperate on staging and on the merge; wave 0
-// alone runs the compaction, the chain and the emission (the chain is a single-wave algorithm).
+// The merged clusters of group g, one bit each in L.bitmap, become its queues; all waves of the block call this.  SPLIT: a long
+// list -- every wave compacts, looks up, gathers, runs chains of sub-problems and writes queues, wave 0 finds the sub-problems.
+// Otherwise wave 0 does it all alone, one chain, and the others leave.  Bits set in `skip` (nullable, not with SPLIT) are left out.
+template <int NT, bool SPLIT>
+__device__ __forceinline__ void map_assign(const MapArgs& a, int64_t g, int h, const MapLds& L, int stage_tab, const uint32_t* skip, uint32_t flags) {
+    const int nwords = L.nwords;
+    uint32_t *bitmap = L.bitmap, *list = L.list, *mask_lo = L.mask_lo, *mask_hi = L.mask_hi, *wgt = L.wgt, *order = L.order,
+             *assign = L.assign, *off = L.off, *order2 = L.order2;
+    const int32_t *s_rep = L.s_rep, *s_wgt = L.s_wgt;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t cbase = (int64_t)h * a.Nc;
+    if (!SPLIT && wave != 0) {
+        if (flags) atomicOr(a.dev_flags, flags);
+        return;
+    }
+    uint32_t m = 0, load = 0, cnt = 0, wsum = 0;
+    const int D = a.D;
+    // Long lists are compacted by every thread instead of wave 0 alone walking the bitmap.  A short bitmap: a thread places the
+    // cluster of its own bit (the words' popcounts are scanned by every wave for itself: lane j = word j).  A long one: a thread
+    // owns a run of words, mostly with a bit or none (256 words on wave 0: 4700 cycles).
+    uint32_t m_par = 0;
+    if (SPLIT) {
+        if (nwords <= 64) {
+            const uint32_t wexcl = wave_excl_scan(lane < nwords ? (uint32_t)__popc(bitmap[lane]) : 0u, &m_par);
+            for (int b0 = 0; b0 < nwords * 32; b0 += NT) {
+                const int bit = b0 + tid, w = bit >> 5;
+                const uint32_t word = w < nwords ? bitmap[w] : 0u;
+                const uint32_t before = (uint32_t)__shfl((int)wexcl, w & 63, 64);
+                if ((word >> (bit & 31)) & 1u) {
+                    const uint32_t pos = before + (uint32_t)__popc(word & ((1u << (bit & 31)) - 1u));
+                    if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)bit;
+                }
+            }
+        } else {
+            const int wpt = (nwords + NT - 1) / NT;
+            const int w0 = min(tid * wpt, nwords), w1 = min(w0 + wpt, nwords);
+            uint32_t mine = 0, wtot;
+            for (int w = w0; w < w1; ++w) mine += (uint32_t)__popc(bitmap[w]);
+            uint32_t pos = wave_excl_scan(mine, &wtot);
+            if (lane == 0) L.pub_cnt[wave] = wtot;
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < NT / 64; ++v) {
+                const uint32_t t = L.pub_cnt[v];
+                pos += v < wave ? t : 0u;
+                m_par += t;
+            }
+            for (int w = w0; w < w1; ++w) {
+                uint32_t bits = bitmap[w];
+                while (bits) {
+                    const int bit = __ffs(bits) - 1;
+                    bits &= bits - 1;
+                    if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)(w * 32 + bit);
+                    ++pos;
+                }
+            }
+        }
+    }
+    if (wave == 0) {
+    // compaction in ascending cluster id; a lane takes a slice of 8, 16 or 32 bits, the narrowest that still puts
+    // the whole bitmap on the 64 lanes at once, so that a densely set, short bitmap is not walked by a few lanes
+    const int pw_shift = nwords <= 16 ? 2 : nwords <= 32 ? 1 : 0;     // log2 of the slices per word
+    const int sbits = 32 >> pw_shift, nslices = nwords << pw_shift;   // slice width: 8, 16 or 32 bits
+    m = m_par;
+    for (int s0 = 0; s0 < (SPLIT ? 0 : nslices); s0 += 64) {
+        const int sl = s0 + lane;
+        const int w = sl >> pw_shift, sh = (sl & ((1 << pw_shift) - 1)) * sbits;
+        const uint32_t word = sl < nslices ? bitmap[w] & ~(!SPLIT && skip ? skip[w] : 0u) : 0u;
+        uint32_t bits = (sl < nslices) ? ((word >> sh) & (sbits == 32 ? 0xffffffffu : (1u << sbits) - 1u)) : 0u;
+        uint32_t total;
+        uint32_t pos = m + wave_excl_scan(__popc(bits), &total);
+        while (bits) {
+            const int bit = __ffs(bits) - 1;
+            bits &= bits - 1;
+            if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)(w * 32 + sh + bit);
+            ++pos;
+        }
+        m += total;
+    }
+    if (__builtin_expect(m > (uint32_t)a.cap, 0)) { flags |= SWARM_DEV_CAP; m = a.cap; }
+    L.pub_load[lane] = 0u;
+    if (SPLIT) {                        // what the other waves need for their share of the per-item pass
+        if (lane == 0) { off[1] = m; off[2] = INF32; off[3] = 0u; off[4] = 0u; }
+        L.adj_lo[lane] = 0u;
+        L.adj_hi[lane] = 0u;
+        L.seg_cnt[lane] = 0u;
+        L.seg_first[lane] = 0u;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    }   // wave 0
+
+    // per item: candidate SSD mask, weight, replication factor -- by wave 0 alone for a short list, by every thread
+    // for a long one (which also gathers, per SSD, the union of the candidate masks that contain it)
+    uint32_t rf_min = INF32, rf_max = 0;
+    // TAB is a compile-time copy of stage_tab (a run-time choice between the LDS and the memory copy of a table
+    // makes its look-ups flat loads); the replica slots are read four at a time, all in flight together (the index
+    // is clamped: a slot read twice sets the same bit twice).
+    auto item = [&](uint32_t i, auto tab_tag) __attribute__((always_inline)) {
+        constexpr bool TAB = decltype(tab_tag)::value;
+        const uint32_t c = list[i];
+        const int64_t gc = cbase + c;
+        uint64_t mask = 0;
+        const int R = a.R;
+        for (int r0 = 0; r0 < R; r0 += 4) {
+            int32_t dsk[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int r = min(r0 + u, R - 1);
+                dsk[u] = TAB ? s_rep[c * R + r] : a.replicas[gc * R + r];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {                         // selects, not branches: one basic block for the four slots
+                flags |= (dsk[u] >= a.D) ? SWARM_DEV_BAD_SSD : 0u;
+                mask |= ((uint32_t)dsk[u] < (uint32_t)a.D) ? (1ull << (dsk[u] & 63)) : 0ull;      // negative: an unused slot
+            }
+        }
+        if (mask == 0) flags |= SWARM_DEV_BAD_SSD;
+        mask_lo[i] = (uint32_t)mask;
+        mask_hi[i] = (uint32_t)(mask >> 32);
+        const int32_t wraw = TAB ? s_wgt[c] : (a.weight ? a.weight[gc] : 1);
+        const uint32_t wv = (uint32_t)max(wraw, 0);
+        wgt[i] = wv;
+        wsum = min(wsum + min(wv, 1u << 26), 1u << 26);       // saturating: only "below 2^26" matters
+        const uint32_t rf = __popcll(mask);
+        order[i] = rf;                               // replication factor for now
+        assign[i] = INF32;
+        rf_min = min(rf_min, rf);
+        rf_max = max(rf_max, rf);
+        return mask;
+    };
+    auto reduce_wave = [&]() __attribute__((always_inline)) {
+        rf_min = waveops::wave_min_u32(rf_min);
+        rf_max = ~waveops::wave_min_u32(~rf_max);
+        const bool any_big = __ballot(wsum >= (1u << 26)) != 0ull;
+        uint32_t total;
+        (void)wave_excl_scan(min(wsum, (1u << 26) - 1u), &total);     // <= 64 * (2^26 - 1): no wrap
+        wsum = any_big ? (1u << 26) : min(total, 1u << 26);
+    };
+    if (SPLIT) {
+        __syncthreads();
+        const uint32_t mm = off[1];
+        // with it, which SSDs share an item, and how many items have each SSD as their lowest candidate
+        for (uint32_t i = tid; i < mm; i += NT) {
+            uint64_t bits = stage_tab ? item(i, std::true_type{}) : item(i, std::false_type{});
+            const uint32_t lo = (uint32_t)bits, hi = (uint32_t)(bits >> 32);
+            if (bits) atomicAdd(&L.seg_first[__ffsll((unsigned long long)bits) - 1], 1u);
+            while (bits) {
+                const int d = __ffsll((unsigned long long)bits) - 1;
+                bits &= bits - 1;
+                if (lo) atomicOr(&L.adj_lo[d], lo);
+                if (hi) atomicOr(&L.adj_hi[d], hi);
+            }
+        }
+        reduce_wave();
+        if (lane == 0) {                             // at most 16 waves x 2^26: no wrap
+            atomicMin(&off[2], rf_min);
+            atomicMax(&off[3], rf_max);
+            atomicAdd(&off[4], wsum);
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+    if (SPLIT) {
+        rf_min = off[2];
+        rf_max = off[3];
+        wsum = min(off[4], 1u << 26);
+    } else {
+        if (stage_tab) { for (uint32_t i = lane; i < m; i += 64) (void)item(i, std::true_type{}); }
+        else { for (uint32_t i = lane; i < m; i += 64) (void)item(i, std::false_type{}); }
+        reduce_wave();
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+
+    // visiting order: stable by replication factor (identity when all factors agree); a list that may be split is brought into
+    // this order when a sub-problem gathers its items
+    const bool identity = m > 0 && rf_min == rf_max;
+    uint32_t singles = identity && rf_min <= 1 ? m : 0u;             // items with at most one candidate: the first ones visited
+    if (SPLIT || __builtin_expect(identity, 1)) {
+        // the list order is the visiting order: the chains read it without a look-up, the table stays unwritten
+    } else if (m > 0) {
+        uint32_t* rfv = assign;                      // assign is rewritten below, before the chain runs
+        for (uint32_t i = lane; i < m; i += 64) rfv[i] = order[i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        uint32_t outpos = 0;
+        for (uint32_t v = rf_min; v <= rf_max; ++v) {
+            for (uint32_t i0 = 0; i0 < m; i0 += 64) {
+                const uint32_t i = i0 + lane;
+                const bool hit = (i < m) && (rfv[i] == v);
+                const uint64_t b = __ballot(hit);
+                if (hit) order[outpos + __popcll(b & ((1ull << lane) - 1ull))] = i;
+                outpos += __popcll(b);
+            }
+            if (v <= 1) singles = outpos;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        for (uint32_t i = lane; i < m; i += 64) assign[i] = INF32;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+
+    // Independent sub-problems: two SSDs interact only through an item that has both as candidates, so the
+    // connected components of "share a routed item" never meet in a comparison and their chains can run side
+    // by side, each in the visiting order of its own items (an SSD's bucket is filled by one component only,
+    // so bucket positions are unchanged).  Lane d holds the set of SSDs reachable from d; Warshall's closure
+    // by rows; a component is named by its lowest SSD.
+    uint32_t ncomp = 1;
+    if (SPLIT && wsum < (1u << 26)) {
+        uint64_t reach = ((uint64_t)L.adj_hi[lane] << 32) | L.adj_lo[lane];
+        const bool active = reach != 0ull;           // some routed item has SSD `lane` as a candidate (then reach holds lane itself)
+        for (int kk = 0; kk < D; ++kk) {
+            const uint64_t rk = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(reach >> 32), kk) << 32) |
+                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)reach, kk);
+            if ((reach >> kk) & 1ull) reach |= rk;
+        }
+        const int rep = active ? __ffsll((unsigned long long)reach) - 1 : 64;
+        const uint64_t reps = __ballot(active && rep == lane);
+        ncomp = (uint32_t)__popcll(reps);
+        const uint32_t my_comp = active ? (uint32_t)__popcll(reps & ((1ull << rep) - 1ull)) : 0xffu;
+        L.comp_of[lane] = my_comp;
+        // an item belongs to the sub-problem of its lowest candidate SSD: the sub-problems' sizes from the per-SSD counts
+        if (active && L.seg_first[lane]) atomicAdd(&L.seg_cnt[my_comp], L.seg_first[lane]);
+    }
+    if (lane == 0) off[0] = ncomp;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    if (!SPLIT) {
+        // greedy least-loaded assignment, one chain
+        if (__builtin_expect(wsum < (1u << 26), 1)) {
+            uint32_t keybase = (uint32_t)lane;
+            if (singles < place_singles_min(SPLIT, D)) singles = 0;
+            if (singles) place_singles(singles, lane, order, identity, mask_lo, mask_hi, wgt, assign, L.pub_load, keybase, cnt, ~0ull);
+            if (m > singles) run_chain_packed(D, m - singles, lane, order + singles, mask_lo, mask_hi, wgt, assign, keybase, cnt, identity);
+            load = keybase >> 6;
+        } else {
+            if (D <= 16) greedy_chain_wide<4>(m, lane, order, mask_lo, mask_hi, wgt, assign, load, cnt, identity);
+            else greedy_chain_wide<6>(m, lane, order, mask_lo, mask_hi, wgt, assign, load, cnt, identity);
+        }
+    }
+    }   // wave 0
+    bool wide = false;                                     // loads beyond the packed chain's range: one chain over everything
+    if (SPLIT) {
+        __syncthreads();
+        const uint32_t ncomp = off[0], mm = off[1], rf_lo = off[2], rf_hi = off[3];
+        wide = off[4] >= (1u << 26);
+        constexpr uint32_t NW = NT / 64;
+        // A wave gathers a sub-problem's items (those with a candidate among the SSDs given) in visiting order: a pass over the
+        // list per replication factor, stable, four batches of look-ups in flight together.
+        auto gather = [&](uint64_t ssds, uint32_t* dst, uint32_t& singles) __attribute__((always_inline)) -> uint32_t {
+            const uint32_t ssds_lo = (uint32_t)ssds, ssds_hi = (uint32_t)(ssds >> 32);
+            uint32_t run = 0;
+            singles = 0;
+            for (uint32_t v = max(rf_lo, 1u); v <= rf_hi; ++v) {
+                for (uint32_t i0 = 0; i0 < mm; i0 += 256) {
+                    uint32_t ml[4], mh[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t i = i0 + u * 64 + lane;
+                        ml[u] = mask_lo[min(i, mm - 1)];              // clamped, not branched around: the four are in flight together
+                        mh[u] = D > 32 ? mask_hi[min(i, mm - 1)] : 0u;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        // an item's candidates all lie in one sub-problem: any of them tells which
+                        const bool hit = i0 + u * 64 + lane < mm && ((ml[u] & ssds_lo) | (mh[u] & ssds_hi)) != 0u &&
+                                         (uint32_t)(__popc(ml[u]) + __popc(mh[u])) == v;
+                        const uint64_t b = __ballot(hit);
+                        if (hit) dst[run + (uint32_t)__popcll(b & ((1ull << lane) - 1ull))] = i0 + u * 64 + lane;
+                        run += (uint32_t)__popcll(b);
+                    }
+                }
+                if (v == 1) singles = run;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            return run;
+        };
+        uint32_t singles;
+        if (wide) {
+            if (wave == 0) {
+                const uint32_t run = gather(~0ull, order2, singles);
+                if (D <= 16) greedy_chain_wide<4>(run, lane, order2, mask_lo, mask_hi, wgt, assign, load, cnt);
+                else greedy_chain_wide<6>(run, lane, order2, mask_lo, mask_hi, wgt, assign, load, cnt);
+            }
+        } else {
+            // component c on wave c mod (number of waves): a wave that gets several components runs them one after the
+            // other on the same registers (their SSDs are disjoint)
+            uint32_t routed;
+            const uint32_t seg = wave_excl_scan(L.seg_cnt[lane], &routed);      // lanes >= ncomp hold 0
+            uint32_t keybase = (uint32_t)lane, mycnt = 0;
+            for (uint32_t c = (uint32_t)wave; c < ncomp; c += NW) {
+                const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)seg, (int)c);
+                const uint64_t ssds = __ballot(lane < D && L.comp_of[lane] == c);         // the component's SSDs
+                const uint32_t run = gather(ssds, order2 + base, singles);
+                if (D <= 32 && __popcll(ssds) <= 2 && ssds != 0ull) {
+                    const int sa = __ffsll((unsigned long long)ssds) - 1, sb = 63 - __clzll((unsigned long long)ssds);
+                    greedy_chain_pair(run, lane, order2 + base, mask_lo, wgt, assign, keybase, mycnt, sa, sb != sa ? sb : -1);
+                } else {
+                    if (singles < place_singles_min(SPLIT, D)) singles = 0;
+                    if (singles) place_singles(singles, lane, order2 + base, false, mask_lo, mask_hi, wgt, assign, L.pub_load, keybase, mycnt, ssds);
+                    if (run > singles)
+                        run_chain_packed(D, run - singles, lane, order2 + base + singles, mask_lo, mask_hi, wgt, assign, keybase, mycnt);
+                }
+            }
+            if (lane < D) {
+                const uint32_t c = L.comp_of[lane];
+                if (c != 0xffu && c % NW == (uint32_t)wave) {
+                    L.pub_load[lane] = keybase >> 6;
+                    L.pub_cnt[lane] = mycnt;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // Bucket offsets are single-wave work; the scatter of the queues is per-item work, which the long-list kernels
+    // leave to all their waves when those are still here (they are after a split into sub-problems).
+    constexpr bool all_emit = SPLIT;
+    if (wave != 0 && !all_emit) {
+        if (flags) atomicOr(a.dev_flags, flags);
+        return;
+    }
+    uint32_t total = 0;
+    if (wave == 0) {
+        if (SPLIT && !wide) {
+            const bool active = lane < D && L.comp_of[lane] != 0xffu;
+            load = active ? L.pub_load[lane] : 0u;
+            cnt = active ? L.pub_cnt[lane] : 0u;
+        }
+        // buckets SSD-major, insertion order inside a bucket
+        const uint32_t my_off = wave_excl_scan(lane < D ? cnt : 0u, &total);
+        off[lane] = my_off;
+        int32_t* q_off = a.q_off + g * (D + 1);
+        if (lane < D) {
+            q_off[lane] = (int32_t)my_off;
+            a.q_load[g * D + lane] = (int32_t)load;
+        }
+        if (lane == 0) {
+            q_off[D] = (int32_t)total;
+            if (all_emit) { L.seg_cnt[0] = total; L.seg_cnt[1] = m; }      // the sub-problems' sizes have been read
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    }
+    uint32_t m_emit = m;
+    if (all_emit) {
+        __syncthreads();
+        total = L.seg_cnt[0];
+        m_emit = L.seg_cnt[1];
+    }
+    const uint32_t first = all_emit ? (uint32_t)tid : (uint32_t)lane, step = all_emit ? (uint32_t)NT : 64u;
+    int32_t* qc = a.q_cluster + g * a.cap;
+    for (uint32_t i = first; i < m_emit; i += step) {
+        const uint32_t as = assign[i];
+        if (as != INF32) qc[off[as >> 24] + (as & 0xffffffu)] = (int32_t)list[i];
+    }
+    for (uint32_t p = total + first; p < (uint32_t)a.cap; p += step) qc[p] = -1;
+
+    if (flags) atomicOr(a.dev_flags, flags);
+}
+
+// One group on a block of NT threads.  All waves cooperate on staging and on the merge; map_assign does the rest.
 // When the head's lookup tables are small they are staged in LDS by one burst of independent loads,
 // so that the kernel pays one memory round trip instead of three dependent ones (selection ->
 // cluster of entry -> replica row).  PRESTAGED: the caller has already filled the staged tables,
 // cleared the bitmap and synchronised, and `sel` points into LDS; or it has set the activated clusters' bits as well (merged),
 // resident ones among them: those are left out through the bitmap `skip`.
 // BIG: the kernel is meant for thousands of merged picks: it takes eight of them per thread in its first burst and the merge
-// marks bytes.  The fused kernel of short selections (PRESTAGED, not BIG) also leaves out the split into sub-problems -- it is
-// not only unused there, its mere presence between the phases cost 0.25 us per launch.
-template <int NT, bool PRESTAGED, bool BIG, bool STRIDED = false>
+// marks bytes, of the clusters or first of the entries (ENTRY_MARKS, see below).
+// SPLIT: the list may be long enough to be divided into sub-problems; whether it is, the number of clusters found decides.
+// Both ways have a body of their own, and a launch whose lists cannot be long takes a kernel without the second one, because
+// what is only passed over costs too (scalar registers spilled for it, instructions fetched from further away): with one body
+// for both 64 picks of 256 clusters mapped in 7.2 us, now in 6.5; 128 picks of 256 clusters in 8.8 us, now in 8.4.
+template <int NT, bool PRESTAGED, bool BIG, bool STRIDED = false, bool SPLIT = BIG, bool ENTRY_MARKS = false>
 __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int32_t* __restrict__ sel, uint32_t* smem,
                                           int stage_e2c, int stage_tab, bool merged = false, const uint32_t* skip = nullptr) {
     // position of the group's s-th entry behind `sel`
@@ -424,8 +789,7 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     };
     const MapLds L(smem, a, stage_e2c, stage_tab);
     const int nwords = L.nwords;
-    uint32_t *bitmap = L.bitmap, *list = L.list, *mask_lo = L.mask_lo, *mask_hi = L.mask_hi, *wgt = L.wgt, *order = L.order,
-             *assign = L.assign, *off = L.off, *order2 = L.order2;
+    uint32_t *bitmap = L.bitmap, *order2 = L.order2;
     int32_t *s_e2c = L.s_e2c, *s_rep = L.s_rep, *s_wgt = L.s_wgt;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -440,10 +804,10 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     // harmless) and the bytes are folded into the bitmap afterwards.  The byte map borrows the room of the split
     // arrays, which are not in use yet.  Where the picks outnumber the entries (streams that share a prefix pick the same
     // ones again and again), the entries are marked first, a byte each, and only the N entries look their cluster up, lane by
-    // lane in order, instead of the S picks all over the table: 8192 picks of 2048 entries merge in 3900 cycles, not 5100.
-    const bool byte_marks = BIG && !PRESTAGED && a.split_off != 0 && a.S >= 2048 && (size_t)a.cap * 8 >= (size_t)a.Nc + 64;
+    // lane in order, instead of the S picks all over the table: 8192 picks of 2048 entries merge in 3900 cycles, not 5100
+    // (ENTRY_MARKS, a kernel of its own: merges that passed over this code took 0.5 us longer).
+    const bool byte_marks = ENTRY_MARKS || (BIG && !PRESTAGED && a.split_off != 0 && a.S >= 2048 && (size_t)a.cap * 8 >= (size_t)a.Nc + 64);
     const int mark_bytes = (a.Nc + 63) / 64 * 64;
-    const bool entry_marks = byte_marks && a.S >= 2 * a.N && (size_t)a.cap * 8 >= (size_t)mark_bytes + (size_t)a.N + 4;
     uint8_t* marks = reinterpret_cast<uint8_t*>(order2);
     uint8_t* picked = marks + mark_bytes;
     constexpr int SEL_REGS = BIG ? 8 : 4;           // long lists: 8192 merged picks on 1024 threads are one burst of loads, not two round trips
@@ -456,7 +820,7 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
             my_sel[r] = (s0 < a.S) ? sel[at(s0)] : -1;
         }
         if (byte_marks)
-            for (int i = tid; i < (mark_bytes + (entry_marks ? a.N + 3 : 0)) >> 2; i += NT) reinterpret_cast<uint32_t*>(marks)[i] = 0u;
+            for (int i = tid; i < (mark_bytes + (ENTRY_MARKS ? a.N + 3 : 0)) >> 2; i += NT) reinterpret_cast<uint32_t*>(marks)[i] = 0u;
         // Replica and weight tables of at most two resp. one 16-byte vector per thread travel through registers beside the
         // entry->cluster table: staged one after the other, each table waited for a memory round trip of its own.
         const int nrep = a.Nc * a.R;
@@ -529,7 +893,7 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
             }
             return;
         }
-        if (entry_marks) {
+        if (ENTRY_MARKS) {
             auto pick = [&](int32_t e) __attribute__((always_inline)) {
                 if ((uint32_t)e < (uint32_t)a.N) picked[e] = 1;
                 else flags |= e != -1 ? SWARM_DEV_BAD_ENTRY : 0u;
@@ -582,372 +946,30 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
         __syncthreads();
     }
 
-    // Every wave counts the merged clusters (a popcount of the bitmap).  Few of them: wave 0 does all the rest
-    // alone, as one chain.  Many: wave 0 compacts, orders and looks for independent sub-problems, whose chains
-    // then run side by side on the other waves; all waves meet at the barriers in between (the decision is
-    // the same in every wave, so either all of them go to the barriers or none).
-    constexpr bool SPLIT = BIG || !PRESTAGED;        // the fused short-list kernel (one step's selection) leaves the split out
-    uint32_t m_all = 0;
-    if (SPLIT) {
-        for (int w0 = 0; w0 < nwords; w0 += 64) m_all += (w0 + lane < nwords) ? __popc(bitmap[w0 + lane]) : 0;
-        uint32_t total;
-        (void)wave_excl_scan(m_all, &total);
-        m_all = min(total, (uint32_t)a.cap);
-    }
-    const bool try_split = SPLIT && NT > 64 && a.split_off != 0 && m_all >= MAP_SPLIT_MIN_ITEMS;
-    if (wave != 0 && !try_split) {
-        if (flags) atomicOr(a.dev_flags, flags);
-        return;
-    }
-    uint32_t m = 0, load = 0, cnt = 0, wsum = 0;
-    const int D = a.D;
-    // Long lists are compacted by every thread instead of wave 0 alone walking the bitmap.  A short bitmap: a thread places the
-    // cluster of its own bit (the words' popcounts are scanned by every wave for itself: lane j = word j).  A long one: a thread
-    // owns a run of words, mostly with a bit or none (256 words on wave 0: 4700 cycles).
-    const bool par_compact = SPLIT && try_split;
-    uint32_t m_par = 0;
-    if (par_compact) {
-        if (nwords <= 64) {
-            const uint32_t wexcl = wave_excl_scan(lane < nwords ? (uint32_t)__popc(bitmap[lane]) : 0u, &m_par);
-            for (int b0 = 0; b0 < nwords * 32; b0 += NT) {
-                const int bit = b0 + tid, w = bit >> 5;
-                const uint32_t word = w < nwords ? bitmap[w] : 0u;
-                const uint32_t before = (uint32_t)__shfl((int)wexcl, w & 63, 64);
-                if ((word >> (bit & 31)) & 1u) {
-                    const uint32_t pos = before + (uint32_t)__popc(word & ((1u << (bit & 31)) - 1u));
-                    if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)bit;
-                }
-            }
-        } else {
-            const int wpt = (nwords + NT - 1) / NT;
-            const int w0 = min(tid * wpt, nwords), w1 = min(w0 + wpt, nwords);
-            uint32_t mine = 0, wtot;
-            for (int w = w0; w < w1; ++w) mine += (uint32_t)__popc(bitmap[w]);
-            uint32_t pos = wave_excl_scan(mine, &wtot);
-            if (lane == 0) L.pub_cnt[wave] = wtot;
-            __syncthreads();
-#pragma unroll
-            for (int v = 0; v < NT / 64; ++v) {
-                const uint32_t t = L.pub_cnt[v];
-                pos += v < wave ? t : 0u;
-                m_par += t;
-            }
-            for (int w = w0; w < w1; ++w) {
-                uint32_t bits = bitmap[w];
-                while (bits) {
-                    const int bit = __ffs(bits) - 1;
-                    bits &= bits - 1;
-                    if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)(w * 32 + bit);
-                    ++pos;
-                }
-            }
+    // Few clusters: wave 0 does all the rest alone, as one chain.  Many (every wave counts the bits for itself, so all of them take
+    // the same way): all waves share the work, and independent sub-problems run as chains of their own, side by side.
+    if constexpr (SPLIT) {
+        uint32_t mine = 0, total;
+        for (int w0 = 0; w0 < nwords; w0 += 64) mine += (w0 + lane < nwords) ? __popc(bitmap[w0 + lane]) : 0;
+        (void)wave_excl_scan(mine, &total);
+        if ((!BIG || a.split_off != 0) && min(total, (uint32_t)a.cap) >= MAP_SPLIT_MIN_ITEMS) {
+            map_assign<NT, true>(a, g, h, L, stage_tab, nullptr, flags);
+            return;
         }
     }
-    if (wave == 0) {
-    // compaction in ascending cluster id; a lane takes a slice of 8, 16 or 32 bits, the narrowest that still puts
-    // the whole bitmap on the 64 lanes at once, so that a densely set, short bitmap is not walked by a few lanes
-    const int pw_shift = nwords <= 16 ? 2 : nwords <= 32 ? 1 : 0;     // log2 of the slices per word
-    const int sbits = 32 >> pw_shift, nslices = nwords << pw_shift;   // slice width: 8, 16 or 32 bits
-    m = m_par;
-    for (int s0 = 0; s0 < (par_compact ? 0 : nslices); s0 += 64) {
-        const int sl = s0 + lane;
-        const int w = sl >> pw_shift, sh = (sl & ((1 << pw_shift) - 1)) * sbits;
-        const uint32_t word = sl < nslices ? bitmap[w] & ~(PRESTAGED && !BIG && skip ? skip[w] : 0u) : 0u;
-        uint32_t bits = (sl < nslices) ? ((word >> sh) & (sbits == 32 ? 0xffffffffu : (1u << sbits) - 1u)) : 0u;
-        uint32_t total;
-        uint32_t pos = m + wave_excl_scan(__popc(bits), &total);
-        while (bits) {
-            const int bit = __ffs(bits) - 1;
-            bits &= bits - 1;
-            if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)(w * 32 + sh + bit);
-            ++pos;
-        }
-        m += total;
-    }
-    if (__builtin_expect(m > (uint32_t)a.cap, 0)) { flags |= SWARM_DEV_CAP; m = a.cap; }
-    L.pub_load[lane] = 0u;
-    if (SPLIT && try_split) {                        // what the other waves need for their share of the per-item pass
-        if (lane == 0) { off[1] = m; off[2] = INF32; off[3] = 0u; off[4] = 0u; }
-        L.adj_lo[lane] = 0u;
-        L.adj_hi[lane] = 0u;
-        L.seg_cnt[lane] = 0u;
-        L.seg_first[lane] = 0u;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    }   // wave 0
-
-    // per item: candidate SSD mask, weight, replication factor -- by wave 0 alone for a short list, by every thread
-    // for a long one (which also gathers, per SSD, the union of the candidate masks that contain it)
-    uint32_t rf_min = INF32, rf_max = 0;
-    // TAB is a compile-time copy of stage_tab (a run-time choice between the LDS and the memory copy of a table
-    // makes its look-ups flat loads); the replica slots are read four at a time, all in flight together (the index
-    // is clamped: a slot read twice sets the same bit twice).
-    auto item = [&](uint32_t i, auto tab_tag) __attribute__((always_inline)) {
-        constexpr bool TAB = decltype(tab_tag)::value;
-        const uint32_t c = list[i];
-        const int64_t gc = cbase + c;
-        uint64_t mask = 0;
-        const int R = a.R;
-        for (int r0 = 0; r0 < R; r0 += 4) {
-            int32_t dsk[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int r = min(r0 + u, R - 1);
-                dsk[u] = TAB ? s_rep[c * R + r] : a.replicas[gc * R + r];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {                         // selects, not branches: one basic block for the four slots
-                flags |= (dsk[u] >= a.D) ? SWARM_DEV_BAD_SSD : 0u;
-                mask |= ((uint32_t)dsk[u] < (uint32_t)a.D) ? (1ull << (dsk[u] & 63)) : 0ull;      // negative: an unused slot
-            }
-        }
-        if (mask == 0) flags |= SWARM_DEV_BAD_SSD;
-        mask_lo[i] = (uint32_t)mask;
-        mask_hi[i] = (uint32_t)(mask >> 32);
-        const int32_t wraw = TAB ? s_wgt[c] : (a.weight ? a.weight[gc] : 1);
-        const uint32_t wv = (uint32_t)max(wraw, 0);
-        wgt[i] = wv;
-        wsum = min(wsum + min(wv, 1u << 26), 1u << 26);       // saturating: only "below 2^26" matters
-        const uint32_t rf = __popcll(mask);
-        order[i] = rf;                               // replication factor for now
-        assign[i] = INF32;
-        rf_min = min(rf_min, rf);
-        rf_max = max(rf_max, rf);
-        return mask;
-    };
-    auto reduce_wave = [&]() __attribute__((always_inline)) {
-        rf_min = waveops::wave_min_u32(rf_min);
-        rf_max = ~waveops::wave_min_u32(~rf_max);
-        const bool any_big = __ballot(wsum >= (1u << 26)) != 0ull;
-        uint32_t total;
-        (void)wave_excl_scan(min(wsum, (1u << 26) - 1u), &total);     // <= 64 * (2^26 - 1): no wrap
-        wsum = any_big ? (1u << 26) : min(total, 1u << 26);
-    };
-    if (SPLIT && try_split) {
-        __syncthreads();
-        const uint32_t mm = off[1];
-        // with it, which SSDs share an item, and how many items have each SSD as their lowest candidate
-        for (uint32_t i = tid; i < mm; i += NT) {
-            uint64_t bits = stage_tab ? item(i, std::true_type{}) : item(i, std::false_type{});
-            const uint32_t lo = (uint32_t)bits, hi = (uint32_t)(bits >> 32);
-            if (bits) atomicAdd(&L.seg_first[__ffsll((unsigned long long)bits) - 1], 1u);
-            while (bits) {
-                const int d = __ffsll((unsigned long long)bits) - 1;
-                bits &= bits - 1;
-                if (lo) atomicOr(&L.adj_lo[d], lo);
-                if (hi) atomicOr(&L.adj_hi[d], hi);
-            }
-        }
-        reduce_wave();
-        if (lane == 0) {                             // at most 16 waves x 2^26: no wrap
-            atomicMin(&off[2], rf_min);
-            atomicMax(&off[3], rf_max);
-            atomicAdd(&off[4], wsum);
-        }
-        __syncthreads();
-    }
-    if (wave == 0) {
-    if (SPLIT && try_split) {
-        rf_min = off[2];
-        rf_max = off[3];
-        wsum = min(off[4], 1u << 26);
-    } else {
-        if (stage_tab) { for (uint32_t i = lane; i < m; i += 64) (void)item(i, std::true_type{}); }
-        else { for (uint32_t i = lane; i < m; i += 64) (void)item(i, std::false_type{}); }
-        reduce_wave();
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-
-    // visiting order: stable by replication factor (identity when all factors agree); a list that may be split is brought into
-    // this order when a sub-problem gathers its items
-    const bool identity = m > 0 && rf_min == rf_max;
-    uint32_t singles = identity && rf_min <= 1 ? m : 0u;             // items with at most one candidate: the first ones visited
-    if (try_split || __builtin_expect(identity, 1)) {
-        // the list order is the visiting order: the chains read it without a look-up, the table stays unwritten
-    } else if (m > 0) {
-        uint32_t* rfv = assign;                      // assign is rewritten below, before the chain runs
-        for (uint32_t i = lane; i < m; i += 64) rfv[i] = order[i];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        uint32_t outpos = 0;
-        for (uint32_t v = rf_min; v <= rf_max; ++v) {
-            for (uint32_t i0 = 0; i0 < m; i0 += 64) {
-                const uint32_t i = i0 + lane;
-                const bool hit = (i < m) && (rfv[i] == v);
-                const uint64_t b = __ballot(hit);
-                if (hit) order[outpos + __popcll(b & ((1ull << lane) - 1ull))] = i;
-                outpos += __popcll(b);
-            }
-            if (v <= 1) singles = outpos;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        for (uint32_t i = lane; i < m; i += 64) assign[i] = INF32;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-
-    // Independent sub-problems: two SSDs interact only through an item that has both as candidates, so the
-    // connected components of "share a routed item" never meet in a comparison and their chains can run side
-    // by side, each in the visiting order of its own items (an SSD's bucket is filled by one component only,
-    // so bucket positions are unchanged).  Lane d holds the set of SSDs reachable from d; Warshall's closure
-    // by rows; a component is named by its lowest SSD.
-    uint32_t ncomp = 1;
-    if (try_split && wsum < (1u << 26)) {
-        uint64_t reach = ((uint64_t)L.adj_hi[lane] << 32) | L.adj_lo[lane];
-        const bool active = reach != 0ull;           // some routed item has SSD `lane` as a candidate (then reach holds lane itself)
-        for (int kk = 0; kk < D; ++kk) {
-            const uint64_t rk = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(reach >> 32), kk) << 32) |
-                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)reach, kk);
-            if ((reach >> kk) & 1ull) reach |= rk;
-        }
-        const int rep = active ? __ffsll((unsigned long long)reach) - 1 : 64;
-        const uint64_t reps = __ballot(active && rep == lane);
-        ncomp = (uint32_t)__popcll(reps);
-        const uint32_t my_comp = active ? (uint32_t)__popcll(reps & ((1ull << rep) - 1ull)) : 0xffu;
-        L.comp_of[lane] = my_comp;
-        // an item belongs to the sub-problem of its lowest candidate SSD: the sub-problems' sizes from the per-SSD counts
-        if (active && L.seg_first[lane]) atomicAdd(&L.seg_cnt[my_comp], L.seg_first[lane]);
-    }
-    if (lane == 0) off[0] = ncomp;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    if (!try_split) {
-        // greedy least-loaded assignment, one chain
-        if (__builtin_expect(wsum < (1u << 26), 1)) {
-            uint32_t keybase = (uint32_t)lane;
-            if (singles) place_singles(singles, lane, order, identity, mask_lo, mask_hi, wgt, assign, L.pub_load, keybase, cnt, D, ~0ull);
-            if (m > singles) run_chain_packed(D, m - singles, lane, order + singles, mask_lo, mask_hi, wgt, assign, keybase, cnt, identity);
-            load = keybase >> 6;
-        } else {
-            if (D <= 16) greedy_chain_wide<4>(m, lane, order, mask_lo, mask_hi, wgt, assign, load, cnt, identity);
-            else greedy_chain_wide<6>(m, lane, order, mask_lo, mask_hi, wgt, assign, load, cnt, identity);
-        }
-    }
-    }   // wave 0
-    bool wide = false;                                     // loads beyond the packed chain's range: one chain over everything
-    if (SPLIT && try_split) {
-        __syncthreads();
-        const uint32_t ncomp = off[0], mm = off[1], rf_lo = off[2], rf_hi = off[3];
-        wide = off[4] >= (1u << 26);
-        constexpr uint32_t NW = NT / 64;
-        // A wave gathers a sub-problem's items (those with a candidate among the SSDs given) in visiting order: a pass over the
-        // list per replication factor, stable, four batches of look-ups in flight together.
-        auto gather = [&](uint64_t ssds, uint32_t* dst, uint32_t& singles) __attribute__((always_inline)) -> uint32_t {
-            const uint32_t ssds_lo = (uint32_t)ssds, ssds_hi = (uint32_t)(ssds >> 32);
-            uint32_t run = 0;
-            singles = 0;
-            for (uint32_t v = max(rf_lo, 1u); v <= rf_hi; ++v) {
-                for (uint32_t i0 = 0; i0 < mm; i0 += 256) {
-                    uint32_t ml[4], mh[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const uint32_t i = i0 + u * 64 + lane;
-                        ml[u] = mask_lo[min(i, mm - 1)];              // clamped, not branched around: the four are in flight together
-                        mh[u] = D > 32 ? mask_hi[min(i, mm - 1)] : 0u;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        // an item's candidates all lie in one sub-problem: any of them tells which
-                        const bool hit = i0 + u * 64 + lane < mm && ((ml[u] & ssds_lo) | (mh[u] & ssds_hi)) != 0u &&
-                                         (uint32_t)(__popc(ml[u]) + __popc(mh[u])) == v;
-                        const uint64_t b = __ballot(hit);
-                        if (hit) dst[run + (uint32_t)__popcll(b & ((1ull << lane) - 1ull))] = i0 + u * 64 + lane;
-                        run += (uint32_t)__popcll(b);
-                    }
-                }
-                if (v == 1) singles = run;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-            return run;
-        };
-        uint32_t singles;
-        if (wide) {
-            if (wave == 0) {
-                const uint32_t run = gather(~0ull, order2, singles);
-                if (D <= 16) greedy_chain_wide<4>(run, lane, order2, mask_lo, mask_hi, wgt, assign, load, cnt);
-                else greedy_chain_wide<6>(run, lane, order2, mask_lo, mask_hi, wgt, assign, load, cnt);
-            }
-        } else {
-            // component c on wave c mod (number of waves): a wave that gets several components runs them one after the
-            // other on the same registers (their SSDs are disjoint)
-            uint32_t routed;
-            const uint32_t seg = wave_excl_scan(L.seg_cnt[lane], &routed);      // lanes >= ncomp hold 0
-            uint32_t keybase = (uint32_t)lane, mycnt = 0;
-            for (uint32_t c = (uint32_t)wave; c < ncomp; c += NW) {
-                const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)seg, (int)c);
-                const uint64_t ssds = __ballot(lane < D && L.comp_of[lane] == c);         // the component's SSDs
-                const uint32_t run = gather(ssds, order2 + base, singles);
-                if (D <= 32 && __popcll(ssds) <= 2 && ssds != 0ull) {
-                    const int sa = __ffsll((unsigned long long)ssds) - 1, sb = 63 - __clzll((unsigned long long)ssds);
-                    greedy_chain_pair(run, lane, order2 + base, mask_lo, wgt, assign, keybase, mycnt, sa, sb != sa ? sb : -1);
-                } else {
-                    if (singles) place_singles(singles, lane, order2 + base, false, mask_lo, mask_hi, wgt, assign, L.pub_load, keybase, mycnt, D, ssds);
-                    if (run > singles)
-                        run_chain_packed(D, run - singles, lane, order2 + base + singles, mask_lo, mask_hi, wgt, assign, keybase, mycnt);
-                }
-            }
-            if (lane < D) {
-                const uint32_t c = L.comp_of[lane];
-                if (c != 0xffu && c % NW == (uint32_t)wave) {
-                    L.pub_load[lane] = keybase >> 6;
-                    L.pub_cnt[lane] = mycnt;
-                }
-            }
-        }
-        __syncthreads();
-    }
-    // Bucket offsets are single-wave work; the scatter of the queues is per-item work, which the long-list kernels
-    // leave to all their waves when those are still here (they are after a split into sub-problems).
-    const bool all_emit = SPLIT && try_split;
-    if (wave != 0 && !all_emit) {
-        if (flags) atomicOr(a.dev_flags, flags);
-        return;
-    }
-    uint32_t total = 0;
-    if (wave == 0) {
-        if (SPLIT && try_split && !wide) {
-            const bool active = lane < D && L.comp_of[lane] != 0xffu;
-            load = active ? L.pub_load[lane] : 0u;
-            cnt = active ? L.pub_cnt[lane] : 0u;
-        }
-        // buckets SSD-major, insertion order inside a bucket
-        const uint32_t my_off = wave_excl_scan(lane < D ? cnt : 0u, &total);
-        off[lane] = my_off;
-        int32_t* q_off = a.q_off + g * (D + 1);
-        if (lane < D) {
-            q_off[lane] = (int32_t)my_off;
-            a.q_load[g * D + lane] = (int32_t)load;
-        }
-        if (lane == 0) {
-            q_off[D] = (int32_t)total;
-            if (all_emit) { L.seg_cnt[0] = total; L.seg_cnt[1] = m; }      // the sub-problems' sizes have been read
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    }
-    uint32_t m_emit = m;
-    if (all_emit) {
-        __syncthreads();
-        total = L.seg_cnt[0];
-        m_emit = L.seg_cnt[1];
-    }
-    const uint32_t first = all_emit ? (uint32_t)tid : (uint32_t)lane, step = all_emit ? (uint32_t)NT : 64u;
-    int32_t* qc = a.q_cluster + g * a.cap;
-    for (uint32_t i = first; i < m_emit; i += step) {
-        const uint32_t as = assign[i];
-        if (as != INF32) qc[off[as >> 24] + (as & 0xffffffu)] = (int32_t)list[i];
-    }
-    for (uint32_t p = total + first; p < (uint32_t)a.cap; p += step) qc[p] = -1;
-
-    if (flags) atomicOr(a.dev_flags, flags);
+    map_assign<NT, false>(a, g, h, L, stage_tab, skip, flags);
 }
 
 // NT = 256 for a step's selection; 1024 for long merged selections, whose merge is plain per-entry work that
 // scales with the number of threads.
 // STRIDED: group g = (step g / H, head g % H) merges the B streams of that step out of selections laid out
 // [step][stream][head][k], the layout the selection step writes.
-template <int NT, bool STRIDED = false>
+template <int NT, bool STRIDED, bool SPLIT, bool ENTRY_MARKS = false>
 __global__ __launch_bounds__(NT) void map_requests_kernel(MapArgs a, int stage_e2c, int stage_tab) {
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     const int64_t g = blockIdx.x;
     const int32_t* sel = STRIDED ? a.sel + (g / a.H) * (int64_t)a.S * a.H + (g % a.H) * a.piece : a.sel + g * a.S;
-    map_group<NT, false, (NT > 256), STRIDED>(a, g, sel, smem, stage_e2c, stage_tab);
+    map_group<NT, false, (NT > 256), STRIDED, SPLIT, ENTRY_MARKS>(a, g, sel, smem, stage_e2c, stage_tab);
 }
 
 // Copies n words to LDS through registers in two steps, so that the loads are in flight while something else runs: up to 4 VECS
@@ -1071,16 +1093,20 @@ swarm_status launch_map(swarm_ctx* ctx, const int32_t* sel, int64_t groups, int 
     if (lds + tab_bytes <= budget) { stage_tab = 1; lds += tab_bytes; }
     if (lds + e2c_bytes <= budget) { stage_e2c = 1; lds += e2c_bytes; }
     if (lds + (size_t)cap * 8 <= budget) { a.split_off = (int)(lds / 4); lds += (size_t)cap * 8; }
-    if (piece > 0 && S >= 2048)
-        hipLaunchKernelGGL((map_requests_kernel<1024, true>), dim3((unsigned)groups), dim3(1024), lds, ctx->stream, a, stage_e2c, stage_tab);
-    else if (piece > 0)
-        hipLaunchKernelGGL((map_requests_kernel<MAP_THREADS, true>), dim3((unsigned)groups), dim3(MAP_THREADS), lds, ctx->stream, a,
-                           stage_e2c, stage_tab);
-    else if (S >= 2048)
-        hipLaunchKernelGGL(map_requests_kernel<1024>, dim3((unsigned)groups), dim3(1024), lds, ctx->stream, a, stage_e2c, stage_tab);
-    else
-        hipLaunchKernelGGL(map_requests_kernel<MAP_THREADS>, dim3((unsigned)groups), dim3(MAP_THREADS), lds, ctx->stream, a, stage_e2c,
-                           stage_tab);
+    using kernel_t = void (*)(MapArgs, int, int);
+    kernel_t kernel;
+    if (S >= 2048) {
+        // the entries are marked where the picks outnumber them two to one and their marks fit beside those of the clusters
+        const size_t room = a.split_off ? (size_t)cap * 8 : 0;
+        const bool entry_marks = S / 2 >= N && room >= (size_t)Nc + 64 && room >= ((size_t)Nc + 63) / 64 * 64 + (size_t)N + 4;
+        kernel = entry_marks ? (piece > 0 ? map_requests_kernel<1024, true, true, true> : map_requests_kernel<1024, false, true, true>)
+                             : (piece > 0 ? map_requests_kernel<1024, true, true> : map_requests_kernel<1024, false, true>);
+    } else {
+        const bool split = a.split_off != 0 && (S < cap ? S : cap) >= (int)MAP_SPLIT_MIN_ITEMS;
+        kernel = split ? (piece > 0 ? map_requests_kernel<MAP_THREADS, true, true> : map_requests_kernel<MAP_THREADS, false, true>)
+                       : (piece > 0 ? map_requests_kernel<MAP_THREADS, true, false> : map_requests_kernel<MAP_THREADS, false, false>);
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(S >= 2048 ? 1024 : MAP_THREADS), lds, ctx->stream, a, stage_e2c, stage_tab);
     return swarm_check_launch(ctx, "map_requests_kernel");
 }
 

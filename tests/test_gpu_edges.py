@@ -295,3 +295,57 @@ def test_merged_lists_of_replica_pairs(sw, N, Nc, S, D, top):
             for g, e in zip(got, oracle.map_requests(good, H, N, np.minimum(e2c, Nc - 1), Nc, rep, D, weight, res, cap=cap)):
                 assert np.array_equal(g.cpu().numpy(), e)
         assert (sw.device_status() != 0) == bad
+
+
+@pytest.mark.parametrize("D,R,picks,singles", [
+    (8, 2, 95, 23), (8, 2, 96, 24), (8, 3, 97, 25), (16, 2, 96, 95), (17, 2, 60, 7), (24, 1, 95, 95), (24, 3, 130, 8), (64, 2, 95, 9), (64, 1, 200, 200),
+    (6, 2, 200, 100), (4, 2, 40, 23), (4, 2, 40, 24)])
+def test_mapping_on_both_sides_of_the_split(sw, D, R, picks, singles):
+    """Lists of just fewer and just more clusters than are divided into sub-problems, by the number of picks and by what residency
+    leaves of them; just fewer and just more single copies than are placed without the chain, on both sides of 16 SSDs."""
+    H, Nc = 2, 700
+    rng = np.random.default_rng(D * picks + singles)
+    rep = np.stack([rng.permutation(D)[:R] for _ in range(H * Nc)]).astype(np.int32)
+    weight = rng.integers(0, 5, H * Nc).astype(np.int32)
+    e2c = np.stack([np.arange(Nc), rng.permutation(Nc)]).astype(np.int32)
+    sel = np.stack([rng.permutation(Nc)[:picks] for _ in range(4)]).astype(np.int32)
+    clusters = np.stack([e2c[g % H][sel[g]] for g in range(4)])
+    for g in range(2):                                               # heads 0 and 1: the first `singles` picks of groups 0 and 1
+        rep[g * Nc + clusters[g][:singles], 1:] = -1
+    for left in (picks, 96, 95, singles, 1, 0):                      # what is left of groups 0 and 1 after residency
+        if left > picks:
+            continue
+        bits = np.zeros(H * Nc, bool)
+        for g in range(2):
+            bits[g * Nc + clusters[g][left:]] = True
+        res = np.packbits(np.pad(bits, (0, -len(bits) % 32)), bitorder="little").view(np.uint32)
+        for s in (sel, np.concatenate([sel, sel[:, ::-1], np.full((4, 3), -1, np.int32)], 1)):   # picks repeated, padding
+            cap = min(s.shape[1], Nc)
+            got = sw.map_requests(dev(s), H, Nc, dev(e2c), Nc, dev(rep), D, dev(weight), dev(res.view(np.int32)), cap=cap)
+            for a, e in zip(got, oracle.map_requests(s, H, Nc, e2c, Nc, rep, D, weight, res, cap=cap)):
+                assert np.array_equal(a.cpu().numpy(), e), left
+        streams = np.ascontiguousarray(np.stack([sel[:2], sel[2:]], 0))                          # [B][H][k]: both streams of a head merged
+        merged = np.concatenate([sel[:2], sel[2:]], 1)
+        cap = min(2 * picks, Nc)
+        got = sw.map_requests_streams(dev(streams), Nc, dev(e2c), Nc, dev(rep), D, dev(weight), dev(res.view(np.int32)), cap=cap)
+        for a, e in zip(got, oracle.map_requests(merged, H, Nc, e2c, Nc, rep, D, weight, res, cap=cap)):
+            assert np.array_equal(a.cpu().numpy(), e), left
+    assert sw.device_status() == 0
+
+
+@pytest.mark.parametrize("N,Nc", [(59, 64), (60, 64), (1, 1), (1024, 128), (1025, 128)])
+def test_marks_of_entries_and_clusters(sw, N, Nc):
+    """2048 picks of few entries and of few clusters: their byte marks on both sides of the room they share, and on both sides of
+    two picks to an entry."""
+    H, D, groups = 2, 4, 3
+    rng = np.random.default_rng(N)
+    e2c = rng.integers(0, Nc, (H, N)).astype(np.int32)
+    rep = rng.integers(0, D, (H * Nc, 1)).astype(np.int32)
+    for cap in sorted({min(N, Nc), (Nc + N + 3) // 8, (Nc + N + 4 + 7) // 8, (Nc + 64 + 7) // 8, (Nc + 63) // 8, Nc}):
+        if cap < min(N, Nc):
+            continue
+        sel = rng.integers(0, N, (groups, 2048)).astype(np.int32)
+        got = sw.map_requests(dev(sel), H, N, dev(e2c), Nc, dev(rep), D, cap=cap)
+        for a, e in zip(got, oracle.map_requests(sel, H, N, e2c, Nc, rep, D, cap=cap)):
+            assert np.array_equal(a.cpu().numpy(), e), cap
+    assert sw.device_status() == 0
