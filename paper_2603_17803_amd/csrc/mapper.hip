@@ -30,7 +30,8 @@ struct MapArgs {
     const int32_t* sel; int S; int H; int N; const int32_t* e2c; int Nc; const int32_t* replicas; int R; int D;
     const int32_t* weight; const uint32_t* resident; int32_t* q_off; int32_t* q_cluster; int32_t* q_load; int cap;
     uint32_t* dev_flags;
-    int split_off;      // word offset of the 2 * cap words the split into independent sub-problems needs; 0 = no room, never split
+    int split_off;      // word offset of the cap words the split into independent sub-problems needs; 0 = no room, never split
+    int split_bytes;    // size of the region there: the merge keeps its byte marks in it where they fit, before the split needs it
     int piece;          // strided selections (the streams of a step, as the selection writes them): a group's S entries are
     int piece_stride;   // pieces of `piece` consecutive ids, `piece_stride` words apart; unused by the contiguous kernels
     int piece_shift;    // log2(piece) when it is a power of two (a shift instead of a division per entry), -1 otherwise
@@ -382,7 +383,7 @@ __device__ __forceinline__ void stage_words(int32_t* __restrict__ dst, const int
 constexpr int MAP_AUX_WORDS = 8 * 64;        // off, adj_lo, adj_hi, comp_of, seg_first, seg_cnt, pub_load, pub_cnt: 64 words each
 
 struct MapLds {
-    uint32_t *bitmap, *list, *mask_lo, *mask_hi, *wgt, *order, *assign, *order2, *comp_item, *off;
+    uint32_t *bitmap, *list, *mask_lo, *mask_hi, *wgt, *order, *assign, *order2, *off;
     uint32_t *adj_lo, *adj_hi, *comp_of, *seg_first, *seg_cnt, *pub_load, *pub_cnt;
     int32_t *s_e2c, *s_rep, *s_wgt;
     int nwords;
@@ -397,7 +398,6 @@ struct MapLds {
         assign = order + a.cap;
         off = assign + a.cap;                 // MAP_AUX_WORDS words from here
         order2 = smem + a.split_off;          // visiting order regrouped by independent sub-problem (only when split_off != 0)
-        comp_item = order2 + a.cap;           // sub-problem of every item
         adj_lo = off + 64;
         adj_hi = adj_lo + 64;
         comp_of = adj_hi + 64;
@@ -806,7 +806,7 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     // ones again and again), the entries are marked first, a byte each, and only the N entries look their cluster up, lane by
     // lane in order, instead of the S picks all over the table: 8192 picks of 2048 entries merge in 3900 cycles, not 5100
     // (ENTRY_MARKS, a kernel of its own: merges that passed over this code took 0.5 us longer).
-    const bool byte_marks = ENTRY_MARKS || (BIG && !PRESTAGED && a.split_off != 0 && a.S >= 2048 && (size_t)a.cap * 8 >= (size_t)a.Nc + 64);
+    const bool byte_marks = ENTRY_MARKS || (BIG && !PRESTAGED && a.split_off != 0 && a.S >= 2048 && a.split_bytes >= a.Nc + 64);
     const int mark_bytes = (a.Nc + 63) / 64 * 64;
     uint8_t* marks = reinterpret_cast<uint8_t*>(order2);
     uint8_t* picked = marks + mark_bytes;
@@ -1083,7 +1083,7 @@ size_t map_lds_base_bytes(int Nc, int cap) { return ((size_t)(Nc + 31) / 32 + (s
 swarm_status launch_map(swarm_ctx* ctx, const int32_t* sel, int64_t groups, int S, int H, int N, const int32_t* e2c,
                         int Nc, const int32_t* replicas, int R, int D, const int32_t* weight,
                         const uint32_t* resident, int32_t* q_off, int32_t* q_cluster, int32_t* q_load, int cap, int piece) {
-    MapArgs a{sel, S, H, N, e2c, Nc, replicas, R, D, weight, resident, q_off, q_cluster, q_load, cap, ctx->dev_flags, 0, piece, H * piece,
+    MapArgs a{sel, S, H, N, e2c, Nc, replicas, R, D, weight, resident, q_off, q_cluster, q_load, cap, ctx->dev_flags, 0, 0, piece, H * piece,
               (piece > 0 && (piece & (piece - 1)) == 0) ? __builtin_ctz((unsigned)piece) : -1};
     size_t lds = map_lds_base_bytes(Nc, cap);
     const size_t budget = 64u * 1024u;
@@ -1092,12 +1092,14 @@ swarm_status launch_map(swarm_ctx* ctx, const int32_t* sel, int64_t groups, int 
     lds = (lds + 15) / 16 * 16;
     if (lds + tab_bytes <= budget) { stage_tab = 1; lds += tab_bytes; }
     if (lds + e2c_bytes <= budget) { stage_e2c = 1; lds += e2c_bytes; }
-    if (lds + (size_t)cap * 8 <= budget) { a.split_off = (int)(lds / 4); lds += (size_t)cap * 8; }
+    // room for the split, twice as much where a merge of many picks may keep its byte marks there
+    a.split_bytes = S >= 2048 && lds + (size_t)cap * 8 <= budget ? cap * 8 : lds + (size_t)cap * 4 <= budget ? cap * 4 : 0;
+    if (a.split_bytes) { a.split_off = (int)(lds / 4); lds += (size_t)a.split_bytes; }
     using kernel_t = void (*)(MapArgs, int, int);
     kernel_t kernel;
     if (S >= 2048) {
         // the entries are marked where the picks outnumber them two to one and their marks fit beside those of the clusters
-        const size_t room = a.split_off ? (size_t)cap * 8 : 0;
+        const size_t room = (size_t)a.split_bytes;
         const bool entry_marks = S / 2 >= N && room >= (size_t)Nc + 64 && room >= ((size_t)Nc + 63) / 64 * 64 + (size_t)N + 4;
         kernel = entry_marks ? (piece > 0 ? map_requests_kernel<1024, true, true, true> : map_requests_kernel<1024, false, true, true>)
                              : (piece > 0 ? map_requests_kernel<1024, true, true> : map_requests_kernel<1024, false, true>);
@@ -1122,7 +1124,7 @@ swarm_status launch_select_map(swarm_ctx* ctx, const float* scores, int H, int N
     // short rows select with smaller blocks, four scores per thread (see launch_select)
     const int NT = sliced ? selcore::NT : N <= 4 * 256 ? 256 : N <= 4 * 512 ? 512 : selcore::NT;
     if (N > 64 * NT && !sliced) return SWARM_OK;
-    MapArgs a{nullptr, k, H, N, e2c, Nc, replicas, R, D, weight, resident, q_off, q_cluster, q_load, cap, ctx->dev_flags, 0, 0, 0, -1};
+    MapArgs a{nullptr, k, H, N, e2c, Nc, replicas, R, D, weight, resident, q_off, q_cluster, q_load, cap, ctx->dev_flags, 0, 0, 0, 0, -1};
     size_t lds = map_lds_base_bytes(Nc, cap);
     const size_t budget = 64u * 1024u;                     // dynamic part; the selection's static 12.6 KiB come on top
     lds = (lds + 15) / 16 * 16;
@@ -1137,7 +1139,7 @@ swarm_status launch_select_map(swarm_ctx* ctx, const float* scores, int H, int N
     lds += ((size_t)k > skip_words ? (size_t)k : skip_words) * 4;
     if (lds > budget) return SWARM_OK;
     lds = (lds + 15) / 16 * 16;
-    if (lds + (size_t)cap * 8 <= budget) { a.split_off = (int)(lds / 4); lds += (size_t)cap * 8; }
+    if (sliced && lds + (size_t)cap * 4 <= budget) { a.split_off = (int)(lds / 4); lds += (size_t)cap * 4; }
     const dim3 grid((unsigned)H), block(NT);
     hipStream_t st = ctx->stream;
     if (!sliced) select_reserve(ctx, H, N, k);

@@ -349,3 +349,23 @@ def test_marks_of_entries_and_clusters(sw, N, Nc):
         for a, e in zip(got, oracle.map_requests(sel, H, N, e2c, Nc, rep, D, cap=cap)):
             assert np.array_equal(a.cpu().numpy(), e), cap
     assert sw.device_status() == 0
+
+
+@pytest.mark.parametrize("cap,Nc,S,R,D", [
+    (1900, 5000, 1900, 2, 8), (2048, 3000, 2047, 3, 8), (2048, 3000, 2048, 1, 12), (2048, 16000, 6000, 2, 40), (2250, 2250, 9000, 2, 6), (2600, 2600, 5000, 4, 16)])
+def test_mapping_of_the_longest_lists(sw, cap, Nc, S, R, D):
+    """Lists that leave little of the on-chip memory: room for the split but not for marks beside it, and room for neither."""
+    H, groups, N = 2, 4, Nc
+    rng = np.random.default_rng(cap + S)
+    e2c = np.stack([rng.permutation(Nc) for _ in range(H)]).astype(np.int32)
+    rep = np.stack([rng.permutation(D)[:R] for _ in range(H * Nc)]).astype(np.int32)
+    rep[rng.random(H * Nc) < 0.5, 1:] = -1
+    weight = rng.integers(0, 100, H * Nc).astype(np.int32)
+    pool = np.stack([rng.permutation(N)[:cap] for _ in range(groups)])          # at most cap clusters to a group
+    sel = np.take_along_axis(pool, rng.integers(0, cap, (groups, S)), 1).astype(np.int32)
+    sel[:, :min(S, cap)] = pool[:, :min(S, cap)]
+    for w in (weight, np.full_like(weight, 1 << 20)):
+        got = sw.map_requests(dev(sel), H, N, dev(e2c), Nc, dev(rep), D, dev(w), cap=cap)
+        for a, e in zip(got, oracle.map_requests(sel, H, N, e2c, Nc, rep, D, w, cap=cap)):
+            assert np.array_equal(a.cpu().numpy(), e)
+    assert sw.device_status() == 0
