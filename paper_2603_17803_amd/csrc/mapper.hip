@@ -414,8 +414,10 @@ struct MapLds {
 // The merged clusters of group g, one bit each in L.bitmap, become its queues; all waves of the block call this.  SPLIT: a long
 // list -- every wave compacts, looks up, gathers, runs chains of sub-problems and writes queues, wave 0 finds the sub-problems.
 // Otherwise wave 0 does it all alone, one chain, and the others leave.  Bits set in `skip` (nullable, not with SPLIT) are left out.
+// before, found (SPLIT, up to 64 words of bits): the bits in words below word `lane`, and in all of them.
 template <int NT, bool SPLIT>
-__device__ __forceinline__ void map_assign(const MapArgs& a, int64_t g, int h, const MapLds& L, int stage_tab, const uint32_t* skip, uint32_t flags) {
+__device__ __forceinline__ void map_assign(const MapArgs& a, int64_t g, int h, const MapLds& L, int stage_tab, const uint32_t* skip, uint32_t flags,
+                                           uint32_t before = 0, uint32_t found = 0) {
     const int nwords = L.nwords;
     uint32_t *bitmap = L.bitmap, *list = L.list, *mask_lo = L.mask_lo, *mask_hi = L.mask_hi, *wgt = L.wgt, *order = L.order,
              *assign = L.assign, *off = L.off, *order2 = L.order2;
@@ -434,13 +436,13 @@ __device__ __forceinline__ void map_assign(const MapArgs& a, int64_t g, int h, c
     uint32_t m_par = 0;
     if (SPLIT) {
         if (nwords <= 64) {
-            const uint32_t wexcl = wave_excl_scan(lane < nwords ? (uint32_t)__popc(bitmap[lane]) : 0u, &m_par);
+            m_par = found;
             for (int b0 = 0; b0 < nwords * 32; b0 += NT) {
                 const int bit = b0 + tid, w = bit >> 5;
                 const uint32_t word = w < nwords ? bitmap[w] : 0u;
-                const uint32_t before = (uint32_t)__shfl((int)wexcl, w & 63, 64);
+                const uint32_t first = (uint32_t)__shfl((int)before, w & 63, 64);
                 if ((word >> (bit & 31)) & 1u) {
-                    const uint32_t pos = before + (uint32_t)__popc(word & ((1u << (bit & 31)) - 1u));
+                    const uint32_t pos = first + (uint32_t)__popc(word & ((1u << (bit & 31)) - 1u));
                     if (pos < (uint32_t)a.cap) list[pos] = (uint32_t)bit;
                 }
             }
@@ -951,9 +953,9 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
     if constexpr (SPLIT) {
         uint32_t mine = 0, total;
         for (int w0 = 0; w0 < nwords; w0 += 64) mine += (w0 + lane < nwords) ? __popc(bitmap[w0 + lane]) : 0;
-        (void)wave_excl_scan(mine, &total);
+        const uint32_t before = wave_excl_scan(mine, &total);
         if ((!BIG || a.split_off != 0) && min(total, (uint32_t)a.cap) >= MAP_SPLIT_MIN_ITEMS) {
-            map_assign<NT, true>(a, g, h, L, stage_tab, nullptr, flags);
+            map_assign<NT, true>(a, g, h, L, stage_tab, nullptr, flags, before, total);
             return;
         }
     }
