@@ -207,6 +207,56 @@ def test_expansion_edges(sw, Sc, Nc, most, cap):
     assert sw.device_status() == (binding.SWARM_DEV_CAP if ref_n.max() > cap else 0)
 
 
+def expanded(picks, H, Nc, off, ent, cap):
+    """Picks out of range and clusters with unusable offsets are passed over: entries, counts and whether any was met."""
+    E = ent.shape[1]
+    out, count, bad = np.full((len(picks), cap), -1, np.int32), np.zeros(len(picks), np.int32), False
+    for g, row in enumerate(picks):
+        h = g % H
+        bad |= bool(((row < -1) | (row >= Nc)).any())
+        got = [np.zeros(0, np.int32)]
+        for c in np.unique(row[(row >= 0) & (row < Nc)]):
+            lo, hi = int(off[h, c]), int(off[h, c + 1])
+            if lo < 0 or hi < lo or hi > E:
+                bad = True
+            else:
+                got.append(ent[h, lo:hi])
+        got = np.concatenate(got)[:cap]
+        out[g, :len(got)], count[g] = got, len(got)
+    return out, count, bad
+
+
+@pytest.mark.parametrize("Sc,groups", [(1, 6), (2, 1030), (17, 6), (63, 1024), (64, 1023), (64, 1025), (64, 2049), (65, 6), (300, 6), (2048, 4), (2049, 4)])
+def test_expansion_passes_over_bad_picks_and_offsets(sw, Sc, groups):
+    """Picks just outside the clusters and offset pairs below zero, falling or past the end, each alone and together, in
+    ascending lists and in any order, on both sides of the kernels' numbers of picks and groups."""
+    from paper_2603_17803_amd import binding
+    H, Nc = 2, max(40, Sc)
+    rng = np.random.default_rng(Sc + groups)
+    off = np.zeros((H, Nc + 1), np.int32)
+    off[:, 1:] = np.cumsum(rng.integers(0, 6, (H, Nc)), 1)
+    E = int(off.max())
+    ent = rng.integers(0, 1 << 20, (H, E)).astype(np.int32)
+    broken = off.copy()
+    for h in range(H):
+        broken[h, 3], broken[h, 11], broken[h, 20] = -5, off[h, 9] - 1, E + 1          # below zero; falling; past the end
+    for ascending in (True, False):
+        picks = rng.integers(0, Nc, (groups, Sc)).astype(np.int32)
+        if ascending:
+            picks = np.sort(np.stack([rng.permutation(Nc)[:Sc] for _ in range(groups)]), 1).astype(np.int32)
+        foreign = picks.copy()
+        foreign[rng.random(picks.shape) < 0.2] = -1
+        foreign[:, -1], foreign[::2, 0] = Nc, -2
+        for p in (picks, foreign):
+            for o in (off, broken):
+                for cap in (max(1, Sc), 7 * Sc):
+                    entries, count = sw.expand_clusters(dev(p), H, Nc, dev(o), dev(ent), cap)
+                    ref, n, bad = expanded(p, H, Nc, o, ent, cap)
+                    assert np.array_equal(entries.cpu().numpy(), ref) and np.array_equal(count.cpu().numpy(), n)
+                    flags = sw.device_status()
+                    assert bool(flags & binding.SWARM_DEV_BAD_CLUSTER) == bad and not flags & ~(binding.SWARM_DEV_BAD_CLUSTER | binding.SWARM_DEV_CAP)
+
+
 @pytest.mark.parametrize("N,k,Nc,R,H", [
     (1, 1, 1, 1, 1), (3, 2, 5, 2, 3), (255, 255, 33, 3, 3), (1023, 64, 341, 3, 2), (1025, 100, 1023, 2, 3), (2047, 300, 65, 1, 5), (2049, 17, 700, 3, 2),
     (4095, 512, 1365, 3, 1), (4097, 256, 1024, 4, 2), (8191, 1024, 2047, 2, 3), (8193, 200, 1024, 3, 2), (16383, 900, 1000, 2, 1), (33001, 640, 1500, 2, 2)])
