@@ -371,6 +371,16 @@ void launch_lean(hipStream_t st, const swarm_keys* keys, const void* q, int B, f
                        static_cast<const uint16_t*>(q), scores, keys->N, keys->H, __builtin_ctz(keys->H));
 }
 
+// Whether every stream sweeps the keys for itself, in workgroups of its own.  A read shared by four streams saves bandwidth, but its
+// workgroups carry four streams' sums one after the other, and while all sweeps together are short it is the length of a
+// workgroup that counts.  Measured over 160 calls by the bytes that all sweeps read: the lean kernel's are 4 to 33 % faster up
+// to 16 MiB, level up to 24 and up to 8 % slower at 32 (4 streams of 8 x 1024 tokens of 128 channels: 2.8 us shared, 2.2 apart; 2
+// of 8 x 8192 pages: 6.2 and 7.7); with grouped heads or a row list, whose workgroups also fold the weights, they are 4 to 25 %
+// faster up to 8 MiB, level up to 16 and up to 15 % slower at 32.
+bool streams_apart(const swarm_keys* keys, int B, int rows, int CH, bool lean) {
+    return (int64_t)B * keys->H * rows * CH * 16 <= (int64_t)(lean ? 24 : 8) << 20;
+}
+
 template <int LPR, bool PAGE, int NB, bool LISTED>
 void launch_group_nb(hipStream_t st, const swarm_keys* keys, const void* q, int B, float* scores, const int32_t* row_ids, int M,
                      uint32_t* dev_flags) {
@@ -389,11 +399,12 @@ void launch_group_nb(hipStream_t st, const swarm_keys* keys, const void* q, int 
 template <int LPR, bool PAGE>
 void launch_group(hipStream_t st, const swarm_keys* keys, const void* q, int B, float* scores, const int32_t* row_ids, int M,
                   uint32_t* dev_flags) {
+    const bool apart = B == 1 || streams_apart(keys, B, row_ids ? M : keys->N, LPR, false);
     if (row_ids) {
-        if (B == 1) launch_group_nb<LPR, PAGE, 1, true>(st, keys, q, B, scores, row_ids, M, dev_flags);
+        if (apart) launch_group_nb<LPR, PAGE, 1, true>(st, keys, q, B, scores, row_ids, M, dev_flags);
         else launch_group_nb<LPR, PAGE, 4, true>(st, keys, q, B, scores, row_ids, M, dev_flags);
     } else {
-        if (B == 1) launch_group_nb<LPR, PAGE, 1, false>(st, keys, q, B, scores, row_ids, M, dev_flags);
+        if (apart) launch_group_nb<LPR, PAGE, 1, false>(st, keys, q, B, scores, row_ids, M, dev_flags);
         else if (B == 2) launch_group_nb<LPR, PAGE, 2, false>(st, keys, q, B, scores, row_ids, M, dev_flags);
         else launch_group_nb<LPR, PAGE, 4, false>(st, keys, q, B, scores, row_ids, M, dev_flags);
     }
@@ -402,7 +413,7 @@ void launch_group(hipStream_t st, const swarm_keys* keys, const void* q, int B, 
 template <bool PAGE>
 void dispatch(hipStream_t st, const swarm_keys* keys, const void* q, int B, float* scores, int CH, const int32_t* row_ids, int M,
               uint32_t* dev_flags) {
-    if (!row_ids && keys->G == 1 && B == 1 && (keys->H & (keys->H - 1)) == 0) {      // one stream, no grouped heads: the lean kernel
+    if (!row_ids && keys->G == 1 && (keys->H & (keys->H - 1)) == 0 && (B == 1 || streams_apart(keys, B, keys->N, CH, true))) {      // no grouped heads, no shared read: the lean kernel
         if (CH == 32) return launch_lean<32, PAGE>(st, keys, q, B, scores);
         if (CH == 16) return launch_lean<16, PAGE>(st, keys, q, B, scores);
         if (CH == 8) return launch_lean<8, PAGE>(st, keys, q, B, scores);

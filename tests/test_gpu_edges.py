@@ -207,6 +207,28 @@ def test_expansion_edges(sw, Sc, Nc, most, cap):
     assert sw.device_status() == (binding.SWARM_DEV_CAP if ref_n.max() > cap else 0)
 
 
+@pytest.mark.parametrize("unit,d,H,G,B,N", [
+    ("token", 256, 8, 1, 6, 1024), ("token", 256, 8, 1, 6, 1025), ("page", 128, 8, 1, 2, 3072), ("page", 128, 8, 1, 2, 3073), ("token", 64, 8, 1, 9, 2731),
+    ("page", 128, 4, 3, 4, 1024), ("page", 128, 4, 3, 4, 1025), ("token", 128, 3, 1, 5, 2184), ("token", 128, 3, 1, 5, 2185), ("token", 64, 2, 4, 11, 2999)])
+def test_streams_apart_and_together(sw, unit, d, H, G, B, N):
+    """Sweeps just short and just long enough that streams share a read of the keys, of whole heads and of row lists."""
+    cfg = W.CONFIGS["llama8b_32k"].scaled(N=N, k=1, T=1, H=H, G=G, B=B, d=d, unit=unit, page_size=16 if unit == "page" else 1)
+    K, q = W.keys(cfg), W.queries(cfg, 0, 1)[0]
+    flat = torch.full((B * H * N + 64,), -7.5, dtype=torch.float32, device="cuda")
+    sw.score(unit, dev(K), dev(q), G=G, out_scores=flat[:B * H * N].view(B, H, N))
+    _, ref64, ab = oracle.score(unit, K, q, G, nthreads=8)
+    tol = (d * (2 if unit == "page" else 1) + G) * 2.0 ** -24 * ab              # as above: no shape here reaches the matrix cores
+    assert (np.abs(flat[:B * H * N].view(B, H, N).cpu().numpy() - ref64) <= tol).all()
+    assert (flat[B * H * N:] == -7.5).all()
+    bytes_per_row = B * H * d * 2 * (2 if unit == "page" else 1)
+    for M in ((8 << 20) // bytes_per_row, (8 << 20) // bytes_per_row + 1):      # the last list that is read apart, the first that is not
+        ids = np.random.default_rng(M).integers(0, N, (H, M)).astype(np.int32)
+        _, sc = sw.score_select_indexed(unit, dev(K), dev(ids), dev(q), 1, G=G, want_scores=True)
+        h = np.arange(H)[:, None]
+        assert (np.abs(sc.cpu().numpy() - ref64[:, h, ids]) <= tol[:, h, ids]).all()
+    assert sw.device_status() == 0
+
+
 def expanded(picks, H, Nc, off, ent, cap):
     """Picks out of range and clusters with unusable offsets are passed over: entries, counts and whether any was met."""
     E = ent.shape[1]
