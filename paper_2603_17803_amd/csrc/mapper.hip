@@ -1136,8 +1136,9 @@ swarm_status launch_select_map(swarm_ctx* ctx, const float* scores, int H, int N
     const bool e2c_regs = N <= 8 * NT;
     if (tab_regs && lds + tab_bytes <= budget) { stage_tab = 1; lds += tab_bytes; }
     if (e2c_regs && lds + e2c_bytes <= budget) { stage_e2c = 1; lds += e2c_bytes; }
-    const int sel_off = (int)(lds / 4);                    // the selection's list, or (never both) the resident clusters' bits
-    const size_t skip_words = resident ? ((size_t)Nc + 31) / 32 : 0;
+    // the selection's list, or (never both: clusters marked where the entries are found) the resident clusters' bits
+    const int sel_off = (int)(lds / 4);
+    const size_t skip_words = resident && !sliced && stage_e2c ? ((size_t)Nc + 31) / 32 : 0;
     lds += ((size_t)k > skip_words ? (size_t)k : skip_words) * 4;
     if (lds > budget) return SWARM_OK;
     lds = (lds + 15) / 16 * 16;

@@ -282,7 +282,8 @@ def test_expansion_passes_over_bad_picks_and_offsets(sw, Sc, groups):
 
 @pytest.mark.parametrize("N,k,Nc,R,H", [
     (1, 1, 1, 1, 1), (3, 2, 5, 2, 3), (255, 255, 33, 3, 3), (1023, 64, 341, 3, 2), (1025, 100, 1023, 2, 3), (2047, 300, 65, 1, 5), (2049, 17, 700, 3, 2),
-    (4095, 512, 1365, 3, 1), (4097, 256, 1024, 4, 2), (8191, 1024, 2047, 2, 3), (8193, 200, 1024, 3, 2), (16383, 900, 1000, 2, 1), (33001, 640, 1500, 2, 2)])
+    (4095, 512, 1365, 3, 1), (4097, 256, 1024, 4, 2), (8191, 1024, 2047, 2, 3), (8193, 200, 1024, 3, 2), (16383, 900, 1000, 2, 1), (33001, 640, 1500, 2, 2), (8300, 5, 260000, 1, 2),
+    (8000, 5, 260000, 1, 2), (20000, 7, 250000, 1, 1)])
 def test_one_call_step_edges(sw, N, k, Nc, R, H):
     """The one-call step against the separate calls and the oracle, with resident clusters: tables parked with and without
     room, ragged in every length, on both sides of each block size; equal scores in quantity and NaN among them."""
