@@ -29,7 +29,8 @@ struct swarm_ctx {
     size_t trace_bytes = 0;
     int64_t* totals = nullptr;     // per-head grand totals of C when the caller keeps none
     size_t totals_bytes = 0;
-    bool trace_lds_opt_in = false, syrk_lds_opt_in = false, batched_lds_opt_in = false;   // large dynamic LDS enabled for this context's device
+    bool trace_lds_opt_in = false, syrk_lds_opt_in = false;   // large dynamic LDS enabled for this context's device
+    uint32_t batched_lds_opt_in = 0;                          // the same, a bit per form of the many-stream scorer
     uint32_t* dev_flags = nullptr; // sticky SWARM_DEV_* bits (one word)
     void* static_scratch = nullptr; // this device's copy of the library's static scratch array (address resolved at create)
     std::vector<std::pair<int, int32_t*>> tile_orders;   // co-activation tile schedules, one per tile count, never rewritten

@@ -582,14 +582,17 @@ swarm_status launch_batched(swarm_ctx* ctx, const swarm_keys* keys, const void* 
     constexpr int CHQ = PAGE ? KSTEPS : KSTEPS * 2;
     constexpr size_t LDS_W = (size_t)SB_GT * (PAGE ? 2 : 1) * 32 * (CHQ + 1) * 16, LDS_K = (size_t)4 * 32 * (KSTEPS * 2 + 1) * 16;
     constexpr size_t LDS = LDS_W > LDS_K ? LDS_W : LDS_K;
-    if (LDS > 64 * 1024 && !ctx->batched_lds_opt_in) {     // per context: the attribute belongs to the device the context is bound to
+    // per context, because the attribute belongs to the device the context is bound to, and per kernel, because it belongs to that
+    constexpr uint32_t THIS = 1u << ((KSTEPS == 16 ? 2 : 0) + (PAGE ? 1 : 0));
+    static_assert(KSTEPS == 8 || KSTEPS == 16, "");
+    if (LDS > 64 * 1024 && !(ctx->batched_lds_opt_in & THIS)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_batched_kernel<KSTEPS, PAGE>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
         if (e != hipSuccess) {
             snprintf(ctx->err, sizeof(ctx->err), "score: cannot opt in to %zu bytes of LDS: %s", LDS, hipGetErrorString(e));
             return SWARM_EHIP;
         }
-        ctx->batched_lds_opt_in = true;
+        ctx->batched_lds_opt_in |= THIS;
     }
     dim3 grid((keys->N + 127) / 128, keys->H, (B + 31) / 32);
     hipLaunchKernelGGL((score_batched_kernel<KSTEPS, PAGE>), grid, dim3(256), LDS, ctx->stream, static_cast<const u32x4*>(keys->data),

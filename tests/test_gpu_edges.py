@@ -230,6 +230,25 @@ def test_streams_apart_and_together(sw, unit, d, H, G, B, N):
     assert sw.device_status() == 0
 
 
+@pytest.mark.parametrize("order", [(0, 1, 2, 3), (3, 2, 1, 0)])
+def test_every_many_stream_scorer_on_a_context_of_its_own(order):
+    """The four forms of the scorer for many streams, two of which need more LDS than a kernel gets unasked, one after the other
+    on a fresh context."""
+    from paper_2603_17803_amd import binding
+    s = binding.Swarm(0)
+    try:
+        for i in order:
+            unit, d = (("page", 128), ("token", 256), ("page", 64), ("token", 128))[i]
+            cfg = W.CONFIGS["llama8b_32k"].scaled(N=140, k=1, T=1, H=2, G=4, B=33, d=d, unit=unit, page_size=16 if unit == "page" else 1)
+            K, q = W.keys(cfg), W.queries(cfg, 0, 1)[0]
+            got = s.score(unit, dev(K), dev(q), G=4).cpu().numpy()
+            _, ref64, ab = oracle.score(unit, K, q, 4)
+            assert (np.abs(got - ref64) <= d * (2 if unit == "page" else 1) * 4 * 2.0 ** -24 * ab).all(), (unit, d)
+        assert s.device_status() == 0
+    finally:
+        s.close()
+
+
 def expanded(picks, H, Nc, off, ent, cap):
     """Picks out of range and clusters with unusable offsets are passed over: entries, counts and whether any was met."""
     E = ent.shape[1]
