@@ -18,7 +18,9 @@
  *    for it; results are valid once the caller has synchronised that stream.
  *  - Scratch memory belongs to the context and grows on demand.  Growing allocates (and
  *    synchronises the stream); a call whose shapes are no larger than those of an earlier call
- *    allocates nothing, so a warmed-up call sequence may be captured into a HIP graph.
+ *    needs no more scratch, so a warmed-up call sequence may be captured into a HIP graph.  (The
+ *    co-activation calls also keep one small schedule per number of entries, N rounded up to 256:
+ *    the first call with another N allocates that, and cannot be the recorded one.)
  *  - The return value is the only host-side error channel.  Nothing throws or aborts.  Bad
  *    arguments give SWARM_EINVAL before anything is enqueued.  Bad *data* (an index outside
  *    its range) never makes a kernel read or write out of bounds: the offending item is
@@ -104,10 +106,11 @@ swarm_status swarm_device_status(swarm_ctx* ctx, uint32_t* flags);
  *   Products of two bf16 values are exact in fp32 and are accumulated in fp32.  A page term is computed as
  *   min(q_c,0) * min_c + max(q_c,0) * max_c, which equals max(q_c * min_c, q_c * max_c) when the summary is finite
  *   and min_c <= max_c -- the precondition of page scoring: an infinite or NaN summary channel, or min_c > max_c,
- *   gives a score that differs from the formula above (a zero weight times an infinity is NaN).  With up to seven
- *   streams the G query heads of a group are first added into fp32 weights (one rounding per head), then multiplied;
- *   with eight or more streams every query head is its own exact bf16 operand of the bf16 matrix cores and the heads
- *   add in their fp32 accumulators.  Either way a score differs from the exact sum by fp32 accumulation error only.
+ *   gives a score that differs from the formula above (a zero weight times an infinity is NaN).  The G query
+ *   heads of a group are first added into fp32 weights (one rounding per head), then multiplied; with eight or more
+ *   streams over all rows of 128 or 256 values (d, or 2 d for pages) every query head is its own exact bf16 operand of
+ *   the bf16 matrix cores instead and the heads add in their fp32 accumulators.  Either way a score differs from the
+ *   exact sum by fp32 accumulation error only.
  *   select: the k largest of s[b][h][0..N); equal scores are won by the lower index; -0 equals
  *   +0; NaN ranks below every number.  The k indices come out in ascending order.
  *
@@ -117,7 +120,7 @@ swarm_status swarm_device_status(swarm_ctx* ctx, uint32_t* flags);
  * out_idx     device, int32 [B][H][k].
  * out_scores  device, fp32 [B][H][N], or NULL to keep the scores in the context's scratch.
  * Errors: SWARM_EINVAL for a NULL required pointer, misaligned data/q, k outside [1,N], d not a
- * multiple of 8 or above 512, H/N/G/B < 1, N > 2^30, H > 65535, B*H > 2^24.
+ * multiple of 8 or above 512, H/N/G/B < 1, N > 2^30, H or B > 65535, B*H > 2^24, (N/16 + 1) * H > 2^31 - 1.
  */
 swarm_status swarm_score_select(swarm_ctx* ctx, const swarm_keys* keys, const void* q, int32_t B, int32_t k,
                                 int32_t* out_idx, float* out_scores);
@@ -272,7 +275,7 @@ swarm_status swarm_window_assign(swarm_ctx* ctx, const int32_t* sel, int32_t W, 
  *            clusters than cap is truncated and flagged (SWARM_DEV_CAP).
  * weight entries must be >= 0 (negative ones count as 0).
  * Errors: SWARM_EINVAL for NULL required pointers, R < 1, R > D, D > 64, Nc > 2^20, cap < 1,
- * S/H/N/Nc/groups < 1, or on-chip staging too large: 24 * cap + Nc / 8 + 256 bytes must fit in 64 KiB.
+ * S/H/N/Nc/groups < 1, or on-chip staging too large: 24 * cap + Nc / 8 + 2048 bytes must fit in 64 KiB.
  */
 swarm_status swarm_map_requests(swarm_ctx* ctx, const int32_t* sel, int64_t groups, int32_t S, int32_t H, int32_t N,
                                 const int32_t* e2c, int32_t Nc, const int32_t* replicas, int32_t R, int32_t D,

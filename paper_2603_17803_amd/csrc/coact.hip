@@ -4,7 +4,7 @@
 // The trace is binary, so it is kept in memory as bits: for every head and every run of 128 trace
 // rows one 16-byte word per entry, bits[h][run][entry], one bit per trace row of the run (rows 32w ..
 // 32w+31 in dword w, in the order of trace_bit below).  Both operands of the product are entry panels of this one array.  On the way
-// to the matrix cores the bits are expanded to 4-bit 0/1 operands -- the 256 tile rows by the workgroup, into LDS
+// to the matrix cores the bits are expanded to 4-bit 0/1 operands -- the 128 tile rows by the workgroup, into LDS
 // (contraction index contiguous), the 64 tile columns of a wave by the wave itself, in registers -- and the product
 // runs on the 4-bit form of v_mfma_f32_32x32x64_f8f6f4, exact for these operands (see below).  Feeding expanded
 // operands from memory instead would multiply the traffic through the L2 by four to eight; the bit form keeps a
@@ -165,9 +165,8 @@ static_assert(SYRK_LDS_BYTES >= RAW_BASE + RAW_DEPTH * RAW_CHUNK, "operand ring 
 // gfx950: a 16-byte LDS read is served 16 consecutive lanes at a time across 64 four-byte banks, a
 // 16-byte write 8 consecutive lanes at a time with only address bits 4..6 telling lanes apart.
 // Fragment reads take one piece of 16 consecutive rows, so rows that agree in bits 0..1 need
-// different swz; the expansion writes of 8 consecutive lanes cover 8 rows (A panel: thread = row)
-// or 4 rows x 2 halves (B panel), so rows that agree in bit 0 within 8 need different swz, and bit 0
-// of swz must follow bit 1 of the row.  swz = (bit1 ^ bit3) | bit2 << 1 does all of it.
+// different swz; the expansion writes of 8 consecutive lanes cover 4 rows x 2 halves, so bit 0 of swz
+// must follow bit 1 of the row.  swz = (bit1 ^ bit3) | bit2 << 1 does both.
 __device__ __forceinline__ int lds_swz(int row) { return (((row >> 1) ^ (row >> 3)) & 1) | (((row >> 2) & 1) << 1); }
 __device__ __forceinline__ int lds_off(int row, int piece) { return row * KC + ((piece ^ lds_swz(row)) << 4); }
 

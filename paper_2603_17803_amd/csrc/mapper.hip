@@ -880,7 +880,7 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
         else atomicOr(&bitmap[c >> 5], 1u << (c & 31));
     };
     auto merge_all = [&](auto staged_tag) __attribute__((always_inline)) {
-        if (PRESTAGED) {                             // the selection is in LDS: nothing to batch
+        if (PRESTAGED) {                             // the selection is in LDS, at most a few entries to a thread
             for (int s0 = tid; s0 < a.S; s0 += NT) {
                 const int32_t e = sel[s0];
                 if (e == -1) continue;
@@ -1003,7 +1003,8 @@ struct TableInFlight {
 // histogram.  Then a thread that finds a selected entry writes it out and marks its cluster on the spot: the merge needs no
 // list of the selection, no pass over it and no barrier of its own (parked after the selection, merged from a list in LDS: 17.6
 // instead of 17.2 us per decode step over 8 x 8192 pages, scoring included).  Clusters in DRAM are marked like the others and left out when the marks are compacted.
-// An entry->cluster table too large for LDS is read through the list of the selection, all look-ups of a batch in flight.
+// With an entry->cluster table too large for LDS, and for sliced rows, the clusters are marked from the list of the selection: each
+// thread walks its share of it, a look-up (and, with residency, a second one) per entry.
 // CAND: second stage of the sliced selection of a long row -- the scores are those of the M listed winners of
 // the row's slices (ascending entry id), and the selected list positions are turned back into entry ids.
 template <int IPT, bool CAND, int NT = selcore::NT>

@@ -602,6 +602,10 @@ swarm_status launch_batched(swarm_ctx* ctx, const swarm_keys* keys, const void* 
 
 }  // namespace
 
+// Forms of the many-stream scorer exist for rows of 128 and 256 values, those of the head dimensions served.  Shorter ones (token
+// keys of 64 channels, pages of 32) would fit it as well but have none yet: they take the kernel for few streams, four to a read
+// of the keys, and no other route has been measured for them (64 streams of four heads over 8 x 4096 tokens: 8.7 us with 64 channels in
+// that kernel, 10.7 us over 8 x 8192 with 128 in the scorer above).
 static bool score_is_batched(const swarm_keys* keys, int B, bool listed) {
     const int L = keys->kind == SWARM_KEYS_PAGE_MINMAX ? 2 * keys->d : keys->d;
     return !listed && B >= SWARM_BATCHED_MIN_STREAMS && (L == 128 || L == 256) && keys->H <= 65535;
