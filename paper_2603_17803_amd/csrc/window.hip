@@ -64,18 +64,19 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const v4u* __restrict__
     const uint32_t base = (PLACE && base64 >= 0) ? (uint32_t)(base64 % D) : 0u;
 
     // new entries per run: as few as let one pass hold all of this workgroup's, at most WIN_PER_SEG
-    const int per = min(WIN_PER_SEG, ((PLACE ? n_new : share) + SEGS - 1) / SEGS);
-    const int a_begin = PLACE ? 0 : (int)blockIdx.z * share, a_end = PLACE ? n_new : min(n_new, a_begin + share);
+    const int per = min(WIN_PER_SEG, ((PLACE ? n_new : share) - 1) / SEGS + 1);
+    const int a_begin = PLACE ? 0 : (int)blockIdx.z * share, a_end = PLACE || share >= n_new - a_begin ? n_new : a_begin + share;
     uint32_t grown = 0;                                        // joiners of earlier passes
-    for (int a0 = a_begin; a0 < a_end; a0 += SEGS * per) {
-        const int first = a0 + seg * per, count = min(per, a_end - first);          // <= 0: an empty run
+    for (uint32_t a0 = (uint32_t)a_begin; a0 < (uint32_t)a_end; a0 += SEGS * per) {    // unsigned: the last pass may end past 2^31
+        const uint32_t first = a0 + seg * per;
+        const int count = min(per, (int)((uint32_t)a_end - first));                  // <= 0: an empty run
         uint32_t joins = 0;
         constexpr int AHEAD = NR <= 2 ? 4 : NR <= 4 ? 2 : 1;   // new entries whose trace words are in flight together
         for (int e0 = 0; e0 < per; e0 += AHEAD) {
             int32_t id[AHEAD];
             v4u o[AHEAD][NR];
 #pragma unroll
-            for (int u = 0; u < AHEAD; ++u) id[u] = new_ids[(size_t)h * n_new + min(first + e0 + u, n_new - 1)];
+            for (int u = 0; u < AHEAD; ++u) id[u] = new_ids[(size_t)h * n_new + min(first + e0 + u, (uint32_t)n_new - 1u)];
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) {
                 const bool e_ok = id[u] >= 0 && id[u] < N;
@@ -147,7 +148,7 @@ swarm_status launch_window(swarm_ctx* ctx, int nruns, int Npad, int N, int W, in
     const int64_t most = ((int64_t)n_new + halves - 1) / halves;
     parts = parts < 1 ? 1 : parts > most ? most : parts;
     const int share = (int)((n_new + parts - 1) / parts);
-    const dim3 grid((unsigned)((Nc + 31) / 32), (unsigned)H, (unsigned)((n_new + share - 1) / share));
+    const dim3 grid((unsigned)((Nc + 31) / 32), (unsigned)H, (unsigned)(((int64_t)n_new + share - 1) / share));
 #define SWARM_WINDOW(NR, NW) hipLaunchKernelGGL((disk ? window_kernel<NR, NW, true> : window_kernel<NR, NW, false>), grid, dim3(64 * NW), 0, ctx->stream, \
                                                 reinterpret_cast<const v4u*>(ctx->trace), nruns, Npad, N, W, new_ids, n_new, share, medoids, Nc, tau, \
                                                 primary, size, D, f_out, member, disk, ctx->dev_flags)

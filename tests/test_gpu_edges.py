@@ -124,6 +124,17 @@ def test_window_places_from_negative_first_disks(sw, n_new, Nc):
     assert sw.device_status() == 0
 
 
+def test_window_of_the_most_new_entries(sw):
+    """As many new entries as a call can name: the last share ends short of 2^31, the last pass of it beyond."""
+    n_new = (1 << 31) - 1
+    sel = torch.tensor([[[0]], [[1]]], dtype=torch.int32, device="cuda")
+    new_ids = torch.zeros((1, n_new), dtype=torch.int32, device="cuda")
+    new_ids[0, -1] = 1
+    _, member, _ = sw.window_assign(sel, 2, new_ids, torch.zeros((1, 1), dtype=torch.int32, device="cuda"), 0.6, want_counts=False)
+    member = member.view(-1)
+    assert int(member[-1]) == 0 and bool(member[:-1].all()) and sw.device_status() == 0
+
+
 def test_window_of_nearly_all_of_the_most_entries(sw):
     """128 steps that each select all but one of 2^24 entries: the list of a run's ids ends 128 short of 2^31, less than what
     the trace builder steps past it.  A few seconds: each of the 2048 spans scans the whole list."""
