@@ -6,6 +6,8 @@
 // f is a thin (new entries x medoids) slice of the window's A^T A.  The window's trace is built as
 // bits (the same builder as for the full co-activation matrix), so a count is a handful of
 // AND + popcount operations on the two entries' 16-byte words.
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
@@ -24,13 +26,16 @@ constexpr int WIN_PER_SEG = 8;            // new entries of a run and pass
 // What is left is writing: 9 bytes per pair, in half-wave rows of 128 bytes.
 // Without places nothing ties the new entries together: they are dealt to gridDim.z workgroups of `share` entries each, so
 // that few clusters do not leave the device idle.  With places (PLACE) one workgroup walks them all.
-template <int NR, int NW, bool PLACE>
+// WIDE: positions of new entries in 64 bits, for lists whose last pass could end past 2^31.  Signed 32-bit positions otherwise:
+// unsigned ones that may pass 2^31 took 191 us where these take 183 (8192 new entries, 64 clusters, places), counting down as much.
+template <int NR, int NW, bool PLACE, bool WIDE>
 __global__ __launch_bounds__(64 * NW) void window_kernel(const v4u* __restrict__ bits, int nruns, int Npad, int N, int W,
                                                                 const int32_t* __restrict__ new_ids, int n_new, int share,
                                                                 const int32_t* __restrict__ medoids, int Nc, double tau,
                                                                 const int32_t* __restrict__ primary, const int32_t* __restrict__ size, int D,
                                                                 int32_t* __restrict__ f_out, uint8_t* __restrict__ member,
                                                                 int32_t* __restrict__ disk, uint32_t* __restrict__ dev_flags) {
+    using pos_t = std::conditional_t<WIDE, int64_t, int>;
     constexpr int SEGS = 2 * NW;                               // runs of consecutive new entries, one per half wave
     __shared__ uint32_t joined[SEGS][32];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -64,19 +69,19 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const v4u* __restrict__
     const uint32_t base = (PLACE && base64 >= 0) ? (uint32_t)(base64 % D) : 0u;
 
     // new entries per run: as few as let one pass hold all of this workgroup's, at most WIN_PER_SEG
-    const int per = min(WIN_PER_SEG, ((PLACE ? n_new : share) - 1) / SEGS + 1);
-    const int a_begin = PLACE ? 0 : (int)blockIdx.z * share, a_end = PLACE || share >= n_new - a_begin ? n_new : a_begin + share;
+    const int per = (int)min((pos_t)WIN_PER_SEG, ((PLACE ? n_new : share) + (pos_t)(SEGS - 1)) / SEGS);
+    const pos_t a_begin = PLACE ? 0 : (pos_t)blockIdx.z * share, a_end = PLACE ? n_new : min((pos_t)n_new, a_begin + share);
     uint32_t grown = 0;                                        // joiners of earlier passes
-    for (uint32_t a0 = (uint32_t)a_begin; a0 < (uint32_t)a_end; a0 += SEGS * per) {    // unsigned: the last pass may end past 2^31
-        const uint32_t first = a0 + seg * per;
-        const int count = min(per, (int)((uint32_t)a_end - first));                  // <= 0: an empty run
+    for (pos_t a0 = a_begin; a0 < a_end; a0 += SEGS * per) {
+        const pos_t first = a0 + seg * per;
+        const int count = (int)min((pos_t)per, a_end - first);                        // <= 0: an empty run
         uint32_t joins = 0;
         constexpr int AHEAD = NR <= 2 ? 4 : NR <= 4 ? 2 : 1;   // new entries whose trace words are in flight together
         for (int e0 = 0; e0 < per; e0 += AHEAD) {
             int32_t id[AHEAD];
             v4u o[AHEAD][NR];
 #pragma unroll
-            for (int u = 0; u < AHEAD; ++u) id[u] = new_ids[(size_t)h * n_new + min(first + e0 + u, (uint32_t)n_new - 1u)];
+            for (int u = 0; u < AHEAD; ++u) id[u] = new_ids[(size_t)h * n_new + min(first + e0 + u, (pos_t)(n_new - 1))];
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) {
                 const bool e_ok = id[u] >= 0 && id[u] < N;
@@ -148,8 +153,10 @@ swarm_status launch_window(swarm_ctx* ctx, int nruns, int Npad, int N, int W, in
     const int64_t most = ((int64_t)n_new + halves - 1) / halves;
     parts = parts < 1 ? 1 : parts > most ? most : parts;
     const int share = (int)((n_new + parts - 1) / parts);
+    const bool wide = n_new > (1 << 30);                       // below, no sum of a position and a pass or a share passes 2^31
     const dim3 grid((unsigned)((Nc + 31) / 32), (unsigned)H, (unsigned)(((int64_t)n_new + share - 1) / share));
-#define SWARM_WINDOW(NR, NW) hipLaunchKernelGGL((disk ? window_kernel<NR, NW, true> : window_kernel<NR, NW, false>), grid, dim3(64 * NW), 0, ctx->stream, \
+#define SWARM_WINDOW(NR, NW) hipLaunchKernelGGL((wide ? (disk ? window_kernel<NR, NW, true, true> : window_kernel<NR, NW, false, true>) \
+                                                      : (disk ? window_kernel<NR, NW, true, false> : window_kernel<NR, NW, false, false>)), grid, dim3(64 * NW), 0, ctx->stream, \
                                                 reinterpret_cast<const v4u*>(ctx->trace), nruns, Npad, N, W, new_ids, n_new, share, medoids, Nc, tau, \
                                                 primary, size, D, f_out, member, disk, ctx->dev_flags)
     if (nruns <= 2) SWARM_WINDOW(2, 16);
