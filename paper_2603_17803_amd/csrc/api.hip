@@ -96,6 +96,7 @@ swarm_status swarm_destroy(swarm_ctx* ctx) {
     if (ctx->trace) (void)hipFree(ctx->trace);
     if (ctx->cand) (void)hipFree(ctx->cand);
     if (ctx->totals) (void)hipFree(ctx->totals);
+    if (ctx->lists) (void)hipFree(ctx->lists);
     for (auto& t : ctx->tile_orders) (void)hipFree(t.second);
     for (void* p : ctx->retired) (void)hipFree(p);
     if (ctx->dev_flags) (void)hipFree(ctx->dev_flags);
@@ -230,6 +231,22 @@ static swarm_status check_coact_args(swarm_ctx* ctx, const char* fn, const int32
     return SWARM_OK;
 }
 
+// Whether an overwriting count goes row by row, with the room it needs.  Both ways give the same counts, so a recording or a device
+// without that room takes the dense one; what the dense one keeps per size is there after either, for the recordings that follow.
+static swarm_status take_rows_route(swarm_ctx* ctx, int64_t rows, int32_t H, int32_t k, int32_t N, int Npad, bool* sparse) {
+    *sparse = rows_route(rows, H, N, k);
+    if (!*sparse) return SWARM_OK;
+    const size_t bytes = rows_list_bytes(rows, H, k, N);
+    if (ctx->lists_bytes < bytes && ctx->capturing) {
+        *sparse = false;
+        return SWARM_OK;
+    }
+    const swarm_status st = swarm_grow(ctx, &ctx->lists, &ctx->lists_bytes, bytes);
+    if (st == SWARM_ENOMEM) *sparse = false;
+    else if (st != SWARM_OK) return st;
+    return coact_reserve_tiles(ctx, Npad);
+}
+
 swarm_status swarm_coact_accumulate(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int32_t H, int32_t k,
                                     int32_t N, int32_t* C, uint32_t decay_q16, uint32_t flags) {
     SWARM_ENTER(ctx);
@@ -244,6 +261,12 @@ swarm_status swarm_coact_accumulate(swarm_ctx* ctx, const int32_t* idx, int64_t 
     st = launch_trace_build(ctx, idx, rows, H, k, N, Npad, nruns, flags);
     if (st != SWARM_OK) return st;
     if (flags & SWARM_COACT_POPCOUNT) return launch_coact_popcount(ctx, H, N, Npad, nruns, C, decay_q16);
+    if (decay_q16 == 0u) {
+        bool sparse;
+        st = take_rows_route(ctx, rows, H, k, N, Npad, &sparse);
+        if (st != SWARM_OK) return st;
+        if (sparse) return launch_coact_rows(ctx, idx, rows, H, k, N, Npad, nruns, C, ctx->lists);
+    }
     return launch_coact_syrk(ctx, H, N, Npad, nruns, C, decay_q16);
 }
 
@@ -266,13 +289,17 @@ swarm_status swarm_coact_build_density(swarm_ctx* ctx, const int32_t* idx, int64
     st = swarm_grow(ctx, reinterpret_cast<void**>(&ctx->totals), &ctx->totals_bytes,
                     sizeof(int64_t) * 2 * (size_t)H + sizeof(int32_t) * trace_count_words(nruns, H, Npad));
     if (st != SWARM_OK) return st;
+    bool sparse;
+    st = take_rows_route(ctx, rows, H, k, N, Npad, &sparse);
+    if (st != SWARM_OK) return st;
     int64_t* totals = totals_out ? totals_out : ctx->totals;
     int64_t* cstar = ctx->totals + H;
     int32_t* row_count = reinterpret_cast<int32_t*>(ctx->totals + 2 * (size_t)H);
 
     st = launch_trace_build(ctx, idx, rows, H, k, N, Npad, nruns, flags, row_count, rho);
     if (st == SWARM_OK) st = launch_trace_totals_thresholds(ctx, row_count, slabs, H, nruns * 128, tau, rho_flags, totals, cstar);
-    if (st == SWARM_OK) st = launch_coact_syrk(ctx, H, N, Npad, nruns, C, 0u, cstar, rho);
+    if (st == SWARM_OK) st = sparse ? launch_coact_rows(ctx, idx, rows, H, k, N, Npad, nruns, C, ctx->lists, cstar, rho)
+                                    : launch_coact_syrk(ctx, H, N, Npad, nruns, C, 0u, cstar, rho);
     if (st == SWARM_OK && (rho_flags & SWARM_RHO_EXCLUDE_SELF)) st = launch_rho_exclude_self(ctx, C, H, N, cstar, rho);
     if (st == SWARM_OK && queue) st = launch_medoid_rank(ctx, rho, H, N, queue);
     return st;

@@ -26,12 +26,6 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// Position, inside its 32-bit word, of the bit of trace row r (0..31) of the word's group: row 8q + b is
-// bit 4b + q, i.e. eight consecutive rows are the same bit of the word's eight nibbles.  Any fixed order
-// serves the counts (both operands of a product, and both sides of an AND + popcount, use the same one);
-// this one makes the expansion to 4-bit operands a shift and a mask.
-__device__ __forceinline__ int trace_bit(int r) { return 4 * (r & 7) + (r >> 3); }
-
 constexpr int TRACE_SPAN = 8192;   // entries one trace-building workgroup covers at most (128 KiB of LDS)
 constexpr int TRACE_SPAN_MIN = 512;
 constexpr int TRACE_THREADS = 1024;
@@ -713,6 +707,12 @@ static swarm_status tile_order_for(swarm_ctx* ctx, int ntm, const int32_t** out)
     free(host);
     *out = dev;
     return st;
+}
+
+swarm_status coact_reserve_tiles(swarm_ctx* ctx, int Npad) {
+    if (ctx->capturing || Npad / TM > 65535) return SWARM_OK;
+    const int32_t* order;
+    return tile_order_for(ctx, Npad / TM, &order);
 }
 
 // cstar and rho both null: plain update of C.  Both given (overwriting form only): the

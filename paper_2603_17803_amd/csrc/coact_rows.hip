@@ -1,0 +1,350 @@
+// Co-activation counts of sparse traces (Section 5.1, Step 1: the same C = A^T A as coact.hip, the same integers).
+//
+// Row i of C is the sum of the selections of the trace rows that activate entry i: k increments for each of them, k^2 per
+// trace row and head, where the dense product does N^2 multiply-adds whatever k is.  The increments are LDS atomics, and a
+// compute unit takes one wave instruction of them every 4.2 cycles (4.8 on random addresses, however many lanes take part),
+// some 13 increments a cycle against 16 thousand operations of the 4-bit matrix cores: from k = N / 64 down this is the shorter way.
+//
+// What bounds the obvious form (a workgroup per row of C, 128 KiB of counters) is the reading of the selections: each is read
+// k times, 17 GB for 8192 of 1024 out of 65536 entries, which do not fit an L2 (3.9 ms without a single increment).  So the
+// columns are cut into eight segments, one per XCD (workgroup b runs on XCD b % 8): an XCD meets only its segment's part of
+// every selection, 2.7 MB of records that stay in its own L2, and a segment's 8192 counters leave room for four workgroups per
+// compute unit.  Blocks of 64 columns are dealt to the segments in turn, so that a run of neighbouring entries is spread evenly.
+// Records have a fixed size -- the mean share of a segment, some standard deviations, and what completes a wave's division by
+// whole records -- because walking ragged pieces costs more than the increments (pieces through a work list: 4.8 ms); the ids
+// beyond it, rare unless the ids prefer one segment, go to an overflow that a whole wave reads at once.
+// 8192 selections of 1024 out of 65536 entries: 5.7 ms by the dense product, 3.5 ms here with trace and records; 3.3 ms are
+// increments, listing and clearing, 3.1 to 3.3 ms the writing of C by itself (5.5 TB/s, what row pieces reach), side by side.
+#include <type_traits>
+
+#include "common.h"
+#include "wave_ops.h"
+
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4i_row __attribute__((ext_vector_type(4), aligned(4)));   // rows of C are 4-byte aligned when N is odd
+
+constexpr int MAX_SEGMENTS = 8;       // one per XCD
+constexpr int MAX_SEGMENT = 8192;     // columns of a segment: 32 KiB of counters
+constexpr int BLOCK = 64;             // columns dealt to the segments together
+constexpr int LIST_WAVES = 4;
+constexpr int LIST_MAX_K = 1024;      // N / 64
+constexpr int DUMMY_WORDS = 32;       // counters behind a segment's, taken by padding
+constexpr int RT = 512;               // threads of a counting workgroup; with 256 the same within 2 %
+constexpr int T_CAP = 512;            // trace rows listed at a time
+constexpr uint32_t MORE = 0xffffu;    // last slot of a record: the piece goes on in the overflow
+
+__host__ __device__ __forceinline__ int seg_columns(int N, int nseg) { return (N + nseg * BLOCK - 1) / (nseg * BLOCK) * BLOCK; }
+
+// Every selection becomes one record per segment: the byte offsets of its distinct valid ids' counters, 16 bits each, in L
+// groups of eight, and the rest in the overflow.  Slot p of a record is element p / L of group p % L, so that the lanes of a
+// wave, a group each, meet neighbouring ids together (a run of entries then falls on distinct LDS banks).  One wave per
+// selection: 30 us for 8192 of 1024.
+__global__ __launch_bounds__(64 * LIST_WAVES) void list_build_kernel(const int32_t* __restrict__ idx, int64_t rows, int recs, int H, int k, int N, int nseg_log2,
+                                                                     int L, int ext_groups, uint4* __restrict__ lists, uint4* __restrict__ ext,
+                                                                     uint32_t* __restrict__ meta) {
+    __shared__ uint16_t el_all[LIST_WAVES][LIST_MAX_K];
+    __shared__ uint32_t piece_all[LIST_WAVES][MAX_SEGMENTS], more_all[LIST_WAVES][MAX_SEGMENTS];
+    extern __shared__ uint32_t seen_all[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t r = (int64_t)blockIdx.x * LIST_WAVES + wave;          // row * H + head, as the selections lie in memory
+    if (r >= rows * H) return;
+    const int h = (int)(r % H);
+    const int64_t row = r / H, t = (row & ~31ll) | trace_bit((int)(row & 31));       // records lie in the order of the trace's bits
+    const int32_t* sel = idx + r * k;
+    const int nseg = 1 << nseg_log2;
+    const int cols = seg_columns(N, nseg);
+    uint16_t* el = el_all[wave];
+    uint32_t *piece = piece_all[wave], *more = more_all[wave];
+    if (lane < MAX_SEGMENTS) piece[lane] = 0u;
+    bool fine = true;
+    for (int p0 = 0; p0 < k; p0 += 64) {
+        const int p = p0 + lane;
+        if (p < k) {
+            const int32_t e = sel[p];
+            fine &= (uint32_t)e < (uint32_t)N && (p == 0 || sel[p - 1] < e);
+        }
+    }
+    int n = k;
+    auto seg_of = [&](uint32_t e) __attribute__((always_inline)) { return (e / BLOCK) & (nseg - 1); };
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (__ballot(!fine) == 0) {
+        for (int p = lane; p < k; p += 64) {
+            const int32_t e = sel[p];
+            el[p] = (uint16_t)e;
+            atomicAdd(&piece[seg_of(e)], 1u);
+        }
+    } else {
+        // repeated, unsorted or invalid ids: the distinct valid ones through a bitmap of the wave's own
+        uint32_t* seen = seen_all + wave * ((N + 31) / 32);
+        for (int w = lane; w < (N + 31) / 32; w += 64) seen[w] = 0u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        n = 0;
+        for (int p0 = 0; p0 < k; p0 += 64) {
+            const int p = p0 + lane;
+            const int32_t e = p < k ? sel[p] : -1;
+            bool fresh = false;
+            if ((uint32_t)e < (uint32_t)N) fresh = !(atomicOr(&seen[e >> 5], 1u << (e & 31)) >> (e & 31) & 1u);
+            const uint64_t b = __ballot(fresh);
+            if (fresh) {
+                el[n + __popcll(b & ((1ull << lane) - 1ull))] = (uint16_t)e;
+                atomicAdd(&piece[seg_of(e)], 1u);
+            }
+            n += __popcll(b);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const uint32_t slots = 8u * L, cap = nseg > 1 ? slots - 1 : slots;
+    const uint32_t cnt = lane < nseg ? piece[lane] : 0u;
+    const uint32_t ng = cnt > cap ? (cnt - cap + 7) / 8 : 0u;
+    uint32_t total;
+    const uint32_t off = waveops::wave_excl_scan(ng, &total);
+    const size_t seg_stride = (size_t)recs * L;
+    uint16_t* out = reinterpret_cast<uint16_t*>(lists + ((size_t)h * nseg * recs + t) * L);
+    uint16_t* eout = reinterpret_cast<uint16_t*>(ext + ((size_t)h * recs + t) * ext_groups);
+    if (lane < nseg) {
+        more[lane] = off * 8;
+        piece[lane] = 0u;
+        if (ng) meta[((size_t)h * nseg + lane) * recs + t] = off | ng << 16;
+        for (uint32_t p = cnt > cap ? cnt - cap : 0u; p < ng * 8; ++p) eout[off * 8 + p] = (uint16_t)((cols + (lane & (DUMMY_WORDS - 1))) * 4);
+    }
+    // padding of the records, and the mark of those that go on
+    for (int s = 0; s < nseg; ++s) {
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cnt, s);
+        for (uint32_t p = min(c, cap) + lane; p < slots; p += 64) {
+            out[s * seg_stride * 8 + (p % L) * 8 + p / L] = (uint16_t)(p >= cap && c > cap ? MORE : (cols + (p & (DUMMY_WORDS - 1))) * 4);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int i = lane; i < n; i += 64) {
+        const uint32_t e = el[i], s = seg_of(e), c = ((e / BLOCK) >> nseg_log2) * BLOCK + (e & (BLOCK - 1));
+        const uint32_t p = atomicAdd(&piece[s], 1u);
+        if (p < cap) out[s * seg_stride * 8 + (p % L) * 8 + p / L] = (uint16_t)(c * 4);
+        else eout[more[s] + p - cap] = (uint16_t)(c * 4);
+    }
+}
+
+// Persistent workgroups: a workgroup takes rows of C one after the other, its XCD's segment of each.  While a row's records are
+// summed, the trace rows of the next one are listed and the trace words of the one after are on their way, so a row costs two
+// barriers.  The trace words of an entry's column (bits, see coact.hip) say which records to sum; a wave reads 64 / L records at
+// once, a group of eight ids per lane.
+// RHO: also counts, per row, the elements that reach the head's threshold (rho must be zero before).  SEG: more than one segment.
+template <bool RHO, bool SEG>
+__global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __restrict__ bits, const uint4* __restrict__ lists, int recs, int H, int N,
+                                                           int Npad, int nruns, int nseg_log2, int L, int ext_groups, int32_t* __restrict__ C,
+                                                           const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
+    const int nseg = 1 << nseg_log2, cols = seg_columns(N, nseg);
+    uint32_t* cnt = smem;                                                        // cols + DUMMY_WORDS counters
+    uint16_t* tl = reinterpret_cast<uint16_t*>(smem + cols + DUMMY_WORDS);       // [2][T_CAP]
+    __shared__ uint32_t tcount[2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
+    const int seg = xcd & (nseg - 1), parts = 8 >> nseg_log2, part = xcd >> nseg_log2;
+    const int nwords = nruns * 4, chunks = (nwords + RT - 1) / RT;
+    const int stride = slots * parts;
+    const int lpw = 64 / L, my_list = lane / L, my_group = lane - my_list * L;   // lists a wave works on side by side
+    for (int w = tid; w < (cols + DUMMY_WORDS) / 4; w += RT) reinterpret_cast<v4i*>(cnt)[w] = v4i{0, 0, 0, 0};
+    if (tid < 2) tcount[tid] = 0;
+    __syncthreads();
+
+    struct Place { int h, i, chunk; };
+    auto advance = [&](Place& p) __attribute__((always_inline)) {
+        if (++p.chunk < chunks) return;
+        p.chunk = 0;
+        p.i += stride;
+        while (p.i >= N) { p.i -= N; ++p.h; }
+    };
+    const uint32_t word_off = ((uint32_t)(tid >> 2) * (uint32_t)Npad * 4 + (tid & 3)) * 4;       // bytes, inside a head's trace
+    auto load_word = [&](const Place& p) __attribute__((always_inline)) -> uint32_t {
+        if (p.chunk * RT + tid >= nwords || p.h >= H) return 0u;
+        const char* base = reinterpret_cast<const char*>(bits) + (((size_t)p.h * nruns + p.chunk * (RT / 4)) * Npad + p.i) * 16;
+        return *reinterpret_cast<const uint32_t*>(base + word_off);
+    };
+    // lists the records of the trace rows of this thread's word
+    auto list_rows = [&](uint32_t word, int chunk, int buf) __attribute__((always_inline)) {
+        if (word) {
+            uint32_t at = atomicAdd(&tcount[buf], (uint32_t)__popc(word));
+            const uint32_t t0 = (uint32_t)(chunk * RT + tid) * 32;
+            while (word) {
+                tl[buf * T_CAP + (at & (T_CAP - 1))] = (uint16_t)(t0 + __ffs(word) - 1);
+                word &= word - 1;
+                ++at;
+            }
+        }
+    };
+    auto add = [&](uint32_t at) __attribute__((always_inline)) {
+        __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(cnt) + at), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    const uint32_t end = (uint32_t)cols * 4;
+    auto add8 = [&](const uint4& x, uint32_t last) __attribute__((always_inline)) {
+        add(x.x & 0xffffu); add(x.x >> 16);
+        add(x.y & 0xffffu); add(x.y >> 16);
+        add(x.z & 0xffffu); add(x.z >> 16);
+        add(x.w & 0xffffu);
+        if (__ballot(last < end) != 0) add(last);             // the last eighth of the slots is mostly padding
+    };
+    const uint32_t rec_bytes = (uint32_t)L * 16, group_off = (uint32_t)my_group * 16;
+
+    Place at{0, slot * parts + part, 0};
+    while (at.i >= N) { at.i -= N; ++at.h; }
+    Place ahead = at;
+    int buf = 0;
+    uint32_t word = load_word(at);
+    list_rows(word, 0, 0);
+    advance(ahead);
+    uint32_t next = load_word(ahead);
+    __syncthreads();
+    while (at.h < H) {
+        const char* hl = reinterpret_cast<const char*>(lists + ((size_t)at.h * nseg + seg) * recs * L);
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)tcount[buf]), word_now = word;
+        list_rows(next, ahead.chunk, buf ^ 1);                // the rows of the step after this one listed, the words after those requested
+        word = next;
+        const Place after = ahead;
+        advance(ahead);
+        next = load_word(ahead);
+        const int parts_of = n <= T_CAP ? 1 : RT / 16;        // too many for the list: the words sixteen at a time
+        for (int s = 0; s < parts_of; ++s) {
+            uint32_t m = n;
+            if (parts_of > 1) {
+                __syncthreads();
+                if (tid == 0) tcount[buf] = 0;
+                __syncthreads();
+                if ((tid >> 4) == s) list_rows(word_now, at.chunk, buf);
+                __syncthreads();
+                m = (uint32_t)__builtin_amdgcn_readfirstlane((int)tcount[buf]);
+            }
+            constexpr int U = 3;                              // records in flight per lane; 2, 3, 4 and 6 within 2 %
+            const uint16_t* t_of = tl + buf * T_CAP;
+            const uint32_t step = (RT / 64) * lpw;
+            if (my_list < lpw) {
+                for (uint32_t p0 = wave * lpw; p0 < m; p0 += U * step) {
+                    uint4 v[U];
+                    uint32_t t[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        t[u] = t_of[min(p0 + u * step + my_list, m - 1)];
+                        v[u] = *reinterpret_cast<const uint4*>(hl + (t[u] * rec_bytes + group_off));
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (p0 + u * step >= m) break;
+                        uint32_t last = v[u].w >> 16;
+                        const bool on = p0 + u * step + my_list < m;
+                        const uint64_t goes_on = SEG ? __ballot(on && last == MORE) : 0ull;      // known to all lanes: they read the overflow together
+                        if (SEG) last = last == MORE ? end : last;
+                        if (on) add8(v[u], last);
+                        if (SEG && __builtin_expect(goes_on != 0, 0)) {
+                            uint32_t nrec = (uint32_t)recs;
+                            asm volatile("" : "+s"(nrec));
+                            const uint4* ext = lists + (size_t)nrec * H * L * nseg;
+                            const uint32_t* meta = reinterpret_cast<const uint32_t*>(ext + (size_t)nrec * H * ext_groups) + ((size_t)at.h * nseg + seg) * nrec;
+                            for (uint64_t left = goes_on; left; left &= left - 1) {
+                                const int l = __ffsll((unsigned long long)left) - 1;
+                                const uint32_t tt = (uint32_t)__builtin_amdgcn_readlane((int)t[u], l);
+                                const uint32_t x = meta[tt];
+                                const uint4* e = ext + ((size_t)at.h * nrec + tt) * ext_groups + (x & 0xffffu);
+                                for (uint32_t g = lane; g < x >> 16; g += lpw * L) {
+                                    const uint4 y = e[g];
+                                    add8(y, y.w >> 16);
+                                }
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (tid == 0) tcount[buf] = 0;
+        buf ^= 1;
+        if (after.chunk == 0) {
+            // the row's segment leaves, its counters are cleared
+            char* row = reinterpret_cast<char*>(C + ((size_t)at.h * N + at.i) * N);
+            int32_t c32 = 0x7fffffff;
+            if (RHO) {
+                const int64_t c = cstar[at.h];
+                if (c < 0x7fffffffll) c32 = (int32_t)c;
+            }
+            int near = 0;
+            uint32_t e = (((tid >> 4) << nseg_log2) + seg) * BLOCK + (tid & 15) * 4;
+            auto leave = [&](auto whole_tag) __attribute__((always_inline)) {
+                constexpr bool WHOLE = decltype(whole_tag)::value;
+                for (int w = tid; w < cols / 4; w += RT, e += (RT / 16 * BLOCK) << nseg_log2) {
+                    const v4i v = reinterpret_cast<const v4i*>(cnt)[w];
+                    reinterpret_cast<v4i*>(cnt)[w] = v4i{0, 0, 0, 0};
+                    if (WHOLE || e + 4 <= (uint32_t)N) {
+                        __builtin_nontemporal_store((v4i_row)v, reinterpret_cast<v4i_row*>(row + e * 4));
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (e + q < (uint32_t)N) reinterpret_cast<int32_t*>(row)[e + q] = v[q];
+                    }
+                    if (RHO) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) near += __popcll(__ballot(v[q] >= c32 && (WHOLE || e + q < (uint32_t)N)));
+                    }
+                }
+            };
+            if ((cols << nseg_log2) == N) leave(std::true_type{});
+            else leave(std::false_type{});
+            if (RHO && lane == 0 && near) atomicAdd(rho + (size_t)at.h * N + at.i, near);
+        }
+        at = after;
+        __syncthreads();
+    }
+}
+
+struct RowsPlan { int nseg_log2, L, ext_groups; };
+RowsPlan plan_of(int N, int k) {
+    RowsPlan p{0, 0, 0};
+    while ((1 << p.nseg_log2) < MAX_SEGMENTS && N > (MAX_SEGMENT << p.nseg_log2)) ++p.nseg_log2;
+    const int nseg = 1 << p.nseg_log2;
+    int room = k;
+    if (nseg > 1) {
+        const int mean = (k + nseg - 1) / nseg;
+        int s = 1;                                            // 2.5 standard deviations of ids that fall anywhere
+        while (4 * s * s < 25 * mean) ++s;
+        room = mean + s + 1;
+    }
+    p.L = 64 / (64 / ((room + 7) / 8));                       // as long as as many records fit a wave
+    p.ext_groups = (k + 7 * nseg) / 8;
+    return p;
+}
+
+}  // namespace
+
+// Where the increments win, measured on both ways for N from 2048 to 65536, 1024 to 16384 trace rows, k from N / 44 to N / 128:
+//  - k <= N / 64: 8192 rows 1.1 to 1.7 times as fast at N / 64, 0.75 to 1.0 at N / 44 (three records to a wave become two);
+//  - 6144 rows: below, the dense product waits for the writing of C as well (4096 rows 0.91 to 1.1, 5120 0.97 to 1.2, 6144 1.04 to 1.4);
+//  - N >= 4096: a row of 2048 is over before the two barriers are (8192 rows of 4 heads: 0.89);
+//  - N a multiple of 16: a 64-byte piece of C shared by two XCDs is written twice (N = 12289: 0.85, 24592: 1.27 at 6144 rows).
+// The ids of a segment and the trace rows have to fit 16 bits, a wave per selection one launch.
+bool rows_route(int64_t rows, int H, int N, int k) {
+    return rows * H <= (int64_t)1 << 25 && rows >= 6144 && rows <= 65535 && N >= 4096 && N <= MAX_SEGMENTS * MAX_SEGMENT && N % 16 == 0 && k <= N / 64;
+}
+
+// Scratch for the records, their overflow and where a piece's overflow lies.
+size_t rows_list_bytes(int64_t rows, int H, int k, int N) {
+    const RowsPlan p = plan_of(N, k);
+    const int64_t recs = (rows + 31) / 32 * 32;
+    return (size_t)recs * H * ((((size_t)p.L << p.nseg_log2) + p.ext_groups) * 16 + (4 << p.nseg_log2));
+}
+
+swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int H, int k, int N, int Npad, int nruns, int32_t* C,
+                               void* scratch, const int64_t* cstar, int32_t* rho) {
+    const RowsPlan p = plan_of(N, k);
+    const int recs = (int)((rows + 31) / 32 * 32);
+    uint4* lists = static_cast<uint4*>(scratch);
+    uint4* ext = lists + ((size_t)recs * H * p.L << p.nseg_log2);
+    uint32_t* meta = reinterpret_cast<uint32_t*>(ext + (size_t)recs * H * p.ext_groups);
+    hipLaunchKernelGGL(list_build_kernel, dim3((unsigned)((rows * H + LIST_WAVES - 1) / LIST_WAVES)), dim3(64 * LIST_WAVES),
+                       (size_t)LIST_WAVES * ((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext, meta);
+    swarm_status st = swarm_check_launch(ctx, "list_build_kernel");
+    if (st != SWARM_OK) return st;
+    const int lds = (seg_columns(N, 1 << p.nseg_log2) + DUMMY_WORDS) * 4 + 2 * T_CAP * 2;
+    hipLaunchKernelGGL(p.nseg_log2 ? (cstar ? coact_rows_kernel<true, true> : coact_rows_kernel<false, true>)
+                                   : (cstar ? coact_rows_kernel<true, false> : coact_rows_kernel<false, false>), dim3(256 * 4), dim3(RT), lds, ctx->stream,
+                       reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns, p.nseg_log2, p.L, p.ext_groups, C, cstar, rho);
+    return swarm_check_launch(ctx, "coact_rows_kernel");
+}

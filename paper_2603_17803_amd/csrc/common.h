@@ -10,6 +10,12 @@
 
 #include "swarm.h"
 
+// Position, inside its 32-bit word, of the bit of trace row r (0..31) of the word's group: row 8q + b is
+// bit 4b + q, i.e. eight consecutive rows are the same bit of the word's eight nibbles.  Any fixed order
+// serves the counts (both operands of a product, and both sides of an AND + popcount, use the same one);
+// this one makes the expansion to 4-bit operands a shift and a mask.
+__device__ __forceinline__ int trace_bit(int r) { return 4 * (r & 7) + (r >> 3); }
+
 struct swarm_graph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -27,6 +33,8 @@ struct swarm_ctx {
     size_t scores_bytes = 0;
     void* trace = nullptr;         // binary trace as bits: uint4 [H][runs of 128 rows][Npad]
     size_t trace_bytes = 0;
+    void* lists = nullptr;         // selections as records of ids (sparse traces, see coact_rows.hip)
+    size_t lists_bytes = 0;
     int64_t* totals = nullptr;     // per-head grand totals of C when the caller keeps none
     size_t totals_bytes = 0;
     bool trace_lds_opt_in = false, syrk_lds_opt_in = false;   // large dynamic LDS enabled for this context's device
@@ -103,8 +111,13 @@ int trace_slabs(int nruns, int H, int Npad);           // spans of entries the b
 size_t trace_count_words(int nruns, int H, int Npad);  // room for row_count: at least what the call needs, never less for a larger shape
 swarm_status launch_trace_totals_thresholds(swarm_ctx* ctx, const int32_t* row_count, int slabs, int H, int nrows, double tau, uint32_t flags,
                                             int64_t* totals, int64_t* cstar);
+swarm_status coact_reserve_tiles(swarm_ctx* ctx, int Npad);   // the dense product's tile schedule for this size (not while recording)
 swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns, int32_t* C, uint32_t decay_q16,
                                const int64_t* cstar = nullptr, int32_t* rho = nullptr);
+bool rows_route(int64_t rows, int H, int N, int k);       // sparse enough to be summed row by row (coact_rows.hip)
+size_t rows_list_bytes(int64_t rows, int H, int k, int N);
+swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int H, int k, int N, int Npad, int nruns, int32_t* C,
+                               void* lists, const int64_t* cstar = nullptr, int32_t* rho = nullptr);
 swarm_status launch_rho_exclude_self(swarm_ctx* ctx, const int32_t* C, int H, int N, const int64_t* cstar, int32_t* rho);
 swarm_status launch_medoid_rank(swarm_ctx* ctx, const int32_t* rho, int H, int N, int32_t* queue);
 swarm_status launch_coact_popcount(swarm_ctx* ctx, int H, int N, int Npad, int nruns, int32_t* C, uint32_t decay_q16);

@@ -1,0 +1,104 @@
+"""GPU parity of the counts of sparse traces (k <= N / 64, 6144 trace rows and more, overwriting): summed row by row, against the
+popcount route on the device and against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+POPCOUNT = 2
+
+
+@pytest.fixture(scope="module")
+def sw():
+    from paper_2603_17803_amd import binding
+    s = binding.Swarm(0, stream=torch.cuda.Stream())
+    yield s
+    s.close()
+
+
+def selections(kind, rows, H, k, N, seed=0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed * 1000 + N + rows)
+    if kind == "spread":                                    # ascending, one per stratum
+        u = torch.rand(rows, H, k, generator=g, device="cuda", dtype=torch.float64)
+        return ((torch.arange(k, device="cuda") + u) * (N / k)).long().clamp_(max=N - 1).int()
+    if kind == "runs":                                      # a run of neighbours each: every entry of it in one stretch of the columns
+        start = torch.randint(0, N - k + 1, (rows, H, 1), generator=g, device="cuda")
+        return (start + torch.arange(k, device="cuda")).int()
+    if kind == "any":                                       # any order, repeated and invalid ids
+        return torch.randint(-3, N + 3, (rows, H, k), generator=g, device="cuda", dtype=torch.int32)
+    if kind == "crowded":                                   # every eighth block of 64 columns: a segment has far more than its share
+        block = torch.randint(0, (N + 511) // 512, (rows, H, k), generator=g, device="cuda")
+        return (block * 512 + torch.randint(0, 64, (rows, H, k), generator=g, device="cuda")).clamp_(max=N - 1).int()
+    same = torch.randperm(N, generator=g, device="cuda")[:k].sort().values      # "same": k entries in every row
+    return same.expand(rows, H, k).int().contiguous()
+
+
+# one, two, four and eight segments; whole and partial last blocks of columns; the fewest rows, a partial run of rows and more
+# rows than the workgroup's words cover at a time; the widest selection and a single entry
+@pytest.mark.parametrize("rows,H,k,N", [(6144, 1, 64, 4096), (6151, 3, 1, 4112), (17000, 1, 60, 4096), (6200, 2, 128, 8208), (6144, 1, 300, 24576),
+                                        (33000, 1, 100, 8192), (6500, 1, 512, 32784)])
+@pytest.mark.parametrize("kind", ["spread", "runs", "any", "crowded", "same"])
+def test_sparse_counts_equal_the_popcount_route(sw, rows, H, k, N, kind):
+    sel = selections(kind, rows, H, k, N)
+    with torch.cuda.stream(sw.stream):
+        sw.stream.wait_stream(torch.cuda.default_stream())
+        C = torch.full((H, N, N), -7, dtype=torch.int32, device="cuda")
+        ref = torch.full((H, N, N), -9, dtype=torch.int32, device="cuda")
+        sw.coact_accumulate(sel, N, C, decay_q16=0)
+        sw.coact_accumulate(sel, N, ref, decay_q16=0, flags=POPCOUNT)
+        assert torch.equal(C, ref)
+        C.fill_(-7)
+        tau = 1.0 - 3.0 / float(ref.sum(dtype=torch.int64) // H + 1)
+        rho, queue, totals = sw.coact_build_density(sel, N, C, tau)
+        assert torch.equal(C, ref)
+        rho2, queue2, totals2 = sw.coact_density(ref, tau)
+        assert torch.equal(totals, totals2) and torch.equal(rho, rho2) and torch.equal(queue, queue2)
+    sw.stream.synchronize()
+    try:
+        sw.device_status()
+    except Exception:
+        assert kind == "any"
+
+
+def test_sparse_counts_equal_the_oracle(sw):
+    rows, H, k, N = 6150, 1, 32, 4096                       # strata of 128 entries: distinct ids, as the oracle asks
+    sel = selections("spread", rows, H, k, N, seed=5)
+    torch.cuda.synchronize()
+    C = torch.empty(H, N, N, dtype=torch.int32, device="cuda")
+    sw.coact_accumulate(sel, N, C, decay_q16=0)
+    sw.stream.synchronize()
+    assert np.array_equal(C.cpu().numpy(), oracle.coact_update(sel.cpu().numpy(), N, nthreads=8))
+
+
+@pytest.mark.parametrize("first", ["dense", "sparse"])
+def test_recordings_take_the_way_that_has_its_room(first):
+    """A recording of either kind of trace is accepted after an eager call of the other kind, and every replay is right."""
+    from paper_2603_17803_amd import binding
+    sw = binding.Swarm(0, stream=torch.cuda.Stream())
+    N, rows = 4096, 6144
+    sparse, dense = selections("spread", rows, 1, 64, N, 1), selections("spread", rows, 1, 100, N, 1)
+    C = torch.empty(1, N, N, dtype=torch.int32, device="cuda")
+    ref = torch.empty_like(C)
+    torch.cuda.synchronize()
+    sw.coact_accumulate(dense if first == "dense" else sparse, N, C, decay_q16=0)
+    sel = sparse if first == "dense" else dense
+    sw.stream.synchronize()
+    sw.capture_begin()
+    sw.coact_accumulate(sel, N, C, decay_q16=0)
+    graph = sw.capture_end()
+    for rep in range(3):
+        sel.copy_(selections("spread", rows, 1, sel.shape[2], N, 10 + rep))
+        torch.cuda.synchronize()
+        C.fill_(-1)
+        torch.cuda.synchronize()
+        sw.graph_launch(graph)
+        sw.coact_accumulate(sel, N, ref, decay_q16=0, flags=POPCOUNT)
+        sw.stream.synchronize()
+        assert torch.equal(C, ref)
+    binding.swarm_graph_destroy(graph)
+    sw.close()
