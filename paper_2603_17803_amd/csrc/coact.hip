@@ -202,9 +202,10 @@ __device__ __forceinline__ int lds_off(int row, int piece) { return row * KC + (
 // give those of the direct tile's rows; a diagonal tile is computed in full, and by
 // symmetry its column counts are its row counts.  Counts meet in LDS and leave as one
 // atomic add per row and tile.
+// STREAM (MODE 0): C leaves in streaming stores, past the caches.
 typedef __attribute__((address_space(3))) void lds_void;
 
-template <int MODE, bool RHO = false>
+template <int MODE, bool RHO = false, bool STREAM = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns, int32_t* __restrict__ C, uint32_t decay_q16,
                        int tiles_per_head, int total_tiles, int per_xcd, const int32_t* __restrict__ tile_order,
@@ -371,7 +372,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     // columns of two rows): the direct tile leaves straight from the accumulators in 4-byte stores,
     // with nothing to wait for.  In the mirrored tile a lane's register quadruple is 16 contiguous
     // bytes but the lines are spread over lanes, so that tile is re-laid out through the (now idle)
-    // LDS and leaves in 16-byte stores that cover whole lines.  Streaming stores when C is not read.
+    // LDS and leaves in 16-byte stores that cover whole lines.
     // the counts as integers (exact: every partial sum is an integer below 2^24)
     v16i acc[2][2];
 #pragma unroll
@@ -415,6 +416,10 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     auto combine = [&](int32_t old, int32_t v) __attribute__((always_inline)) {
         return updated_count<MODE == 0 ? 1 : MODE>(old, v, decay_q16, ovf);
     };
+    auto put = [](int32_t v, int32_t* p) __attribute__((always_inline)) {
+        if (STREAM) __builtin_nontemporal_store(v, p);
+        else *p = v;
+    };
     // four consecutive counts of a row, `cols` of them inside C (four unless the tile reaches past N)
     auto load_row = [](const int32_t* p, int cols) __attribute__((always_inline)) {
         if (cols >= 4) return (v4i) *reinterpret_cast<const v4i_row*>(p);
@@ -422,7 +427,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     };
     auto store_row = [](int32_t* p, v4i w, int cols) __attribute__((always_inline)) {
         if (cols >= 4) {
-            if (MODE == 0) __builtin_nontemporal_store((v4i_row)w, reinterpret_cast<v4i_row*>(p));
+            if (STREAM) __builtin_nontemporal_store((v4i_row)w, reinterpret_cast<v4i_row*>(p));
             else *reinterpret_cast<v4i_row*>(p) = w;
         } else {
             p[0] = w.x;
@@ -447,8 +452,8 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
                     const int urow = i * 32 + (r >> 2) * 8 + (r & 3);
                     int32_t* p = Cd + (size_t)urow * N;
                     if (!GUARD || gi_base + urow + row_in < N) {
-                        if (c0_ok) __builtin_nontemporal_store(acc[i][0][r], at(p, lane_direct));
-                        if (c1_ok) __builtin_nontemporal_store(acc[i][1][r], at(p + 32, lane_direct));
+                        if (c0_ok) put(acc[i][0][r], at(p, lane_direct));
+                        if (c1_ok) put(acc[i][1][r], at(p + 32, lane_direct));
                         if (RHO && c0_ok) colc0 += reaches(acc[i][0][r]);
                         if (RHO && c1_ok) colc1 += reaches(acc[i][1][r]);
                     }
@@ -738,23 +743,33 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     }
     using kernel_t = void (*)(const v4i*, int, int, int, int32_t*, uint32_t, int, int, int, const int32_t*, uint32_t*,
                               const int64_t*, int32_t*);
-    static const kernel_t kernels[3] = {coact_syrk_kernel<0>, coact_syrk_kernel<1>, coact_syrk_kernel<2>};
-    static const kernel_t fused_kernel = coact_syrk_kernel<0, true>;
+    static const kernel_t kernels[2][3] = {{coact_syrk_kernel<0>, coact_syrk_kernel<1>, coact_syrk_kernel<2>},
+                                           {coact_syrk_kernel<0, false, true>, coact_syrk_kernel<1>, coact_syrk_kernel<2>}};
+    static const kernel_t fused_kernels[2] = {coact_syrk_kernel<0, true>, coact_syrk_kernel<0, true, true>};
     constexpr int RHO_LDS_BYTES = SYRK_LDS_BYTES + (TM + TN) * 4;
     if (!ctx->syrk_lds_opt_in) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           RHO_LDS_BYTES);
-        for (int m = 0; m < 3 && e == hipSuccess; ++m)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[m]), hipFuncAttributeMaxDynamicSharedMemorySize, SYRK_LDS_BYTES);
+        hipError_t e = hipSuccess;
+        for (int t = 0; t < 2; ++t) {
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_kernels[t]), hipFuncAttributeMaxDynamicSharedMemorySize, RHO_LDS_BYTES);
+            for (int m = 0; m < 3 && e == hipSuccess; ++m)
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[t][m]), hipFuncAttributeMaxDynamicSharedMemorySize, SYRK_LDS_BYTES);
+        }
         if (e != hipSuccess) {
             snprintf(ctx->err, sizeof(ctx->err), "coact: cannot opt in to %d bytes of LDS: %s", RHO_LDS_BYTES, hipGetErrorString(e));
             return SWARM_EHIP;
         }
         ctx->syrk_lds_opt_in = true;
     }
+    // A large C of whole 64-byte pieces streams: cached, its lines push the trace out of the L2 (8 x 8192^2, 4096 rows: 434 us
+    // streamed, 650 cached; 65536^2: 3.5 and 5.5 ms).  Rows of C that start inside a 64-byte piece share it with their neighbour
+    // tiles, and streamed, each of the two writes it to memory by itself: 4 x 4001^2, 256 rows 124 us streamed, 51 cached, 4096 rows
+    // 137 and 75; 12289^2 291 and 197, 300 and 222; 12304^2 154 and 157.  A C that fits the 256 MiB last-level cache is written there:
+    // 8 x 2048^2 33 us streamed, 28 cached, 4 x 4096^2 57 and 48 (4096 rows: 74.5 and 73).
+    const int stream = N % 16 == 0 && (int64_t)H * N * N > (int64_t)1 << 26;
     dim3 grid((unsigned)(per_xcd * 8)), block(64 * SYRK_WAVES);
     const int tph = (int)tiles_per_head, tot = (int)total;
-    hipLaunchKernelGGL(fused ? fused_kernel : kernels[mode], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
+    hipLaunchKernelGGL(fused ? fused_kernels[stream] : kernels[stream][mode], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
                        ctx->stream, reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, tph, tot, per_xcd,
                        tile_order, ctx->dev_flags, cstar, rho);
     return swarm_check_launch(ctx, "coact_syrk_kernel");
