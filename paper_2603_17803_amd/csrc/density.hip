@@ -146,7 +146,7 @@ __global__ void rho_exclude_self_kernel(const int32_t* __restrict__ C, int N, co
     if ((int64_t)C[((size_t)h * N + i) * N + i] >= cstar[h]) rho[(size_t)h * N + i] -= 1;
 }
 
-// Position of entry i in the medoid queue = entries with a higher density + entries with the same
+// The queue without scratch (a recording that finds none, for more entries than one workgroup sorts): position of entry i = entries with a higher density + entries with the same
 // density and a lower id: N^2 comparisons per head, tiled through LDS.  A workgroup ranks 256 entries;
 // its four quarters (256 threads each) take a quarter of every staged tile of 1024 densities, and the
 // partial ranks meet in LDS: four times the waves per compute unit of one thread per entry.
@@ -187,6 +187,191 @@ __global__ __launch_bounds__(RANK_ENTRIES * RANK_PARTS) void medoid_rank_kernel(
     }
 }
 
+// The same order as a stable radix sort of the ids by N - rho, ascending: comparing all pairs grows with N^2 (one
+// head of 65536 entries 352 us), two passes over the ids are four short launches (34 us; 18 of them a move that waits for its counts).
+// A pass moves the ids only and looks their densities up; digits of at most 9 bits, so up to 2^18 entries take two passes.
+// One workgroup per SORT_BLOCK places of the list, each wave a contiguous part of it.
+constexpr int SORT_THREADS = 256, SORT_STEPS = 8, SORT_BLOCK = SORT_THREADS * SORT_STEPS, SORT_BITS = 9;
+
+// The entry at place p of the list (src null: the list is in ascending id) and its digit; -1 past the end.
+__device__ __forceinline__ int sort_digit(const int32_t* __restrict__ rho, const int32_t* __restrict__ src, int N, int p, int shift, int mask, int& id) {
+    id = p < N ? (src ? src[p] : p) : 0;
+    return p < N ? ((N - rho[id]) >> shift) & mask : -1;
+}
+
+__global__ __launch_bounds__(SORT_THREADS) void rank_count_kernel(const int32_t* __restrict__ rho, const int32_t* __restrict__ src, int N, int shift, int bits,
+                                                                  uint32_t* __restrict__ counts) {
+    __shared__ uint32_t hist[1 << SORT_BITS];
+    const int bins = 1 << bits, h = blockIdx.y;
+    for (int d = threadIdx.x; d < bins; d += SORT_THREADS) hist[d] = 0u;
+    __syncthreads();
+    const int32_t *rh = rho + (size_t)h * N, *sh = src ? src + (size_t)h * N : nullptr;
+#pragma unroll
+    for (int s = 0; s < SORT_STEPS; ++s) {
+        int id;
+        const int d = sort_digit(rh, sh, N, blockIdx.x * SORT_BLOCK + s * SORT_THREADS + threadIdx.x, shift, bins - 1, id);
+        if (d >= 0) atomicAdd(&hist[d], 1u);
+    }
+    __syncthreads();
+    uint32_t* out = counts + ((size_t)h * gridDim.x + blockIdx.x) * bins;
+    for (int d = threadIdx.x; d < bins; d += SORT_THREADS) out[d] = hist[d];
+}
+
+// Lanes of the wave with the same digit (`on` lanes only), a ballot per digit bit.
+__device__ __forceinline__ uint64_t same_digit(int digit, bool on, int bits) {
+    uint64_t same = __ballot(on);
+    for (int b = 0; b < bits; ++b) {
+        const bool bit = (digit >> b) & 1;
+        const uint64_t with = __ballot(bit);
+        same &= bit ? with : ~with;
+    }
+    return same;
+}
+
+// How many entries of the wave with its digit come before this one: those of earlier steps, which `seen` (the wave's own) counts per
+// digit, and those on lower lanes.  A counter is added to by one lane of each digit: equal densities are the rule, and an atomic per
+// lane would queue on their counter.
+__device__ __forceinline__ uint32_t rank_in_wave(int digit, bool on, int bits, uint32_t* seen) {
+    const uint64_t same = same_digit(digit, on, bits);
+    const uint32_t below = (uint32_t)__popcll(same & ((1ull << (threadIdx.x & 63)) - 1ull));
+    uint32_t r = 0;
+    if (on) {
+        r = seen[digit];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (below == 0) seen[digit] = r + (uint32_t)__popcll(same);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return r + below;
+}
+
+// Where a digit's entries of this workgroup go: behind all smaller digits and the same digit of the workgroups before, whose counts
+// every workgroup adds up for itself.
+__global__ __launch_bounds__(SORT_THREADS) void rank_move_kernel(const int32_t* __restrict__ rho, const int32_t* __restrict__ src, int N, int shift, int bits,
+                                                                 const uint32_t* __restrict__ counts, int32_t* __restrict__ dst) {
+    constexpr int WAVES = SORT_THREADS / 64, PER = (1 << SORT_BITS) / SORT_THREADS;
+    __shared__ uint32_t at[WAVES][1 << SORT_BITS], wave_total[WAVES];
+    const int bins = 1 << bits, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t *rh = rho + (size_t)h * N, *sh = src ? src + (size_t)h * N : nullptr;
+    int id[SORT_STEPS], digit[SORT_STEPS];
+#pragma unroll
+    for (int s = 0; s < SORT_STEPS; ++s)
+        digit[s] = sort_digit(rh, sh, N, blockIdx.x * SORT_BLOCK + (wave * SORT_STEPS + s) * 64 + lane, shift, bins - 1, id[s]);
+    // PER consecutive digits per thread
+    uint32_t all[PER], before[PER], sum = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        all[u] = before[u] = 0u;
+        const int d = tid * PER + u;
+        if (d < bins) {
+            const uint32_t* c = counts + (size_t)h * gridDim.x * bins + d;
+#pragma unroll 8
+            for (uint32_t b = 0; b < gridDim.x; ++b) {
+                const uint32_t n = c[(size_t)b * bins];
+                all[u] += n;
+                before[u] += b < blockIdx.x ? n : 0u;
+            }
+        }
+        sum += all[u];
+    }
+    for (int d = lane; d < bins; d += 64) at[wave][d] = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    uint32_t place[SORT_STEPS];
+#pragma unroll
+    for (int s = 0; s < SORT_STEPS; ++s) place[s] = rank_in_wave(digit[s], digit[s] >= 0, bits, at[wave]);
+    uint32_t total;
+    uint32_t first = waveops::wave_excl_scan(sum, &total);
+    if (lane == 0) wave_total[wave] = total;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) first += w < wave ? wave_total[w] : 0u;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int d = tid * PER + u;
+        if (d < bins) {
+            uint32_t p = first + before[u];
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const uint32_t n = at[w][d];
+                at[w][d] = p;
+                p += n;
+            }
+        }
+        first += all[u];
+    }
+    __syncthreads();
+    int32_t* out = dst + (size_t)h * N;
+#pragma unroll
+    for (int s = 0; s < SORT_STEPS; ++s)
+        if (digit[s] >= 0) {
+            const uint32_t p = at[wave][digit[s]] + place[s];
+            if (p < (uint32_t)N) out[p] = id[s];                       // always holds
+        }
+}
+
+// A head that fits one workgroup is sorted in LDS, all passes in one launch: key << 13 | id per entry, 7 bits a pass.  8 heads of
+// 6001 entries 13 us (all pairs 36, the four launches above 30); the density calls of 1000 to 8192 entries lost 4 to 35 us.
+constexpr int SMALL_MAX = 8192, SMALL_THREADS = 1024, SMALL_BITS = 7;
+
+template <int STEPS>
+__global__ __launch_bounds__(SMALL_THREADS) void rank_small_kernel(const int32_t* __restrict__ rho, int N, int passes, int32_t* __restrict__ queue) {
+    constexpr int WAVES = SMALL_THREADS / 64, BINS = 1 << SMALL_BITS;
+    __shared__ uint32_t list[STEPS * SMALL_THREADS], at[WAVES][BINS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t* rh = rho + (size_t)blockIdx.x * N;
+    const int p0 = wave * STEPS * 64 + lane;
+    uint32_t x[STEPS];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        const int i = p0 + s * 64;
+        x[s] = i < N ? (uint32_t)(N - rh[i]) << 13 | (uint32_t)i : 0u;
+    }
+    for (int pass = 0; pass < passes; ++pass) {
+#pragma unroll
+        for (int u = 0; u < BINS / 64; ++u) at[wave][u * 64 + lane] = 0u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint32_t place[STEPS];
+        int digit[STEPS];
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            digit[s] = (int)(x[s] >> (13 + pass * SMALL_BITS)) & (BINS - 1);
+            place[s] = rank_in_wave(digit[s], p0 + s * 64 < N, SMALL_BITS, at[wave]);
+        }
+        __syncthreads();
+        if (wave == 0) {                                      // two digits per lane: the waves' counts become their first places
+            uint32_t n[2][WAVES], sum[2] = {0u, 0u};
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    n[u][w] = at[w][2 * lane + u];
+                    sum[u] += n[u][w];
+                }
+            uint32_t total;
+            uint32_t p = waveops::wave_excl_scan(sum[0] + sum[1], &total);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) {
+                    at[w][2 * lane + u] = p;
+                    p += n[u][w];
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+            if (p0 + s * 64 < N) {
+                const uint32_t p = at[wave][digit[s]] + place[s];
+                if (p < (uint32_t)N) list[p] = x[s];                   // always holds
+            }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) x[s] = p0 + s * 64 < N ? list[p0 + s * 64] : 0u;
+    }
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s)
+        if (p0 + s * 64 < N) queue[(size_t)blockIdx.x * N + p0 + s * 64] = (int32_t)(x[s] & 8191u);
+}
+
 }  // namespace
 
 swarm_status launch_density(swarm_ctx* ctx, const int32_t* C, int H, int N, const int64_t* totals_in, double tau,
@@ -209,10 +394,46 @@ swarm_status launch_density(swarm_ctx* ctx, const int32_t* C, int H, int N, cons
     return launch_medoid_rank(ctx, rho, H, N, queue);
 }
 
+// Scratch of the sort: a list of ids and, per workgroup, the digits' counts.
+static size_t rank_scratch_words(int H, int N) {
+    return (size_t)H * N + (((size_t)H * ((N + SORT_BLOCK - 1) / SORT_BLOCK)) << SORT_BITS);
+}
+
 swarm_status launch_medoid_rank(swarm_ctx* ctx, const int32_t* rho, int H, int N, int32_t* queue) {
-    hipLaunchKernelGGL(medoid_rank_kernel, dim3((unsigned)((N + RANK_ENTRIES - 1) / RANK_ENTRIES), (unsigned)H),
-                       dim3(RANK_ENTRIES * RANK_PARTS), 0, ctx->stream, rho, N, queue);
-    return swarm_check_launch(ctx, "medoid_rank_kernel");
+    int width = 1;                                            // bits of the largest key, N
+    while (N >> width) ++width;
+    if (N <= SMALL_MAX) {
+        const int passes = (width + SMALL_BITS - 1) / SMALL_BITS;
+        using kernel_t = void (*)(const int32_t*, int, int, int32_t*);
+        const kernel_t kernel = N <= SMALL_THREADS ? rank_small_kernel<1> : N <= 2 * SMALL_THREADS ? rank_small_kernel<2>
+                              : N <= 4 * SMALL_THREADS ? rank_small_kernel<4> : rank_small_kernel<8>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)H), dim3(SMALL_THREADS), 0, ctx->stream, rho, N, passes, queue);
+        return swarm_check_launch(ctx, "rank_small_kernel");
+    }
+    const size_t words = rank_scratch_words(H, N);
+    bool sorted = !ctx->capturing || ctx->rank_bytes >= words * 4;      // a recording without the room compares, as does a device without it
+    if (sorted) {
+        const swarm_status st = swarm_grow(ctx, reinterpret_cast<void**>(&ctx->rank), &ctx->rank_bytes, words * 4);
+        if (st == SWARM_ENOMEM) sorted = false;
+        else if (st != SWARM_OK) return st;
+    }
+    if (!sorted) {
+        hipLaunchKernelGGL(medoid_rank_kernel, dim3((unsigned)((N + RANK_ENTRIES - 1) / RANK_ENTRIES), (unsigned)H),
+                           dim3(RANK_ENTRIES * RANK_PARTS), 0, ctx->stream, rho, N, queue);
+        return swarm_check_launch(ctx, "medoid_rank_kernel");
+    }
+    int32_t* ids = ctx->rank;
+    uint32_t* counts = reinterpret_cast<uint32_t*>(ctx->rank + (size_t)H * N);
+    const int passes = (width + SORT_BITS - 1) / SORT_BITS, bits = (width + passes - 1) / passes;
+    const dim3 grid((unsigned)((N + SORT_BLOCK - 1) / SORT_BLOCK), (unsigned)H);
+    const int32_t* src = nullptr;
+    for (int p = 0; p < passes; ++p) {
+        int32_t* dst = (passes - 1 - p) % 2 ? ids : queue;    // the last pass writes the queue
+        hipLaunchKernelGGL(rank_count_kernel, grid, dim3(SORT_THREADS), 0, ctx->stream, rho, src, N, p * bits, bits, counts);
+        hipLaunchKernelGGL(rank_move_kernel, grid, dim3(SORT_THREADS), 0, ctx->stream, rho, src, N, p * bits, bits, counts, dst);
+        src = dst;
+    }
+    return swarm_check_launch(ctx, "rank_move_kernel");
 }
 
 swarm_status launch_trace_totals_thresholds(swarm_ctx* ctx, const int32_t* row_count, int slabs, int H, int nrows, double tau, uint32_t flags,
