@@ -28,11 +28,10 @@ typedef int v4i_row __attribute__((ext_vector_type(4), aligned(4)));   // rows o
 constexpr int MAX_SEGMENTS = 8;       // one per XCD
 constexpr int MAX_SEGMENT = 8192;     // columns of a segment: 32 KiB of counters
 constexpr int BLOCK = 64;             // columns dealt to the segments together
-constexpr int LIST_WAVES = 4;
 constexpr int LIST_MAX_K = 1024;      // N / 64
 constexpr int DUMMY_WORDS = 32;       // counters behind a segment's, taken by padding
 constexpr int RT = 512;               // threads of a counting workgroup; with 256 the same within 2 %
-constexpr int T_CAP = 512;            // trace rows listed at a time
+constexpr int T_CAP = 1024;           // trace rows listed at a time
 constexpr uint32_t MORE = 0xffffu;    // last slot of a record: the piece goes on in the overflow
 
 __host__ __device__ __forceinline__ int seg_columns(int N, int nseg) { return (N + nseg * BLOCK - 1) / (nseg * BLOCK) * BLOCK; }
@@ -41,87 +40,81 @@ __host__ __device__ __forceinline__ int seg_columns(int N, int nseg) { return (N
 // groups of eight, and the rest in the overflow.  Slot p of a record is element p / L of group p % L, so that the lanes of a
 // wave, a group each, meet neighbouring ids together (a run of entries then falls on distinct LDS banks).  One wave per
 // selection: 30 us for 8192 of 1024.
-__global__ __launch_bounds__(64 * LIST_WAVES) void list_build_kernel(const int32_t* __restrict__ idx, int64_t rows, int recs, int H, int k, int N, int nseg_log2,
-                                                                     int L, int ext_groups, uint4* __restrict__ lists, uint4* __restrict__ ext,
-                                                                     uint32_t* __restrict__ meta) {
-    __shared__ uint16_t el_all[LIST_WAVES][LIST_MAX_K];
-    __shared__ uint32_t piece_all[LIST_WAVES][MAX_SEGMENTS], more_all[LIST_WAVES][MAX_SEGMENTS];
-    extern __shared__ uint32_t seen_all[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t r = (int64_t)blockIdx.x * LIST_WAVES + wave;          // row * H + head, as the selections lie in memory
-    if (r >= rows * H) return;
+__global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restrict__ idx, int64_t rows, int recs, int H, int k, int N, int nseg_log2,
+                                                        int L, int ext_groups, uint4* __restrict__ lists, uint4* __restrict__ ext,
+                                                        uint32_t* __restrict__ meta) {
+    constexpr int PER = LIST_MAX_K / 64;
+    __shared__ uint32_t piece[MAX_SEGMENTS];
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
+    const int lane = threadIdx.x;
+    const int64_t r = blockIdx.x;                                       // row * H + head, as the selections lie in memory
     const int h = (int)(r % H);
     const int64_t row = r / H, t = (row & ~31ll) | trace_bit((int)(row & 31));       // records lie in the order of the trace's bits
+    const int nseg = 1 << nseg_log2, cols = seg_columns(N, nseg);
     const int32_t* sel = idx + r * k;
-    const int nseg = 1 << nseg_log2;
-    const int cols = seg_columns(N, nseg);
-    uint16_t* el = el_all[wave];
-    uint32_t *piece = piece_all[wave], *more = more_all[wave];
+    uint4* rec4 = reinterpret_cast<uint4*>(dyn);                        // the records, segment after segment
+    uint16_t* rec = reinterpret_cast<uint16_t*>(dyn);
+    uint32_t* seen = dyn + (L * 4 << nseg_log2);                        // N bits
+    int32_t e[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) e[u] = u * 64 + lane < k ? sel[u * 64 + lane] : N;
     if (lane < MAX_SEGMENTS) piece[lane] = 0u;
-    bool fine = true;
-    for (int p0 = 0; p0 < k; p0 += 64) {
-        const int p = p0 + lane;
-        if (p < k) {
-            const int32_t e = sel[p];
-            fine &= (uint32_t)e < (uint32_t)N && (p == 0 || sel[p - 1] < e);
-        }
+    for (int g = lane; g < L << nseg_log2; g += 64) {                   // padding everywhere, a bank of its own for every lane that meets it
+        const uint32_t d = (uint32_t)(cols + (g & (DUMMY_WORDS - 1))) * 4 * 0x10001u;
+        rec4[g] = make_uint4(d, d, d, d);
     }
-    int n = k;
-    auto seg_of = [&](uint32_t e) __attribute__((always_inline)) { return (e / BLOCK) & (nseg - 1); };
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (__ballot(!fine) == 0) {
-        for (int p = lane; p < k; p += 64) {
-            const int32_t e = sel[p];
-            el[p] = (uint16_t)e;
-            atomicAdd(&piece[seg_of(e)], 1u);
-        }
-    } else {
-        // repeated, unsorted or invalid ids: the distinct valid ones through a bitmap of the wave's own
-        uint32_t* seen = seen_all + wave * ((N + 31) / 32);
+    bool fine = true;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        int32_t prev = __shfl_up(e[u], 1, 64);
+        if (lane == 0) prev = u ? __builtin_amdgcn_readlane(e[u ? u - 1 : 0], 63) : -1;
+        if (u * 64 + lane < k) fine &= (uint32_t)e[u] < (uint32_t)N && prev < e[u];
+        else e[u] = -1;
+    }
+    if (__ballot(!fine) != 0) {                                         // repeated, unsorted or invalid ids: the distinct valid ones stay
         for (int w = lane; w < (N + 31) / 32; w += 64) seen[w] = 0u;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        n = 0;
-        for (int p0 = 0; p0 < k; p0 += 64) {
-            const int p = p0 + lane;
-            const int32_t e = p < k ? sel[p] : -1;
-            bool fresh = false;
-            if ((uint32_t)e < (uint32_t)N) fresh = !(atomicOr(&seen[e >> 5], 1u << (e & 31)) >> (e & 31) & 1u);
-            const uint64_t b = __ballot(fresh);
-            if (fresh) {
-                el[n + __popcll(b & ((1ull << lane) - 1ull))] = (uint16_t)e;
-                atomicAdd(&piece[seg_of(e)], 1u);
-            }
-            n += __popcll(b);
-        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if ((uint32_t)e[u] >= (uint32_t)N || (atomicOr(&seen[e[u] >> 5], 1u << (e[u] & 31)) >> (e[u] & 31)) & 1u) e[u] = -1;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const uint32_t slots = 8u * L, cap = nseg > 1 ? slots - 1 : slots;
-    const uint32_t cnt = lane < nseg ? piece[lane] : 0u;
-    const uint32_t ng = cnt > cap ? (cnt - cap + 7) / 8 : 0u;
-    uint32_t total;
-    const uint32_t off = waveops::wave_excl_scan(ng, &total);
-    const size_t seg_stride = (size_t)recs * L;
-    uint16_t* out = reinterpret_cast<uint16_t*>(lists + ((size_t)h * nseg * recs + t) * L);
-    uint16_t* eout = reinterpret_cast<uint16_t*>(ext + ((size_t)h * recs + t) * ext_groups);
-    if (lane < nseg) {
-        more[lane] = off * 8;
-        piece[lane] = 0u;
-        if (ng) meta[((size_t)h * nseg + lane) * recs + t] = off | ng << 16;
-        for (uint32_t p = cnt > cap ? cnt - cap : 0u; p < ng * 8; ++p) eout[off * 8 + p] = (uint16_t)((cols + (lane & (DUMMY_WORDS - 1))) * 4);
-    }
-    // padding of the records, and the mark of those that go on
-    for (int s = 0; s < nseg; ++s) {
-        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cnt, s);
-        for (uint32_t p = min(c, cap) + lane; p < slots; p += 64) {
-            out[s * seg_stride * 8 + (p % L) * 8 + p / L] = (uint16_t)(p >= cap && c > cap ? MORE : (cols + (p & (DUMMY_WORDS - 1))) * 4);
+    const uint32_t inv = (65536u + L - 1) / L;                          // p / L for p < 1024
+    auto slot = [&](uint32_t s, uint32_t p) __attribute__((always_inline)) { const uint32_t q = p * inv >> 16; return s * slots + (p - q * L) * 8 + q; };
+    auto seg_of = [&](int32_t x) __attribute__((always_inline)) { return (uint32_t)(x / BLOCK) & (uint32_t)(nseg - 1); };
+    auto counter_of = [&](int32_t x) __attribute__((always_inline)) { return (uint16_t)((((x / BLOCK) >> nseg_log2) * BLOCK + (x & (BLOCK - 1))) * 4); };
+    uint32_t place[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        place[u] = 0;
+        if (e[u] >= 0) {
+            place[u] = atomicAdd(&piece[seg_of(e[u])], 1u);
+            if (place[u] < cap) rec[slot(seg_of(e[u]), place[u])] = counter_of(e[u]);
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    for (int i = lane; i < n; i += 64) {
-        const uint32_t e = el[i], s = seg_of(e), c = ((e / BLOCK) >> nseg_log2) * BLOCK + (e & (BLOCK - 1));
-        const uint32_t p = atomicAdd(&piece[s], 1u);
-        if (p < cap) out[s * seg_stride * 8 + (p % L) * 8 + p / L] = (uint16_t)(c * 4);
-        else eout[more[s] + p - cap] = (uint16_t)(c * 4);
+    const uint32_t cnt = lane < nseg ? piece[lane] : 0u;
+    if (__ballot(cnt > cap) != 0) {                                     // pieces that go on in the overflow, in whole groups
+        const uint32_t ng = cnt > cap ? (cnt - cap + 7) / 8 : 0u;
+        uint32_t total;
+        const uint32_t off = waveops::wave_excl_scan(ng, &total);
+        uint16_t* out = reinterpret_cast<uint16_t*>(ext + ((size_t)h * recs + t) * ext_groups);
+        if (ng) {
+            rec[slot(lane, slots - 1)] = (uint16_t)MORE;
+            meta[((size_t)h * nseg + lane) * recs + t] = off | ng << 16;
+            for (uint32_t p = cnt - cap; p < ng * 8; ++p) out[off * 8 + p] = (uint16_t)((cols + (lane & (DUMMY_WORDS - 1))) * 4);
+            piece[lane] = off * 8;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (e[u] >= 0 && place[u] >= cap) out[piece[seg_of(e[u])] + place[u] - cap] = counter_of(e[u]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int g = lane; g < L << nseg_log2; g += 64) {
+        const int s = g / L;
+        lists[(((size_t)h * nseg + s) * recs + t) * L + (g - s * L)] = rec4[g];
     }
 }
 
@@ -204,14 +197,14 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
         const Place after = ahead;
         advance(ahead);
         next = load_word(ahead);
-        const int parts_of = n <= T_CAP ? 1 : RT / 16;        // too many for the list: the words sixteen at a time
+        const int parts_of = n <= T_CAP ? 1 : RT / 32;        // too many for the list: the words 32 at a time
         for (int s = 0; s < parts_of; ++s) {
             uint32_t m = n;
             if (parts_of > 1) {
                 __syncthreads();
                 if (tid == 0) tcount[buf] = 0;
                 __syncthreads();
-                if ((tid >> 4) == s) list_rows(word_now, at.chunk, buf);
+                if ((tid >> 5) == s) list_rows(word_now, at.chunk, buf);
                 __syncthreads();
                 m = (uint32_t)__builtin_amdgcn_readfirstlane((int)tcount[buf]);
             }
@@ -338,8 +331,8 @@ swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows,
     uint4* lists = static_cast<uint4*>(scratch);
     uint4* ext = lists + ((size_t)recs * H * p.L << p.nseg_log2);
     uint32_t* meta = reinterpret_cast<uint32_t*>(ext + (size_t)recs * H * p.ext_groups);
-    hipLaunchKernelGGL(list_build_kernel, dim3((unsigned)((rows * H + LIST_WAVES - 1) / LIST_WAVES)), dim3(64 * LIST_WAVES),
-                       (size_t)LIST_WAVES * ((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext, meta);
+    hipLaunchKernelGGL(list_build_kernel, dim3((unsigned)(rows * H)), dim3(64),
+                       ((size_t)p.L * 16 << p.nseg_log2) + (size_t)((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext, meta);
     swarm_status st = swarm_check_launch(ctx, "list_build_kernel");
     if (st != SWARM_OK) return st;
     const int lds = (seg_columns(N, 1 << p.nseg_log2) + DUMMY_WORDS) * 4 + 2 * T_CAP * 2;
