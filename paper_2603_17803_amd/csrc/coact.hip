@@ -202,10 +202,12 @@ __device__ __forceinline__ int lds_off(int row, int piece) { return row * KC + (
 // give those of the direct tile's rows; a diagonal tile is computed in full, and by
 // symmetry its column counts are its row counts.  Counts meet in LDS and leave as one
 // atomic add per row and tile.
-// STREAM (MODE 0): C leaves in streaming stores, past the caches.
+// FORM: STREAM (MODE 0) lets C leave in streaming stores, past the caches; STAGGER makes the workgroups of a compute unit finish
+// one after the other.  launch_coact_syrk says when.
+enum { PLAIN, STREAM, STAGGER };
 typedef __attribute__((address_space(3))) void lds_void;
 
-template <int MODE, bool RHO = false, bool STREAM = false>
+template <int MODE, bool RHO = false, int FORM = PLAIN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns, int32_t* __restrict__ C, uint32_t decay_q16,
                        int tiles_per_head, int total_tiles, int per_xcd, const int32_t* __restrict__ tile_order,
@@ -357,7 +359,18 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
 #pragma unroll
         for (int j = 0; j < 2; ++j) expand_b(nset, 0, j);
     };
-    __builtin_amdgcn_s_setprio(2);                          // the contraction outranks the other waves' epilogue stores
+    // The contraction outranks the other waves' epilogue stores.  STAGGER: of the workgroups that share a compute unit (an XCD's
+    // workgroups are dealt to its 32 compute units in turn) each outranks the later ones.
+    if constexpr (FORM == STAGGER) {
+        switch ((slot_id >> 5) & 3) {
+            case 0: __builtin_amdgcn_s_setprio(3); break;
+            case 1: __builtin_amdgcn_s_setprio(2); break;
+            case 2: __builtin_amdgcn_s_setprio(1); break;
+            default: __builtin_amdgcn_s_setprio(0);
+        }
+    } else {
+        __builtin_amdgcn_s_setprio(2);
+    }
     for (int d = 0; d < nruns; d += 2) {                    // nruns is a multiple of 4
         chunk_body(d, 0);
         chunk_body(d + 1, 1);
@@ -417,7 +430,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
         return updated_count<MODE == 0 ? 1 : MODE>(old, v, decay_q16, ovf);
     };
     auto put = [](int32_t v, int32_t* p) __attribute__((always_inline)) {
-        if (STREAM) __builtin_nontemporal_store(v, p);
+        if (FORM == STREAM) __builtin_nontemporal_store(v, p);
         else *p = v;
     };
     // four consecutive counts of a row, `cols` of them inside C (four unless the tile reaches past N)
@@ -427,7 +440,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     };
     auto store_row = [](int32_t* p, v4i w, int cols) __attribute__((always_inline)) {
         if (cols >= 4) {
-            if (STREAM) __builtin_nontemporal_store((v4i_row)w, reinterpret_cast<v4i_row*>(p));
+            if (FORM == STREAM) __builtin_nontemporal_store((v4i_row)w, reinterpret_cast<v4i_row*>(p));
             else *reinterpret_cast<v4i_row*>(p) = w;
         } else {
             p[0] = w.x;
@@ -743,18 +756,17 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     }
     using kernel_t = void (*)(const v4i*, int, int, int, int32_t*, uint32_t, int, int, int, const int32_t*, uint32_t*,
                               const int64_t*, int32_t*);
-    static const kernel_t kernels[2][3] = {{coact_syrk_kernel<0>, coact_syrk_kernel<1>, coact_syrk_kernel<2>},
-                                           {coact_syrk_kernel<0, false, true>, coact_syrk_kernel<1>, coact_syrk_kernel<2>}};
-    static const kernel_t fused_kernels[2] = {coact_syrk_kernel<0, true>, coact_syrk_kernel<0, true, true>};
+    static const kernel_t kernels[3][4] = {
+        {coact_syrk_kernel<0>, coact_syrk_kernel<1>, coact_syrk_kernel<2>, coact_syrk_kernel<0, true>},
+        {coact_syrk_kernel<0, false, STREAM>, coact_syrk_kernel<1>, coact_syrk_kernel<2>, coact_syrk_kernel<0, true, STREAM>},
+        {coact_syrk_kernel<0, false, STAGGER>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>, coact_syrk_kernel<0, true, STAGGER>}};
     constexpr int RHO_LDS_BYTES = SYRK_LDS_BYTES + (TM + TN) * 4;
     if (!ctx->syrk_lds_opt_in) {
         hipError_t e = hipSuccess;
-        for (int t = 0; t < 2; ++t) {
-            if (e == hipSuccess)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_kernels[t]), hipFuncAttributeMaxDynamicSharedMemorySize, RHO_LDS_BYTES);
-            for (int m = 0; m < 3 && e == hipSuccess; ++m)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[t][m]), hipFuncAttributeMaxDynamicSharedMemorySize, SYRK_LDS_BYTES);
-        }
+        for (int f = 0; f < 3; ++f)
+            for (int m = 0; m < 4 && e == hipSuccess; ++m)
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[f][m]), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        m == 3 ? RHO_LDS_BYTES : SYRK_LDS_BYTES);
         if (e != hipSuccess) {
             snprintf(ctx->err, sizeof(ctx->err), "coact: cannot opt in to %d bytes of LDS: %s", RHO_LDS_BYTES, hipGetErrorString(e));
             return SWARM_EHIP;
@@ -766,10 +778,16 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     // tiles, and streamed, each of the two writes it to memory by itself: 4 x 4001^2, 256 rows 124 us streamed, 51 cached, 4096 rows
     // 137 and 75; 12289^2 291 and 197, 300 and 222; 12304^2 154 and 157.  A C that fits the 256 MiB last-level cache is written there:
     // 8 x 2048^2 33 us streamed, 28 cached, 4 x 4096^2 57 and 48 (4096 rows: 74.5 and 73).
-    const int stream = N % 16 == 0 && (int64_t)H * N * N > (int64_t)1 << 26;
+    const bool stream = N % 16 == 0 && (int64_t)H * N * N > (int64_t)1 << 26;
+    // A little more than the 1024 tiles that the device holds at once: all of those contract together, then all write, and the rest
+    // runs nearly alone.  One after the other, the first ones' writing and the rest's start overlap the others' contraction: 16384
+    // rows of 8 x 2048 (1088 tiles) 126 -> 114 us without the trace, of 1 x 6000 (1128) 142 -> 130 with it, of 8 x 2304 (1368)
+    // 170 -> 167.  Nothing below (1012 tiles 101.2 -> 101.7), and past 1.4 rounds it is in the way (1680 tiles 213 -> 226).
+    const bool stagger = total > 1024 && total <= 1408;       // never with a C that streams: 1408 tiles hold less than that
+    const int form = stagger ? STAGGER : stream ? STREAM : PLAIN;
     dim3 grid((unsigned)(per_xcd * 8)), block(64 * SYRK_WAVES);
     const int tph = (int)tiles_per_head, tot = (int)total;
-    hipLaunchKernelGGL(fused ? fused_kernels[stream] : kernels[stream][mode], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
+    hipLaunchKernelGGL(kernels[form][fused ? 3 : mode], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
                        ctx->stream, reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, tph, tot, per_xcd,
                        tile_order, ctx->dev_flags, cstar, rho);
     return swarm_check_launch(ctx, "coact_syrk_kernel");

@@ -102,3 +102,24 @@ def test_recordings_take_the_way_that_has_its_room(first):
         assert torch.equal(C, ref)
     binding.swarm_graph_destroy(graph)
     sw.close()
+
+
+# 1088, 1128 (ragged rows of C) and 1368 tiles, where the dense product's workgroups finish one after the other; 1024 and 1410 around them
+@pytest.mark.parametrize("rows,H,k,N", [(130, 8, 60, 2048), (70, 1, 200, 6001), (300, 8, 100, 2304), (40, 64, 9, 512), (40, 141, 9, 512)])
+def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N):
+    sel = selections("any", rows, H, k, N).clamp_(0, N - 1)
+    with torch.cuda.stream(sw.stream):
+        sw.stream.wait_stream(torch.cuda.default_stream())
+        C = torch.randint(0, 1 << 20, (H, N, N), dtype=torch.int32, device="cuda")
+        ref = C.clone()
+        for decay in (65536, 64881, 0):
+            sw.coact_accumulate(sel, N, C, decay_q16=decay)
+            sw.coact_accumulate(sel, N, ref, decay_q16=decay, flags=POPCOUNT)
+            assert torch.equal(C, ref)
+        C.fill_(-7)
+        rho, queue, totals = sw.coact_build_density(sel, N, C, 1.0 - 3.0 / (rows * k * k))
+        assert torch.equal(C, ref)
+        for got, want in zip((rho, queue, totals), sw.coact_density(ref, 1.0 - 3.0 / (rows * k * k))):
+            assert torch.equal(got, want)
+    sw.stream.synchronize()
+    assert sw.device_status() == 0
