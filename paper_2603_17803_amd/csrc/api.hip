@@ -98,6 +98,7 @@ swarm_status swarm_destroy(swarm_ctx* ctx) {
     if (ctx->totals) (void)hipFree(ctx->totals);
     if (ctx->lists) (void)hipFree(ctx->lists);
     if (ctx->rank) (void)hipFree(ctx->rank);
+    if (ctx->part) (void)hipFree(ctx->part);
     for (auto& t : ctx->tile_orders) (void)hipFree(t.second);
     for (void* p : ctx->retired) (void)hipFree(p);
     if (ctx->dev_flags) (void)hipFree(ctx->dev_flags);

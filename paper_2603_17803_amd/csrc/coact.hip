@@ -25,6 +25,7 @@ typedef int v4i_row __attribute__((ext_vector_type(4), aligned(4)));   // four c
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int TRACE_SPAN = 8192;   // entries one trace-building workgroup covers at most (128 KiB of LDS)
 constexpr int TRACE_SPAN_MIN = 512;
@@ -204,26 +205,31 @@ __device__ __forceinline__ int lds_off(int row, int piece) { return row * KC + (
 // atomic add per row and tile.
 // FORM: STREAM (MODE 0) lets C leave in streaming stores, past the caches; STAGGER makes the workgroups of a compute unit finish
 // one after the other.  launch_coact_syrk says when.
-enum { PLAIN, STREAM, STAGGER };
+// PART contracts one piece of the trace rows and leaves the tile's partial counts in `part`; FINISH adds a tile's pieces up in place
+// of the contraction, a workgroup per wave of the other forms.
+enum { PLAIN, STREAM, STAGGER, PART, FINISH };
 typedef __attribute__((address_space(3))) void lds_void;
 
 template <int MODE, bool RHO = false, int FORM = PLAIN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns, int32_t* __restrict__ C, uint32_t decay_q16,
                        int tiles_per_head, int total_tiles, int per_xcd, const int32_t* __restrict__ tile_order,
-                       uint32_t* __restrict__ dev_flags, const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
+                       uint32_t* __restrict__ dev_flags, const int64_t* __restrict__ cstar, int32_t* __restrict__ rho,
+                       v4f* __restrict__ part, int pieces, int piece_runs) {
     static_assert(!RHO || MODE == 0, "the fused density count belongs to the overwriting form");
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;
-    const int t = xcd * per_xcd + slot_id;
-    if (slot_id >= per_xcd || t >= total_tiles) return;
+    // PART: the pieces of a tile one after the other, and per_xcd, total_tiles counts of pieces
+    const int unit = FORM == FINISH ? blockIdx.x >> 2 : xcd * per_xcd + slot_id;
+    if (FORM != FINISH && (slot_id >= per_xcd || unit >= total_tiles)) return;
+    const int t = FORM == PART ? unit / pieces : unit;
     const int h = t / tiles_per_head;
     const int32_t packed = tile_order[t - h * tiles_per_head];
     const int ti = packed >> 16, tj = packed & 0xffff;       // tile row, tile column (tj >= ti)
     const bool diag = tj == ti;                              // a diagonal tile is computed in full: no mirror
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = FORM == FINISH ? (int)blockIdx.x & 3 : __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wy = wave >> 1, wx = wave & 1;
     const int frow = lane & 31, fhalf = lane >> 5;
 
@@ -231,9 +237,11 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     // LDS in the same order: waves 0 and 1 bring rows [64 w, +64) of the tile, waves 2 and 3 columns [64 (w - 2), +64); lane l
     // of a load carries 16 bytes to byte 16 l of the wave's KiB.  One buffer descriptor per run (its range is the run:
     // 16 Npad bytes), so an offset past the run would read zeros, not memory.
-    const char* panel = reinterpret_cast<const char*>(bits) + (size_t)h * nruns * Npad * 16;
+    const int first_run = FORM == PART ? (unit - t * pieces) * piece_runs : 0;
+    const int runs = FORM == PART ? min(piece_runs, nruns - first_run) : nruns;        // even
+    const char* panel = reinterpret_cast<const char*>(bits) + ((size_t)h * nruns + first_run) * Npad * 16;
     const uint32_t src_lane = (uint32_t)(((wave < 2 ? ti * TM + wave * 64 : tj * TN + (wave - 2) * 64) + lane) * 16);
-    const int last_run = nruns - 1;
+    const int last_run = runs - 1;
     auto issue_load = [&](int run) __attribute__((always_inline)) {                   // clamped: a redundant reload past the end is harmless
         {
             const char* runp = panel + (size_t)min(run, last_run) * Npad * 16;
@@ -306,6 +314,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
         facc[m >> 1][m & 1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, facc[m >> 1][m & 1], 4, 4, 0, 0, 0, 0);
     };
 
+    if constexpr (FORM != FINISH) {
     // start-up: chunks 0 .. RAW_DEPTH-1 on their way; chunk 0 expanded; chunk RAW_DEPTH into the slot of chunk 0
 #pragma unroll
     for (int c = 0; c < RAW_DEPTH; ++c) issue_load(c);
@@ -371,7 +380,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     } else {
         __builtin_amdgcn_s_setprio(2);
     }
-    for (int d = 0; d < nruns; d += 2) {                    // nruns is a multiple of 4
+    for (int d = 0; d < runs; d += 2) {                     // nruns is a multiple of 4
         chunk_body(d, 0);
         chunk_body(d + 1, 1);
     }
@@ -380,6 +389,34 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     __syncthreads();
 
     __builtin_amdgcn_s_setprio(0);
+    }
+    if constexpr (FORM == PART) {
+        v4f* out = part + ((size_t)unit * SYRK_WAVES + wave) * (16 * 64) + lane;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    out[((i * 2 + j) * 4 + q) * 64] = v4f{facc[i][j][4 * q], facc[i][j][4 * q + 1], facc[i][j][4 * q + 2], facc[i][j][4 * q + 3]};
+        return;
+    }
+    if constexpr (FORM == FINISH) {
+        // sums of integers up to 2^24: exact in any order
+        for (int p = 0; p < pieces; ++p) {
+            const v4f* in = part + (((size_t)t * pieces + p) * SYRK_WAVES + wave) * (16 * 64) + lane;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const v4f v = in[((i * 2 + j) * 4 + q) * 64];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) facc[i][j][4 * q + r] += v[r];
+                    }
+        }
+    }
     // 32x32 result layout: lane l, register r -> column l%32, row 8*(r/4) + 4*(l/32) + r%4.  One
     // register of a wave is therefore two whole 128-byte lines of the direct tile (32 consecutive
     // columns of two rows): the direct tile leaves straight from the accumulators in 4-byte stores,
@@ -396,7 +433,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
             for (int r = 0; r < 16; ++r) acc[i][j][r] = (int32_t)facc[i][j][r];
     int32_t* Ch = C + (size_t)h * N * N;
     const int col_in = lane & 31, half = lane >> 5, row_in = half * 4;
-    int8_t* tbuf = lds + wave * (32 * TROW);
+    int8_t* tbuf = lds + (FORM == FINISH ? 0 : wave * (32 * TROW));
     const int gi_base = ti * TM + wy * 64;
     const int mrow = lane >> 4, c16 = lane & 15;             // mirrored tile: a store covers 4 rows of 64 columns, 16 bytes per lane
     // Addresses are a wave-uniform row pointer (scalar arithmetic) plus one per-lane element offset
@@ -409,14 +446,13 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
         return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(base) + byte_off);
     };
     // density counters behind everything else in LDS: 128 direct-tile rows, then 128 direct-tile columns
-    uint32_t* cnt_row = reinterpret_cast<uint32_t*>(lds + SYRK_LDS_BYTES);
+    uint32_t* cnt_row = reinterpret_cast<uint32_t*>(lds + (FORM == FINISH ? 32 * TROW : SYRK_LDS_BYTES));
     uint32_t* cnt_col = cnt_row + TM;
     int32_t c32 = 0x7fffffff;                              // counts never reach it (rows <= 2^24): "nothing is within the radius"
     if (RHO) {
         const int64_t c = cstar[h];
         if (c < 0x7fffffffll) c32 = (int32_t)c;
-        if (threadIdx.x < TM) cnt_row[threadIdx.x] = 0u;
-        else if (threadIdx.x < TM + TN) cnt_col[threadIdx.x - TM] = 0u;
+        for (int u = threadIdx.x; u < TM + TN; u += FORM == FINISH ? 64 : 256) cnt_row[u] = 0u;       // the columns' lie behind the rows'
         __syncthreads();                                   // the waves' counts meet in these counters
     }
     // 1 where v >= c32, 0 elsewhere, without a compare: counts lie in [0, 2^24] and c32 in [0, 2^31), so
@@ -545,9 +581,10 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
         }
         __syncthreads();
         int32_t* rh = rho + (size_t)h * N;
-        const int u = threadIdx.x;
-        if (!diag && u < TM && ti * TM + u < N && cnt_row[u]) atomicAdd(rh + ti * TM + u, (int32_t)cnt_row[u]);
-        if (u >= TM && u < TM + TN && tj * TN + u - TM < N && cnt_col[u - TM]) atomicAdd(rh + tj * TN + u - TM, (int32_t)cnt_col[u - TM]);
+        for (int u = threadIdx.x; u < TM + TN; u += FORM == FINISH ? 64 : 256) {
+            if (!diag && u < TM && ti * TM + u < N && cnt_row[u]) atomicAdd(rh + ti * TM + u, (int32_t)cnt_row[u]);
+            if (u >= TM && tj * TN + u - TM < N && cnt_col[u - TM]) atomicAdd(rh + tj * TN + u - TM, (int32_t)cnt_col[u - TM]);
+        }
     }
 }
 
@@ -727,6 +764,21 @@ static swarm_status tile_order_for(swarm_ctx* ctx, int ntm, const int32_t** out)
     return st;
 }
 
+// Whether the trace rows are contracted in pieces: so many that they fill the device, of 24 runs or more (8 to 32 measured alike),
+// and only where the rows saved outweigh the partial counts (64 KiB a piece, written and read) and the second launch.  Both ways,
+// decayed updates: 36 tiles, 4096 rows 20.2 us whole, 20.7 in pieces, 8192 30.6 and 26.0, 16384 51.7 and 30.2; 136 tiles, 8192 rows
+// 34 and 33 (overwriting 30 and 35), 12000 45 and 37, 16384 55 and 39; 300 tiles, 12000 rows 65 and 66, 16384 75.7 and 71.7, 33000
+// 130 and 103.
+static bool split_rows(int64_t total, int nruns, int* pieces, int* piece_runs) {
+    constexpr int MIN_RUNS = 24;
+    if (total + 32 > 2 * (int64_t)nruns) return false;
+    const int64_t fill = 1024 / total, most = fill < nruns / MIN_RUNS ? fill : nruns / MIN_RUNS;
+    if (most < 2) return false;
+    *piece_runs = (int)((nruns + 2 * most - 1) / (2 * most)) * 2;         // even
+    *pieces = (nruns + *piece_runs - 1) / *piece_runs;                    // none of them empty
+    return *pieces > 1;
+}
+
 swarm_status coact_reserve_tiles(swarm_ctx* ctx, int Npad) {
     if (ctx->capturing || Npad / TM > 65535) return SWARM_OK;
     const int32_t* order;
@@ -755,11 +807,13 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
         return SWARM_EINVAL;
     }
     using kernel_t = void (*)(const v4i*, int, int, int, int32_t*, uint32_t, int, int, int, const int32_t*, uint32_t*,
-                              const int64_t*, int32_t*);
-    static const kernel_t kernels[3][4] = {
+                              const int64_t*, int32_t*, v4f*, int, int);
+    static const kernel_t kernels[4][4] = {
         {coact_syrk_kernel<0>, coact_syrk_kernel<1>, coact_syrk_kernel<2>, coact_syrk_kernel<0, true>},
         {coact_syrk_kernel<0, false, STREAM>, coact_syrk_kernel<1>, coact_syrk_kernel<2>, coact_syrk_kernel<0, true, STREAM>},
-        {coact_syrk_kernel<0, false, STAGGER>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>, coact_syrk_kernel<0, true, STAGGER>}};
+        {coact_syrk_kernel<0, false, STAGGER>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>, coact_syrk_kernel<0, true, STAGGER>},
+        {coact_syrk_kernel<0, false, FINISH>, coact_syrk_kernel<1, false, FINISH>, coact_syrk_kernel<2, false, FINISH>, coact_syrk_kernel<0, true, FINISH>}};
+    static const kernel_t part_kernel = coact_syrk_kernel<0, false, PART>;
     constexpr int RHO_LDS_BYTES = SYRK_LDS_BYTES + (TM + TN) * 4;
     if (!ctx->syrk_lds_opt_in) {
         hipError_t e = hipSuccess;
@@ -767,6 +821,8 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
             for (int m = 0; m < 4 && e == hipSuccess; ++m)
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[f][m]), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         m == 3 ? RHO_LDS_BYTES : SYRK_LDS_BYTES);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(part_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, SYRK_LDS_BYTES);
         if (e != hipSuccess) {
             snprintf(ctx->err, sizeof(ctx->err), "coact: cannot opt in to %d bytes of LDS: %s", RHO_LDS_BYTES, hipGetErrorString(e));
             return SWARM_EHIP;
@@ -785,11 +841,33 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     // 170 -> 167.  Nothing below (1012 tiles 101.2 -> 101.7), and past 1.4 rounds it is in the way (1680 tiles 213 -> 226).
     const bool stagger = total > 1024 && total <= 1408;       // never with a C that streams: 1408 tiles hold less than that
     const int form = stagger ? STAGGER : stream ? STREAM : PLAIN;
+    // Few tiles over many trace rows leave most of the device idle: the rows are cut into pieces.
+    int pieces = 1, piece_runs = nruns;
+    if (split_rows(total, nruns, &pieces, &piece_runs)) {
+        const size_t bytes = (size_t)total * pieces * (TM * TN * sizeof(float));
+        if (ctx->capturing && ctx->part_bytes < bytes) pieces = 1;      // a recording without the room goes without, as does a device without it
+        else {
+            st = swarm_grow(ctx, &ctx->part, &ctx->part_bytes, bytes);
+            if (st == SWARM_ENOMEM) pieces = 1;
+            else if (st != SWARM_OK) return st;
+        }
+    }
+    if (pieces > 1) {
+        const int units = (int)total * pieces, units_xcd = (units + 7) / 8;
+        v4f* part = static_cast<v4f*>(ctx->part);
+        hipLaunchKernelGGL(part_kernel, dim3((unsigned)(units_xcd * 8)), dim3(64 * SYRK_WAVES), SYRK_LDS_BYTES, ctx->stream,
+                           reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, (int)tiles_per_head, units, units_xcd, tile_order,
+                           ctx->dev_flags, nullptr, nullptr, part, pieces, piece_runs);
+        hipLaunchKernelGGL(kernels[3][fused ? 3 : mode], dim3((unsigned)(total * SYRK_WAVES)), dim3(64), 32 * TROW + (TM + TN) * 4, ctx->stream,
+                           reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, (int)tiles_per_head, (int)total, 0, tile_order,
+                           ctx->dev_flags, cstar, rho, part, pieces, piece_runs);
+        return swarm_check_launch(ctx, "coact_syrk_kernel (pieces)");
+    }
     dim3 grid((unsigned)(per_xcd * 8)), block(64 * SYRK_WAVES);
     const int tph = (int)tiles_per_head, tot = (int)total;
     hipLaunchKernelGGL(kernels[form][fused ? 3 : mode], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
                        ctx->stream, reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, tph, tot, per_xcd,
-                       tile_order, ctx->dev_flags, cstar, rho);
+                       tile_order, ctx->dev_flags, cstar, rho, nullptr, 1, nruns);
     return swarm_check_launch(ctx, "coact_syrk_kernel");
 }
 

@@ -35,6 +35,8 @@ struct swarm_ctx {
     size_t trace_bytes = 0;
     void* lists = nullptr;         // selections as records of ids (sparse traces, see coact_rows.hip)
     size_t lists_bytes = 0;
+    void* part = nullptr;          // partial counts of tiles whose trace rows are contracted in pieces
+    size_t part_bytes = 0;
     int32_t* rank = nullptr;       // ids and digit counts of the medoid queue's sort
     size_t rank_bytes = 0;
     int64_t* totals = nullptr;     // per-head grand totals of C when the caller keeps none

@@ -123,3 +123,52 @@ def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N):
             assert torch.equal(got, want)
     sw.stream.synchronize()
     assert sw.device_status() == 0
+
+
+# few tiles over many trace rows: contracted in pieces (the last one shorter), with the fewest rows, ragged rows of C, two heads, and
+# one run of rows below
+@pytest.mark.parametrize("rows,H,k,N", [(8192, 1, 40, 1000), (6144, 1, 40, 1024), (6100, 1, 40, 1024), (12300, 2, 30, 701), (33000, 1, 9, 260), (11000, 1, 60, 2048),
+                                        (21300, 1, 70, 3000)])
+def test_counts_of_few_tiles_in_pieces(sw, rows, H, k, N):
+    sel = selections("any", rows, H, k, N).clamp_(0, N - 1)
+    with torch.cuda.stream(sw.stream):
+        sw.stream.wait_stream(torch.cuda.default_stream())
+        C = torch.randint(0, 1 << 20, (H, N, N), dtype=torch.int32, device="cuda")
+        ref = C.clone()
+        for decay in (65536, 64881, 0):
+            sw.coact_accumulate(sel, N, C, decay_q16=decay)
+            sw.coact_accumulate(sel, N, ref, decay_q16=decay, flags=POPCOUNT)
+            assert torch.equal(C, ref)
+        C.fill_(-7)
+        tau = 1.0 - rows * k * k / float(N * N) / (rows * k * k)             # a pair of average count is near
+        rho, queue, totals = sw.coact_build_density(sel, N, C, tau)
+        assert torch.equal(C, ref)
+        for got, want in zip((rho, queue, totals), sw.coact_density(ref, tau)):
+            assert torch.equal(got, want)
+    sw.stream.synchronize()
+    assert sw.device_status() == 0
+
+
+def test_recorded_pieces_need_no_room():
+    """A recording that finds no room for partial counts contracts each tile whole."""
+    from paper_2603_17803_amd import binding
+    sw = binding.Swarm(0, stream=torch.cuda.Stream())
+    N, rows = 1024, 8192
+    sel = selections("spread", rows, 1, 32, N, 3)
+    C = torch.empty(1, N, N, dtype=torch.int32, device="cuda")
+    ref = torch.empty_like(C)
+    torch.cuda.synchronize()
+    sw.coact_accumulate(sel, N, ref, decay_q16=0, flags=POPCOUNT)            # the trace's room
+    sw.coact_accumulate(sel[:600].contiguous(), N, C, decay_q16=0)           # the tile schedule
+    sw.stream.synchronize()
+    sw.capture_begin()
+    sw.coact_accumulate(sel, N, C, decay_q16=0)
+    graph = sw.capture_end()
+    for _ in range(2):
+        C.fill_(-1)
+        torch.cuda.synchronize()
+        sw.graph_launch(graph)
+        sw.stream.synchronize()
+        assert torch.equal(C, ref)
+    binding.swarm_graph_destroy(graph)
+    sw.close()
