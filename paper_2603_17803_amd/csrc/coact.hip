@@ -829,17 +829,21 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
         }
         ctx->syrk_lds_opt_in = true;
     }
-    // A large C of whole 64-byte pieces streams: cached, its lines push the trace out of the L2 (8 x 8192^2, 4096 rows: 434 us
-    // streamed, 650 cached; 65536^2: 3.5 and 5.5 ms).  Rows of C that start inside a 64-byte piece share it with their neighbour
-    // tiles, and streamed, each of the two writes it to memory by itself: 4 x 4001^2, 256 rows 124 us streamed, 51 cached, 4096 rows
-    // 137 and 75; 12289^2 291 and 197, 300 and 222; 12304^2 154 and 157.  A C that fits the 256 MiB last-level cache is written there:
-    // 8 x 2048^2 33 us streamed, 28 cached, 4 x 4096^2 57 and 48 (4096 rows: 74.5 and 73).
-    const bool stream = N % 16 == 0 && (int64_t)H * N * N > (int64_t)1 << 26;
+    // A C of whole 64-byte pieces streams: cached, the lines of a large one push the trace out of the L2 (8 x 8192^2, 4096 rows: 434 us
+    // streamed, 650 cached; 65536^2: 3.5 and 5.5 ms) and those of a small one are all written out when the kernel ends (2 x 2048^2, 2048
+    // rows 17.3 and 19.0).  In between, from 128 MiB up to the 256 MiB last-level cache, the cached one wins: 8 x 2048^2, 2048 rows 42.7
+    // and 34.6, 8000 rows 75.6 and 67.8, 4 x 4096^2, 256 rows 57 and 48 (6 x 2048^2: level).  Rows of C that start inside a 64-byte
+    // piece share it with their neighbour tiles, and streamed, each of the two writes it to memory by itself: 4 x 4001^2, 256 rows
+    // 124 us streamed, 51 cached, 4096 rows 137 and 75; 12289^2 291 and 197, 300 and 222; 12304^2 154 and 157; but a small one of whole
+    // 16-byte vectors is better streamed (64 x 300^2, 2048 rows 25.7 and 26.9; 8 x 700^2 15.5 and 15.7; 8 x 1025^2 15.4 and 14.4).
+    const int64_t elements = (int64_t)H * N * N;
+    const bool whole = N % 16 == 0 || (N % 4 == 0 && elements < (int64_t)1 << 23);
+    const bool stream = whole && (elements < (int64_t)1 << 25 || elements > (int64_t)1 << 26);
     // A little more than the 1024 tiles that the device holds at once: all of those contract together, then all write, and the rest
     // runs nearly alone.  One after the other, the first ones' writing and the rest's start overlap the others' contraction: 16384
     // rows of 8 x 2048 (1088 tiles) 126 -> 114 us without the trace, of 1 x 6000 (1128) 142 -> 130 with it, of 8 x 2304 (1368)
     // 170 -> 167.  Nothing below (1012 tiles 101.2 -> 101.7), and past 1.4 rounds it is in the way (1680 tiles 213 -> 226).
-    const bool stagger = total > 1024 && total <= 1408;       // never with a C that streams: 1408 tiles hold less than that
+    const bool stagger = total > 1024 && total <= 1408;       // their C is cached whatever its rows: 16 to 23 million counts
     const int form = stagger ? STAGGER : stream ? STREAM : PLAIN;
     // Few tiles over many trace rows leave most of the device idle: the rows are cut into pieces.
     int pieces = 1, piece_runs = nruns;
