@@ -152,7 +152,12 @@ class Harness:
         return out
 
 
-def coact_rooflines(H, N, rows, coact_ms, peaks, decayed):
+def summed_by_rows(N, rows, k):
+    """Whether the library sums a fresh build row by row (sparse traces) instead of contracting it on the matrix cores."""
+    return 6144 <= rows <= 65535 and 4096 <= N <= 65536 and N % 16 == 0 and k <= N // 64
+
+
+def coact_rooflines(H, N, rows, k, coact_ms, peaks, decayed):
     """Both roofs of the co-activation build and the one that binds it.  C is written once (read and written when an
     old matrix is updated), so below peak_ops / peak_bytes operations per byte it is the memory system."""
     Tpad = (rows + 511) // 512 * 512
@@ -167,6 +172,10 @@ def coact_rooflines(H, N, rows, coact_ms, peaks, decayed):
             "frac_of_measured_fp4_peak": round(tops / peaks["mfma_fp4_TOPs"], 4)}
     hbm = {"achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4), "bytes": nbytes,
            "frac_of_measured_write_peak": round(gbs / peaks["hbm_write_GBs"], 4)}
+    if not decayed and summed_by_rows(N, rows, k):                             # no matrix instruction is issued
+        return {"kernel": "coact_rows_kernel (rows of C summed in LDS, exact counts)", "bound": "hbm", "achieved": hbm["achieved"], "peak": hbm["peak"],
+                "unit": hbm["unit"], "frac": hbm["frac"], "why": "C written once beside an equal time of LDS increments", "mfma": None, "hbm": hbm,
+                "issued_ops": None, "increments": float(rows) * H * k * k}
     roof = hbm if hbm_bound else mfma
     return {"kernel": "coact_syrk_kernel (4-bit matrix-core form, exact counts)", "bound": "hbm" if hbm_bound else "mfma",
             "achieved": roof["achieved"], "peak": roof["peak"], "unit": roof["unit"], "frac": roof["frac"],
@@ -305,7 +314,7 @@ def single_stream(args, cfg, binding, W, torch, np, stream):
     roof_steps = HBM_PEAK_GBS * 1e9 / unit_bytes
     dense_ops = 2.0 * H * N * N * T
     increments = float(T) * H * k * k                                            # the trace's own work: k^2 pair counts per row
-    roof_coact = coact_rooflines(H, N, T, coact_ms, peaks, decayed=False)
+    roof_coact = coact_rooflines(H, N, T, k, coact_ms, peaks, decayed=False)
     roof_coact.update({"dense_equivalent_tops": round(dense_ops / (coact_ms * 1e-3) / 1e12, 1),
                        "ms_per_build_incl_trace": round(coact_ms, 3), "ms_min": round(coact_us_min * 1e-3, 3),
                        "pair_increments_per_s": round(increments / (coact_ms * 1e-3), 0),
@@ -335,7 +344,7 @@ def single_stream(args, cfg, binding, W, torch, np, stream):
                            "whole_step": {"us_per_step": round(step_us, 3), "steps_per_s": round(1e6 / step_us, 1),
                                           "frac": round(1e6 / step_us / roof_steps, 4)}},
         "roofline_coact": roof_coact,
-        "density_pass": {"what": "grand total, rho and medoid queue from C (two sweeps of C plus an N^2 ranking)",
+        "density_pass": {"what": "grand total, rho and medoid queue from C (two sweeps of C plus a sort of the densities)",
                          "ms": round(dens_us * 1e-3, 3), "ms_min": round(dens_us_min * 1e-3, 3), "bound": "hbm",
                          "bytes": 2 * H * N * N * 4, "achieved_GBs": round(2 * H * N * N * 4 / (dens_us * 1e-6) / 1e9, 1)},
         "build_density_one_pass": {"what": "trace + C + rho + queue with the radius test in the C kernel's epilogue (C written once, never read)",
@@ -448,7 +457,7 @@ def batched(args, cfg, binding, W, torch, np, stream):
     unit_bytes = H * N * row_bytes + B * H * G * cfg.d * 2 + B * H * k * 4
     roof_steps = HBM_PEAK_GBS * 1e9 / unit_bytes
     coact_ms = coact_us * 1e-3
-    roof_coact = coact_rooflines(H, N, win * B, coact_ms, peaks, decayed=True)
+    roof_coact = coact_rooflines(H, N, win * B, cfg.k, coact_ms, peaks, decayed=True)
     roof_coact.update({"ms_per_window_incl_trace": round(coact_ms, 3), "ms_min": round(coact_us_min * 1e-3, 3),
                        "trace_rows_per_window": win * B})
     step_us = wall / args.steps / T * 1e6
@@ -514,6 +523,11 @@ def only_coact(args, cfg, binding, W, torch, stream):
     ms = e0.elapsed_time(e1) / args.steps
     tiles = (N + 255) // 256 * 2
     issued = 2.0 * H * (tiles * (tiles + 1) // 2) * 128 * 128 * ((T + 511) // 512 * 512)
+    if summed_by_rows(N, T, k):
+        print(json.dumps({"only": "coact", "workload": cfg.name, "kernel": "coact_rows_kernel", "ms_per_build_incl_trace": round(ms, 3),
+                          "increments": float(T) * H * k * k, "C_write_GBs": round(H * N * N * 4 / (ms * 1e-3) / 1e9, 1)}), flush=True)
+        sw.close()
+        return
     print(json.dumps({"only": "coact", "workload": cfg.name, "ms_per_build_incl_trace": round(ms, 3), "issued_ops": issued,
                       "TOPs": round(issued / (ms * 1e-3) / 1e12, 1), "frac_of_int8_peak_5000": round(issued / (ms * 1e-3) / 5e15, 4),
                       "frac_of_fp4_peak_10100": round(issued / (ms * 1e-3) / 10.1e15, 4),
