@@ -152,9 +152,9 @@ class Harness:
         return out
 
 
-def summed_by_rows(N, rows, k):
+def summed_by_rows(H, N, rows, k):
     """Whether the library sums a fresh build row by row (sparse traces) instead of contracting it on the matrix cores."""
-    return 6144 <= rows <= 65535 and 4096 <= N <= 65536 and N % 16 == 0 and k <= N // 64
+    return H * N * N >= 1 << 29 and 6144 <= rows <= 65535 and 4096 <= N <= 65536 and N % 16 == 0 and k <= N // 64
 
 
 def coact_rooflines(H, N, rows, k, coact_ms, peaks, decayed):
@@ -172,7 +172,7 @@ def coact_rooflines(H, N, rows, k, coact_ms, peaks, decayed):
             "frac_of_measured_fp4_peak": round(tops / peaks["mfma_fp4_TOPs"], 4)}
     hbm = {"achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4), "bytes": nbytes,
            "frac_of_measured_write_peak": round(gbs / peaks["hbm_write_GBs"], 4)}
-    if not decayed and summed_by_rows(N, rows, k):                             # no matrix instruction is issued
+    if not decayed and summed_by_rows(H, N, rows, k):                          # no matrix instruction is issued
         return {"kernel": "coact_rows_kernel (rows of C summed in LDS, exact counts)", "bound": "hbm", "achieved": hbm["achieved"], "peak": hbm["peak"],
                 "unit": hbm["unit"], "frac": hbm["frac"], "why": "C written once beside an equal time of LDS increments", "mfma": None, "hbm": hbm,
                 "issued_ops": None, "increments": float(rows) * H * k * k}
@@ -523,7 +523,7 @@ def only_coact(args, cfg, binding, W, torch, stream):
     ms = e0.elapsed_time(e1) / args.steps
     tiles = (N + 255) // 256 * 2
     issued = 2.0 * H * (tiles * (tiles + 1) // 2) * 128 * 128 * ((T + 511) // 512 * 512)
-    if summed_by_rows(N, T, k):
+    if summed_by_rows(H, N, T, k):
         print(json.dumps({"only": "coact", "workload": cfg.name, "kernel": "coact_rows_kernel", "ms_per_build_incl_trace": round(ms, 3),
                           "increments": float(T) * H * k * k, "C_write_GBs": round(H * N * N * 4 / (ms * 1e-3) / 1e9, 1)}), flush=True)
         sw.close()

@@ -31,6 +31,7 @@ constexpr int BLOCK = 64;             // columns dealt to the segments together
 constexpr int LIST_MAX_K = 1024;      // N / 64
 constexpr int DUMMY_WORDS = 32;       // counters behind a segment's, taken by padding
 constexpr int RT = 512;               // threads of a counting workgroup; with 256 the same within 2 %
+constexpr int SLOTS = 128;            // workgroups of an XCD, four on each of its 32 compute units
 constexpr int T_CAP = 1024;           // trace rows listed at a time
 constexpr uint32_t MORE = 0xffffu;    // last slot of a record: the piece goes on in the overflow
 
@@ -83,7 +84,11 @@ __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restric
     const uint32_t inv = (65536u + L - 1) / L;                          // p / L for p < 1024
     auto slot = [&](uint32_t s, uint32_t p) __attribute__((always_inline)) { const uint32_t q = p * inv >> 16; return s * slots + (p - q * L) * 8 + q; };
     auto seg_of = [&](int32_t x) __attribute__((always_inline)) { return (uint32_t)(x / BLOCK) & (uint32_t)(nseg - 1); };
-    auto counter_of = [&](int32_t x) __attribute__((always_inline)) { return (uint16_t)((((x / BLOCK) >> nseg_log2) * BLOCK + (x & (BLOCK - 1))) * 4); };
+    // The counters of a block are turned by four words from block to block: entries 64 apart would otherwise share one LDS bank.
+    auto counter_of = [&](int32_t x) __attribute__((always_inline)) {
+        const int block = (x / BLOCK) >> nseg_log2;
+        return (uint16_t)((block * BLOCK + ((x + 4 * block) & (BLOCK - 1))) * 4);
+    };
     uint32_t place[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
@@ -133,7 +138,8 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
     uint16_t* tl = reinterpret_cast<uint16_t*>(smem + cols + DUMMY_WORDS);       // [2][T_CAP]
     __shared__ uint32_t tcount[2];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    constexpr int slots = SLOTS;
     const int seg = xcd & (nseg - 1), parts = 8 >> nseg_log2, part = xcd >> nseg_log2;
     const int nwords = nruns * 4, chunks = (nwords + RT - 1) / RT;
     const int stride = slots * parts;
@@ -142,12 +148,22 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
     if (tid < 2) tcount[tid] = 0;
     __syncthreads();
 
-    struct Place { int h, i, chunk; };
+    // A round hands a stretch of neighbouring rows to the segment's workgroups, turned from round to round by a hash of its number, so
+    // that often activated entries at a fixed distance do not all fall to the same workgroups (every 64th entry in each of 8192
+    // selections of 1024 took 470 ms by equal rounds, all on two workgroups of an XCD; now 4.4).
+    struct Place { int h, i, chunk, round, first_h, first_i; };
+    auto settle = [&](Place& p) __attribute__((always_inline)) {
+        p.h = p.first_h;
+        p.i = p.first_i + ((slot * parts + part + (int)((uint32_t)p.round * 0x9e3779b1u >> 22)) & (stride - 1));         // stride: a power of two, 1024 at most
+        while (p.i >= N) { p.i -= N; ++p.h; }
+    };
     auto advance = [&](Place& p) __attribute__((always_inline)) {
         if (++p.chunk < chunks) return;
         p.chunk = 0;
-        p.i += stride;
-        while (p.i >= N) { p.i -= N; ++p.h; }
+        ++p.round;
+        p.first_i += stride;
+        while (p.first_i >= N) { p.first_i -= N; ++p.first_h; }
+        settle(p);
     };
     const uint32_t word_off = ((uint32_t)(tid >> 2) * (uint32_t)Npad * 4 + (tid & 3)) * 4;       // bytes, inside a head's trace
     auto load_word = [&](const Place& p) __attribute__((always_inline)) -> uint32_t {
@@ -180,8 +196,8 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
     };
     const uint32_t rec_bytes = (uint32_t)L * 16, group_off = (uint32_t)my_group * 16;
 
-    Place at{0, slot * parts + part, 0};
-    while (at.i >= N) { at.i -= N; ++at.h; }
+    Place at{0, 0, 0, 0, 0, 0};
+    settle(at);
     Place ahead = at;
     int buf = 0;
     uint32_t word = load_word(at);
@@ -261,11 +277,14 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
             }
             int near = 0;
             uint32_t e = (((tid >> 4) << nseg_log2) + seg) * BLOCK + (tid & 15) * 4;
+            const int turned = (tid + (tid >> 4)) & 15;                // block w / 16 of vector w: RT / 16 blocks on, the turn is the same
+            static_assert(RT / 16 % 16 == 0, "the turn of a thread's blocks");
             auto leave = [&](auto whole_tag) __attribute__((always_inline)) {
                 constexpr bool WHOLE = decltype(whole_tag)::value;
                 for (int w = tid; w < cols / 4; w += RT, e += (RT / 16 * BLOCK) << nseg_log2) {
-                    const v4i v = reinterpret_cast<const v4i*>(cnt)[w];
-                    reinterpret_cast<v4i*>(cnt)[w] = v4i{0, 0, 0, 0};
+                    const int at_w = (w & ~15) | turned;
+                    const v4i v = reinterpret_cast<const v4i*>(cnt)[at_w];
+                    reinterpret_cast<v4i*>(cnt)[at_w] = v4i{0, 0, 0, 0};
                     if (WHOLE || e + 4 <= (uint32_t)N) {
                         __builtin_nontemporal_store((v4i_row)v, reinterpret_cast<v4i_row*>(row + e * 4));
                     } else {
@@ -312,9 +331,11 @@ RowsPlan plan_of(int N, int k) {
 //  - 6144 rows: below, the dense product waits for the writing of C as well (4096 rows 0.91 to 1.1, 5120 0.97 to 1.2, 6144 1.04 to 1.4);
 //  - N >= 4096: a row of 2048 is over before the two barriers are (8192 rows of 4 heads: 0.89);
 //  - N a multiple of 16: a 64-byte piece of C shared by two XCDs is written twice (N = 12289: 0.85, 24592: 1.27 at 6144 rows).
+//  - 2^29 counts: an entry that all of 8192 rows activate keeps one workgroup busy for up to 350 us, which a build of this size (800
+//    us and more by the dense product) hides and a smaller one does not.
 // The ids of a segment and the trace rows have to fit 16 bits, a wave per selection one launch.
 bool rows_route(int64_t rows, int H, int N, int k) {
-    return rows * H <= (int64_t)1 << 25 && rows >= 6144 && rows <= 65535 && N >= 4096 && N <= MAX_SEGMENTS * MAX_SEGMENT && N % 16 == 0 && k <= N / 64;
+    return rows * H <= (int64_t)1 << 25 && (int64_t)H * N * N >= (int64_t)1 << 29 && rows >= 6144 && rows <= 65535 && N >= 4096 && N <= MAX_SEGMENTS * MAX_SEGMENT && N % 16 == 0 && k <= N / 64;
 }
 
 // Scratch for the records, their overflow and where a piece's overflow lies.
@@ -337,7 +358,7 @@ swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows,
     if (st != SWARM_OK) return st;
     const int lds = (seg_columns(N, 1 << p.nseg_log2) + DUMMY_WORDS) * 4 + 2 * T_CAP * 2;
     hipLaunchKernelGGL(p.nseg_log2 ? (cstar ? coact_rows_kernel<true, true> : coact_rows_kernel<false, true>)
-                                   : (cstar ? coact_rows_kernel<true, false> : coact_rows_kernel<false, false>), dim3(256 * 4), dim3(RT), lds, ctx->stream,
+                                   : (cstar ? coact_rows_kernel<true, false> : coact_rows_kernel<false, false>), dim3(8 * SLOTS), dim3(RT), lds, ctx->stream,
                        reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns, p.nseg_log2, p.L, p.ext_groups, C, cstar, rho);
     return swarm_check_launch(ctx, "coact_rows_kernel");
 }

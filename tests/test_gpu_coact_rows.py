@@ -1,4 +1,4 @@
-"""GPU parity of the counts of sparse traces (k <= N / 64, 6144 trace rows and more, overwriting): summed row by row, against the
+"""GPU parity of the counts of sparse traces (k <= N / 64, 6144 trace rows and 2^29 counts or more, overwriting): summed row by row, against the
 popcount route on the device and against the oracle."""
 import numpy as np
 import pytest
@@ -40,8 +40,8 @@ def selections(kind, rows, H, k, N, seed=0):
 
 # one, two, four and eight segments; whole and partial last blocks of columns; the fewest rows, a partial run of rows and more
 # rows than the workgroup's words cover at a time; the widest selection and a single entry
-@pytest.mark.parametrize("rows,H,k,N", [(6144, 1, 64, 4096), (6151, 3, 1, 4112), (17000, 1, 60, 4096), (6200, 2, 128, 8208), (6144, 1, 300, 24576),
-                                        (33000, 1, 100, 8192), (6500, 1, 512, 32784)])
+@pytest.mark.parametrize("rows,H,k,N", [(6144, 32, 64, 4096), (6151, 32, 1, 4112), (17000, 32, 60, 4096), (6200, 8, 128, 8208), (6144, 1, 300, 24576),
+                                        (33000, 8, 100, 8192), (6500, 1, 512, 32784)])
 @pytest.mark.parametrize("kind", ["spread", "runs", "any", "crowded", "same"])
 def test_sparse_counts_equal_the_popcount_route(sw, rows, H, k, N, kind):
     sel = selections(kind, rows, H, k, N)
@@ -66,7 +66,7 @@ def test_sparse_counts_equal_the_popcount_route(sw, rows, H, k, N, kind):
 
 
 def test_sparse_counts_equal_the_oracle(sw):
-    rows, H, k, N = 6150, 1, 32, 4096                       # strata of 128 entries: distinct ids, as the oracle asks
+    rows, H, k, N = 6150, 32, 32, 4096                       # strata of 128 entries: distinct ids, as the oracle asks
     sel = selections("spread", rows, H, k, N, seed=5)
     torch.cuda.synchronize()
     C = torch.empty(H, N, N, dtype=torch.int32, device="cuda")
@@ -80,9 +80,9 @@ def test_recordings_take_the_way_that_has_its_room(first):
     """A recording of either kind of trace is accepted after an eager call of the other kind, and every replay is right."""
     from paper_2603_17803_amd import binding
     sw = binding.Swarm(0, stream=torch.cuda.Stream())
-    N, rows = 4096, 6144
-    sparse, dense = selections("spread", rows, 1, 64, N, 1), selections("spread", rows, 1, 100, N, 1)
-    C = torch.empty(1, N, N, dtype=torch.int32, device="cuda")
+    N, rows, H = 8192, 6144, 8
+    sparse, dense = selections("spread", rows, H, 64, N, 1), selections("spread", rows, H, 200, N, 1)
+    C = torch.empty(H, N, N, dtype=torch.int32, device="cuda")
     ref = torch.empty_like(C)
     torch.cuda.synchronize()
     sw.coact_accumulate(dense if first == "dense" else sparse, N, C, decay_q16=0)
@@ -92,7 +92,7 @@ def test_recordings_take_the_way_that_has_its_room(first):
     sw.coact_accumulate(sel, N, C, decay_q16=0)
     graph = sw.capture_end()
     for rep in range(3):
-        sel.copy_(selections("spread", rows, 1, sel.shape[2], N, 10 + rep))
+        sel.copy_(selections("spread", rows, H, sel.shape[2], N, 10 + rep))
         torch.cuda.synchronize()
         C.fill_(-1)
         torch.cuda.synchronize()
