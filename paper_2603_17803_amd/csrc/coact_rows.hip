@@ -9,10 +9,11 @@
 // k times, 17 GB for 8192 of 1024 out of 65536 entries, which do not fit an L2 (3.9 ms without a single increment).  So the
 // columns are cut into eight segments, one per XCD (workgroup b runs on XCD b % 8): an XCD meets only its segment's part of
 // every selection, 2.7 MB of records that stay in its own L2, and a segment's 8192 counters leave room for four workgroups per
-// compute unit.  Blocks of 64 columns are dealt to the segments in turn, so that a run of neighbouring entries is spread evenly.
+// compute unit.  Blocks of 32 columns (a line of C) are dealt to the segments, so that a run of neighbouring entries is spread evenly:
+// with blocks of 64 a selection of whole pages of 64 entries takes 4.7 ms and not 4.4, with 16 the writing of C half as long again.
 // Records have a fixed size -- the mean share of a segment, some standard deviations, and what completes a wave's division by
 // whole records -- because walking ragged pieces costs more than the increments (pieces through a work list: 4.8 ms); the ids
-// beyond it, rare unless the ids prefer one segment, go to an overflow that a whole wave reads at once.
+// beyond it, rare unless the ids come in whole blocks, go to an overflow.
 // 8192 selections of 1024 out of 65536 entries: 5.7 ms by the dense product, 3.5 ms here with trace and records; 3.3 ms are
 // increments, listing and clearing, 3.1 to 3.3 ms the writing of C by itself (5.5 TB/s, what row pieces reach), side by side.
 #include <type_traits>
@@ -27,13 +28,18 @@ typedef int v4i_row __attribute__((ext_vector_type(4), aligned(4)));   // rows o
 
 constexpr int MAX_SEGMENTS = 8;       // one per XCD
 constexpr int MAX_SEGMENT = 8192;     // columns of a segment: 32 KiB of counters
-constexpr int BLOCK = 64;             // columns dealt to the segments together
+constexpr int BLOCK = 32;             // columns dealt to the segments together
 constexpr int LIST_MAX_K = 1024;      // N / 64
 constexpr int DUMMY_WORDS = 32;       // counters behind a segment's, taken by padding
 constexpr int RT = 512;               // threads of a counting workgroup; with 256 the same within 2 %
 constexpr int SLOTS = 128;            // workgroups of an XCD, four on each of its 32 compute units
 constexpr int T_CAP = 1024;           // trace rows listed at a time
-constexpr uint32_t MORE = 0xffffu;    // last slot of a record: the piece goes on in the overflow
+
+// Each group of nseg blocks deals one to every segment, turned from group to group by a hash of its number: dealt in turn, entries at
+// a distance of a multiple of 32 nseg fall to one segment, that is to one XCD of eight, and nearly all of them to the overflow (8192
+// selections of 1024 out of every eighth 64 of 65536 entries took 18.3 ms; now 4.3).  Of all distances of up to a sixth of a segment's
+// blocks, and 4 x 8192 to 65536 entries, this constant leaves the fullest segment at most 1 + 2.4 / sqrt(n) times its share of n blocks.
+__host__ __device__ __forceinline__ uint32_t turn_of(uint32_t group) { return group * 0xf2ee4e45u >> 29; }
 
 __host__ __device__ __forceinline__ int seg_columns(int N, int nseg) { return (N + nseg * BLOCK - 1) / (nseg * BLOCK) * BLOCK; }
 
@@ -42,8 +48,7 @@ __host__ __device__ __forceinline__ int seg_columns(int N, int nseg) { return (N
 // wave, a group each, meet neighbouring ids together (a run of entries then falls on distinct LDS banks).  One wave per
 // selection: 30 us for 8192 of 1024.
 __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restrict__ idx, int64_t rows, int recs, int H, int k, int N, int nseg_log2,
-                                                        int L, int ext_groups, uint4* __restrict__ lists, uint4* __restrict__ ext,
-                                                        uint32_t* __restrict__ meta) {
+                                                        int L, int ext_groups, uint4* __restrict__ lists, uint4* __restrict__ ext) {
     constexpr int PER = LIST_MAX_K / 64;
     __shared__ uint32_t piece[MAX_SEGMENTS];
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
@@ -83,7 +88,10 @@ __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restric
     const uint32_t slots = 8u * L, cap = nseg > 1 ? slots - 1 : slots;
     const uint32_t inv = (65536u + L - 1) / L;                          // p / L for p < 1024
     auto slot = [&](uint32_t s, uint32_t p) __attribute__((always_inline)) { const uint32_t q = p * inv >> 16; return s * slots + (p - q * L) * 8 + q; };
-    auto seg_of = [&](int32_t x) __attribute__((always_inline)) { return (uint32_t)(x / BLOCK) & (uint32_t)(nseg - 1); };
+    auto seg_of = [&](int32_t x) __attribute__((always_inline)) {
+        const uint32_t block = (uint32_t)x / BLOCK;
+        return (block + turn_of(block >> nseg_log2)) & (uint32_t)(nseg - 1);
+    };
     // The counters of a block are turned by four words from block to block: entries 64 apart would otherwise share one LDS bank.
     auto counter_of = [&](int32_t x) __attribute__((always_inline)) {
         const int block = (x / BLOCK) >> nseg_log2;
@@ -106,8 +114,7 @@ __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restric
         const uint32_t off = waveops::wave_excl_scan(ng, &total);
         uint16_t* out = reinterpret_cast<uint16_t*>(ext + ((size_t)h * recs + t) * ext_groups);
         if (ng) {
-            rec[slot(lane, slots - 1)] = (uint16_t)MORE;
-            meta[((size_t)h * nseg + lane) * recs + t] = off | ng << 16;
+            rec[slot(lane, slots - 1)] = (uint16_t)(1u | off << 1 | (ng - 1) << 9);        // odd, as no counter's offset is; off < 136, ng <= 128
             for (uint32_t p = cnt - cap; p < ng * 8; ++p) out[off * 8 + p] = (uint16_t)((cols + (lane & (DUMMY_WORDS - 1))) * 4);
             piece[lane] = off * 8;
         }
@@ -195,6 +202,7 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
         if (__ballot(last < end) != 0) add(last);             // the last eighth of the slots is mostly padding
     };
     const uint32_t rec_bytes = (uint32_t)L * 16, group_off = (uint32_t)my_group * 16;
+    const uint4* ext = lists + ((size_t)recs * H * L << nseg_log2);
 
     Place at{0, 0, 0, 0, 0, 0};
     settle(at);
@@ -236,28 +244,39 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
                         t[u] = t_of[min(p0 + u * step + my_list, m - 1)];
                         v[u] = *reinterpret_cast<const uint4*>(hl + (t[u] * rec_bytes + group_off));
                     }
+                    // Pieces that go on: the lanes of a record read its overflow, for all records side by side, and the first of it
+                    // before anything is added.
+                    uint64_t goes_on = 0;
+                    uint32_t rest[U];                          // groups of overflow from this lane's first on
+                    const uint4* from[U];
+                    uint4 y[U];
+                    if (SEG) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) goes_on |= __ballot((v[u].w >> 16) & 1u);
+                        if (__builtin_expect(goes_on != 0, 0)) {
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const uint32_t x = (uint32_t)__shfl((int)(v[u].w >> 16), my_list * L + L - 1, 64);     // the record's last slot
+                                const uint32_t ng = (x & 1u) && p0 + u * step + my_list < m ? (x >> 9) + 1 : 0u;
+                                rest[u] = ng > (uint32_t)my_group ? ng - (uint32_t)my_group : 0u;
+                                from[u] = ext + ((size_t)at.h * recs + t[u]) * ext_groups + ((x >> 1) & 0xffu) + my_group;
+                                if (rest[u]) y[u] = *from[u];
+                            }
+                        }
+                    }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        if (p0 + u * step >= m) break;
                         uint32_t last = v[u].w >> 16;
-                        const bool on = p0 + u * step + my_list < m;
-                        const uint64_t goes_on = SEG ? __ballot(on && last == MORE) : 0ull;      // known to all lanes: they read the overflow together
-                        if (SEG) last = last == MORE ? end : last;
-                        if (on) add8(v[u], last);
-                        if (SEG && __builtin_expect(goes_on != 0, 0)) {
-                            uint32_t nrec = (uint32_t)recs;
-                            asm volatile("" : "+s"(nrec));
-                            const uint4* ext = lists + (size_t)nrec * H * L * nseg;
-                            const uint32_t* meta = reinterpret_cast<const uint32_t*>(ext + (size_t)nrec * H * ext_groups) + ((size_t)at.h * nseg + seg) * nrec;
-                            for (uint64_t left = goes_on; left; left &= left - 1) {
-                                const int l = __ffsll((unsigned long long)left) - 1;
-                                const uint32_t tt = (uint32_t)__builtin_amdgcn_readlane((int)t[u], l);
-                                const uint32_t x = meta[tt];
-                                const uint4* e = ext + ((size_t)at.h * nrec + tt) * ext_groups + (x & 0xffffu);
-                                for (uint32_t g = lane; g < x >> 16; g += lpw * L) {
-                                    const uint4 y = e[g];
-                                    add8(y, y.w >> 16);
-                                }
+                        if (SEG) last = last & 1u ? end : last;
+                        if (p0 + u * step + my_list < m) add8(v[u], last);
+                    }
+                    if (SEG && __builtin_expect(goes_on != 0, 0)) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            if (rest[u]) add8(y[u], y[u].w >> 16);
+                            for (uint32_t g = L; g < rest[u]; g += L) {
+                                const uint4 z = from[u][g];
+                                add8(z, z.w >> 16);
                             }
                         }
                     }
@@ -276,13 +295,15 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
                 if (c < 0x7fffffffll) c32 = (int32_t)c;
             }
             int near = 0;
-            uint32_t e = (((tid >> 4) << nseg_log2) + seg) * BLOCK + (tid & 15) * 4;
-            const int turned = (tid + (tid >> 4)) & 15;                // block w / 16 of vector w: RT / 16 blocks on, the turn is the same
-            static_assert(RT / 16 % 16 == 0, "the turn of a thread's blocks");
+            constexpr int VECS = BLOCK / 4;
+            const int turned = (tid + tid / VECS) & (VECS - 1);        // block w / VECS of vector w: RT / VECS blocks on, the turn is the same
+            static_assert(RT / VECS % VECS == 0, "the turn of a thread's blocks");
             auto leave = [&](auto whole_tag) __attribute__((always_inline)) {
                 constexpr bool WHOLE = decltype(whole_tag)::value;
-                for (int w = tid; w < cols / 4; w += RT, e += (RT / 16 * BLOCK) << nseg_log2) {
-                    const int at_w = (w & ~15) | turned;
+                for (int w = tid; w < cols / 4; w += RT) {
+                    const int at_w = (w & ~(VECS - 1)) | turned;
+                    const uint32_t group = (uint32_t)w / VECS;
+                    const uint32_t e = ((group << nseg_log2) + (((uint32_t)seg - turn_of(group)) & (uint32_t)(nseg - 1))) * BLOCK + (w & (VECS - 1)) * 4;
                     const v4i v = reinterpret_cast<const v4i*>(cnt)[at_w];
                     reinterpret_cast<v4i*>(cnt)[at_w] = v4i{0, 0, 0, 0};
                     if (WHOLE || e + 4 <= (uint32_t)N) {
@@ -338,11 +359,11 @@ bool rows_route(int64_t rows, int H, int N, int k) {
     return rows * H <= (int64_t)1 << 25 && (int64_t)H * N * N >= (int64_t)1 << 29 && rows >= 6144 && rows <= 65535 && N >= 4096 && N <= MAX_SEGMENTS * MAX_SEGMENT && N % 16 == 0 && k <= N / 64;
 }
 
-// Scratch for the records, their overflow and where a piece's overflow lies.
+// Scratch for the records and their overflow.
 size_t rows_list_bytes(int64_t rows, int H, int k, int N) {
     const RowsPlan p = plan_of(N, k);
     const int64_t recs = (rows + 31) / 32 * 32;
-    return (size_t)recs * H * ((((size_t)p.L << p.nseg_log2) + p.ext_groups) * 16 + (4 << p.nseg_log2));
+    return (size_t)recs * H * ((((size_t)p.L << p.nseg_log2) + p.ext_groups) * 16);
 }
 
 swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int H, int k, int N, int Npad, int nruns, int32_t* C,
@@ -351,9 +372,8 @@ swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows,
     const int recs = (int)((rows + 31) / 32 * 32);
     uint4* lists = static_cast<uint4*>(scratch);
     uint4* ext = lists + ((size_t)recs * H * p.L << p.nseg_log2);
-    uint32_t* meta = reinterpret_cast<uint32_t*>(ext + (size_t)recs * H * p.ext_groups);
     hipLaunchKernelGGL(list_build_kernel, dim3((unsigned)(rows * H)), dim3(64),
-                       ((size_t)p.L * 16 << p.nseg_log2) + (size_t)((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext, meta);
+                       ((size_t)p.L * 16 << p.nseg_log2) + (size_t)((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext);
     swarm_status st = swarm_check_launch(ctx, "list_build_kernel");
     if (st != SWARM_OK) return st;
     const int lds = (seg_columns(N, 1 << p.nseg_log2) + DUMMY_WORDS) * 4 + 2 * T_CAP * 2;

@@ -34,6 +34,13 @@ def selections(kind, rows, H, k, N, seed=0):
     if kind == "crowded":                                   # every eighth block of 64 columns: a segment has far more than its share
         block = torch.randint(0, (N + 511) // 512, (rows, H, k), generator=g, device="cuda")
         return (block * 512 + torch.randint(0, 64, (rows, H, k), generator=g, device="cuda")).clamp_(max=N - 1).int()
+    if kind == "one segment":                               # blocks of 32 columns that all fall to the first segment: most ids beyond its records
+        segments = next(n for n in (1, 2, 4, 8) if N <= 8192 * n)
+        block = torch.arange(N // 32, device="cuda")
+        turn = ((block // segments) * 0xf2ee4e45 & 0xffffffff) >> 29
+        pool = block[(block + turn) % segments == 0]
+        e = torch.randint(0, pool.numel() * 32, (rows, H, k), generator=g, device="cuda")
+        return (pool[e // 32] * 32 + e % 32).int()
     same = torch.randperm(N, generator=g, device="cuda")[:k].sort().values      # "same": k entries in every row
     return same.expand(rows, H, k).int().contiguous()
 
@@ -42,7 +49,7 @@ def selections(kind, rows, H, k, N, seed=0):
 # rows than the workgroup's words cover at a time; the widest selection and a single entry
 @pytest.mark.parametrize("rows,H,k,N", [(6144, 32, 64, 4096), (6151, 32, 1, 4112), (17000, 32, 60, 4096), (6200, 8, 128, 8208), (6144, 1, 300, 24576),
                                         (33000, 8, 100, 8192), (6500, 1, 512, 32784)])
-@pytest.mark.parametrize("kind", ["spread", "runs", "any", "crowded", "same"])
+@pytest.mark.parametrize("kind", ["spread", "runs", "any", "crowded", "one segment", "same"])
 def test_sparse_counts_equal_the_popcount_route(sw, rows, H, k, N, kind):
     sel = selections(kind, rows, H, k, N)
     with torch.cuda.stream(sw.stream):

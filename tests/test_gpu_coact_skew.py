@@ -1,0 +1,62 @@
+"""What a build of sparse selections costs does not depend on which entries they prefer: the time of one-sided selections against
+that of selections spread over all entries, at the same sizes, both sides timed in turn (best of five)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+ROWS = 8192
+
+
+@pytest.fixture(scope="module")
+def sw():
+    from paper_2603_17803_amd import binding
+    s = binding.Swarm(0)
+    yield s
+    s.close()
+
+
+def selections(kind, distance, H, k, N):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + distance)
+    ar = torch.arange(k, device="cuda")
+    if kind == "spread":                                     # one entry per stratum
+        return ((ar + torch.rand(ROWS, H, k, generator=g, device="cuda")) * (N / k)).long().clamp_(max=N - 1).int()
+    if kind == "pages":                                      # whole blocks of 64 entries, of the blocks at multiples of a distance
+        pool = torch.arange(0, N // 64, distance // 64, device="cuda")
+        block = pool[torch.rand(ROWS, H, pool.numel(), generator=g, device="cuda").topk(k // 64, -1).indices].sort(-1).values
+        return (block[..., None] * 64 + torch.arange(64, device="cuda")).reshape(ROWS, H, k).int().contiguous()
+    if kind == "scattered":                                  # entries of the blocks of 64 at multiples of a distance
+        e = torch.rand(ROWS, H, N // distance * 64, generator=g, device="cuda").topk(k, -1).indices.sort(-1).values
+        return (e // 64 * distance + e % 64).int()
+    n = N // distance                                        # "same": a few neighbours at every multiple of a distance, in every row
+    ids = torch.arange(n, device="cuda")[:, None] * distance + torch.arange(max(1, k // n), device="cuda")
+    return ids.flatten()[:k].int().expand(ROWS, H, min(k, ids.numel())).contiguous()
+
+
+def times(sw, calls):
+    best = [float("inf")] * len(calls)
+    for rep in range(6):                                     # the first one is not counted
+        for i, call in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            if rep:
+                best[i] = min(best[i], a.elapsed_time(b))
+    return best
+
+
+# bound: half way between what was measured with the columns or rows dealt in turn (in brackets) and now
+@pytest.mark.parametrize("kind,distance,H,k,N,bound", [
+    ("scattered", 512, 2, 256, 16384, 2.0),                  # 2.98 -> 1.15: one of two segments, nearly all in the overflow
+    ("pages", 1024, 2, 256, 16384, 2.0),                     # 2.96 -> 1.04
+])
+def test_time_does_not_depend_on_the_entries(sw, kind, distance, H, k, N, bound):
+    C = torch.empty(H, N, N, dtype=torch.int32, device="cuda")
+    even, skewed = selections("spread", 0, H, k, N), selections(kind, distance, H, k, N)
+    t = times(sw, [lambda: sw.coact_accumulate(even, N, C, decay_q16=0), lambda: sw.coact_accumulate(skewed, N, C, decay_q16=0)])
+    assert sw.device_status() == 0
+    assert t[1] < bound * t[0], t
