@@ -34,10 +34,11 @@ constexpr int DUMMY_WORDS = 32;       // counters behind a segment's, taken by p
 constexpr int RT = 512;               // threads of a counting workgroup; with 256 the same within 2 %
 constexpr int SLOTS = 128;            // workgroups of an XCD, four on each of its 32 compute units
 constexpr int T_CAP = 1024;           // trace rows listed at a time
+constexpr int QUEUE_STRIDE = 32;      // words from one XCD's counter of rows handed out to the next
 
 // Each group of nseg blocks deals one to every segment, turned from group to group by a hash of its number: dealt in turn, entries at
 // a distance of a multiple of 32 nseg fall to one segment, that is to one XCD of eight, and nearly all of them to the overflow (8192
-// selections of 1024 out of every eighth 64 of 65536 entries took 18.3 ms; now 4.3).  Of all distances of up to a sixth of a segment's
+// selections of 1024 out of every eighth 64 of 65536 entries took 18.3 ms; now 3.5).  Of all distances of up to a sixth of a segment's
 // blocks, and 4 x 8192 to 65536 entries, this constant leaves the fullest segment at most 1 + 2.4 / sqrt(n) times its share of n blocks.
 __host__ __device__ __forceinline__ uint32_t turn_of(uint32_t group) { return group * 0xf2ee4e45u >> 29; }
 
@@ -48,7 +49,8 @@ __host__ __device__ __forceinline__ int seg_columns(int N, int nseg) { return (N
 // wave, a group each, meet neighbouring ids together (a run of entries then falls on distinct LDS banks).  One wave per
 // selection: 30 us for 8192 of 1024.
 __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restrict__ idx, int64_t rows, int recs, int H, int k, int N, int nseg_log2,
-                                                        int L, int ext_groups, uint4* __restrict__ lists, uint4* __restrict__ ext) {
+                                                        int L, int ext_groups, uint4* __restrict__ lists, uint4* __restrict__ ext,
+                                                        uint32_t* __restrict__ queue) {
     constexpr int PER = LIST_MAX_K / 64;
     __shared__ uint32_t piece[MAX_SEGMENTS];
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
@@ -65,6 +67,7 @@ __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restric
 #pragma unroll
     for (int u = 0; u < PER; ++u) e[u] = u * 64 + lane < k ? sel[u * 64 + lane] : N;
     if (lane < MAX_SEGMENTS) piece[lane] = 0u;
+    if (blockIdx.x == 0 && lane < 8) queue[lane * QUEUE_STRIDE] = 0u;     // for the counting kernel that follows
     for (int g = lane; g < L << nseg_log2; g += 64) {                   // padding everywhere, a bank of its own for every lane that meets it
         const uint32_t d = (uint32_t)(cols + (g & (DUMMY_WORDS - 1))) * 4 * 0x10001u;
         rec4[g] = make_uint4(d, d, d, d);
@@ -137,41 +140,40 @@ __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restric
 // RHO: also counts, per row, the elements that reach the head's threshold (rho must be zero before).  SEG: more than one segment.
 template <bool RHO, bool SEG>
 __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __restrict__ bits, const uint4* __restrict__ lists, int recs, int H, int N,
-                                                           int Npad, int nruns, int nseg_log2, int L, int ext_groups, int32_t* __restrict__ C,
-                                                           const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
+                                                           int Npad, int nruns, int nseg_log2, int L, int ext_groups, uint32_t* __restrict__ queue,
+                                                           int32_t* __restrict__ C, const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     const int nseg = 1 << nseg_log2, cols = seg_columns(N, nseg);
     uint32_t* cnt = smem;                                                        // cols + DUMMY_WORDS counters
     uint16_t* tl = reinterpret_cast<uint16_t*>(smem + cols + DUMMY_WORDS);       // [2][T_CAP]
-    __shared__ uint32_t tcount[2];
+    __shared__ uint32_t tcount[2], fetched;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    constexpr int slots = SLOTS;
     const int seg = xcd & (nseg - 1), parts = 8 >> nseg_log2, part = xcd >> nseg_log2;
     const int nwords = nruns * 4, chunks = (nwords + RT - 1) / RT;
-    const int stride = slots * parts;
     const int lpw = 64 / L, my_list = lane / L, my_group = lane - my_list * L;   // lists a wave works on side by side
     for (int w = tid; w < (cols + DUMMY_WORDS) / 4; w += RT) reinterpret_cast<v4i*>(cnt)[w] = v4i{0, 0, 0, 0};
     if (tid < 2) tcount[tid] = 0;
     __syncthreads();
 
-    // A round hands a stretch of neighbouring rows to the segment's workgroups, turned from round to round by a hash of its number, so
-    // that often activated entries at a fixed distance do not all fall to the same workgroups (every 64th entry in each of 8192
-    // selections of 1024 took 470 ms by equal rounds, all on two workgroups of an XCD; now 4.4).
-    struct Place { int h, i, chunk, round, first_h, first_i; };
-    auto settle = [&](Place& p) __attribute__((always_inline)) {
-        p.h = p.first_h;
-        p.i = p.first_i + ((slot * parts + part + (int)((uint32_t)p.round * 0x9e3779b1u >> 22)) & (stride - 1));         // stride: a power of two, 1024 at most
-        while (p.i >= N) { p.i -= N; ++p.h; }
-    };
-    auto advance = [&](Place& p) __attribute__((always_inline)) {
-        if (++p.chunk < chunks) return;
+    // An XCD's rows are handed out in order, each to the first workgroup that gets there: what a row costs differs by its entry's count,
+    // and dealt beforehand, by equal rounds or rounds turned by a hash, often activated entries pile up on some workgroups (every 64th
+    // entry in each of 8192 selections of 1024: 470 ms and 4.7, handed out 4.3; nine neighbours every 576 entries 9.6 and 3.9; any 1024
+    // entries 5.8 and 4.2; ids spread evenly 3.45 and 3.1).  A workgroup's first two rows are known; the number of a later one is asked
+    // for while two others are before it.  Where several XCDs share a segment, the rows are dealt to them as the blocks to the segments.
+    struct Place { int h, i, chunk, before; };                 // before: rows of earlier heads
+    auto begin = [&](Place& p, uint32_t place) __attribute__((always_inline)) {
         p.chunk = 0;
-        ++p.round;
-        p.first_i += stride;
-        while (p.first_i >= N) { p.first_i -= N; ++p.first_h; }
-        settle(p);
+        p.i = (int)(place * (uint32_t)parts + ((part + turn_of(place)) & (uint32_t)(parts - 1))) - p.before;
+        while (p.i >= N) { p.i -= N; p.before += N; ++p.h; }
     };
+    uint32_t upcoming = slot + SLOTS;
+    auto advance = [&](Place& p) __attribute__((always_inline)) {
+        if (++p.chunk < chunks) return false;
+        begin(p, upcoming);
+        return true;
+    };
+    auto ask = [&]() __attribute__((always_inline)) { return 2 * SLOTS + __hip_atomic_fetch_add(queue + xcd * QUEUE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     const uint32_t word_off = ((uint32_t)(tid >> 2) * (uint32_t)Npad * 4 + (tid & 3)) * 4;       // bytes, inside a head's trace
     auto load_word = [&](const Place& p) __attribute__((always_inline)) -> uint32_t {
         if (p.chunk * RT + tid >= nwords || p.h >= H) return 0u;
@@ -204,14 +206,17 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
     const uint32_t rec_bytes = (uint32_t)L * 16, group_off = (uint32_t)my_group * 16;
     const uint4* ext = lists + ((size_t)recs * H * L << nseg_log2);
 
-    Place at{0, 0, 0, 0, 0, 0};
-    settle(at);
+    Place at{0, 0, 0, 0};
+    begin(at, slot);
     Place ahead = at;
     int buf = 0;
     uint32_t word = load_word(at);
     list_rows(word, 0, 0);
-    advance(ahead);
+    const bool took_first = advance(ahead);
     uint32_t next = load_word(ahead);
+    if (tid == 0) fetched = took_first ? ask() : upcoming;
+    __syncthreads();
+    upcoming = (uint32_t)__builtin_amdgcn_readfirstlane((int)fetched);
     __syncthreads();
     while (at.h < H) {
         const char* hl = reinterpret_cast<const char*>(lists + ((size_t)at.h * nseg + seg) * recs * L);
@@ -219,9 +224,11 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
         list_rows(next, ahead.chunk, buf ^ 1);                // the rows of the step after this one listed, the words after those requested
         word = next;
         const Place after = ahead;
-        advance(ahead);
+        const bool took = advance(ahead);
         next = load_word(ahead);
-        const int parts_of = n <= T_CAP ? 1 : RT / 32;        // too many for the list: the words 32 at a time
+        uint32_t asked = 0;
+        if (took && tid == 0) asked = ask();
+        const int parts_of = n <= T_CAP ? 1 : (min(nwords - at.chunk * RT, RT) + 31) / 32;        // too many for the list: the words 32 at a time
         for (int s = 0; s < parts_of; ++s) {
             uint32_t m = n;
             if (parts_of > 1) {
@@ -283,7 +290,9 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
                 }
             }
         }
+        if (took && tid == 0) fetched = asked;
         __syncthreads();
+        upcoming = (uint32_t)__builtin_amdgcn_readfirstlane((int)fetched);
         if (tid == 0) tcount[buf] = 0;
         buf ^= 1;
         if (after.chunk == 0) {
@@ -359,11 +368,11 @@ bool rows_route(int64_t rows, int H, int N, int k) {
     return rows * H <= (int64_t)1 << 25 && (int64_t)H * N * N >= (int64_t)1 << 29 && rows >= 6144 && rows <= 65535 && N >= 4096 && N <= MAX_SEGMENTS * MAX_SEGMENT && N % 16 == 0 && k <= N / 64;
 }
 
-// Scratch for the records and their overflow.
+// Scratch for the records, their overflow and the counters of rows handed out.
 size_t rows_list_bytes(int64_t rows, int H, int k, int N) {
     const RowsPlan p = plan_of(N, k);
     const int64_t recs = (rows + 31) / 32 * 32;
-    return (size_t)recs * H * ((((size_t)p.L << p.nseg_log2) + p.ext_groups) * 16);
+    return (size_t)recs * H * ((((size_t)p.L << p.nseg_log2) + p.ext_groups) * 16) + 8 * QUEUE_STRIDE * 4;
 }
 
 swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int H, int k, int N, int Npad, int nruns, int32_t* C,
@@ -372,13 +381,14 @@ swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows,
     const int recs = (int)((rows + 31) / 32 * 32);
     uint4* lists = static_cast<uint4*>(scratch);
     uint4* ext = lists + ((size_t)recs * H * p.L << p.nseg_log2);
+    uint32_t* queue = reinterpret_cast<uint32_t*>(ext + (size_t)recs * H * p.ext_groups);
     hipLaunchKernelGGL(list_build_kernel, dim3((unsigned)(rows * H)), dim3(64),
-                       ((size_t)p.L * 16 << p.nseg_log2) + (size_t)((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext);
+                       ((size_t)p.L * 16 << p.nseg_log2) + (size_t)((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext, queue);
     swarm_status st = swarm_check_launch(ctx, "list_build_kernel");
     if (st != SWARM_OK) return st;
     const int lds = (seg_columns(N, 1 << p.nseg_log2) + DUMMY_WORDS) * 4 + 2 * T_CAP * 2;
     hipLaunchKernelGGL(p.nseg_log2 ? (cstar ? coact_rows_kernel<true, true> : coact_rows_kernel<false, true>)
                                    : (cstar ? coact_rows_kernel<true, false> : coact_rows_kernel<false, false>), dim3(8 * SLOTS), dim3(RT), lds, ctx->stream,
-                       reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns, p.nseg_log2, p.L, p.ext_groups, C, cstar, rho);
+                       reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns, p.nseg_log2, p.L, p.ext_groups, queue, C, cstar, rho);
     return swarm_check_launch(ctx, "coact_rows_kernel");
 }
