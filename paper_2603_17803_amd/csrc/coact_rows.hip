@@ -38,15 +38,20 @@ constexpr int QUEUE_STRIDE = 32;      // words from one XCD's counter of rows ha
 
 // Each group of nseg blocks deals one to every segment, turned from group to group by a hash of its number: dealt in turn, entries at
 // a distance of a multiple of 32 nseg fall to one segment, that is to one XCD of eight, and nearly all of them to the overflow (8192
-// selections of 1024 out of every eighth 64 of 65536 entries took 18.3 ms; now 3.5).  Of all distances of up to a sixth of a segment's
+// selections of 1024 out of every eighth 64 of 65536 entries took 18.3 ms; now 3.4).  Of all distances of up to a sixth of a segment's
 // blocks, and 4 x 8192 to 65536 entries, this constant leaves the fullest segment at most 1 + 2.4 / sqrt(n) times its share of n blocks.
 __host__ __device__ __forceinline__ uint32_t turn_of(uint32_t group) { return group * 0xf2ee4e45u >> 29; }
+// Entries at a fixed distance would share a bank: the counters of each pair of blocks lie in an order of their own, place i at i ^ mix
+// (every 64th entry in each of 8192 selections of 128 out of 8 x 8192 entries 1.07 -> 0.63 ms, where blocks turned by four words meet
+// eight banks).
+__host__ __device__ __forceinline__ uint32_t mix_of(uint32_t pair) { return pair * 0x9e3779b1u >> 26; }
 
-__host__ __device__ __forceinline__ int seg_columns(int N, int nseg) { return (N + nseg * BLOCK - 1) / (nseg * BLOCK) * BLOCK; }
+// Columns of a segment: whole pairs of blocks, a counter on each of the 64 LDS banks.
+__host__ __device__ __forceinline__ int seg_columns(int N, int nseg) { return (N + nseg * 64 - 1) / (nseg * 64) * 64; }
 
 // Every selection becomes one record per segment: the byte offsets of its distinct valid ids' counters, 16 bits each, in L
-// groups of eight, and the rest in the overflow.  Slot p of a record is element p / L of group p % L, so that the lanes of a
-// wave, a group each, meet neighbouring ids together (a run of entries then falls on distinct LDS banks).  One wave per
+// groups of eight, and the rest in the overflow.  Id p of a record is in group p % L, so that the lanes of a wave, a
+// group each, meet neighbouring ids together (a run of entries then falls on distinct LDS banks).  One wave per
 // selection: 30 us for 8192 of 1024.
 __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restrict__ idx, int64_t rows, int recs, int H, int k, int N, int nseg_log2,
                                                         int L, int ext_groups, uint4* __restrict__ lists, uint4* __restrict__ ext,
@@ -90,15 +95,20 @@ __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restric
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const uint32_t slots = 8u * L, cap = nseg > 1 ? slots - 1 : slots;
     const uint32_t inv = (65536u + L - 1) / L;                          // p / L for p < 1024
-    auto slot = [&](uint32_t s, uint32_t p) __attribute__((always_inline)) { const uint32_t q = p * inv >> 16; return s * slots + (p - q * L) * 8 + q; };
+    // Records of neighbouring trace rows list an id as different ones of a group's first seven: lanes of a wave that add to one counter at
+    // once wait for each other (the same 1024 entries in every row 4.2 -> 3.45 ms).
+    const uint32_t turn = (uint32_t)t % 7u;
+    auto slot = [&](uint32_t s, uint32_t p) __attribute__((always_inline)) {
+        const uint32_t q = p * inv >> 16, turned = q + turn < 7u ? q + turn : q + turn - 7u;
+        return s * slots + (p - q * L) * 8 + (q < 7u ? turned : 7u);
+    };
     auto seg_of = [&](int32_t x) __attribute__((always_inline)) {
         const uint32_t block = (uint32_t)x / BLOCK;
         return (block + turn_of(block >> nseg_log2)) & (uint32_t)(nseg - 1);
     };
-    // The counters of a block are turned by four words from block to block: entries 64 apart would otherwise share one LDS bank.
     auto counter_of = [&](int32_t x) __attribute__((always_inline)) {
-        const int block = (x / BLOCK) >> nseg_log2;
-        return (uint16_t)((block * BLOCK + ((x + 4 * block) & (BLOCK - 1))) * 4);
+        const uint32_t in_seg = ((uint32_t)x / BLOCK >> nseg_log2) * BLOCK + (uint32_t)x % BLOCK;
+        return (uint16_t)((in_seg ^ mix_of(in_seg / 64)) * 4);
     };
     uint32_t place[PER];
 #pragma unroll
@@ -304,16 +314,15 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
                 if (c < 0x7fffffffll) c32 = (int32_t)c;
             }
             int near = 0;
-            constexpr int VECS = BLOCK / 4;
-            const int turned = (tid + tid / VECS) & (VECS - 1);        // block w / VECS of vector w: RT / VECS blocks on, the turn is the same
-            static_assert(RT / VECS % VECS == 0, "the turn of a thread's blocks");
             auto leave = [&](auto whole_tag) __attribute__((always_inline)) {
                 constexpr bool WHOLE = decltype(whole_tag)::value;
                 for (int w = tid; w < cols / 4; w += RT) {
-                    const int at_w = (w & ~(VECS - 1)) | turned;
-                    const uint32_t group = (uint32_t)w / VECS;
-                    const uint32_t e = ((group << nseg_log2) + (((uint32_t)seg - turn_of(group)) & (uint32_t)(nseg - 1))) * BLOCK + (w & (VECS - 1)) * 4;
-                    const v4i v = reinterpret_cast<const v4i*>(cnt)[at_w];
+                    const uint32_t group = (uint32_t)w / (BLOCK / 4), mix = mix_of((uint32_t)w / 16);
+                    const uint32_t e = ((group << nseg_log2) + (((uint32_t)seg - turn_of(group)) & (uint32_t)(nseg - 1))) * BLOCK + (w & (BLOCK / 4 - 1)) * 4;
+                    const uint32_t at_w = (uint32_t)w ^ (mix >> 2);
+                    v4i v = reinterpret_cast<const v4i*>(cnt)[at_w];
+                    v = mix & 1u ? v4i{v.y, v.x, v.w, v.z} : v;
+                    v = mix & 2u ? v4i{v.z, v.w, v.x, v.y} : v;
                     reinterpret_cast<v4i*>(cnt)[at_w] = v4i{0, 0, 0, 0};
                     if (WHOLE || e + 4 <= (uint32_t)N) {
                         __builtin_nontemporal_store((v4i_row)v, reinterpret_cast<v4i_row*>(row + e * 4));
