@@ -96,6 +96,23 @@ const char* swarm_source_hash(void);
  * flag was set, SWARM_EDATA otherwise; *flags (nullable, host) receives the SWARM_DEV_* bits. */
 swarm_status swarm_device_status(swarm_ctx* ctx, uint32_t* flags);
 
+/* For tests and measurement: by which kernels the last co-activation count and the last medoid queue on this context were made, or
+ * recorded (SWARM_WAY_NONE: none yet; all ways give the same results), and the bytes of scratch the context holds.  Each pointer may be
+ * NULL.  Host only: nothing is enqueued or waited for. */
+typedef enum {
+    SWARM_WAY_NONE = 0,
+    SWARM_WAY_DENSE = 1,           /* matrix cores, C written through the caches                   */
+    SWARM_WAY_DENSE_STREAMED = 2,  /* the same, C written past them                                */
+    SWARM_WAY_DENSE_STAGGERED = 3, /* the same, for a little more tiles than the device holds      */
+    SWARM_WAY_DENSE_PIECES = 4,    /* the same, the trace rows of a tile in pieces                 */
+    SWARM_WAY_ROWS = 5,            /* sparse selections added up row by row of C                   */
+    SWARM_WAY_POPCOUNT = 6,        /* SWARM_COACT_POPCOUNT                                         */
+    SWARM_WAY_QUEUE_LDS = 16,      /* queue sorted by one workgroup per head                       */
+    SWARM_WAY_QUEUE_SORTED = 17,   /* queue sorted with scratch                                    */
+    SWARM_WAY_QUEUE_COMPARED = 18  /* queue by comparing all pairs, without scratch                */
+} swarm_way;
+swarm_status swarm_last_way(const swarm_ctx* ctx, int32_t* count_way, int32_t* queue_way, size_t* scratch_bytes);
+
 /*
  * Score + select (Section 2.3: every KV entry gets a relevance score against the query -- inner
  * products being the example the section names -- and the entries with the highest scores are kept).

@@ -18,8 +18,11 @@ SWARM_KEYS_TOKEN, SWARM_KEYS_PAGE_MINMAX = 0, 1
 SWARM_CHECK_IDX = 1
 SWARM_DEV_BAD_ENTRY, SWARM_DEV_BAD_CLUSTER, SWARM_DEV_BAD_SSD, SWARM_DEV_CAP, SWARM_DEV_DUP_ENTRY = 1, 2, 4, 8, 16
 SWARM_DEV_BAD_OFFSETS, SWARM_DEV_OVERFLOW = 32, 64
+(SWARM_WAY_NONE, SWARM_WAY_DENSE, SWARM_WAY_DENSE_STREAMED, SWARM_WAY_DENSE_STAGGERED, SWARM_WAY_DENSE_PIECES, SWARM_WAY_ROWS,
+ SWARM_WAY_POPCOUNT) = range(7)
+SWARM_WAY_QUEUE_LDS, SWARM_WAY_QUEUE_SORTED, SWARM_WAY_QUEUE_COMPARED = 16, 17, 18
 
-EXPORTS = ["swarm_create", "swarm_destroy", "swarm_last_error", "swarm_source_hash", "swarm_device_status", "swarm_score", "swarm_score_select", "swarm_score_select_static",
+EXPORTS = ["swarm_create", "swarm_destroy", "swarm_last_error", "swarm_source_hash", "swarm_device_status", "swarm_last_way", "swarm_score", "swarm_score_select", "swarm_score_select_static",
            "swarm_coact_accumulate", "swarm_coact_build_density", "swarm_map_requests", "swarm_map_requests_streams", "swarm_coact_density", "swarm_window_assign", "swarm_score_select_indexed", "swarm_expand_clusters",
            "swarm_submission_order", "swarm_step", "swarm_calibrate", "swarm_capture_begin", "swarm_capture_end",
            "swarm_graph_launch", "swarm_graph_destroy"]
@@ -55,6 +58,7 @@ def load() -> C.CDLL:
     L.swarm_source_hash.argtypes = []
     L.swarm_source_hash.restype = C.c_char_p
     L.swarm_device_status.argtypes = [vp, C.POINTER(u32)]
+    L.swarm_last_way.argtypes = [vp, C.POINTER(i32), C.POINTER(i32), C.POINTER(C.c_size_t)]
     L.swarm_score_select.argtypes = [vp, C.POINTER(swarm_keys), vp, i32, i32, vp, vp]
     L.swarm_score_select_static.argtypes = [vp, C.POINTER(swarm_keys), vp, i32, i32, vp]
     L.swarm_score.argtypes = [vp, C.POINTER(swarm_keys), vp, i32, vp]
@@ -111,6 +115,12 @@ def swarm_device_status(ctx: int) -> Tuple[int, int]:
     flags = C.c_uint32(0)
     rc = load().swarm_device_status(C.c_void_p(ctx), C.byref(flags))
     return rc, flags.value
+
+
+def swarm_last_way(ctx: int) -> Tuple[int, int, int, int]:
+    count, queue, scratch = C.c_int32(0), C.c_int32(0), C.c_size_t(0)
+    rc = load().swarm_last_way(C.c_void_p(ctx), C.byref(count), C.byref(queue), C.byref(scratch))
+    return rc, count.value, queue.value, scratch.value
 
 
 def swarm_score_select(ctx: int, kind: int, data: int, H: int, N: int, d: int, G: int, q: int, B: int, k: int,
@@ -556,6 +566,10 @@ class Swarm:
 
     def graph_launch(self, graph: int):
         self._check("swarm_graph_launch", swarm_graph_launch(self.ctx, graph))
+
+    def last_way(self) -> Tuple[int, int, int]:
+        """(SWARM_WAY_* of the last count, of the last medoid queue, bytes of scratch held); waits for nothing."""
+        return swarm_last_way(self.ctx)[1:]
 
     def device_status(self) -> int:
         """Synchronises, returns and clears the sticky SWARM_DEV_* flags."""

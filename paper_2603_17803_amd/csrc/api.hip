@@ -131,6 +131,14 @@ swarm_status swarm_device_status(swarm_ctx* ctx, uint32_t* flags) {
     return SWARM_OK;
 }
 
+swarm_status swarm_last_way(const swarm_ctx* ctx, int32_t* count_way, int32_t* queue_way, size_t* scratch_bytes) {
+    if (!ctx) return SWARM_EINVAL;
+    if (count_way) *count_way = ctx->count_way;
+    if (queue_way) *queue_way = ctx->queue_way;
+    if (scratch_bytes) *scratch_bytes = ctx->scores_bytes + ctx->cand_bytes + ctx->trace_bytes + ctx->lists_bytes + ctx->part_bytes + ctx->rank_bytes + ctx->totals_bytes;
+    return SWARM_OK;
+}
+
 }  // extern "C"
 
 swarm_status swarm_check_score_args(swarm_ctx* ctx, const char* fn, const swarm_keys* keys, const void* q, int32_t B) {

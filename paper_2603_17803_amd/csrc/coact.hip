@@ -865,6 +865,7 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
         hipLaunchKernelGGL(kernels[3][fused ? 3 : mode], dim3((unsigned)(total * SYRK_WAVES)), dim3(64), 32 * TROW + (TM + TN) * 4, ctx->stream,
                            reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, (int)tiles_per_head, (int)total, 0, tile_order,
                            ctx->dev_flags, cstar, rho, part, pieces, piece_runs);
+        ctx->count_way = SWARM_WAY_DENSE_PIECES;
         return swarm_check_launch(ctx, "coact_syrk_kernel (pieces)");
     }
     dim3 grid((unsigned)(per_xcd * 8)), block(64 * SYRK_WAVES);
@@ -872,6 +873,7 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     hipLaunchKernelGGL(kernels[form][fused ? 3 : mode], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
                        ctx->stream, reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, tph, tot, per_xcd,
                        tile_order, ctx->dev_flags, cstar, rho, nullptr, 1, nruns);
+    ctx->count_way = form == STAGGER ? SWARM_WAY_DENSE_STAGGERED : form == STREAM && mode == 0 ? SWARM_WAY_DENSE_STREAMED : SWARM_WAY_DENSE;
     return swarm_check_launch(ctx, "coact_syrk_kernel");
 }
 
@@ -886,5 +888,6 @@ swarm_status launch_coact_popcount(swarm_ctx* ctx, int H, int N, int Npad, int n
     if (decay_q16 == 0u) hipLaunchKernelGGL(coact_popcount_kernel<0>, grid, block, 0, ctx->stream, bits, N, Npad, nruns, C, decay_q16, ctx->dev_flags);
     else if (decay_q16 == 65536u) hipLaunchKernelGGL(coact_popcount_kernel<1>, grid, block, 0, ctx->stream, bits, N, Npad, nruns, C, decay_q16, ctx->dev_flags);
     else hipLaunchKernelGGL(coact_popcount_kernel<2>, grid, block, 0, ctx->stream, bits, N, Npad, nruns, C, decay_q16, ctx->dev_flags);
+    ctx->count_way = SWARM_WAY_POPCOUNT;
     return swarm_check_launch(ctx, "coact_popcount_kernel");
 }

@@ -399,5 +399,6 @@ swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows,
     hipLaunchKernelGGL(p.nseg_log2 ? (cstar ? coact_rows_kernel<true, true> : coact_rows_kernel<false, true>)
                                    : (cstar ? coact_rows_kernel<true, false> : coact_rows_kernel<false, false>), dim3(8 * SLOTS), dim3(RT), lds, ctx->stream,
                        reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns, p.nseg_log2, p.L, p.ext_groups, queue, C, cstar, rho);
+    ctx->count_way = SWARM_WAY_ROWS;
     return swarm_check_launch(ctx, "coact_rows_kernel");
 }

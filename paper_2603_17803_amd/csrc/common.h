@@ -41,6 +41,7 @@ struct swarm_ctx {
     size_t rank_bytes = 0;
     int64_t* totals = nullptr;     // per-head grand totals of C when the caller keeps none
     size_t totals_bytes = 0;
+    int count_way = SWARM_WAY_NONE, queue_way = SWARM_WAY_NONE;   // what the last count and queue were made by
     bool trace_lds_opt_in = false, syrk_lds_opt_in = false;   // large dynamic LDS enabled for this context's device
     uint32_t batched_lds_opt_in = 0;                          // the same, a bit per form of the many-stream scorer
     uint32_t* dev_flags = nullptr; // sticky SWARM_DEV_* bits (one word)

@@ -408,6 +408,7 @@ swarm_status launch_medoid_rank(swarm_ctx* ctx, const int32_t* rho, int H, int N
         const kernel_t kernel = N <= SMALL_THREADS ? rank_small_kernel<1> : N <= 2 * SMALL_THREADS ? rank_small_kernel<2>
                               : N <= 4 * SMALL_THREADS ? rank_small_kernel<4> : rank_small_kernel<8>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)H), dim3(SMALL_THREADS), 0, ctx->stream, rho, N, passes, queue);
+        ctx->queue_way = SWARM_WAY_QUEUE_LDS;
         return swarm_check_launch(ctx, "rank_small_kernel");
     }
     const size_t words = rank_scratch_words(H, N);
@@ -420,6 +421,7 @@ swarm_status launch_medoid_rank(swarm_ctx* ctx, const int32_t* rho, int H, int N
     if (!sorted) {
         hipLaunchKernelGGL(medoid_rank_kernel, dim3((unsigned)((N + RANK_ENTRIES - 1) / RANK_ENTRIES), (unsigned)H),
                            dim3(RANK_ENTRIES * RANK_PARTS), 0, ctx->stream, rho, N, queue);
+        ctx->queue_way = SWARM_WAY_QUEUE_COMPARED;
         return swarm_check_launch(ctx, "medoid_rank_kernel");
     }
     int32_t* ids = ctx->rank;
@@ -433,6 +435,7 @@ swarm_status launch_medoid_rank(swarm_ctx* ctx, const int32_t* rho, int H, int N
         hipLaunchKernelGGL(rank_move_kernel, grid, dim3(SORT_THREADS), 0, ctx->stream, rho, src, N, p * bits, bits, counts, dst);
         src = dst;
     }
+    ctx->queue_way = SWARM_WAY_QUEUE_SORTED;
     return swarm_check_launch(ctx, "rank_move_kernel");
 }
 

@@ -1,5 +1,5 @@
 """GPU parity of the counts of sparse traces (k <= N / 64, 6144 trace rows and 2^29 counts or more, overwriting): summed row by row, against the
-popcount route on the device and against the oracle."""
+popcount route on the device and against the oracle; and of the forms of the dense product.  Each call's way is asserted."""
 import numpy as np
 import pytest
 
@@ -10,6 +10,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 POPCOUNT = 2
+DENSE, STREAMED, STAGGERED, PIECES, ROWS, BY_POPCOUNT = range(1, 7)           # SWARM_WAY_*
 
 
 @pytest.fixture(scope="module")
@@ -57,19 +58,39 @@ def test_sparse_counts_equal_the_popcount_route(sw, rows, H, k, N, kind):
         C = torch.full((H, N, N), -7, dtype=torch.int32, device="cuda")
         ref = torch.full((H, N, N), -9, dtype=torch.int32, device="cuda")
         sw.coact_accumulate(sel, N, C, decay_q16=0)
+        assert sw.last_way()[0] == ROWS
         sw.coact_accumulate(sel, N, ref, decay_q16=0, flags=POPCOUNT)
+        assert sw.last_way()[0] == BY_POPCOUNT
         assert torch.equal(C, ref)
         C.fill_(-7)
         tau = 1.0 - 3.0 / float(ref.sum(dtype=torch.int64) // H + 1)
         rho, queue, totals = sw.coact_build_density(sel, N, C, tau)
+        assert sw.last_way()[0] == ROWS
         assert torch.equal(C, ref)
         rho2, queue2, totals2 = sw.coact_density(ref, tau)
         assert torch.equal(totals, totals2) and torch.equal(rho, rho2) and torch.equal(queue, queue2)
     sw.stream.synchronize()
-    try:
-        sw.device_status()
-    except Exception:
-        assert kind == "any"
+    from paper_2603_17803_amd import binding
+    assert sw.device_status() == (binding.SWARM_DEV_BAD_ENTRY if kind == "any" else 0)
+
+
+# just inside and just outside each bound of the rule: trace rows, counts, k against N / 64, N and its alignment
+@pytest.mark.parametrize("rows,H,k,N,way", [
+    (6144, 32, 64, 4096, ROWS), (6143, 32, 64, 4096, STREAMED), (6144, 31, 64, 4096, STREAMED), (6144, 32, 65, 4096, STREAMED),
+    (6144, 33, 63, 4080, STREAMED), (6144, 32, 64, 4112, ROWS), (6144, 32, 64, 4104, DENSE), (65535, 8, 8, 8192, ROWS),
+    (65536, 8, 8, 8192, STREAMED), (6144, 1, 8, 65536, ROWS), (6144, 1, 8, 65552, STREAMED)])
+def test_the_way_of_a_count(sw, rows, H, k, N, way):
+    sel = selections("spread", rows, H, k, N)
+    torch.cuda.synchronize()
+    C = torch.empty(H, N, N, dtype=torch.int32, device="cuda")
+    sw.coact_accumulate(sel, N, C, decay_q16=0)
+    assert sw.last_way()[0] == way
+    sw.stream.synchronize()
+    sw.coact_accumulate(sel[:1], N, C, decay_q16=0)                            # no update takes the sparse way
+    sw.coact_accumulate(sel, N, C, decay_q16=65536)
+    assert sw.last_way()[0] == DENSE
+    sw.stream.synchronize()
+    assert sw.device_status() == 0
 
 
 def test_sparse_counts_equal_the_oracle(sw):
@@ -78,13 +99,14 @@ def test_sparse_counts_equal_the_oracle(sw):
     torch.cuda.synchronize()
     C = torch.empty(H, N, N, dtype=torch.int32, device="cuda")
     sw.coact_accumulate(sel, N, C, decay_q16=0)
+    assert sw.last_way()[0] == ROWS
     sw.stream.synchronize()
     assert np.array_equal(C.cpu().numpy(), oracle.coact_update(sel.cpu().numpy(), N, nthreads=8))
 
 
-@pytest.mark.parametrize("first", ["dense", "sparse"])
-def test_recordings_take_the_way_that_has_its_room(first):
-    """A recording of either kind of trace is accepted after an eager call of the other kind, and every replay is right."""
+@pytest.mark.parametrize("first,then,way", [("dense", "sparse", STREAMED), ("sparse", "dense", STREAMED), ("sparse", "sparse", ROWS)])
+def test_recordings_take_the_way_that_has_its_room(first, then, way):
+    """A recording of either kind of trace is accepted after an eager call of either kind, and every replay is right."""
     from paper_2603_17803_amd import binding
     sw = binding.Swarm(0, stream=torch.cuda.Stream())
     N, rows, H = 8192, 6144, 8
@@ -93,11 +115,13 @@ def test_recordings_take_the_way_that_has_its_room(first):
     ref = torch.empty_like(C)
     torch.cuda.synchronize()
     sw.coact_accumulate(dense if first == "dense" else sparse, N, C, decay_q16=0)
-    sel = sparse if first == "dense" else dense
-    sw.stream.synchronize()
+    assert sw.last_way()[0] == (STREAMED if first == "dense" else ROWS)
+    sel = (sparse if then == "sparse" else dense).clone()
+    torch.cuda.synchronize()
     sw.capture_begin()
     sw.coact_accumulate(sel, N, C, decay_q16=0)
     graph = sw.capture_end()
+    assert sw.last_way()[0] == way
     for rep in range(3):
         sel.copy_(selections("spread", rows, H, sel.shape[2], N, 10 + rep))
         torch.cuda.synchronize()
@@ -111,9 +135,11 @@ def test_recordings_take_the_way_that_has_its_room(first):
     sw.close()
 
 
-# 1088, 1128 (ragged rows of C) and 1368 tiles, where the dense product's workgroups finish one after the other; 1024 and 1410 around them
-@pytest.mark.parametrize("rows,H,k,N", [(130, 8, 60, 2048), (70, 1, 200, 6001), (300, 8, 100, 2304), (40, 64, 9, 512), (40, 141, 9, 512)])
-def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N):
+# 1088, 1176 (ragged rows of C) and 1368 tiles, where the dense product's workgroups finish one after the other; the fewest and the most
+# of them, 1026 and 1407, and 1020, 1023 and 1410 outside (N up to 256: three tiles a head)
+@pytest.mark.parametrize("rows,H,k,N,way", [(130, 8, 60, 2048, STAGGERED), (70, 1, 200, 6001, STAGGERED), (300, 8, 100, 2304, STAGGERED), (40, 102, 9, 512, STREAMED),
+                                            (150, 341, 9, 256, STREAMED), (150, 342, 9, 256, STAGGERED), (40, 469, 9, 255, STAGGERED), (40, 470, 9, 255, DENSE)])
+def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N, way):
     sel = selections("any", rows, H, k, N).clamp_(0, N - 1)
     with torch.cuda.stream(sw.stream):
         sw.stream.wait_stream(torch.cuda.default_stream())
@@ -121,10 +147,12 @@ def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N):
         ref = C.clone()
         for decay in (65536, 64881, 0):
             sw.coact_accumulate(sel, N, C, decay_q16=decay)
+            assert sw.last_way()[0] == (DENSE if decay and way == STREAMED else way)
             sw.coact_accumulate(sel, N, ref, decay_q16=decay, flags=POPCOUNT)
             assert torch.equal(C, ref)
         C.fill_(-7)
         rho, queue, totals = sw.coact_build_density(sel, N, C, 1.0 - 3.0 / (rows * k * k))
+        assert sw.last_way()[0] == way
         assert torch.equal(C, ref)
         for got, want in zip((rho, queue, totals), sw.coact_density(ref, 1.0 - 3.0 / (rows * k * k))):
             assert torch.equal(got, want)
@@ -132,11 +160,12 @@ def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N):
     assert sw.device_status() == 0
 
 
-# few tiles over many trace rows: contracted in pieces (the last one shorter), with the fewest rows, ragged rows of C, two heads, and
-# one run of rows below
-@pytest.mark.parametrize("rows,H,k,N", [(8192, 1, 40, 1000), (6144, 1, 40, 1024), (6100, 1, 40, 1024), (12300, 2, 30, 701), (33000, 1, 9, 260), (11000, 1, 60, 2048),
-                                        (21300, 1, 70, 3000)])
-def test_counts_of_few_tiles_in_pieces(sw, rows, H, k, N):
+# few tiles over many trace rows: contracted in pieces (the last one shorter), with the fewest rows, ragged rows of C, two heads; one
+# step of rows below, and one tile column too many
+@pytest.mark.parametrize("rows,H,k,N,way", [(8192, 1, 40, 1000, PIECES), (6144, 1, 40, 1024, PIECES), (5633, 1, 40, 1024, PIECES), (5632, 1, 40, 1024, STREAMED),
+                                            (12300, 2, 30, 701, PIECES), (33000, 1, 9, 260, PIECES), (11000, 1, 60, 2048, PIECES), (21300, 1, 70, 3000, PIECES),
+                                            (20992, 1, 70, 3000, DENSE)])
+def test_counts_of_few_tiles_in_pieces(sw, rows, H, k, N, way):
     sel = selections("any", rows, H, k, N).clamp_(0, N - 1)
     with torch.cuda.stream(sw.stream):
         sw.stream.wait_stream(torch.cuda.default_stream())
@@ -144,11 +173,13 @@ def test_counts_of_few_tiles_in_pieces(sw, rows, H, k, N):
         ref = C.clone()
         for decay in (65536, 64881, 0):
             sw.coact_accumulate(sel, N, C, decay_q16=decay)
+            assert sw.last_way()[0] == (DENSE if decay and way == STREAMED else way)
             sw.coact_accumulate(sel, N, ref, decay_q16=decay, flags=POPCOUNT)
             assert torch.equal(C, ref)
         C.fill_(-7)
         tau = 1.0 - rows * k * k / float(N * N) / (rows * k * k)             # a pair of average count is near
         rho, queue, totals = sw.coact_build_density(sel, N, C, tau)
+        assert sw.last_way()[0] == way
         assert torch.equal(C, ref)
         for got, want in zip((rho, queue, totals), sw.coact_density(ref, tau)):
             assert torch.equal(got, want)
@@ -171,6 +202,7 @@ def test_recorded_pieces_need_no_room():
     sw.capture_begin()
     sw.coact_accumulate(sel, N, C, decay_q16=0)
     graph = sw.capture_end()
+    assert sw.last_way()[0] == STREAMED
     for _ in range(2):
         C.fill_(-1)
         torch.cuda.synchronize()

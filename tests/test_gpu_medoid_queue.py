@@ -37,6 +37,7 @@ def test_queue_order(N, kind):
     got, queue, _ = sw.coact_density(C, 0.75, totals_in=total)               # d = 1 - 1/4 <= 0.75
     assert np.array_equal(got.cpu().numpy(), rho)
     assert np.array_equal(queue.cpu().numpy(), np.argsort(-rho, axis=1, kind="stable"))
+    assert sw.last_way()[1] == (binding.SWARM_WAY_QUEUE_LDS if N <= 8192 else binding.SWARM_WAY_QUEUE_SORTED)
     sw.close()
 
 
@@ -57,6 +58,7 @@ def test_recorded_first_call_needs_no_scratch(first_N):
     sw.capture_begin()
     sw.coact_density(C, 0.75, totals_in=total, out=tuple(out))
     graph = sw.capture_end()
+    assert sw.last_way()[1] == (binding.SWARM_WAY_QUEUE_SORTED if first_N > 8192 else binding.SWARM_WAY_QUEUE_COMPARED)
     for kind in ("few", "any", "equal"):
         rho = densities(kind, 1, N)
         C.copy_(counts_with(rho, N))
