@@ -107,6 +107,7 @@ typedef enum {
     SWARM_WAY_DENSE_PIECES = 4,    /* the same, the trace rows of a tile in pieces                 */
     SWARM_WAY_ROWS = 5,            /* sparse selections added up row by row of C                   */
     SWARM_WAY_POPCOUNT = 6,        /* SWARM_COACT_POPCOUNT                                         */
+    SWARM_WAY_DENSE_STAGGERED_STREAMED = 7,
     SWARM_WAY_QUEUE_LDS = 16,      /* queue sorted by one workgroup per head                       */
     SWARM_WAY_QUEUE_SORTED = 17,   /* queue sorted with scratch                                    */
     SWARM_WAY_QUEUE_COMPARED = 18  /* queue by comparing all pairs, without scratch                */

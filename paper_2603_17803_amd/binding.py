@@ -19,7 +19,7 @@ SWARM_CHECK_IDX = 1
 SWARM_DEV_BAD_ENTRY, SWARM_DEV_BAD_CLUSTER, SWARM_DEV_BAD_SSD, SWARM_DEV_CAP, SWARM_DEV_DUP_ENTRY = 1, 2, 4, 8, 16
 SWARM_DEV_BAD_OFFSETS, SWARM_DEV_OVERFLOW = 32, 64
 (SWARM_WAY_NONE, SWARM_WAY_DENSE, SWARM_WAY_DENSE_STREAMED, SWARM_WAY_DENSE_STAGGERED, SWARM_WAY_DENSE_PIECES, SWARM_WAY_ROWS,
- SWARM_WAY_POPCOUNT) = range(7)
+ SWARM_WAY_POPCOUNT, SWARM_WAY_DENSE_STAGGERED_STREAMED) = range(8)
 SWARM_WAY_QUEUE_LDS, SWARM_WAY_QUEUE_SORTED, SWARM_WAY_QUEUE_COMPARED = 16, 17, 18
 
 EXPORTS = ["swarm_create", "swarm_destroy", "swarm_last_error", "swarm_source_hash", "swarm_device_status", "swarm_last_way", "swarm_score", "swarm_score_select", "swarm_score_select_static",

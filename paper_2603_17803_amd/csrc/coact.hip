@@ -204,10 +204,10 @@ __device__ __forceinline__ int lds_off(int row, int piece) { return row * KC + (
 // symmetry its column counts are its row counts.  Counts meet in LDS and leave as one
 // atomic add per row and tile.
 // FORM: STREAM (MODE 0) lets C leave in streaming stores, past the caches; STAGGER makes the workgroups of a compute unit finish
-// one after the other.  launch_coact_syrk says when.
+// one after the other; STAGGER | STREAM is both.  launch_coact_syrk says when.
 // PART contracts one piece of the trace rows and leaves the tile's partial counts in `part`; FINISH adds a tile's pieces up in place
 // of the contraction, a workgroup per wave of the other forms.
-enum { PLAIN, STREAM, STAGGER, PART, FINISH };
+enum { PLAIN = 0, STREAM = 1, STAGGER = 2, PART = 4, FINISH = 8 };
 typedef __attribute__((address_space(3))) void lds_void;
 
 template <int MODE, bool RHO = false, int FORM = PLAIN>
@@ -370,7 +370,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     };
     // The contraction outranks the other waves' epilogue stores.  STAGGER: of the workgroups that share a compute unit (an XCD's
     // workgroups are dealt to its 32 compute units in turn) each outranks the later ones.
-    if constexpr (FORM == STAGGER) {
+    if constexpr ((FORM & STAGGER) != 0) {
         switch ((slot_id >> 5) & 3) {
             case 0: __builtin_amdgcn_s_setprio(3); break;
             case 1: __builtin_amdgcn_s_setprio(2); break;
@@ -466,7 +466,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
         return updated_count<MODE == 0 ? 1 : MODE>(old, v, decay_q16, ovf);
     };
     auto put = [](int32_t v, int32_t* p) __attribute__((always_inline)) {
-        if (FORM == STREAM) __builtin_nontemporal_store(v, p);
+        if (FORM & STREAM) __builtin_nontemporal_store(v, p);
         else *p = v;
     };
     // four consecutive counts of a row, `cols` of them inside C (four unless the tile reaches past N)
@@ -476,7 +476,7 @@ void coact_syrk_kernel(const v4i* __restrict__ bits, int N, int Npad, int nruns,
     };
     auto store_row = [](int32_t* p, v4i w, int cols) __attribute__((always_inline)) {
         if (cols >= 4) {
-            if (FORM == STREAM) __builtin_nontemporal_store((v4i_row)w, reinterpret_cast<v4i_row*>(p));
+            if (FORM & STREAM) __builtin_nontemporal_store((v4i_row)w, reinterpret_cast<v4i_row*>(p));
             else *reinterpret_cast<v4i_row*>(p) = w;
         } else {
             p[0] = w.x;
@@ -779,6 +779,35 @@ static bool split_rows(int64_t total, int nruns, int* pieces, int* piece_runs) {
     return *pieces > 1;
 }
 
+// Whether a C that is not read leaves past the caches.  Cached, its lines push the trace out of them, a C larger than the last-level
+// cache (256 MiB) all the more; streamed, it is on its way to memory from the first tile on, at the rate of the memory.  Times below in
+// us, streamed and cached.
+//  - Rows of C in whole 64-byte pieces: streamed (8 x 8192^2, 4096 rows 434 and 650; 2 x 2048^2, 2048 rows 17.3 and 19.0), but cached from
+//    128 to 256 MiB where the trace leaves it room, C and twice the trace up to 278 MiB (8 x 2048^2, 2048 rows 42.6 and 37.5, 6144 rows
+//    62.9 and 60.6; 60 x 1024^2, 2048 rows 63.4 and 60.6, 6144 rows 96 and 105, 16384 rows 230 and 273; 160 x 512^2, 2048 rows 49.5 and
+//    47.6, 6144 rows 89 and 100; 600 x 256^2, 2048 rows 62.8 and 61.5, 6144 rows 140 and 177).
+//  - Staggered, its writing lies beside the contraction of others, and the trace counts for more: cached from 80 MiB (20 << 20 counts) up
+//    to 230 MiB of C and twice the trace (8 x 2048^2, 2048 rows 40.2 and 34.3, 16384 rows 116 and 118; 103 x 512^2, 2048 rows 40.0 and
+//    38.2, 16384 rows 147 and 167; 400 x 256^2, 2048 rows 47.1 and 45.4, 6144 rows 94 and 105; 103 x 304^2, 2048 rows 37.1 and 38.2).
+//  - Rows that start inside a 64-byte piece share it with their neighbour tiles, and streamed, each of the two writes it to memory by
+//    itself: cached, except where the trace takes 64 MiB (90 x 700^2, 6144 rows 105 and 103, 16384 rows 231 and 263; 300 x 301^2, 6144
+//    rows 163 and 177) or C is larger than the last-level cache and the contraction takes about as long as writing twice (8 x 4001^2,
+//    6144 rows 268 and 209, 10240 rows 266 and 281; 12290^2, 6144 rows 291 and 247, 10240 rows 299 and 317), half as long where the
+//    product of C and trace says that little of either stays (4 x 8190^2, 2048 rows 476 and 364, 6144 rows 440 and 502; 60 x 1500^2, 2048
+//    rows 238 and 191, 6144 rows 232 and 302).  A small C of whole 16-byte vectors is better streamed (64 x 300^2, 2048 rows 25.7 and 26.9).
+static bool streams(int64_t elements, int N, int64_t trace_bytes, int64_t total, int nruns, bool stagger) {
+    constexpr int64_t MIB = 1 << 20;
+    const int64_t c_bytes = elements * 4, both = c_bytes + 2 * trace_bytes;
+    if (N % 16 == 0) {
+        if (stagger) return elements < 20 * MIB || both > 230 * MIB;
+        return elements < 32 * MIB || elements > 64 * MIB || both > 278 * MIB;
+    }
+    if (N % 4 == 0 && elements < 8 * MIB) return true;
+    if (c_bytes <= 256 * MIB) return trace_bytes >= 64 * MIB;
+    const double contraction = 347.0 * total * nruns / elements;          // its time over that of writing C twice
+    return contraction >= 0.85 || (contraction >= 0.45 && (double)c_bytes * trace_bytes >= 1.31e16);
+}
+
 swarm_status coact_reserve_tiles(swarm_ctx* ctx, int Npad) {
     if (ctx->capturing || Npad / TM > 65535) return SWARM_OK;
     const int32_t* order;
@@ -808,16 +837,17 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     }
     using kernel_t = void (*)(const v4i*, int, int, int, int32_t*, uint32_t, int, int, int, const int32_t*, uint32_t*,
                               const int64_t*, int32_t*, v4f*, int, int);
-    static const kernel_t kernels[4][4] = {
+    static const kernel_t kernels[5][4] = {
         {coact_syrk_kernel<0>, coact_syrk_kernel<1>, coact_syrk_kernel<2>, coact_syrk_kernel<0, true>},
         {coact_syrk_kernel<0, false, STREAM>, coact_syrk_kernel<1>, coact_syrk_kernel<2>, coact_syrk_kernel<0, true, STREAM>},
         {coact_syrk_kernel<0, false, STAGGER>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>, coact_syrk_kernel<0, true, STAGGER>},
+        {coact_syrk_kernel<0, false, STAGGER | STREAM>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>, coact_syrk_kernel<0, true, STAGGER | STREAM>},
         {coact_syrk_kernel<0, false, FINISH>, coact_syrk_kernel<1, false, FINISH>, coact_syrk_kernel<2, false, FINISH>, coact_syrk_kernel<0, true, FINISH>}};
     static const kernel_t part_kernel = coact_syrk_kernel<0, false, PART>;
     constexpr int RHO_LDS_BYTES = SYRK_LDS_BYTES + (TM + TN) * 4;
     if (!ctx->syrk_lds_opt_in) {
         hipError_t e = hipSuccess;
-        for (int f = 0; f < 3; ++f)
+        for (int f = 0; f < 4; ++f)
             for (int m = 0; m < 4 && e == hipSuccess; ++m)
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernels[f][m]), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         m == 3 ? RHO_LDS_BYTES : SYRK_LDS_BYTES);
@@ -829,22 +859,16 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
         }
         ctx->syrk_lds_opt_in = true;
     }
-    // A C of whole 64-byte pieces streams: cached, the lines of a large one push the trace out of the L2 (8 x 8192^2, 4096 rows: 434 us
-    // streamed, 650 cached; 65536^2: 3.5 and 5.5 ms) and those of a small one are all written out when the kernel ends (2 x 2048^2, 2048
-    // rows 17.3 and 19.0).  In between, from 128 MiB up to the 256 MiB last-level cache, the cached one wins: 8 x 2048^2, 2048 rows 42.7
-    // and 34.6, 8000 rows 75.6 and 67.8, 4 x 4096^2, 256 rows 57 and 48 (6 x 2048^2: level).  Rows of C that start inside a 64-byte
-    // piece share it with their neighbour tiles, and streamed, each of the two writes it to memory by itself: 4 x 4001^2, 256 rows
-    // 124 us streamed, 51 cached, 4096 rows 137 and 75; 12289^2 291 and 197, 300 and 222; 12304^2 154 and 157; but a small one of whole
-    // 16-byte vectors is better streamed (64 x 300^2, 2048 rows 25.7 and 26.9; 8 x 700^2 15.5 and 15.7; 8 x 1025^2 15.4 and 14.4).
-    const int64_t elements = (int64_t)H * N * N;
-    const bool whole = N % 16 == 0 || (N % 4 == 0 && elements < (int64_t)1 << 23);
-    const bool stream = whole && (elements < (int64_t)1 << 25 || elements > (int64_t)1 << 26);
     // A little more than the 1024 tiles that the device holds at once: all of those contract together, then all write, and the rest
     // runs nearly alone.  One after the other, the first ones' writing and the rest's start overlap the others' contraction: 16384
-    // rows of 8 x 2048 (1088 tiles) 126 -> 114 us without the trace, of 1 x 6000 (1128) 142 -> 130 with it, of 8 x 2304 (1368)
-    // 170 -> 167.  Nothing below (1012 tiles 101.2 -> 101.7), and past 1.4 rounds it is in the way (1680 tiles 213 -> 226).
-    const bool stagger = total > 1024 && total <= 1408;       // their C is cached whatever its rows: 16 to 23 million counts
-    const int form = stagger ? STAGGER : stream ? STREAM : PLAIN;
+    // rows of 8 x 2048 (1088 tiles) 126 -> 114 us without the trace, of 1 x 6000 (1176) 142 -> 130 with it, of 8 x 2304 (1368)
+    // 170 -> 167.  Nothing below (1012 tiles 101.2 -> 101.7), and past 1.4 rounds it is in the way (1680 tiles 213 -> 226), as it is where
+    // there is little to contract or to write (342 x 64^2 decayed, 512 rows 19.0 -> 19.9, 2048 rows 43.2 -> 44.4, 4096 rows 66.7 -> 65.8;
+    // 345 x 100^2, 128 rows 21.9 and 21.9).
+    const int64_t elements = (int64_t)H * N * N;
+    const bool stagger = total > 1024 && total <= 1408 && (nruns >= 32 || elements >= (int64_t)1 << 21);
+    const bool stream = streams(elements, N, (int64_t)H * nruns * Npad * 16, total, nruns, stagger);
+    const int form = (stagger ? STAGGER : PLAIN) | (stream ? STREAM : PLAIN);       // rows of `kernels`
     // Few tiles over many trace rows leave most of the device idle: the rows are cut into pieces.
     int pieces = 1, piece_runs = nruns;
     if (split_rows(total, nruns, &pieces, &piece_runs)) {
@@ -862,7 +886,7 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
         hipLaunchKernelGGL(part_kernel, dim3((unsigned)(units_xcd * 8)), dim3(64 * SYRK_WAVES), SYRK_LDS_BYTES, ctx->stream,
                            reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, (int)tiles_per_head, units, units_xcd, tile_order,
                            ctx->dev_flags, nullptr, nullptr, part, pieces, piece_runs);
-        hipLaunchKernelGGL(kernels[3][fused ? 3 : mode], dim3((unsigned)(total * SYRK_WAVES)), dim3(64), 32 * TROW + (TM + TN) * 4, ctx->stream,
+        hipLaunchKernelGGL(kernels[4][fused ? 3 : mode], dim3((unsigned)(total * SYRK_WAVES)), dim3(64), 32 * TROW + (TM + TN) * 4, ctx->stream,
                            reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, (int)tiles_per_head, (int)total, 0, tile_order,
                            ctx->dev_flags, cstar, rho, part, pieces, piece_runs);
         ctx->count_way = SWARM_WAY_DENSE_PIECES;
@@ -873,7 +897,8 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     hipLaunchKernelGGL(kernels[form][fused ? 3 : mode], grid, block, fused ? RHO_LDS_BYTES : SYRK_LDS_BYTES,
                        ctx->stream, reinterpret_cast<const v4i*>(ctx->trace), N, Npad, nruns, C, decay_q16, tph, tot, per_xcd,
                        tile_order, ctx->dev_flags, cstar, rho, nullptr, 1, nruns);
-    ctx->count_way = form == STAGGER ? SWARM_WAY_DENSE_STAGGERED : form == STREAM && mode == 0 ? SWARM_WAY_DENSE_STREAMED : SWARM_WAY_DENSE;
+    ctx->count_way = stagger ? (stream && mode == 0 ? SWARM_WAY_DENSE_STAGGERED_STREAMED : SWARM_WAY_DENSE_STAGGERED)
+                             : stream && mode == 0 ? SWARM_WAY_DENSE_STREAMED : SWARM_WAY_DENSE;
     return swarm_check_launch(ctx, "coact_syrk_kernel");
 }
 

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 POPCOUNT = 2
-DENSE, STREAMED, STAGGERED, PIECES, ROWS, BY_POPCOUNT = range(1, 7)           # SWARM_WAY_*
+DENSE, STREAMED, STAGGERED, PIECES, ROWS, BY_POPCOUNT, STAGGERED_STREAMED = range(1, 8)           # SWARM_WAY_*
 
 
 @pytest.fixture(scope="module")
@@ -77,7 +77,7 @@ def test_sparse_counts_equal_the_popcount_route(sw, rows, H, k, N, kind):
 # just inside and just outside each bound of the rule: trace rows, counts, k against N / 64, N and its alignment
 @pytest.mark.parametrize("rows,H,k,N,way", [
     (6144, 32, 64, 4096, ROWS), (6143, 32, 64, 4096, STREAMED), (6144, 31, 64, 4096, STREAMED), (6144, 32, 65, 4096, STREAMED),
-    (6144, 33, 63, 4080, STREAMED), (6144, 32, 64, 4112, ROWS), (6144, 32, 64, 4104, DENSE), (65535, 8, 8, 8192, ROWS),
+    (6144, 33, 63, 4080, STREAMED), (6144, 32, 64, 4112, ROWS), (6144, 32, 64, 4104, STREAMED), (65535, 8, 8, 8192, ROWS),
     (65536, 8, 8, 8192, STREAMED), (6144, 1, 8, 65536, ROWS), (6144, 1, 8, 65552, STREAMED)])
 def test_the_way_of_a_count(sw, rows, H, k, N, way):
     sel = selections("spread", rows, H, k, N)
@@ -138,7 +138,9 @@ def test_recordings_take_the_way_that_has_its_room(first, then, way):
 # 1088, 1176 (ragged rows of C) and 1368 tiles, where the dense product's workgroups finish one after the other; the fewest and the most
 # of them, 1026 and 1407, and 1020, 1023 and 1410 outside (N up to 256: three tiles a head)
 @pytest.mark.parametrize("rows,H,k,N,way", [(130, 8, 60, 2048, STAGGERED), (70, 1, 200, 6001, STAGGERED), (300, 8, 100, 2304, STAGGERED), (40, 102, 9, 512, STREAMED),
-                                            (150, 341, 9, 256, STREAMED), (150, 342, 9, 256, STAGGERED), (40, 469, 9, 255, STAGGERED), (40, 470, 9, 255, DENSE)])
+                                            (150, 341, 9, 256, STREAMED), (150, 342, 9, 256, STAGGERED), (40, 469, 9, 255, STAGGERED), (40, 470, 9, 255, DENSE),
+                                            (40, 110, 9, 304, STAGGERED_STREAMED), (5800, 400, 3, 256, STAGGERED_STREAMED), (4700, 400, 3, 256, STAGGERED),
+                                            (3584, 342, 2, 64, STREAMED), (3585, 342, 2, 64, STAGGERED_STREAMED)])
 def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N, way):
     sel = selections("any", rows, H, k, N).clamp_(0, N - 1)
     with torch.cuda.stream(sw.stream):
@@ -147,7 +149,7 @@ def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N, 
         ref = C.clone()
         for decay in (65536, 64881, 0):
             sw.coact_accumulate(sel, N, C, decay_q16=decay)
-            assert sw.last_way()[0] == (DENSE if decay and way == STREAMED else way)
+            assert sw.last_way()[0] == ({STREAMED: DENSE, STAGGERED_STREAMED: STAGGERED}.get(way, way) if decay else way)
             sw.coact_accumulate(sel, N, ref, decay_q16=decay, flags=POPCOUNT)
             assert torch.equal(C, ref)
         C.fill_(-7)
@@ -156,6 +158,30 @@ def test_dense_counts_of_a_little_more_than_the_device_holds(sw, rows, H, k, N, 
         assert torch.equal(C, ref)
         for got, want in zip((rho, queue, totals), sw.coact_density(ref, 1.0 - 3.0 / (rows * k * k))):
             assert torch.equal(got, want)
+    sw.stream.synchronize()
+    assert sw.device_status() == 0
+
+
+# which C leaves past the caches: whole 64-byte pieces below and above the last-level cache and, in between, beside a long trace; rows
+# that start inside a piece beside a trace of 64 MiB, and for a larger C where the contraction covers writing them twice
+@pytest.mark.parametrize("rows,H,k,N,way", [(300, 4, 9, 2800, STREAMED), (300, 12, 9, 2048, DENSE), (300, 17, 9, 2048, STREAMED), (6000, 160, 5, 512, STREAMED), (2048, 160, 5, 512, DENSE),
+                                            (3584, 300, 5, 301, STREAMED), (3072, 300, 5, 301, DENSE), (10240, 1, 100, 8201, STREAMED), (6144, 1, 100, 8201, DENSE),
+                                            (6144, 13, 20, 3003, STREAMED), (5120, 13, 20, 3003, DENSE), (40, 9, 9, 900, STREAMED), (40, 13, 9, 900, DENSE)])
+def test_which_dense_counts_are_streamed(sw, rows, H, k, N, way):
+    sel = selections("any", rows, H, k, N).clamp_(0, N - 1)
+    with torch.cuda.stream(sw.stream):
+        sw.stream.wait_stream(torch.cuda.default_stream())
+        C = torch.full((H, N, N), -7, dtype=torch.int32, device="cuda")
+        ref = torch.empty_like(C)
+        sw.coact_accumulate(sel, N, C, decay_q16=0)
+        assert sw.last_way()[0] == way
+        sw.coact_accumulate(sel, N, ref, decay_q16=0, flags=POPCOUNT)
+        assert torch.equal(C, ref)
+        C.fill_(-7)
+        tau = 1.0 - rows * k * k / float(N * N) / (rows * k * k)
+        got = sw.coact_build_density(sel, N, C, tau)
+        assert sw.last_way()[0] == way and torch.equal(C, ref)
+        assert all(torch.equal(g, w) for g, w in zip(got, sw.coact_density(ref, tau)))
     sw.stream.synchronize()
     assert sw.device_status() == 0
 
