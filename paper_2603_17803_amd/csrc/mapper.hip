@@ -339,9 +339,10 @@ __device__ __forceinline__ void place_singles(uint32_t n, int lane, const uint32
 constexpr int MAP_THREADS = 256;
 constexpr uint32_t MAP_SPLIT_MIN_ITEMS = 96;     // lists that cannot be longer stay one chain: it is shorter than finding the sub-problems
 // Two replicas half the SSDs apart, as the round-robin placement puts them, make D / 2 sub-problems of a pair, whose links are the
-// short ones: there the split pays from here on (86 items over 6 SSDs 8.75 -> 7.9 us, 65 8.3 -> 7.9, over 32 SSDs 19.8 -> 12.9; over
-// 9 to 16 SSDs, whose chain is no longer than over 8 but whose sub-problems take longer to find, 9.1 -> 9.4).  Any other table
-// loses up to 2 us by it (one sub-problem of 16 SSDs, 86 items: 10.3 -> 12.6 us).
+// short ones: there the split pays from here on (86 items over 6 SSDs 8.75 -> 7.9 us, 65 8.3 -> 7.9, over 18 SSDs 17.2 -> 14.2, 32 18.9 ->
+// 13.2; over 9 to 16 SSDs, whose chain is no longer than over 8 but whose sub-problems take longer to find, 9.1 -> 9.4; over 2 SSDs
+// there is one sub-problem, 8.4 -> 9.0, and past 32 more than 16 to be found one after the other: 36 SSDs 19.4 -> 24.8, 64 22.4 -> 45).
+// Any other table loses up to 2 us by it (one sub-problem of 16 SSDs, 86 items: 10.3 -> 12.6 us).
 constexpr uint32_t MAP_SPLIT_MIN_PAIRED = 64;
 
 // Copies n words from global memory to LDS with batches of independent loads (all loads of a batch
@@ -961,7 +962,8 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
         const uint32_t before = wave_excl_scan(mine, &total);
         uint32_t least = MAP_SPLIT_MIN_ITEMS;
         if constexpr (!BIG) {
-            if (__builtin_expect(a.R == 2 && total - MAP_SPLIT_MIN_PAIRED < MAP_SPLIT_MIN_ITEMS - MAP_SPLIT_MIN_PAIRED && stage_tab && (a.D <= 8 || a.D > 16), 0)) {
+            if (__builtin_expect((a.D <= 8 || a.D > 16) && a.D > 2 && a.D <= 32 && a.R == 2 &&
+                                 total - MAP_SPLIT_MIN_PAIRED < MAP_SPLIT_MIN_ITEMS - MAP_SPLIT_MIN_PAIRED && stage_tab, 0)) {
                 // 64 clusters across the table tell; a second slot may be unused where there are more than two pairs
                 const int c = (int)((int64_t)lane * a.Nc >> 6);
                 if (__ballot((s_rep[2 * c + 1] >= 0 || a.D <= 4) && 2 * abs(s_rep[2 * c] - s_rep[2 * c + 1]) != a.D) == 0) least = MAP_SPLIT_MIN_PAIRED;

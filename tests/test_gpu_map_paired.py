@@ -35,3 +35,30 @@ def test_queues_of_paired_replicas(D, items, kind):
     for g, r in zip(got, ref):
         assert np.array_equal(g.cpu().numpy(), r)
     sw.close()
+
+
+@pytest.mark.parametrize("D", [36, 64])
+def test_paired_replicas_over_many_ssds_are_no_slower(D):
+    """75 clusters whose replicas stand half the SSDs apart, against the same list with the second replica one SSD further on, which is one
+    chain: what finding more than 16 sub-problems costs is more than their chains save (64 SSDs 45 and 22 us)."""
+    from paper_2603_17803_amd import binding
+    sw = binding.Swarm(0)
+    H, Nc, N, items = 8, 128, 128, 75
+    e2c = torch.arange(N, dtype=torch.int32, device="cuda").expand(H, N).contiguous()
+    sel = torch.stack([torch.randperm(N, device="cuda")[torch.arange(120, device="cuda") % items] for _ in range(H)]).int()      # 120 picks
+    first = torch.arange(H * Nc, dtype=torch.int32, device="cuda") % D
+    best = [float("inf")] * 2
+    for rep in range(6):
+        for i in range(2):
+            table = torch.stack([first, (first + D // 2 + i) % D], 1).int().contiguous()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            for _ in range(40):
+                sw.map_requests(sel, H, N, e2c, Nc, table, D, None, None)
+            b.record()
+            b.synchronize()
+            if rep:
+                best[i] = min(best[i], a.elapsed_time(b) / 40)
+    sw.close()
+    assert best[0] < 1.15 * best[1], best
