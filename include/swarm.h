@@ -20,7 +20,10 @@
  *    synchronises the stream); a call whose shapes are no larger than those of an earlier call
  *    needs no more scratch, so a warmed-up call sequence may be captured into a HIP graph.  (The
  *    co-activation calls also keep one small schedule per number of entries, N rounded up to 256:
- *    the first call with another N allocates that, and cannot be the recorded one.)
+ *    the first call with another N allocates that, and cannot be the recorded one.)  Some counts and
+ *    queues take a shorter way with scratch of its own, named at their calls: a first call of that
+ *    kind may allocate it whatever came before, and without it -- while a stream is captured, or on
+ *    a device without the room -- the call takes the way that needs none, with the same results.
  *  - The return value is the only host-side error channel.  Nothing throws or aborts.  Bad
  *    arguments give SWARM_EINVAL before anything is enqueued.  Bad *data* (an index outside
  *    its range) never makes a kernel read or write out of bounds: the offending item is
@@ -179,9 +182,8 @@ swarm_status swarm_score(swarm_ctx* ctx, const swarm_keys* keys, const void* q, 
  *     decay_q16 == 0     : C  = A^T A            (C is not read)
  *     otherwise          : C  = floor((C * decay_q16 + 2^15) / 2^16) + A^T A   (int64 intermediate)
  * An overwriting call whose selections are sparse and many (k <= N / 64, 6144 rows, 2^29 counts or more) adds them up row by row of C
- * instead, with copies of the selections in the context's scratch (about 2.3 times H*rows*k*2 bytes), and a call of few tiles
- * over many rows keeps partial counts there (64 MiB at most): the same counts; without that room, or recording before it is
- * there, either goes the way described above.
+ * instead, with copies of the selections in the context's scratch (at most 6 bytes for each id and 300 for each row and head; rows
+ * rounded up to 32), and a call of few tiles over many rows keeps partial counts there (64 MiB at most): the same counts.
  * The decayed form lets stale statistics fade when the workload drifts (the degradation of
  * co-activation statistics is the paper's fourth challenge, Section 3.2); the mechanism itself is
  * not in the paper.
@@ -217,7 +219,8 @@ swarm_status swarm_coact_accumulate(swarm_ctx* ctx, const int32_t* idx, int64_t 
  * C          device, int32 [H][N][N], 16-byte aligned (as produced by swarm_coact_accumulate).
  * totals_in  device, int64 [H], or NULL to sum C (one more pass over C).
  * rho        device out, int32 [H][N].
- * queue      device out, int32 [H][N], or NULL to skip the queue.
+ * queue      device out, int32 [H][N], or NULL to skip the queue.  For more than 8192 entries it is sorted with scratch: H*N ids and
+ *            512 counts for each head and 2048 entries, 4 bytes each.
  * totals_out device out, int64 [H], or NULL.
  * Errors: SWARM_EINVAL for NULL C or rho, H/N < 1, misaligned pointers, unknown flags.
  */

@@ -359,7 +359,7 @@ RowsPlan plan_of(int N, int k) {
         room = mean + s + 1;
     }
     p.L = 64 / (64 / ((room + 7) / 8));                       // as long as as many records fit a wave
-    p.ext_groups = (k + 7 * nseg) / 8;
+    p.ext_groups = nseg > 1 ? (k + 7 * nseg) / 8 : 0;         // a single segment's record holds all of k
     return p;
 }
 
@@ -377,7 +377,7 @@ bool rows_route(int64_t rows, int H, int N, int k) {
     return rows * H <= (int64_t)1 << 25 && (int64_t)H * N * N >= (int64_t)1 << 29 && rows >= 6144 && rows <= 65535 && N >= 4096 && N <= MAX_SEGMENTS * MAX_SEGMENT && N % 16 == 0 && k <= N / 64;
 }
 
-// Scratch for the records, their overflow and the counters of rows handed out.
+// Scratch for the records, their overflow and the counters of rows handed out: at most 6 bytes per id and 300 per selection (row and head).
 size_t rows_list_bytes(int64_t rows, int H, int k, int N) {
     const RowsPlan p = plan_of(N, k);
     const int64_t recs = (rows + 31) / 32 * 32;

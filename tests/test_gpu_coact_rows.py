@@ -93,6 +93,25 @@ def test_the_way_of_a_count(sw, rows, H, k, N, way):
     assert sw.device_status() == 0
 
 
+# one segment and several, wide and narrow selections
+@pytest.mark.parametrize("rows,H,k,N", [(6144, 8, 128, 8192), (6144, 8, 8, 8192), (6151, 2, 256, 16384), (6144, 1, 1, 24576), (6144, 1, 1024, 65536), (6144, 1, 17, 65536), (6144, 1, 1, 65536)])
+def test_scratch_of_a_sparse_count(rows, H, k, N):
+    """What the header says of it: at most 6 bytes for each id and 300 for each row and head, beside the trace; where one segment holds
+    all columns, a record's 16 bytes for eight ids and nothing for pieces that go on."""
+    from paper_2603_17803_amd import binding
+    sw = binding.Swarm(0)
+    sel = selections("spread", rows, H, k, N)
+    sw.coact_accumulate(sel, N, torch.empty(H, N, N, dtype=torch.int32, device="cuda"), decay_q16=0)
+    way, _, held = sw.last_way()
+    trace = H * ((N + 255) // 256 * 256) * ((rows + 511) // 512 * 512) // 8
+    records = (rows + 31) // 32 * 32 * H
+    assert way == ROWS
+    assert held - trace <= records * (6 * k + 300) + 4096
+    if N <= 8192:
+        assert held - trace <= records * (k + 7) // 8 * 16 + 4096
+    sw.close()
+
+
 def test_sparse_counts_equal_the_oracle(sw):
     rows, H, k, N = 6150, 32, 32, 4096                       # strata of 128 entries: distinct ids, as the oracle asks
     sel = selections("spread", rows, H, k, N, seed=5)

@@ -38,6 +38,7 @@ def test_queue_order(N, kind):
     assert np.array_equal(got.cpu().numpy(), rho)
     assert np.array_equal(queue.cpu().numpy(), np.argsort(-rho, axis=1, kind="stable"))
     assert sw.last_way()[1] == (binding.SWARM_WAY_QUEUE_LDS if N <= 8192 else binding.SWARM_WAY_QUEUE_SORTED)
+    assert sw.last_way()[2] == (0 if N <= 8192 else 4 * (H * N + H * ((N + 2047) // 2048) * 512))      # as the header says
     sw.close()
 
 
