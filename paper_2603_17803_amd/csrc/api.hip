@@ -13,8 +13,8 @@ swarm_status swarm_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes) 
         snprintf(ctx->err, sizeof(ctx->err), "scratch must grow to %zu bytes while recording; run the sequence once first", bytes);
         return SWARM_EINVAL;
     }
-    SWARM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (*buf) {
+        SWARM_HIP(ctx, hipStreamSynchronize(ctx->stream));
         if (ctx->recorded) {
             // a recorded graph may replay kernels that use the old buffer: keep it until the context goes
             try {
@@ -38,6 +38,20 @@ swarm_status swarm_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes) 
     }
     *have = bytes;
     return SWARM_OK;
+}
+
+bool swarm_capturing(const swarm_ctx* ctx) {
+    if (ctx->capturing) return true;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return ctx->stream && hipStreamIsCapturing(ctx->stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
+swarm_status swarm_try_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes, bool* there) {
+    *there = *have >= bytes;
+    if (*there || swarm_capturing(ctx)) return SWARM_OK;
+    const swarm_status st = swarm_grow(ctx, buf, have, bytes);
+    *there = st == SWARM_OK;
+    return st == SWARM_ENOMEM ? SWARM_OK : st;
 }
 
 extern "C" {
@@ -246,15 +260,8 @@ static swarm_status check_coact_args(swarm_ctx* ctx, const char* fn, const int32
 static swarm_status take_rows_route(swarm_ctx* ctx, int64_t rows, int32_t H, int32_t k, int32_t N, int Npad, bool* sparse) {
     *sparse = rows_route(rows, H, N, k);
     if (!*sparse) return SWARM_OK;
-    const size_t bytes = rows_list_bytes(rows, H, k, N);
-    if (ctx->lists_bytes < bytes && ctx->capturing) {
-        *sparse = false;
-        return SWARM_OK;
-    }
-    const swarm_status st = swarm_grow(ctx, &ctx->lists, &ctx->lists_bytes, bytes);
-    if (st == SWARM_ENOMEM) *sparse = false;
-    else if (st != SWARM_OK) return st;
-    return coact_reserve_tiles(ctx, Npad);
+    const swarm_status st = swarm_try_grow(ctx, &ctx->lists, &ctx->lists_bytes, rows_list_bytes(rows, H, k, N), sparse);
+    return st == SWARM_OK ? coact_reserve_tiles(ctx, Npad) : st;
 }
 
 swarm_status swarm_coact_accumulate(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int32_t H, int32_t k,

@@ -809,7 +809,7 @@ static bool streams(int64_t elements, int N, int64_t trace_bytes, int64_t total,
 }
 
 swarm_status coact_reserve_tiles(swarm_ctx* ctx, int Npad) {
-    if (ctx->capturing || Npad / TM > 65535) return SWARM_OK;
+    if (swarm_capturing(ctx) || Npad / TM > 65535) return SWARM_OK;
     const int32_t* order;
     return tile_order_for(ctx, Npad / TM, &order);
 }
@@ -872,13 +872,10 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     // Few tiles over many trace rows leave most of the device idle: the rows are cut into pieces.
     int pieces = 1, piece_runs = nruns;
     if (split_rows(total, nruns, &pieces, &piece_runs)) {
-        const size_t bytes = (size_t)total * pieces * (TM * TN * sizeof(float));
-        if (ctx->capturing && ctx->part_bytes < bytes) pieces = 1;      // a recording without the room goes without, as does a device without it
-        else {
-            st = swarm_grow(ctx, &ctx->part, &ctx->part_bytes, bytes);
-            if (st == SWARM_ENOMEM) pieces = 1;
-            else if (st != SWARM_OK) return st;
-        }
+        bool there;
+        st = swarm_try_grow(ctx, &ctx->part, &ctx->part_bytes, (size_t)total * pieces * (TM * TN * sizeof(float)), &there);
+        if (st != SWARM_OK) return st;
+        if (!there) pieces = 1;
     }
     if (pieces > 1) {
         const int units = (int)total * pieces, units_xcd = (units + 7) / 8;

@@ -84,8 +84,12 @@ swarm_status swarm_check_score_args(swarm_ctx* ctx, const char* fn, const swarm_
 swarm_status swarm_static_scratch_init(swarm_ctx* ctx);
 size_t select_cand_bytes(int64_t rows, int N, int k, bool scored);   // scratch the sliced selection takes for its winners (0: not sliced)
 
-// Grows a scratch buffer to at least `bytes` (never shrinks).  Allocation synchronises the stream.
+// Grows a scratch buffer to at least `bytes` (never shrinks).  Outgrowing a buffer synchronises the stream.
 swarm_status swarm_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes);
+// The same for scratch that a call can do without: *there says whether it is there.  It is not grown while the context's stream is
+// captured, by swarm_capture_begin or by the caller's own means, and a device without the room is no error.
+swarm_status swarm_try_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes, bool* there);
+bool swarm_capturing(const swarm_ctx* ctx);
 
 // Fixed scratch handed to the launchers in place of the context's growing buffers (for the entry point that
 // may not allocate): the winners of the sliced selection.

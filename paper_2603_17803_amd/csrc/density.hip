@@ -411,13 +411,9 @@ swarm_status launch_medoid_rank(swarm_ctx* ctx, const int32_t* rho, int H, int N
         ctx->queue_way = SWARM_WAY_QUEUE_LDS;
         return swarm_check_launch(ctx, "rank_small_kernel");
     }
-    const size_t words = rank_scratch_words(H, N);
-    bool sorted = !ctx->capturing || ctx->rank_bytes >= words * 4;      // a recording without the room compares, as does a device without it
-    if (sorted) {
-        const swarm_status st = swarm_grow(ctx, reinterpret_cast<void**>(&ctx->rank), &ctx->rank_bytes, words * 4);
-        if (st == SWARM_ENOMEM) sorted = false;
-        else if (st != SWARM_OK) return st;
-    }
+    bool sorted;
+    const swarm_status st = swarm_try_grow(ctx, reinterpret_cast<void**>(&ctx->rank), &ctx->rank_bytes, rank_scratch_words(H, N) * 4, &sorted);
+    if (st != SWARM_OK) return st;
     if (!sorted) {
         hipLaunchKernelGGL(medoid_rank_kernel, dim3((unsigned)((N + RANK_ENTRIES - 1) / RANK_ENTRIES), (unsigned)H),
                            dim3(RANK_ENTRIES * RANK_PARTS), 0, ctx->stream, rho, N, queue);

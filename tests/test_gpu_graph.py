@@ -215,3 +215,72 @@ def test_a_selection_no_larger_than_an_earlier_one_can_be_recorded(H, large, sma
         finally:
             binding.swarm_graph_destroy(graph)
             sw.close()
+
+
+@pytest.mark.parametrize("kind", ["queue", "pieces", "sparse"])
+def test_a_capture_of_the_callers_own_finds_no_scratch(kind):
+    """Calls whose shorter way has scratch of its own, the first of their kind inside a graph that the caller captures by its own means (no
+    swarm_capture_begin), after calls no smaller than them: they take the way that needs none.  Every replay is right, and an eager call
+    afterwards takes the shorter way."""
+    from paper_2603_17803_amd import binding
+    stream = torch.cuda.Stream()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    sw = binding.Swarm(0, stream=stream)
+    if kind == "queue":
+        N = 8200
+        C = torch.randint(0, 9, (1, N, N), generator=g, device="cuda", dtype=torch.int32)
+        out = (torch.empty(1, N, dtype=torch.int32, device="cuda"), torch.empty(1, N, dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int64, device="cuda"))
+        total = torch.full((1,), 8, dtype=torch.int64, device="cuda")
+        ways = (binding.SWARM_WAY_QUEUE_COMPARED, binding.SWARM_WAY_QUEUE_SORTED)
+
+        def call():
+            sw.coact_density(C, 0.5, totals_in=total, out=out)
+            return sw.last_way()[1]
+
+        def refresh():
+            C.copy_(torch.randint(0, 9, (1, N, N), generator=g, device="cuda", dtype=torch.int32))
+            rho = (C >= 4).sum(2)
+            return [rho.int(), torch.sort(-rho, dim=1, stable=True).indices.int()]
+    else:
+        rows, H, k, N = (8192, 1, 16, 1024) if kind == "pieces" else (6144, 8, 64, 8192)
+        wide = torch.randint(0, N, (rows, H, 4 * k), generator=g, device="cuda", dtype=torch.int32)
+        sel = wide[:, :, :k].contiguous()
+        C = torch.empty(H, N, N, dtype=torch.int32, device="cuda")
+        ref = torch.empty_like(C)
+        out = (C,)
+        ways = (binding.SWARM_WAY_DENSE_STREAMED, binding.SWARM_WAY_DENSE_PIECES if kind == "pieces" else binding.SWARM_WAY_ROWS)
+        torch.cuda.synchronize()
+        sw.coact_accumulate(wide, N, ref, decay_q16=0, flags=2)                # the trace's room
+        sw.coact_accumulate(wide[:600], N, C, decay_q16=0)                     # the tile schedule
+        stream.synchronize()
+
+        def call():
+            sw.coact_accumulate(sel, N, C, decay_q16=0)
+            return sw.last_way()[0]
+
+        def refresh():
+            sel.copy_(torch.randint(0, N, (rows, H, k), generator=g, device="cuda", dtype=torch.int32))
+            torch.cuda.synchronize()
+            sw.coact_accumulate(sel, N, ref, decay_q16=0, flags=2)
+            stream.synchronize()
+            return [ref]
+
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        assert call() == ways[0]
+    for _ in range(3):
+        want = refresh()
+        for o in out:
+            o.fill_(-1)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+    with torch.cuda.stream(stream):
+        assert call() == ways[1]
+    stream.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, want)) and sw.device_status() == 0
+    del graph
+    sw.close()
