@@ -152,14 +152,10 @@ class Harness:
         return out
 
 
-def summed_by_rows(H, N, rows, k):
-    """Whether the library sums a fresh build row by row (sparse traces) instead of contracting it on the matrix cores."""
-    return H * N * N >= 1 << 29 and 6144 <= rows <= 65535 and 4096 <= N <= 65536 and N % 16 == 0 and k <= N // 64
-
-
-def coact_rooflines(H, N, rows, k, coact_ms, peaks, decayed):
+def coact_rooflines(H, N, rows, k, coact_ms, peaks, decayed, by_rows):
     """Both roofs of the co-activation build and the one that binds it.  C is written once (read and written when an
-    old matrix is updated), so below peak_ops / peak_bytes operations per byte it is the memory system."""
+    old matrix is updated), so below peak_ops / peak_bytes operations per byte it is the memory system.
+    by_rows: the library says that it summed C row by row (sparse traces) instead of contracting the trace."""
     Tpad = (rows + 511) // 512 * 512
     tiles = (N + 255) // 256 * 2                                               # tiles of 128 x 128 along one side (the trace is padded to 256 entries)
     issued_ops = 2.0 * H * (tiles * (tiles + 1) // 2) * 128 * 128 * Tpad        # MFMA ops actually issued (tiles on or above the diagonal)
@@ -172,7 +168,7 @@ def coact_rooflines(H, N, rows, k, coact_ms, peaks, decayed):
             "frac_of_measured_fp4_peak": round(tops / peaks["mfma_fp4_TOPs"], 4)}
     hbm = {"achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4), "bytes": nbytes,
            "frac_of_measured_write_peak": round(gbs / peaks["hbm_write_GBs"], 4)}
-    if not decayed and summed_by_rows(H, N, rows, k):                          # no matrix instruction is issued
+    if by_rows:                                                                # no matrix instruction is issued
         return {"kernel": "coact_rows_kernel (rows of C summed in LDS, exact counts)", "bound": "hbm", "achieved": hbm["achieved"], "peak": hbm["peak"],
                 "unit": hbm["unit"], "frac": hbm["frac"], "why": "C written once beside an equal time of LDS increments", "mfma": None, "hbm": hbm,
                 "issued_ops": None, "increments": float(rows) * H * k * k}
@@ -258,6 +254,7 @@ def single_stream(args, cfg, binding, W, torch, np, stream):
     step_us, step_us_min = hx.stage(decode_steps, reps, T)
     map_us, map_us_min = hx.stage(map_steps, reps, T)
     coact_us, coact_us_min = hx.stage(coact, reps, 1)
+    by_rows = sw.last_way()[0] == binding.SWARM_WAY_ROWS
 
     def coact_popcount():
         sw.coact_accumulate(idx_all, N, Cm, decay_q16=0, flags=binding.SWARM_COACT_POPCOUNT)
@@ -314,7 +311,7 @@ def single_stream(args, cfg, binding, W, torch, np, stream):
     roof_steps = HBM_PEAK_GBS * 1e9 / unit_bytes
     dense_ops = 2.0 * H * N * N * T
     increments = float(T) * H * k * k                                            # the trace's own work: k^2 pair counts per row
-    roof_coact = coact_rooflines(H, N, T, k, coact_ms, peaks, decayed=False)
+    roof_coact = coact_rooflines(H, N, T, k, coact_ms, peaks, decayed=False, by_rows=by_rows)
     roof_coact.update({"dense_equivalent_tops": round(dense_ops / (coact_ms * 1e-3) / 1e12, 1),
                        "ms_per_build_incl_trace": round(coact_ms, 3), "ms_min": round(coact_us_min * 1e-3, 3),
                        "pair_increments_per_s": round(increments / (coact_ms * 1e-3), 0),
@@ -447,6 +444,7 @@ def batched(args, cfg, binding, W, torch, np, stream):
     sel_us, sel_us_min = hx.stage(select_steps, reps, win)
     map_us, map_us_min = hx.stage(map_steps, reps, win)
     coact_us, coact_us_min = hx.stage(coact, reps, 1)
+    by_rows = sw.last_way()[0] == binding.SWARM_WAY_ROWS
     peaks = hx.peaks(binding)
 
     L = (2 if cfg.unit == "page" else 1) * cfg.d
@@ -457,7 +455,7 @@ def batched(args, cfg, binding, W, torch, np, stream):
     unit_bytes = H * N * row_bytes + B * H * G * cfg.d * 2 + B * H * k * 4
     roof_steps = HBM_PEAK_GBS * 1e9 / unit_bytes
     coact_ms = coact_us * 1e-3
-    roof_coact = coact_rooflines(H, N, win * B, cfg.k, coact_ms, peaks, decayed=True)
+    roof_coact = coact_rooflines(H, N, win * B, cfg.k, coact_ms, peaks, decayed=True, by_rows=by_rows)
     roof_coact.update({"ms_per_window_incl_trace": round(coact_ms, 3), "ms_min": round(coact_us_min * 1e-3, 3),
                        "trace_rows_per_window": win * B})
     step_us = wall / args.steps / T * 1e6
@@ -523,7 +521,7 @@ def only_coact(args, cfg, binding, W, torch, stream):
     ms = e0.elapsed_time(e1) / args.steps
     tiles = (N + 255) // 256 * 2
     issued = 2.0 * H * (tiles * (tiles + 1) // 2) * 128 * 128 * ((T + 511) // 512 * 512)
-    if summed_by_rows(H, N, T, k):
+    if sw.last_way()[0] == binding.SWARM_WAY_ROWS:
         print(json.dumps({"only": "coact", "workload": cfg.name, "kernel": "coact_rows_kernel", "ms_per_build_incl_trace": round(ms, 3),
                           "increments": float(T) * H * k * k, "C_write_GBs": round(H * N * N * 4 / (ms * 1e-3) / 1e9, 1)}), flush=True)
         sw.close()

@@ -35,3 +35,12 @@ def test_counter_traffic_is_tied_to_the_scoring_source(tmp_path, monkeypatch):
     assert bench.counter_traffic("w") == 12345
     f.write_text(f"traffic_bytes_per_launch: 12345\nscore_hip_sha256: {'0' * 64}\n")
     assert bench.counter_traffic("w") is None
+
+
+def test_the_build_is_priced_by_the_way_that_the_library_took():
+    peaks = {"mfma_fp4_TOPs": 9850.0, "hbm_write_GBs": 6700.0}
+    for by_rows in (False, True):
+        for H, N, rows, k in ((1, 65536, 8192, 1024), (8, 8192, 4096, 256)):         # whatever the sizes
+            roof = bench.coact_rooflines(H, N, rows, k, 3.5, peaks, False, by_rows)
+            assert roof["kernel"].startswith("coact_rows_kernel" if by_rows else "coact_syrk_kernel")
+            assert (roof["issued_ops"] is None) == by_rows
