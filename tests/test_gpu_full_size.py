@@ -156,6 +156,38 @@ def test_token_stress_full_size(sw):
     cfg = W.CONFIGS["token_stress"]
     rng = np.random.default_rng(13)
     run_full(sw, cfg, rng.choice(cfg.T, 3, replace=False), rng)
+    from paper_2603_17803_amd import binding
+    assert sw.last_way()[0] == binding.SWARM_WAY_ROWS
+
+
+def test_token_stress_size_by_the_dense_product(sw):
+    """The same 16 GiB C by the matrix cores: selections one entry too wide for the row sums, overwriting (streamed) with and without the
+    density count, then accumulated and decayed; against the popcount route on the device, and a block of rows against the oracle."""
+    from paper_2603_17803_amd import binding
+    N, k, T = 65536, 1025, 2500
+    rng = np.random.default_rng(17)
+    idx = np.sort(rng.random((T, N), dtype=np.float32).argpartition(k, axis=1)[:, :k].astype(np.int32), axis=1)[:, None]
+    sel = dev(idx)
+    C = torch.empty((1, N, N), dtype=torch.int32, device="cuda")
+    ref = torch.empty_like(C)
+    sw.coact_accumulate(sel, N, ref, decay_q16=0, flags=binding.SWARM_COACT_POPCOUNT)
+    assert np.array_equal(ref[0, 4096:6144].cpu().numpy(), oracle.coact_rows(idx, N, 0, 4096, 6144, nthreads=16))
+    sw.coact_accumulate(sel, N, C, decay_q16=0)
+    assert sw.last_way()[0] == binding.SWARM_WAY_DENSE_STREAMED and torch.equal(C, ref)
+    tau = 1.0 - 3.0 / (float(T) * k * k)
+    want = sw.coact_density(ref, tau)
+    C.fill_(-3)
+    got = sw.coact_build_density(sel, N, C, tau)
+    assert sw.last_way()[0] == binding.SWARM_WAY_DENSE_STREAMED and torch.equal(C, ref)
+    assert all(torch.equal(g, w) for g, w in zip(got, want)) and 0 < int(got[0].max()) < N
+    for decay in (65536, 64881):
+        sw.coact_accumulate(sel[:700], N, C, decay_q16=decay)
+        assert sw.last_way()[0] == binding.SWARM_WAY_DENSE
+        sw.coact_accumulate(sel[:700], N, ref, decay_q16=decay, flags=binding.SWARM_COACT_POPCOUNT)
+        assert torch.equal(C, ref)
+    assert sw.device_status() == 0
+    del C, ref
+    torch.cuda.empty_cache()
 
 
 def test_counts_up_to_the_row_limit_stay_exact(sw):
