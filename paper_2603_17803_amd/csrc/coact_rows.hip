@@ -365,16 +365,23 @@ RowsPlan plan_of(int N, int k) {
 
 }  // namespace
 
-// Where the increments win, measured on both ways for N from 2048 to 65536, 1024 to 16384 trace rows, k from N / 44 to N / 128:
-//  - k <= N / 64: 8192 rows 1.1 to 1.7 times as fast at N / 64, 0.75 to 1.0 at N / 44 (three records to a wave become two);
-//  - 6144 rows: below, the dense product waits for the writing of C as well (4096 rows 0.91 to 1.1, 5120 0.97 to 1.2, 6144 1.04 to 1.4);
-//  - N >= 4096: a row of 2048 is over before the two barriers are (8192 rows of 4 heads: 0.89);
-//  - N a multiple of 16: a 64-byte piece of C shared by two XCDs is written twice (N = 12289: 0.85, 24592: 1.27 at 6144 rows).
-//  - 2^29 counts: an entry that all of 8192 rows activate keeps one workgroup busy for up to 350 us, which a build of this size (800
-//    us and more by the dense product) hides and a smaller one does not.
+// Where the increments win, measured on both ways for N from 2048 to 65536, 1024 to 65535 trace rows, k from N / 44 to N / 128, and ids
+// spread evenly, in pages, with a sink and a window, by Zipf's law, at fixed distances and the same in every row:
+//  - k <= N / 64: at N / 44 three records to a wave become two (8192 rows 0.75 to 1.0 times as fast before rows were handed out);
+//  - 6144 rows: below, the dense product waits for the writing of C as well (5120 rows 0.97 to 1.2);
+//  - N >= 5120, or from 4096 on where more rows or shorter selections outweigh the two barriers of a row: spread ids, and with a sink,
+//    32 x 4096^2, k = 64: 6144 rows 0.96 and 0.83, 8192 1.07 and 0.92, 16384 1.15 and 1.01; k = 32: 6144 rows 1.04 and 0.97, 8192 1.13
+//    and 1.02; 21 x 5120^2, k = 80: 6144 rows 1.11 and 0.98, 8192 1.24 and 1.10;
+//  - N a multiple of 16: a 64-byte piece of C shared by two XCDs is written twice (N = 12289: 0.85);
+//  - 2^29 counts: an entry that all of 8192 rows activate keeps one workgroup busy for some 200 us, which a build of this size (600 us and
+//    more by the dense product) hides and a smaller one does not.
+// 8192 rows, k = N / 64, spread ids: 8 x 8192^2 733 -> 493 us, 4 x 12288^2 829 -> 541, 32768^2 1391 -> 803, 65536^2 5.7 -> 3.2 ms.  The worst
+// that was found inside these bounds: pages of 64 from every ninth block of 40960 entries 0.90, the same ids in all of 6144 rows 0.96.
 // The ids of a segment and the trace rows have to fit 16 bits, a wave per selection one launch.
 bool rows_route(int64_t rows, int H, int N, int k) {
-    return rows * H <= (int64_t)1 << 25 && (int64_t)H * N * N >= (int64_t)1 << 29 && rows >= 6144 && rows <= 65535 && N >= 4096 && N <= MAX_SEGMENTS * MAX_SEGMENT && N % 16 == 0 && k <= N / 64;
+    if (rows < 6144 || rows > 65535 || rows * H > (int64_t)1 << 25) return false;
+    if (N < 4096 || N > MAX_SEGMENTS * MAX_SEGMENT || N % 16 != 0 || k > N / 64 || (int64_t)H * N * N < (int64_t)1 << 29) return false;
+    return N >= 5120 || rows >= 16384 || (rows >= 8192 && k <= N / 128);
 }
 
 // Scratch for the records, their overflow and the counters of rows handed out: at most 6 bytes per id and 300 per selection (row and head).
