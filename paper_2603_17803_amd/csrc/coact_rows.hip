@@ -16,6 +16,7 @@
 // beyond it, rare unless the ids come in whole blocks, go to an overflow.
 // 8192 selections of 1024 out of 65536 entries: 5.7 ms by the dense product, 3.5 ms here with trace and records; 3.3 ms are
 // increments, listing and clearing, 3.1 to 3.3 ms the writing of C by itself (5.5 TB/s, what row pieces reach), side by side.
+#include <numeric>
 #include <type_traits>
 
 #include "common.h"
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restric
 template <bool RHO, bool SEG>
 __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __restrict__ bits, const uint4* __restrict__ lists, int recs, int H, int N,
                                                            int Npad, int nruns, int nseg_log2, int L, int ext_groups, uint32_t* __restrict__ queue,
-                                                           int32_t* __restrict__ C, const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
+                                                           uint32_t row_step, uint32_t groups_inv, int32_t* __restrict__ C, const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     const int nseg = 1 << nseg_log2, cols = seg_columns(N, nseg);
     uint32_t* cnt = smem;                                                        // cols + DUMMY_WORDS counters
@@ -166,16 +167,22 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
     if (tid < 2) tcount[tid] = 0;
     __syncthreads();
 
-    // An XCD's rows are handed out in order, each to the first workgroup that gets there: what a row costs differs by its entry's count,
+    // An XCD's rows are handed out one by one, each to the first workgroup that gets there: what a row costs differs by its entry's count,
     // and dealt beforehand, by equal rounds or rounds turned by a hash, often activated entries pile up on some workgroups (every 64th
     // entry in each of 8192 selections of 1024: 470 ms and 4.7, handed out 4.3; nine neighbours every 576 entries 9.6 and 3.9; any 1024
     // entries 5.8 and 4.2; ids spread evenly 3.45 and 3.1).  A workgroup's first two rows are known; the number of a later one is asked
     // for while two others are before it.  Where several XCDs share a segment, the rows are dealt to them as the blocks to the segments.
-    struct Place { int h, i, chunk, before; };                 // before: rows of earlier heads
+    // They are handed out in groups of eight (whose trace words share lines) spread over the head, not in order: where some region of the
+    // entries is activated more than another, its increments then lie beside the other's writing (half a run, the rest of the ids in the
+    // lower half of 65536: in order 3.97 ms, spread 3.16; pages of 64, as everywhere alike, 3.84 and 4.05).
+    struct Place { int h, i, chunk, before, row; };            // before: rows of earlier heads
     auto begin = [&](Place& p, uint32_t place) __attribute__((always_inline)) {
         p.chunk = 0;
         p.i = (int)(place * (uint32_t)parts + ((part + turn_of(place)) & (uint32_t)(parts - 1))) - p.before;
         while (p.i >= N) { p.i -= N; p.before += N; ++p.h; }
+        const uint32_t groups = (uint32_t)N / 8, x = (uint32_t)p.i / 8 * row_step;
+        const int group = (int)(x - __umulhi(x, groups_inv) * groups);             // x modulo groups, or groups less
+        p.row = (group < 0 ? group + (int)groups : group) * 8 + (p.i & 7);
     };
     uint32_t upcoming = slot + SLOTS;
     auto advance = [&](Place& p) __attribute__((always_inline)) {
@@ -187,7 +194,7 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
     const uint32_t word_off = ((uint32_t)(tid >> 2) * (uint32_t)Npad * 4 + (tid & 3)) * 4;       // bytes, inside a head's trace
     auto load_word = [&](const Place& p) __attribute__((always_inline)) -> uint32_t {
         if (p.chunk * RT + tid >= nwords || p.h >= H) return 0u;
-        const char* base = reinterpret_cast<const char*>(bits) + (((size_t)p.h * nruns + p.chunk * (RT / 4)) * Npad + p.i) * 16;
+        const char* base = reinterpret_cast<const char*>(bits) + (((size_t)p.h * nruns + p.chunk * (RT / 4)) * Npad + p.row) * 16;
         return *reinterpret_cast<const uint32_t*>(base + word_off);
     };
     // lists the records of the trace rows of this thread's word
@@ -216,7 +223,7 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
     const uint32_t rec_bytes = (uint32_t)L * 16, group_off = (uint32_t)my_group * 16;
     const uint4* ext = lists + ((size_t)recs * H * L << nseg_log2);
 
-    Place at{0, 0, 0, 0};
+    Place at{0, 0, 0, 0, 0};
     begin(at, slot);
     Place ahead = at;
     int buf = 0;
@@ -307,7 +314,7 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
         buf ^= 1;
         if (after.chunk == 0) {
             // the row's segment leaves, its counters are cleared
-            char* row = reinterpret_cast<char*>(C + ((size_t)at.h * N + at.i) * N);
+            char* row = reinterpret_cast<char*>(C + ((size_t)at.h * N + at.row) * N);
             int32_t c32 = 0x7fffffff;
             if (RHO) {
                 const int64_t c = cstar[at.h];
@@ -339,7 +346,7 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
             };
             if ((cols << nseg_log2) == N) leave(std::true_type{});
             else leave(std::false_type{});
-            if (RHO && lane == 0 && near) atomicAdd(rho + (size_t)at.h * N + at.i, near);
+            if (RHO && lane == 0 && near) atomicAdd(rho + (size_t)at.h * N + at.row, near);
         }
         at = after;
         __syncthreads();
@@ -402,10 +409,14 @@ swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows,
                        ((size_t)p.L * 16 << p.nseg_log2) + (size_t)((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext, queue);
     swarm_status st = swarm_check_launch(ctx, "list_build_kernel");
     if (st != SWARM_OK) return st;
+    // the groups of eight rows in steps of the golden section, without a common divisor: any stretch of them is spread over the head
+    const uint32_t groups = (uint32_t)N / 8, groups_inv = (uint32_t)((((uint64_t)1 << 32) + groups - 1) / groups);
+    uint32_t row_step = (uint32_t)(0.6180339887 * groups) | 1u;
+    while (std::gcd(row_step, groups) != 1u) row_step += 2;
     const int lds = (seg_columns(N, 1 << p.nseg_log2) + DUMMY_WORDS) * 4 + 2 * T_CAP * 2;
     hipLaunchKernelGGL(p.nseg_log2 ? (cstar ? coact_rows_kernel<true, true> : coact_rows_kernel<false, true>)
                                    : (cstar ? coact_rows_kernel<true, false> : coact_rows_kernel<false, false>), dim3(8 * SLOTS), dim3(RT), lds, ctx->stream,
-                       reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns, p.nseg_log2, p.L, p.ext_groups, queue, C, cstar, rho);
+                       reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns, p.nseg_log2, p.L, p.ext_groups, queue, row_step, groups_inv, C, cstar, rho);
     ctx->count_way = SWARM_WAY_ROWS;
     return swarm_check_launch(ctx, "coact_rows_kernel");
 }

@@ -30,6 +30,8 @@ def selections(kind, distance, H, k, N):
     if kind == "scattered":                                  # entries of the blocks of 64 at multiples of a distance
         e = torch.rand(ROWS, H, N // distance * 64, generator=g, device="cuda").topk(k, -1).indices.sort(-1).values
         return (e // 64 * distance + e % 64).int()
+    if kind == "lower":                                      # entries of the lower part only
+        return ((ar + torch.rand(ROWS, H, k, generator=g, device="cuda")) * (distance / k)).long().clamp_(max=distance - 1).int()
     n = N // distance                                        # "same": a few neighbours at every multiple of a distance, in every row
     ids = torch.arange(n, device="cuda")[:, None] * distance + torch.arange(max(1, k // n), device="cuda")
     return ids.flatten()[:k].int().expand(ROWS, H, min(k, ids.numel())).contiguous()
@@ -55,6 +57,7 @@ def times(sw, calls):
     ("pages", 1024, 2, 256, 16384, 2.0),                     # 2.96 -> 1.04
     ("same", 192, 1, 512, 32768, 2.2),                       # 3.05 -> 1.23: often activated entries that fell to the same workgroups
     ("same", 128, 8, 128, 8192, 2.8),                        # 3.56 -> 1.29: the same XCD of those that share a segment
+    ("lower", 32768, 1, 1024, 65536, 1.2),                   # the rows in order: their increments first, then writing alone
     ("same", 64, 8, 128, 8192, 1.7),                         # 2.08 -> 1.26: counters on few banks, one of them from several lanes at once
 ])
 def test_time_does_not_depend_on_the_entries(sw, kind, distance, H, k, N, bound):
