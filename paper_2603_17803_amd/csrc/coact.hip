@@ -765,10 +765,11 @@ static swarm_status tile_order_for(swarm_ctx* ctx, int ntm, const int32_t** out)
 }
 
 // Whether the trace rows are contracted in pieces: so many that they fill the device, of 24 runs or more (8 to 32 measured alike),
-// and only where the rows saved outweigh the partial counts (64 KiB a piece, written and read) and the second launch.  Both ways,
-// decayed updates: 36 tiles, 4096 rows 20.2 us whole, 20.7 in pieces, 8192 30.6 and 26.0, 16384 51.7 and 30.2; 136 tiles, 8192 rows
-// 34 and 33 (overwriting 30 and 35), 12000 45 and 37, 16384 55 and 39; 300 tiles, 12000 rows 65 and 66, 16384 75.7 and 71.7, 33000
-// 130 and 103.
+// and only where the rows saved outweigh the partial counts (64 KiB a piece, written and read) and the second launch.  Whole and in
+// pieces, decayed updates: 36 tiles, 4096 rows 20.2 and 20.7 us, 8192 30.7 and 26.0, 16384 51.7 and 30.4; 136 tiles, 8192 rows 34 and 33,
+// 11000 42.9 and 34.7, 16384 55 and 40; 300 tiles, 12000 rows 65 and 66, 16384 75.7 and 71.7, 33000 130 and 104.  Overwriting: 36 tiles,
+// 6144 rows 22.7 and 19.9, 8192 28.0 and 24.4; 136 tiles, 8192 rows 30 and 35 (left whole), 11000 38.6 and 34.4; 300 tiles, 33000 rows 122
+// and 89.  With the density count 36 tiles, 6144 rows 34.4 and 32.3; 136 tiles, 11000 rows 61 and 58; 300 tiles, 33000 rows 154 and 124.
 static bool split_rows(int64_t total, int nruns, int* pieces, int* piece_runs) {
     constexpr int MIN_RUNS = 24;
     if (total + 32 > 2 * (int64_t)nruns) return false;
@@ -840,9 +841,12 @@ swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns
     static const kernel_t kernels[5][4] = {
         {coact_syrk_kernel<0>, coact_syrk_kernel<1>, coact_syrk_kernel<2>, coact_syrk_kernel<0, true>},
         {coact_syrk_kernel<0, false, STREAM>, coact_syrk_kernel<1>, coact_syrk_kernel<2>, coact_syrk_kernel<0, true, STREAM>},
-        {coact_syrk_kernel<0, false, STAGGER>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>, coact_syrk_kernel<0, true, STAGGER>},
-        {coact_syrk_kernel<0, false, STAGGER | STREAM>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>, coact_syrk_kernel<0, true, STAGGER | STREAM>},
-        {coact_syrk_kernel<0, false, FINISH>, coact_syrk_kernel<1, false, FINISH>, coact_syrk_kernel<2, false, FINISH>, coact_syrk_kernel<0, true, FINISH>}};
+        {coact_syrk_kernel<0, false, STAGGER>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>,
+         coact_syrk_kernel<0, true, STAGGER>},
+        {coact_syrk_kernel<0, false, STAGGER | STREAM>, coact_syrk_kernel<1, false, STAGGER>, coact_syrk_kernel<2, false, STAGGER>,
+         coact_syrk_kernel<0, true, STAGGER | STREAM>},
+        {coact_syrk_kernel<0, false, FINISH>, coact_syrk_kernel<1, false, FINISH>, coact_syrk_kernel<2, false, FINISH>,
+         coact_syrk_kernel<0, true, FINISH>}};
     static const kernel_t part_kernel = coact_syrk_kernel<0, false, PART>;
     constexpr int RHO_LDS_BYTES = SYRK_LDS_BYTES + (TM + TN) * 4;
     if (!ctx->syrk_lds_opt_in) {

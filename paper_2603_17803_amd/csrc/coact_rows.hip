@@ -14,8 +14,8 @@
 // Records have a fixed size -- the mean share of a segment, some standard deviations, and what completes a wave's division by
 // whole records -- because walking ragged pieces costs more than the increments (pieces through a work list: 4.8 ms); the ids
 // beyond it, rare unless the ids come in whole blocks, go to an overflow.
-// 8192 selections of 1024 out of 65536 entries: 5.7 ms by the dense product, 3.5 ms here with trace and records; 3.3 ms are
-// increments, listing and clearing, 3.1 to 3.3 ms the writing of C by itself (5.5 TB/s, what row pieces reach), side by side.
+// 8192 selections of 1024 out of 65536 entries spread evenly: 5.4 to 5.8 ms by the dense product, 3.1 to 3.3 ms here with trace and records;
+// on one device 3.33, without the writing of C 2.88, without the increments 3.33 (5.2 TB/s, what row pieces reach): they run side by side.
 #include <numeric>
 #include <type_traits>
 
@@ -190,7 +190,9 @@ __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __res
         begin(p, upcoming);
         return true;
     };
-    auto ask = [&]() __attribute__((always_inline)) { return 2 * SLOTS + __hip_atomic_fetch_add(queue + xcd * QUEUE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto ask = [&]() __attribute__((always_inline)) {
+        return 2 * SLOTS + __hip_atomic_fetch_add(queue + xcd * QUEUE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     const uint32_t word_off = ((uint32_t)(tid >> 2) * (uint32_t)Npad * 4 + (tid & 3)) * 4;       // bytes, inside a head's trace
     auto load_word = [&](const Place& p) __attribute__((always_inline)) -> uint32_t {
         if (p.chunk * RT + tid >= nwords || p.h >= H) return 0u;
@@ -380,8 +382,8 @@ RowsPlan plan_of(int N, int k) {
 //    32 x 4096^2, k = 64: 6144 rows 0.96 and 0.83, 8192 1.07 and 0.92, 16384 1.15 and 1.01; k = 32: 6144 rows 1.04 and 0.97, 8192 1.13
 //    and 1.02; 21 x 5120^2, k = 80: 6144 rows 1.11 and 0.98, 8192 1.24 and 1.10;
 //  - N a multiple of 16: a 64-byte piece of C shared by two XCDs is written twice (N = 12289: 0.85);
-//  - 2^29 counts: an entry that all of 8192 rows activate keeps one workgroup busy for some 200 us, which a build of this size (600 us and
-//    more by the dense product) hides and a smaller one does not.
+//  - 2^29 counts: an entry that all of 8192 rows activate keeps one workgroup busy; handed out last it adds 40 us to 495 of 8 x 8192^2, 100 to
+//    3250 of 65536^2, and would add as much to a smaller build.
 // 8192 rows, k = N / 64, spread ids: 8 x 8192^2 733 -> 493 us, 4 x 12288^2 829 -> 541, 32768^2 1391 -> 803, 65536^2 5.7 -> 3.2 ms.  The worst
 // that was found inside these bounds: pages of 64 from every ninth block of 40960 entries 0.90, the same ids in all of 6144 rows 0.96.
 // The ids of a segment and the trace rows have to fit 16 bits, a wave per selection one launch.
@@ -391,7 +393,7 @@ bool rows_route(int64_t rows, int H, int N, int k) {
     return N >= 5120 || rows >= 16384 || (rows >= 8192 && k <= N / 128);
 }
 
-// Scratch for the records, their overflow and the counters of rows handed out: at most 6 bytes per id and 300 per selection (row and head).
+// Scratch for the records, their overflow and the counters of rows handed out: at most 6 bytes per id and 300 per selection.
 size_t rows_list_bytes(int64_t rows, int H, int k, int N) {
     const RowsPlan p = plan_of(N, k);
     const int64_t recs = (rows + 31) / 32 * 32;
@@ -406,7 +408,8 @@ swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows,
     uint4* ext = lists + ((size_t)recs * H * p.L << p.nseg_log2);
     uint32_t* queue = reinterpret_cast<uint32_t*>(ext + (size_t)recs * H * p.ext_groups);
     hipLaunchKernelGGL(list_build_kernel, dim3((unsigned)(rows * H)), dim3(64),
-                       ((size_t)p.L * 16 << p.nseg_log2) + (size_t)((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L, p.ext_groups, lists, ext, queue);
+                       ((size_t)p.L * 16 << p.nseg_log2) + (size_t)((N + 31) / 32) * 4, ctx->stream, idx, rows, recs, H, k, N, p.nseg_log2, p.L,
+                       p.ext_groups, lists, ext, queue);
     swarm_status st = swarm_check_launch(ctx, "list_build_kernel");
     if (st != SWARM_OK) return st;
     // the groups of eight rows in steps of the golden section, without a common divisor: any stretch of them is spread over the head
@@ -415,8 +418,9 @@ swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows,
     while (std::gcd(row_step, groups) != 1u) row_step += 2;
     const int lds = (seg_columns(N, 1 << p.nseg_log2) + DUMMY_WORDS) * 4 + 2 * T_CAP * 2;
     hipLaunchKernelGGL(p.nseg_log2 ? (cstar ? coact_rows_kernel<true, true> : coact_rows_kernel<false, true>)
-                                   : (cstar ? coact_rows_kernel<true, false> : coact_rows_kernel<false, false>), dim3(8 * SLOTS), dim3(RT), lds, ctx->stream,
-                       reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns, p.nseg_log2, p.L, p.ext_groups, queue, row_step, groups_inv, C, cstar, rho);
+                                   : (cstar ? coact_rows_kernel<true, false> : coact_rows_kernel<false, false>),
+                       dim3(8 * SLOTS), dim3(RT), lds, ctx->stream, reinterpret_cast<const uint32_t*>(ctx->trace), lists, recs, H, N, Npad, nruns,
+                       p.nseg_log2, p.L, p.ext_groups, queue, row_step, groups_inv, C, cstar, rho);
     ctx->count_way = SWARM_WAY_ROWS;
     return swarm_check_launch(ctx, "coact_rows_kernel");
 }
