@@ -385,7 +385,8 @@ RowsPlan plan_of(int N, int k) {
 //  - 2^29 counts: an entry that all of 8192 rows activate keeps one workgroup busy; handed out last it adds 40 us to 495 of 8 x 8192^2, 100 to
 //    3250 of 65536^2, and would add as much to a smaller build.
 // 8192 rows, k = N / 64, spread ids: 8 x 8192^2 733 -> 493 us, 4 x 12288^2 829 -> 541, 32768^2 1391 -> 803, 65536^2 5.7 -> 3.2 ms.  The worst
-// that was found inside these bounds: pages of 64 from every ninth block of 40960 entries 0.90, the same ids in all of 6144 rows 0.96.
+// that was found inside these bounds: pages of 64 from every ninth block of 40960 entries 0.90, the same ids in all of 6144 rows 0.96, and
+// ids that were picked to fall to one segment 0.34.
 // The ids of a segment and the trace rows have to fit 16 bits, a wave per selection one launch.
 bool rows_route(int64_t rows, int H, int N, int k) {
     if (rows < 6144 || rows > 65535 || rows * H > (int64_t)1 << 25) return false;

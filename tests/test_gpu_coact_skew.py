@@ -51,7 +51,7 @@ def times(sw, calls):
     return best
 
 
-# bound: half way between what was measured with the columns or rows dealt in turn (in brackets) and now
+# Each comment: the ratio measured before what it names was mended, and since; the bound lies between them.
 @pytest.mark.parametrize("kind,distance,H,k,N,bound", [
     ("scattered", 512, 2, 256, 16384, 2.0),                  # 2.98 -> 1.15: one of two segments, nearly all in the overflow
     ("pages", 1024, 2, 256, 16384, 2.0),                     # 2.96 -> 1.04
