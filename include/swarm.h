@@ -386,8 +386,9 @@ swarm_status swarm_step(swarm_ctx* ctx, const swarm_keys* keys, const void* q, i
  * swarm_device_status must not be called while recording.  A recorded graph also refers to the
  * context's scratch: once a context has recorded, scratch that later calls outgrow is kept (not
  * freed) until swarm_destroy, so earlier graphs stay replayable; destroy graphs before their context.
- * (A graph that the caller captures by its own means is not known to the context: it is replayable
- * until a later call outgrows scratch that it refers to.)
+ * (A graph that the caller captures by its own means is known to the context only where a call in it
+ * takes one of the shorter ways that have scratch of their own: other ones are replayable until a later
+ * call outgrows scratch that they refer to.)
  */
 typedef struct swarm_graph swarm_graph;
 swarm_status swarm_capture_begin(swarm_ctx* ctx);

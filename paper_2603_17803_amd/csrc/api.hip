@@ -48,7 +48,11 @@ bool swarm_capturing(const swarm_ctx* ctx) {
 
 swarm_status swarm_try_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes, bool* there) {
     *there = *have >= bytes;
-    if (*there || swarm_capturing(ctx)) return SWARM_OK;
+    if (swarm_capturing(ctx)) {
+        ctx->recorded |= *there;                                // the caller's own graph refers to it from now on
+        return SWARM_OK;
+    }
+    if (*there) return SWARM_OK;
     const swarm_status st = swarm_grow(ctx, buf, have, bytes);
     *there = st == SWARM_OK;
     return st == SWARM_ENOMEM ? SWARM_OK : st;

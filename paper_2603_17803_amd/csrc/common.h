@@ -48,7 +48,7 @@ struct swarm_ctx {
     void* static_scratch = nullptr; // this device's copy of the library's static scratch array (address resolved at create)
     std::vector<std::pair<int, int32_t*>> tile_orders;   // co-activation tile schedules, one per tile count, never rewritten
     bool capturing = false;
-    bool recorded = false;         // a graph has been recorded on this context: it may refer to any scratch address
+    bool recorded = false;         // a graph has been recorded on this context (or, by the caller's own means, refers to its scratch): it may use any scratch address
     std::vector<void*> retired;    // outgrown scratch that recorded graphs may still use; freed with the context
 };
 
@@ -87,7 +87,8 @@ size_t select_cand_bytes(int64_t rows, int N, int k, bool scored);   // scratch 
 // Grows a scratch buffer to at least `bytes` (never shrinks).  Outgrowing a buffer synchronises the stream.
 swarm_status swarm_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes);
 // The same for scratch that a call can do without: *there says whether it is there.  It is not grown while the context's stream is
-// captured, by swarm_capture_begin or by the caller's own means, and a device without the room is no error.
+// captured, by swarm_capture_begin or by the caller's own means, and a device without the room is no error.  What a capture finds there is
+// kept until the context goes, as its graph refers to it.
 swarm_status swarm_try_grow(swarm_ctx* ctx, void** buf, size_t* have, size_t bytes, bool* there);
 bool swarm_capturing(const swarm_ctx* ctx);
 

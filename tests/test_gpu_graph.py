@@ -284,3 +284,72 @@ def test_a_capture_of_the_callers_own_finds_no_scratch(kind):
     assert all(torch.equal(a, b) for a, b in zip(out, want)) and sw.device_status() == 0
     del graph
     sw.close()
+
+
+@pytest.mark.parametrize("kind", ["queue", "pieces", "sparse"])
+def test_a_capture_of_the_callers_own_outlives_larger_calls(kind):
+    """The same calls captured by the caller's own means once their scratch is there: the graph refers to it, so larger calls of the context
+    afterwards, which outgrow it, leave it in place.  Every replay is right, with the larger calls between them."""
+    from paper_2603_17803_amd import binding
+    stream = torch.cuda.Stream()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    sw = binding.Swarm(0, stream=stream)
+    if kind == "queue":
+        sizes = [8200, 9000, 12000]
+        Cs = [torch.randint(0, 9, (1, n, n), generator=g, device="cuda", dtype=torch.int32) for n in sizes]
+        outs = [(torch.empty(1, n, dtype=torch.int32, device="cuda"), torch.empty(1, n, dtype=torch.int32, device="cuda"),
+                 torch.empty(1, dtype=torch.int64, device="cuda")) for n in sizes]
+        total = torch.full((1,), 8, dtype=torch.int64, device="cuda")
+        way = binding.SWARM_WAY_QUEUE_SORTED
+
+        def call(i):
+            sw.coact_density(Cs[i], 0.5, totals_in=total, out=outs[i])
+            return sw.last_way()[1]
+
+        def want(i):
+            rho = (Cs[i] >= 4).sum(2)
+            return [rho.int(), torch.sort(-rho, dim=1, stable=True).indices.int()]
+    else:
+        shapes = [(8192, 1, 16, 1024), (11000, 1, 16, 1024), (16384, 1, 16, 2048)] if kind == "pieces" else [(6144, 8, 64, 8192), (6200, 8, 128, 8192), (8192, 8, 128, 8192)]
+        sels = [torch.randint(0, n, (rows, H, k), generator=g, device="cuda", dtype=torch.int32) for rows, H, k, n in shapes]
+        outs = [(torch.empty(H, n, n, dtype=torch.int32, device="cuda"),) for _, H, _, n in shapes]
+        way = binding.SWARM_WAY_DENSE_PIECES if kind == "pieces" else binding.SWARM_WAY_ROWS
+
+        def call(i):
+            sw.coact_accumulate(sels[i], shapes[i][3], outs[i][0], decay_q16=0)
+            return sw.last_way()[0]
+
+        def want(i):
+            ref = torch.empty_like(outs[i][0])
+            torch.cuda.synchronize()
+            sw.coact_accumulate(sels[i], shapes[i][3], ref, decay_q16=0, flags=2)
+            stream.synchronize()
+            return [ref]
+
+    torch.cuda.synchronize()
+    expected = want(0)
+    with torch.cuda.stream(stream):
+        assert call(0) == way
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        assert call(0) == way
+    held = sw.last_way()[2]
+    for i in (0, 1, 2):
+        if i:
+            with torch.cuda.stream(stream):
+                assert call(i) == way
+            stream.synchronize()
+            assert sw.last_way()[2] > held
+            held = sw.last_way()[2]
+            assert all(torch.equal(a, b) for a, b in zip(outs[i], want(i)))
+        for o in outs[0]:
+            o.fill_(-1)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs[0], expected))
+    assert sw.device_status() == 0
+    del graph
+    sw.close()
