@@ -153,7 +153,8 @@ swarm_status swarm_last_way(const swarm_ctx* ctx, int32_t* count_way, int32_t* q
     if (!ctx) return SWARM_EINVAL;
     if (count_way) *count_way = ctx->count_way;
     if (queue_way) *queue_way = ctx->queue_way;
-    if (scratch_bytes) *scratch_bytes = ctx->scores_bytes + ctx->cand_bytes + ctx->trace_bytes + ctx->lists_bytes + ctx->part_bytes + ctx->rank_bytes + ctx->totals_bytes;
+    if (scratch_bytes)
+        *scratch_bytes = ctx->scores_bytes + ctx->cand_bytes + ctx->trace_bytes + ctx->lists_bytes + ctx->part_bytes + ctx->rank_bytes + ctx->totals_bytes;
     return SWARM_OK;
 }
 

@@ -152,7 +152,8 @@ __global__ __launch_bounds__(64) void list_build_kernel(const int32_t* __restric
 template <bool RHO, bool SEG>
 __global__ __launch_bounds__(RT, 8) void coact_rows_kernel(const uint32_t* __restrict__ bits, const uint4* __restrict__ lists, int recs, int H, int N,
                                                            int Npad, int nruns, int nseg_log2, int L, int ext_groups, uint32_t* __restrict__ queue,
-                                                           uint32_t row_step, uint32_t groups_inv, int32_t* __restrict__ C, const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
+                                                           uint32_t row_step, uint32_t groups_inv, int32_t* __restrict__ C,
+                                                           const int64_t* __restrict__ cstar, int32_t* __restrict__ rho) {
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     const int nseg = 1 << nseg_log2, cols = seg_columns(N, nseg);
     uint32_t* cnt = smem;                                                        // cols + DUMMY_WORDS counters

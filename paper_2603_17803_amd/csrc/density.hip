@@ -146,8 +146,9 @@ __global__ void rho_exclude_self_kernel(const int32_t* __restrict__ C, int N, co
     if ((int64_t)C[((size_t)h * N + i) * N + i] >= cstar[h]) rho[(size_t)h * N + i] -= 1;
 }
 
-// The queue without scratch (a recording that finds none, for more entries than one workgroup sorts): position of entry i =
-// entries with a higher density + entries with the same density and a lower id: N^2 comparisons per head, tiled through LDS.  A workgroup ranks 256 entries;
+// The queue without scratch (a capture that finds none and a device without the room, for more entries than one workgroup
+// sorts): position of entry i = entries with a higher density + entries with the same density and a lower id: N^2
+// comparisons per head, tiled through LDS.  A workgroup ranks 256 entries;
 // its four quarters (256 threads each) take a quarter of every staged tile of 1024 densities, and the
 // partial ranks meet in LDS: four times the waves per compute unit of one thread per entry.
 constexpr int RANK_ENTRIES = 256, RANK_PARTS = 4, RANK_TILE = 1024;
