@@ -262,8 +262,9 @@ static swarm_status check_coact_args(swarm_ctx* ctx, const char* fn, const int32
 
 // Whether an overwriting count goes row by row, with the room it needs.  Both ways give the same counts, so a recording or a device
 // without that room takes the dense one; what the dense one keeps per size is there after either, for the recordings that follow.
-static swarm_status take_rows_route(swarm_ctx* ctx, int64_t rows, int32_t H, int32_t k, int32_t N, int Npad, bool* sparse) {
-    *sparse = rows_route(rows, H, N, k);
+static swarm_status take_rows_route(swarm_ctx* ctx, int64_t rows, int32_t H, int32_t k, int32_t N, int Npad, const int32_t* C,
+                                    bool* sparse) {
+    *sparse = rows_route(rows, H, N, k, C);
     if (!*sparse) return SWARM_OK;
     const swarm_status st = swarm_try_grow(ctx, &ctx->lists, &ctx->lists_bytes, rows_list_bytes(rows, H, k, N), sparse);
     return st == SWARM_OK ? coact_reserve_tiles(ctx, Npad) : st;
@@ -285,7 +286,7 @@ swarm_status swarm_coact_accumulate(swarm_ctx* ctx, const int32_t* idx, int64_t 
     if (flags & SWARM_COACT_POPCOUNT) return launch_coact_popcount(ctx, H, N, Npad, nruns, C, decay_q16);
     if (decay_q16 == 0u) {
         bool sparse;
-        st = take_rows_route(ctx, rows, H, k, N, Npad, &sparse);
+        st = take_rows_route(ctx, rows, H, k, N, Npad, C, &sparse);
         if (st != SWARM_OK) return st;
         if (sparse) return launch_coact_rows(ctx, idx, rows, H, k, N, Npad, nruns, C, ctx->lists);
     }
@@ -312,7 +313,7 @@ swarm_status swarm_coact_build_density(swarm_ctx* ctx, const int32_t* idx, int64
                     sizeof(int64_t) * 2 * (size_t)H + sizeof(int32_t) * trace_count_words(nruns, H, Npad));
     if (st != SWARM_OK) return st;
     bool sparse;
-    st = take_rows_route(ctx, rows, H, k, N, Npad, &sparse);
+    st = take_rows_route(ctx, rows, H, k, N, Npad, C, &sparse);
     if (st != SWARM_OK) return st;
     int64_t* totals = totals_out ? totals_out : ctx->totals;
     int64_t* cstar = ctx->totals + H;

@@ -382,16 +382,20 @@ RowsPlan plan_of(int N, int k) {
 //  - N >= 5120, or from 4096 on where more rows or shorter selections outweigh the two barriers of a row: spread ids, and with a sink,
 //    32 x 4096^2, k = 64: 6144 rows 0.96 and 0.83, 8192 1.07 and 0.92, 16384 1.15 and 1.01; k = 32: 6144 rows 1.04 and 0.97, 8192 1.13
 //    and 1.02; 21 x 5120^2, k = 80: 6144 rows 1.11 and 0.98, 8192 1.24 and 1.10;
-//  - N a multiple of 16: a 64-byte piece of C shared by two XCDs is written twice (N = 12289: 0.85);
+//  - N a multiple of 16: a 64-byte piece of C shared by two XCDs is written twice (N = 12289: 0.85); so is every one of a C that itself starts inside
+//    a piece (65536^2 14.8 ms, the dense product 8.6; 24576^2 1.97 and 1.2, 4 x 12288^2 1.92 and 1.1), unless one segment holds all
+//    columns (8 x 8192^2 578 and 848 us).  Whole pieces that share a line are level or better (6144 rows, rows of 24592 563 and 634 us, of
+//    16400 563 and 566; a C 64 bytes past a line, 24576^2 645 and 645, 4 x 12288^2 678 and 623);
 //  - 2^29 counts: an entry that all of 8192 rows activate keeps one workgroup busy; handed out last it adds 40 us to 495 of 8 x 8192^2, 100 to
 //    3250 of 65536^2, and would add as much to a smaller build.
 // 8192 rows, k = N / 64, spread ids: 8 x 8192^2 733 -> 493 us, 4 x 12288^2 829 -> 541, 32768^2 1391 -> 803, 65536^2 5.7 -> 3.2 ms.  The worst
 // that was found inside these bounds: pages of 64 from every ninth block of 40960 entries 0.90, the same ids in all of 6144 rows 0.96, and
 // ids that were picked to fall to one segment 0.34.
 // The ids of a segment and the trace rows have to fit 16 bits, a wave per selection one launch.
-bool rows_route(int64_t rows, int H, int N, int k) {
+bool rows_route(int64_t rows, int H, int N, int k, const int32_t* C) {
     if (rows < 6144 || rows > 65535 || rows * H > (int64_t)1 << 25) return false;
     if (N < 4096 || N > MAX_SEGMENTS * MAX_SEGMENT || N % 16 != 0 || k > N / 64 || (int64_t)H * N * N < (int64_t)1 << 29) return false;
+    if (N > MAX_SEGMENT && reinterpret_cast<uintptr_t>(C) % 64 != 0) return false;
     return N >= 5120 || rows >= 16384 || (rows >= 8192 && k <= N / 128);
 }
 

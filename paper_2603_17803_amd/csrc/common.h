@@ -124,7 +124,7 @@ swarm_status launch_trace_totals_thresholds(swarm_ctx* ctx, const int32_t* row_c
 swarm_status coact_reserve_tiles(swarm_ctx* ctx, int Npad);   // the dense product's tile schedule for this size (not while recording)
 swarm_status launch_coact_syrk(swarm_ctx* ctx, int H, int N, int Npad, int nruns, int32_t* C, uint32_t decay_q16,
                                const int64_t* cstar = nullptr, int32_t* rho = nullptr);
-bool rows_route(int64_t rows, int H, int N, int k);       // sparse enough to be summed row by row (coact_rows.hip)
+bool rows_route(int64_t rows, int H, int N, int k, const int32_t* C);       // sparse enough to be summed row by row (coact_rows.hip)
 size_t rows_list_bytes(int64_t rows, int H, int k, int N);
 swarm_status launch_coact_rows(swarm_ctx* ctx, const int32_t* idx, int64_t rows, int H, int k, int N, int Npad, int nruns, int32_t* C,
                                void* lists, const int64_t* cstar = nullptr, int32_t* rho = nullptr);

@@ -93,6 +93,30 @@ def test_the_way_of_a_count(sw, rows, H, k, N, way):
     assert sw.device_status() == 0
 
 
+# C that starts inside a 64-byte piece (the header asks for 16): only where one segment holds all columns
+@pytest.mark.parametrize("H,k,N,words,way", [(8, 128, 8192, 4, ROWS), (8, 128, 8192, 12, ROWS), (3, 200, 13392, 0, ROWS), (3, 200, 13392, 4, STREAMED), (3, 200, 13392, 8, STREAMED),
+                                             (3, 200, 13392, 16, ROWS), (5, 128, 10368, 20, STREAMED), (1, 384, 24576, 12, STREAMED)])
+def test_the_way_follows_where_C_starts(sw, H, k, N, words, way):
+    sel = selections("spread", 6144, H, k, N)
+    with torch.cuda.stream(sw.stream):
+        sw.stream.wait_stream(torch.cuda.default_stream())
+        room = torch.full((H * N * N + 64,), -7, dtype=torch.int32, device="cuda")
+        ref = torch.empty(H, N, N, dtype=torch.int32, device="cuda")
+        assert room.data_ptr() % 64 == 0
+        C = room[words:words + H * N * N].view(H, N, N)
+        sw.coact_accumulate(sel, N, ref, decay_q16=0, flags=POPCOUNT)
+        sw.coact_accumulate(sel, N, C, decay_q16=0)
+        assert sw.last_way()[0] == way and torch.equal(C, ref)
+        tau = 1.0 - 3.0 / (6144.0 * k * k)
+        C.fill_(-7)
+        got = sw.coact_build_density(sel, N, C, tau)
+        assert sw.last_way()[0] == way and torch.equal(C, ref)
+        assert all(torch.equal(g, w) for g, w in zip(got, sw.coact_density(ref, tau)))
+        assert bool((room[:words] == -7).all()) and bool((room[words + H * N * N:] == -7).all())
+    sw.stream.synchronize()
+    assert sw.device_status() == 0
+
+
 # one segment and several, wide and narrow selections
 @pytest.mark.parametrize("rows,H,k,N", [(6144, 8, 128, 8192), (6144, 8, 8, 8192), (6151, 2, 256, 16384), (6144, 1, 1, 24576), (6144, 1, 1024, 65536), (6144, 1, 17, 65536), (6144, 1, 1, 65536)])
 def test_scratch_of_a_sparse_count(rows, H, k, N):
