@@ -339,11 +339,16 @@ __device__ __forceinline__ void place_singles(uint32_t n, int lane, const uint32
 constexpr int MAP_THREADS = 256;
 constexpr uint32_t MAP_SPLIT_MIN_ITEMS = 96;     // lists that cannot be longer stay one chain: it is shorter than finding the sub-problems
 // Two replicas half the SSDs apart, as the round-robin placement puts them, make D / 2 sub-problems of a pair, whose links are the
-// short ones: there the split pays from here on (86 items over 6 SSDs 8.75 -> 7.9 us, 65 8.3 -> 7.9, over 18 SSDs 17.2 -> 14.2, 32 18.9 ->
-// 13.2; over 9 to 16 SSDs, whose chain is no longer than over 8 but whose sub-problems take longer to find, 9.1 -> 9.4; over 2 SSDs
-// there is one sub-problem, 8.4 -> 9.0, and past 32 more than 16 to be found one after the other: 36 SSDs 19.4 -> 24.8, 64 22.4 -> 45).
-// Any other table loses up to 2 us by it (one sub-problem of 16 SSDs, 86 items: 10.3 -> 12.6 us).
-constexpr uint32_t MAP_SPLIT_MIN_PAIRED = 64;
+// short ones: there the split pays earlier.  us as one chain and divided (8 heads; a chain of 64 items is a wave's one pass):
+//  - 17 to 32 SSDs, from 64 items on: 18 SSDs 13.9 and 10.9, 95 items 18.7 and 11.2; 32 SSDs 15.1 and 12.8, 20.5 and 13.0;
+//  - 5 to 8 SSDs, from 65 on: 8 SSDs, 200 clusters, 64 items 7.2 and 7.8, 65 8.15 and 8.0, 76 8.4 and 8.0, 95 8.8 and 8.05; 500 clusters 7.2
+//    and 8.1, 8.05 and 8.1, 8.3 and 8.1, 8.6 and 8.2; 700 clusters 8.15 and 8.25 at 65, 8.4 and 8.3 at 76; but 1024, among which the items
+//    take longer to find, 8.1 and 8.5, 8.35 and 8.5, level at 88;
+//  - not over 2 SSDs, one sub-problem (8.4 and 9.0), nor 4 (500 clusters, 76 items 7.8 and 8.1, level at 88), nor 9 to 16, whose chain is no
+//    longer than over 8 but whose sub-problems take longer to find (9.1 and 9.4), nor past 32, where more than 16 are found one after the
+//    other (36 SSDs 19.4 and 24.8, 64 22.4 and 45).
+// Any other table loses up to 2 us by it (one sub-problem of 16 SSDs, 86 items: 10.3 and 12.6 us) and 0.1 to 0.25 us by the look.
+constexpr uint32_t MAP_SPLIT_MIN_PAIRED = 64, MAP_SPLIT_MIN_PAIRED_SHORT = 65;
 
 // Copies n words from global memory to LDS with batches of independent loads (all loads of a batch
 // are in flight together, so a small table costs one memory round trip).  16-byte loads when the
@@ -962,11 +967,12 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
         const uint32_t before = wave_excl_scan(mine, &total);
         uint32_t least = MAP_SPLIT_MIN_ITEMS;
         if constexpr (!BIG) {
-            if (__builtin_expect((a.D <= 8 || a.D > 16) && a.D > 2 && a.D <= 32 && a.R == 2 &&
-                                 total - MAP_SPLIT_MIN_PAIRED < MAP_SPLIT_MIN_ITEMS - MAP_SPLIT_MIN_PAIRED && stage_tab, 0)) {
-                // 64 clusters across the table tell; a second slot may be unused where there are more than two pairs
-                const int c = (int)((int64_t)lane * a.Nc >> 6);
-                if (__ballot((s_rep[2 * c + 1] >= 0 || a.D <= 4) && 2 * abs(s_rep[2 * c] - s_rep[2 * c + 1]) != a.D) == 0) least = MAP_SPLIT_MIN_PAIRED;
+            const uint32_t paired_from = a.R != 2 || a.D <= 4 || a.D > 32 ? MAP_SPLIT_MIN_ITEMS
+                                       : a.D > 16 ? MAP_SPLIT_MIN_PAIRED : a.D <= 8 && a.Nc <= 704 ? MAP_SPLIT_MIN_PAIRED_SHORT : MAP_SPLIT_MIN_ITEMS;
+            if (__builtin_expect(total >= paired_from && total < MAP_SPLIT_MIN_ITEMS && stage_tab, 0)) {
+                // 64 clusters across the table tell; a second slot may be unused: there are more than two pairs
+                const int c = (int)((uint32_t)lane * (uint32_t)a.Nc >> 6);
+                if (__ballot(s_rep[2 * c + 1] >= 0 && 2 * abs(s_rep[2 * c] - s_rep[2 * c + 1]) != a.D) == 0) least = paired_from;
             }
         }
         if ((!BIG || a.split_off != 0) && min(total, (uint32_t)a.cap) >= least) {
