@@ -35,6 +35,7 @@ struct MapArgs {
     int piece;          // strided selections (the streams of a step, as the selection writes them): a group's S entries are
     int piece_stride;   // pieces of `piece` consecutive ids, `piece_stride` words apart; unused by the contiguous kernels
     int piece_shift;    // log2(piece) when it is a power of two (a shift instead of a division per entry), -1 otherwise
+    uint32_t paired_from;   // lists from here on are divided where the replicas stand in pairs
 };
 
 // Chain over items [0, m) in visiting order.  keybase = (load << 6) | lane.  On return assign[i]
@@ -347,8 +348,12 @@ constexpr uint32_t MAP_SPLIT_MIN_ITEMS = 96;     // lists that cannot be longer 
 //  - not over 2 SSDs, one sub-problem (8.4 and 9.0), nor 4 (500 clusters, 76 items 7.8 and 8.1, level at 88), nor 9 to 16, whose chain is no
 //    longer than over 8 but whose sub-problems take longer to find (9.1 and 9.4), nor past 32, where more than 16 are found one after the
 //    other (36 SSDs 19.4 and 24.8, 64 22.4 and 45).
-// Any other table loses up to 2 us by it (one sub-problem of 16 SSDs, 86 items: 10.3 and 12.6 us) and 0.1 to 0.25 us by the look.
-constexpr uint32_t MAP_SPLIT_MIN_PAIRED = 64, MAP_SPLIT_MIN_PAIRED_SHORT = 65;
+// Any other table loses up to 2 us by it (one sub-problem of 16 SSDs, 86 items: 10.3 and 12.6 us).  The rule is
+// worked out on the host: in the kernel it cost the lists of every other table up to 0.25 us (6 SSDs, 95 of 500 clusters 8.67 and 8.91, now 8.74).
+static uint32_t paired_lists_from(int R, int D, int Nc) {
+    if (R != 2 || D <= 4 || D > 32) return MAP_SPLIT_MIN_ITEMS;
+    return D > 16 ? 64 : D <= 8 && Nc <= 704 ? 65 : MAP_SPLIT_MIN_ITEMS;
+}
 
 // Copies n words from global memory to LDS with batches of independent loads (all loads of a batch
 // are in flight together, so a small table costs one memory round trip).  16-byte loads when the
@@ -967,12 +972,10 @@ __device__ __forceinline__ void map_group(const MapArgs& a, int64_t g, const int
         const uint32_t before = wave_excl_scan(mine, &total);
         uint32_t least = MAP_SPLIT_MIN_ITEMS;
         if constexpr (!BIG) {
-            const uint32_t paired_from = a.R != 2 || a.D <= 4 || a.D > 32 ? MAP_SPLIT_MIN_ITEMS
-                                       : a.D > 16 ? MAP_SPLIT_MIN_PAIRED : a.D <= 8 && a.Nc <= 704 ? MAP_SPLIT_MIN_PAIRED_SHORT : MAP_SPLIT_MIN_ITEMS;
-            if (__builtin_expect(total >= paired_from && total < MAP_SPLIT_MIN_ITEMS && stage_tab, 0)) {
+            if (__builtin_expect(total >= a.paired_from && total < MAP_SPLIT_MIN_ITEMS && stage_tab, 0)) {
                 // 64 clusters across the table tell; a second slot may be unused: there are more than two pairs
                 const int c = (int)((uint32_t)lane * (uint32_t)a.Nc >> 6);
-                if (__ballot(s_rep[2 * c + 1] >= 0 && 2 * abs(s_rep[2 * c] - s_rep[2 * c + 1]) != a.D) == 0) least = paired_from;
+                if (__ballot(s_rep[2 * c + 1] >= 0 && 2 * abs(s_rep[2 * c] - s_rep[2 * c + 1]) != a.D) == 0) least = a.paired_from;
             }
         }
         if ((!BIG || a.split_off != 0) && min(total, (uint32_t)a.cap) >= least) {
@@ -1108,7 +1111,7 @@ swarm_status launch_map(swarm_ctx* ctx, const int32_t* sel, int64_t groups, int 
                         int Nc, const int32_t* replicas, int R, int D, const int32_t* weight,
                         const uint32_t* resident, int32_t* q_off, int32_t* q_cluster, int32_t* q_load, int cap, int piece) {
     MapArgs a{sel, S, H, N, e2c, Nc, replicas, R, D, weight, resident, q_off, q_cluster, q_load, cap, ctx->dev_flags, 0, 0, piece, H * piece,
-              (piece > 0 && (piece & (piece - 1)) == 0) ? __builtin_ctz((unsigned)piece) : -1};
+              (piece > 0 && (piece & (piece - 1)) == 0) ? __builtin_ctz((unsigned)piece) : -1, paired_lists_from(R, D, Nc)};
     size_t lds = map_lds_base_bytes(Nc, cap);
     const size_t budget = 64u * 1024u;
     int stage_tab = 0, stage_e2c = 0;
@@ -1150,7 +1153,7 @@ swarm_status launch_select_map(swarm_ctx* ctx, const float* scores, int H, int N
     // short rows select with smaller blocks, four scores per thread (see launch_select)
     const int NT = sliced ? selcore::NT : N <= 4 * 256 ? 256 : N <= 4 * 512 ? 512 : selcore::NT;
     if (N > 64 * NT && !sliced) return SWARM_OK;
-    MapArgs a{nullptr, k, H, N, e2c, Nc, replicas, R, D, weight, resident, q_off, q_cluster, q_load, cap, ctx->dev_flags, 0, 0, 0, 0, -1};
+    MapArgs a{nullptr, k, H, N, e2c, Nc, replicas, R, D, weight, resident, q_off, q_cluster, q_load, cap, ctx->dev_flags, 0, 0, 0, 0, -1, paired_lists_from(R, D, Nc)};
     size_t lds = map_lds_base_bytes(Nc, cap);
     const size_t budget = 64u * 1024u;                     // dynamic part; the selection's static 12.6 KiB come on top
     lds = (lds + 15) / 16 * 16;
