@@ -182,9 +182,9 @@ swarm_status swarm_score(swarm_ctx* ctx, const swarm_keys* keys, const void* q, 
  *     decay_q16 == 0     : C  = A^T A            (C is not read)
  *     otherwise          : C  = floor((C * decay_q16 + 2^15) / 2^16) + A^T A   (int64 intermediate)
  * An overwriting call whose selections are sparse and many (k <= N / 64, 6144 rows, about 5120 entries, 2^29 counts or
- * more; beyond 8192 entries C on 64 bytes) adds them up row by row of C instead, with copies of the selections in the context's scratch (at most 6 bytes for
- * each id and 300 for each row and head; rows rounded up to 32), and a call of few tiles over many rows keeps partial
- * counts there (64 MiB at most): the same counts.
+ * more; beyond 8192 entries C on 64 bytes) adds them up row by row of C instead, with copies of the selections in the
+ * context's scratch (at most 6 bytes for each id and 300 for each row and head; rows rounded up to 32), and a call of few
+ * tiles over many rows keeps partial counts there (64 MiB at most): the same counts.
  * The decayed form lets stale statistics fade when the workload drifts (the degradation of
  * co-activation statistics is the paper's fourth challenge, Section 3.2); the mechanism itself is
  * not in the paper.

@@ -796,6 +796,7 @@ static bool split_rows(int64_t total, int nruns, int* pieces, int* piece_runs) {
 //    6144 rows 268 and 209, 10240 rows 266 and 281; 12290^2, 6144 rows 291 and 247, 10240 rows 299 and 317), half as long where the
 //    product of C and trace says that little of either stays (4 x 8190^2, 2048 rows 476 and 364, 6144 rows 440 and 502; 60 x 1500^2, 2048
 //    rows 238 and 191, 6144 rows 232 and 302).  A small C of whole 16-byte vectors is better streamed (64 x 300^2, 2048 rows 25.7 and 26.9).
+// Where C itself starts is not looked at: one of N % 16 == 0 that starts inside a piece is streamed like the others of its size.
 static bool streams(int64_t elements, int N, int64_t trace_bytes, int64_t total, int nruns, bool stagger) {
     constexpr int64_t MIB = 1 << 20;
     const int64_t c_bytes = elements * 4, both = c_bytes + 2 * trace_bytes;
